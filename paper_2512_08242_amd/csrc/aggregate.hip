@@ -684,7 +684,8 @@ __global__ __launch_bounds__(kBlock) void k_agg_reduce(
 // pieces in item order: no owner tables, rows numbered by counting piece
 // heads.  Each wavefront works alone on a tile of kWaveTile consecutive
 // items (eight per lane); nothing is shared between the waves of a block.
-// The fast path runs only without a record filter.
+// The fast path runs only without a record filter; what it refuses goes to
+// the election on wave tiles (k_gen_elect below).
 static_assert(kAggIpt == kTileIpt, "wave tiles hold eight items per lane");
 
 // group key from the deepest non-NONE slot
@@ -1327,6 +1328,562 @@ __global__ __launch_bounds__(kBlock) void k_agg_heads_nat(
     atomicOr(&flags[1], kk);
 }
 
+// ---------------------------------------------------- groups of several runs
+// With a filter, or when groups are not runs (a marker that was lost leaves
+// its records to the marker around it, whose group then comes back after
+// every marker inside it; markers numbered out of order), rows are numbered
+// by election: every piece (run of equal keys within a wave tile) puts the
+// smallest position of its group into the group's entry of its level's
+// table, and the piece whose first item is that position owns the row.  The
+// passes share the tiles, the LDS regrouping and the reduction kernel of the
+// fast path; items left out by the filter are regrouped behind the tile's
+// last item.  Positions are input positions on natural tiles (a group never
+// spans GPUs or kinds, inside which input order is (start', index) order)
+// and korder positions otherwise.
+//   k_gen_elect  keys of all levels, one atomicMin per piece (none where the
+//                entry already holds a smaller position)
+//   k_gen_count  owners per tile and level, each lane's owners as a byte of
+//                a mask (so that no later pass reads the tables again), and
+//                whether pieces of one key hold different paths
+//   reduction    rows of the owners; other pieces go to the overflow list
+//                with their key, owners leave their row in the table, and
+//                k_gen_apply adds the list to the rows
+// Against the element-wise passes further up (eight consecutive items per
+// thread, uncoalesced, four passes over the tables), which still take what
+// this path hands back: 2.46M records with 16 counters, two compute streams
+// and one marker in a hundred lost, the whole call 2.62 -> 0.90 ms; a
+// selection of 90 of 100 iterations 1.69 -> 0.54 ms, of which the election
+// is 0.034, the count 0.058 (waiting on the table entries), the records
+// reduction 0.228 (0.187 where groups are runs) and the lists 0.042.
+struct GenTab {
+  uint32_t* own[kMaxLevels];   // by group key; the row, after the reduction
+  int64_t ks[kMaxLevels];
+};
+
+// Largest marker count of this path: keys below 2^31 leave the top bit of an
+// overflow entry to tell the reduction's two levels apart.
+constexpr int64_t kGenMaxM = ((int64_t)1 << 30) - 512;
+
+// Tables to "no position", counters to zero.
+__global__ __launch_bounds__(kBlock) void k_gen_fill(GenTab tab, uint32_t act,
+                                                     uint32_t* flags,
+                                                     uint32_t* interior,
+                                                     uint32_t* ovf_count) {
+  const int li = (int)blockIdx.y;
+  if (blockIdx.x == 0 && li == 0) {
+    if (threadIdx.x < 2) flags[threadIdx.x] = 0;
+    if (threadIdx.x < kMaxLevels) interior[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *ovf_count = 0;
+  }
+  if (!((act >> li) & 1u)) return;
+  uint32_t* p = tab.own[li];
+  const int64_t n4 = tab.ks[li] >> 2;
+  const int64_t step = (int64_t)gridDim.x * kBlock;
+  int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i < (tab.ks[li] & 3)) p[4 * n4 + i] = kNone;
+  for (; i < n4; i += step)
+    ((uint4*)p)[i] = make_uint4(kNone, kNone, kNone, kNone);
+}
+
+// Does the filter keep a record with gpu * 2 + kind gk, class c and level-0
+// marker m0?
+__device__ inline bool filter_keeps(const RecSrc& S, uint32_t gk, uint32_t c,
+                                    uint32_t m0) {
+  const uint32_t g = gk >> 1;
+  if (!((S.f.gpu_mask[g >> 6] >> (g & 63)) & 1ull)) return false;
+  if (c >= 32 || !((S.f.class_mask >> c) & 1u)) return false;
+  if (S.f.use_iter) {
+    if (S.D < 1) return false;
+    if (m0 == kNone || (int64_t)m0 >= S.M) return false;
+    const uint32_t lab = S.mlabel[m0];
+    if (lab < S.f.iter_lo || lab > S.f.iter_hi) return false;
+  }
+  return true;
+}
+
+// As nat_regroup, with valid items anywhere in the tile: n0 valid items of
+// run 0 first, then those of run 1, then the rest.  nv = valid items.
+__device__ inline void gen_regroup(const bool (&valid)[kAggIpt],
+                                   const uint32_t (&run)[kAggIpt], int lane,
+                                   uint32_t (&dst)[kAggIpt], int* n0_out,
+                                   int* nv_out) {
+  uint64_t m0[kAggIpt], m1[kAggIpt];
+  uint32_t n0 = 0, n1 = 0;
+#pragma unroll
+  for (int j = 0; j < kAggIpt; ++j) {
+    m0[j] = __ballot(valid[j] && run[j] == 0u);
+    m1[j] = __ballot(valid[j] && run[j] != 0u);
+    n0 += (uint32_t)__popcll(m0[j]);
+    n1 += (uint32_t)__popcll(m1[j]);
+  }
+  uint32_t c0 = 0, c1 = n0, c2 = n0 + n1;
+#pragma unroll
+  for (int j = 0; j < kAggIpt; ++j) {
+    const uint64_t mx = ~(m0[j] | m1[j]);
+    const uint64_t mine = valid[j] ? (run[j] == 0u ? m0[j] : m1[j]) : mx;
+    const uint32_t c = valid[j] ? (run[j] == 0u ? c0 : c1) : c2;
+    dst[j] = (uint32_t)pad8((int)(c + lanes_below(mine)));
+    c0 += (uint32_t)__popcll(m0[j]);
+    c1 += (uint32_t)__popcll(m1[j]);
+    c2 += (uint32_t)__popcll(mx);
+  }
+  *n0_out = (int)n0;
+  *nv_out = (int)(n0 + n1);
+}
+
+// A wave tile of this path, items striped: records of a natural tile
+// (kNat), records in korder (the items gathered by k_agg_items), or rows of
+// a finer level.
+template <int MaxD>
+struct GenTile {
+  uint32_t rs[kAggIpt];       // record or row
+  uint32_t id[kAggIpt];       // position the election compares
+  uint32_t gk[kAggIpt];
+  uint32_t p[kAggIpt][MaxD];
+  uint32_t dst[kAggIpt];
+  int n0, nv;                 // items of run 0, items of both
+  int64_t e0, e1;             // entries of the runs' counts in a level
+  int64_t prev[2];            // position before each run, -1: none
+};
+
+// False past the last tile (e0, e1 are then entries to clear).
+template <int MaxD, bool kNat>
+__device__ inline bool gen_load(const FromRecords& src, const NatGeom& N,
+                                int64_t w, int D, int lane,
+                                GenTile<MaxD>& X) {
+  const RecSrc& S = src.S;
+  bool valid[kAggIpt];
+  uint32_t run[kAggIpt];
+  if constexpr (kNat) {
+    NatTile T;
+    if (!nat_tile(N, w, T)) {
+      X.e0 = 2 * w;
+      X.e1 = 2 * w + 1;
+      return false;
+    }
+    X.e0 = 2 * (int64_t)T.tbg + T.tl;
+    X.e1 = X.e0 + T.cg;
+    X.prev[0] = T.prev[0];
+    X.prev[1] = T.prev[1];
+    uint32_t c[kAggIpt];
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) {
+      const int q = j * kWave + lane;
+      valid[j] = q < T.tile_n;
+      const int64_t i = T.base + (valid[j] ? q : 0);
+      X.rs[j] = (uint32_t)i;
+      X.id[j] = (uint32_t)i;
+      c[j] = S.cls[i];
+      X.gk[j] = T.g * 2u + (uint32_t)kind_of(c[j]);
+      run[j] = X.gk[j] & 1u;
+#pragma unroll
+      for (int l = 0; l < MaxD; ++l) {
+        const int ll = l < D ? l : (D > 0 ? D - 1 : 0);
+        const uint32_t v = D > 0 ? S.idx[(int64_t)ll * S.n + i] : kNone;
+        X.p[j][l] = l < D ? v : kNone;
+      }
+    }
+    if (S.f.active) {
+#pragma unroll
+      for (int j = 0; j < kAggIpt; ++j)
+        valid[j] = valid[j] && filter_keeps(S, X.gk[j], c[j], X.p[j][0]);
+    }
+  } else {
+    X.e0 = w;
+    X.e1 = w;
+    const int64_t base = w * kWaveTile;
+    X.prev[0] = X.prev[1] = base - 1;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) {
+      const int64_t i = base + j * kWave + lane;
+      const bool in = i < S.n;
+      const int64_t pos = in ? i : base;
+      const uint32_t v = S.igk[pos];
+      valid[j] = in && v != 0xFFFFu;
+      X.rs[j] = S.korder[pos];
+      X.id[j] = (uint32_t)pos;
+      X.gk[j] = v & 511u;
+      run[j] = 0;
+#pragma unroll
+      for (int l = 0; l < MaxD; ++l) {
+        const int ll = l < D ? l : (D > 0 ? D - 1 : 0);
+        const uint32_t u = D > 0 ? S.ipath[(int64_t)ll * S.n + pos] : kNone;
+        X.p[j][l] = l < D ? u : kNone;
+      }
+    }
+  }
+  gen_regroup(valid, run, lane, X.dst, &X.n0, &X.nv);
+  return true;
+}
+
+template <int MaxD, bool kNat>
+__device__ inline bool gen_load(const FromRows& src, const NatGeom&,
+                                int64_t w, int D, int lane,
+                                GenTile<MaxD>& X) {
+  X.e0 = w;
+  X.e1 = w;
+  const int64_t cnt = src.count();
+  const int64_t base = w * kWaveTile;
+  if (base >= cnt) return false;
+  const int n =
+      (int)((cnt - base) < kWaveTile ? (cnt - base) : (int64_t)kWaveTile);
+#pragma unroll
+  for (int j = 0; j < kAggIpt; ++j) {
+    const int q = j * kWave + lane;
+    gather_item<MaxD>(src, base + (q < n ? q : 0), D, X.rs[j], X.gk[j],
+                      X.p[j]);
+    X.id[j] = src.R.firstpos[X.rs[j]];
+    X.dst[j] = (uint32_t)pad8(q);
+  }
+  X.n0 = n;
+  X.nv = n;
+  return true;
+}
+
+// The tile's items to the blocked arrangement (lane holds 8 lane + j).
+template <int MaxD>
+__device__ inline void gen_block(GenTile<MaxD>& X, uint32_t* sk, int lane) {
+  wave_regroup_to_blocked(sk, X.id, X.dst, lane);
+  wave_regroup_to_blocked(sk, X.gk, X.dst, lane);
+#pragma unroll
+  for (int l = 0; l < MaxD; ++l) {
+    uint32_t x[kAggIpt];
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) x[j] = X.p[j][l];
+    wave_regroup_to_blocked(sk, x, X.dst, lane);
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) X.p[j][l] = x[j];
+  }
+}
+
+// Bit j: item j of the lane starts a piece (valid items only).
+__device__ inline uint32_t gen_heads(const uint32_t (&key)[kAggIpt], int n0,
+                                     int nv, int lane) {
+  uint32_t prev = wave_shr1_u32(0u, key[kAggIpt - 1]);
+  uint32_t m = 0;
+#pragma unroll
+  for (int j = 0; j < kAggIpt; ++j) {
+    const int v = lane * kAggIpt + j;
+    if (v < nv && (v == 0 || v == n0 || key[j] != prev)) m |= 1u << j;
+    prev = key[j];
+  }
+  return m;
+}
+
+// kPlain: a piece inside its run of the tile whose marker is numbered above
+// the one before it is new in any trace whose markers are nested and
+// numbered as they open, so it stores its position instead of taking the
+// minimum.  A piece for which that was wrong finds a later position than
+// its own in the count pass, and the host elects again with minima only.
+template <int MaxD, bool kNat, bool kPlain>
+__global__ __launch_bounds__(kBlock) void k_gen_elect(
+    FromRecords src, NatGeom N, uint32_t act, int D, int64_t M, int64_t nwt,
+    GenTab tab, uint32_t* flags) {
+  __shared__ uint32_t s_k[kWavesPerBlock][kSlice];
+  if constexpr (kNat) {
+    if (*N.bad) return;
+  }
+  const int lane = lane_id();
+  const int wv = (int)(threadIdx.x / kWave);
+  const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+  if (w >= nwt) return;
+  GenTile<MaxD> X;
+  if (!gen_load<MaxD, kNat>(src, N, w, D, lane, X)) return;
+  gen_block(X, s_k[wv], lane);
+  // the kept item before each run: a piece that goes on with its group has
+  // nothing to elect (without this every tile would meet at the entries of
+  // the coarse levels: 0.097 instead of 0.034 ms on 2.46M records)
+  uint32_t qp[2][MaxD], qg[2];
+  bool qv[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int64_t i = X.prev[k];
+    qv[k] = i >= 0;
+    const int64_t ii = qv[k] ? i : 0;
+    if constexpr (kNat) {
+      const uint32_t c = src.S.cls[ii];
+      nat_item<MaxD>(src.S, ii, src.S.gpu[ii], D, qg[k], qp[k]);
+      if (src.S.f.active)
+        qv[k] = qv[k] && filter_keeps(src.S, qg[k], c, qp[k][0]);
+    } else {
+      const uint32_t v = src.S.igk[ii];
+      qv[k] = qv[k] && v != 0xFFFFu;
+      qg[k] = v & 511u;
+#pragma unroll
+      for (int l = 0; l < MaxD; ++l)
+        qp[k][l] = l < D ? src.S.ipath[(int64_t)l * src.S.n + ii] : kNone;
+    }
+  }
+  uint32_t qs[2] = {kNone, kNone};
+  uint32_t slot[kAggIpt], key[kAggIpt];
+#pragma unroll
+  for (int j = 0; j < kAggIpt; ++j) slot[j] = kNone;
+  bool unkeyed = false;
+  auto elect = [&](uint32_t* own, bool marker) {
+    uint32_t m = gen_heads(key, X.n0, X.nv, lane);
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) {
+      const int v = lane * kAggIpt + j;
+      if (v != 0 && v != X.n0) continue;
+      const int k = kNat && v == X.n0 ? 1 : 0;
+      const uint32_t qk = marker ? slot_key(k ? qs[1] : qs[0], M,
+                                            k ? qg[1] : qg[0])
+                                 : (k ? qg[1] : qg[0]);
+      if ((k ? qv[1] : qv[0]) && key[j] == qk) m &= ~(1u << j);
+    }
+    if (kPlain && marker) {
+      uint32_t ps = wave_shr1_u32(0u, slot[kAggIpt - 1]);
+#pragma unroll
+      for (int j = 0; j < kAggIpt; ++j) {
+        const int v = lane * kAggIpt + j;
+        if ((m >> j) & 1u && v != 0 && v != X.n0 && key[j] != kNone &&
+            slot[j] + 1u > ps + 1u) {
+          own[key[j]] = X.id[j];
+          m &= ~(1u << j);
+        }
+        ps = slot[j];
+      }
+    }
+    uint32_t cur[kAggIpt];
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+      cur[j] = (m >> j) & 1u && key[j] != kNone ? flag_read(own + key[j]) : 0u;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+      if (cur[j] > X.id[j]) atomicMin(own + key[j], X.id[j]);
+  };
+#pragma unroll
+  for (int li = 0; li < MaxD; ++li) {
+    if (li >= D) continue;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+      slot[j] = X.p[j][li] != kNone ? X.p[j][li] : slot[j];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) qs[k] = qp[k][li] != kNone ? qp[k][li] : qs[k];
+    if (!((act >> li) & 1u)) continue;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) {
+      key[j] = slot_key(slot[j], M, X.gk[j]);
+      if (lane * kAggIpt + j < X.nv && key[j] == kNone) unkeyed = true;
+    }
+    elect(tab.own[li], true);
+  }
+  if ((act >> D) & 1u) {
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) key[j] = X.gk[j];
+    elect(tab.own[D], false);
+  }
+  // (an item whose marker is out of range: left to the element-wise path)
+  wave_flag_or(&flags[0], unkeyed, 1u);
+}
+
+// Owners of levels [lv0, lv1] per tile: tilecnt[(li - lv0) * stride + entry]
+// and omask[(li - lv0) * mstride + 64 w + lane].  From records also: the
+// kinds present (flags[1]), pieces that neither own their row nor start
+// their run of the tile (interior[li]), and PATH_CONFLICT when two items of
+// a key hold different paths.
+template <int MaxD, typename Src, bool kNat>
+__global__ __launch_bounds__(kBlock) void k_gen_count(
+    Src src, NatGeom N, uint32_t act, int lv0, int lv1, int D, int64_t M,
+    int64_t nwt, int64_t stride, GenTab tab, uint32_t* tilecnt,
+    uint8_t* omask, int64_t mstride, uint32_t* flags, uint32_t* interior,
+    uint32_t* ovf_count, uint32_t* status) {
+  __shared__ uint32_t s_k[kWavesPerBlock][kSlice];
+  if constexpr (kNat) {
+    if (*N.bad) return;
+  }
+  // (from rows: the overflow list of the level below has been applied)
+  if (!Src::kRecords && blockIdx.x == 0 && threadIdx.x == 0) *ovf_count = 0;
+  const int lane = lane_id();
+  const int wv = (int)(threadIdx.x / kWave);
+  const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + wv;
+  if (w >= nwt) return;
+  GenTile<MaxD> X;
+  if (!gen_load<MaxD, kNat>(src, N, w, D, lane, X)) {
+    if (lane <= lv1 - lv0) {
+      tilecnt[(int64_t)lane * stride + X.e0] = 0;
+      tilecnt[(int64_t)lane * stride + X.e1] = 0;
+    }
+    return;
+  }
+  gen_block(X, s_k[wv], lane);
+  uint32_t slot[kAggIpt], key[kAggIpt];
+  bool eq[kAggIpt];            // path equal to the item before, so far
+#pragma unroll
+  for (int j = 0; j < kAggIpt; ++j) {
+    slot[j] = kNone;
+    eq[j] = true;
+  }
+  bool conflict = false, late = false;
+  // items of the lane before position n0
+  const int b0 = X.n0 - lane * kAggIpt;
+  const uint32_t m_run0 = b0 <= 0 ? 0u : (b0 >= kAggIpt ? 0xFFu
+                                                        : (1u << b0) - 1u);
+  auto wave_total = [&](uint32_t c) {
+    uint32_t t = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+      t += (uint32_t)__popcll(__ballot((c >> b) & 1u)) << b;
+    return t;
+  };
+  auto level = [&](int li) {
+    const uint32_t m = gen_heads(key, X.n0, X.nv, lane);
+    const uint32_t* own = tab.own[li];
+    uint32_t o[kAggIpt];
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+      o[j] = (m >> j) & 1u && key[j] != kNone ? own[key[j]] : kNone;
+    uint32_t mine = 0, other = 0;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) {
+      const bool h = (m >> j) & 1u && key[j] != kNone;
+      mine |= h && o[j] == X.id[j] ? 1u << j : 0u;
+      other |= h && o[j] != X.id[j] ? 1u << j : 0u;
+      late |= h && o[j] > X.id[j];
+    }
+    if constexpr (Src::kRecords) {
+      if (li < D) {
+        // inside a piece, then the piece against its group's first item
+#pragma unroll
+        for (int j = 0; j < kAggIpt; ++j) {
+          const int v = lane * kAggIpt + j;
+          conflict |= v < X.nv && !((m >> j) & 1u) && key[j] != kNone &&
+                      !eq[j];
+          if ((other >> j) & 1u) {
+#pragma unroll
+            for (int l = 0; l < MaxD; ++l) {
+              if (l > li) continue;
+              const uint32_t* col = kNat ? src.S.idx : src.S.ipath;
+              conflict |= col[(int64_t)l * src.S.n + o[j]] != X.p[j][l];
+            }
+          }
+        }
+      }
+      uint32_t in = other;
+#pragma unroll
+      for (int j = 0; j < kAggIpt; ++j) {
+        const int v = lane * kAggIpt + j;
+        if (v == 0 || v == X.n0) in &= ~(1u << j);
+      }
+      const uint32_t t = wave_total((uint32_t)__popc(in));
+      if (lane == 0 && t) atomicAdd(&interior[li], t);
+    }
+    omask[(int64_t)(li - lv0) * mstride + w * kWave + lane] = (uint8_t)mine;
+    const uint32_t t0 = wave_total((uint32_t)__popc(mine & m_run0));
+    uint32_t* tc = tilecnt + (int64_t)(li - lv0) * stride;
+    if constexpr (kNat) {
+      const uint32_t t1 = wave_total((uint32_t)__popc(mine & ~m_run0));
+      if (lane == 0) tc[X.e1] = t1;
+    }
+    if (lane == 0) tc[X.e0] = t0;
+  };
+#pragma unroll
+  for (int li = 0; li < MaxD; ++li) {
+    if (li >= D) continue;
+    if constexpr (Src::kRecords) {
+      uint32_t prev = wave_shr1_u32(0u, X.p[kAggIpt - 1][li]);
+#pragma unroll
+      for (int j = 0; j < kAggIpt; ++j) {
+        eq[j] = eq[j] && X.p[j][li] == prev;
+        prev = X.p[j][li];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+      slot[j] = X.p[j][li] != kNone ? X.p[j][li] : slot[j];
+    if (li < lv0 || li > lv1) continue;
+    if (!((act >> li) & 1u)) {
+      if (lane == 0) {
+        tilecnt[(int64_t)(li - lv0) * stride + X.e0] = 0;
+        tilecnt[(int64_t)(li - lv0) * stride + X.e1] = 0;
+      }
+      continue;
+    }
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+      key[j] = slot_key(slot[j], M, X.gk[j]);
+    level(li);
+  }
+  if (D <= lv1) {
+    if ((act >> D) & 1u) {
+#pragma unroll
+      for (int j = 0; j < kAggIpt; ++j) key[j] = X.gk[j];
+      level(D);
+    } else if (lane == 0) {
+      tilecnt[(int64_t)(D - lv0) * stride + X.e0] = 0;
+      tilecnt[(int64_t)(D - lv0) * stride + X.e1] = 0;
+    }
+  }
+  for (int li = D + 1; li <= lv1; ++li)
+    if (lane == 0) {
+      tilecnt[(int64_t)(li - lv0) * stride + X.e0] = 0;
+      tilecnt[(int64_t)(li - lv0) * stride + X.e1] = 0;
+    }
+  if constexpr (Src::kRecords) {
+    wave_flag_or(&flags[0], late, 4u);
+    // (a late entry still belongs to the group, so a conflict is one)
+    if (__ballot(conflict) != 0 && lane == 0) {
+      atomicOr(&flags[0], 2u);
+      atomicOr(status, (uint32_t)CHOPPER_ST_PATH_CONFLICT);
+    }
+    uint32_t kinds = 0;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+      if (lane * kAggIpt + j < X.nv) kinds |= 1u << (X.gk[j] & 1u);
+    const uint32_t kk = (__ballot(kinds & 1u) != 0 ? 1u : 0u) |
+                        (__ballot(kinds & 2u) != 0 ? 2u : 0u);
+    if (lane == 0 && kk && (flag_read(&flags[1]) & kk) != kk)
+      atomicOr(&flags[1], kk);
+  }
+}
+
+// What the reduction needs of this path: the owner masks and tables of the
+// level and the next coarser one, and whether later passes read firstpos.
+struct GenRed {
+  const uint8_t* mask = nullptr;
+  const uint8_t* mask2 = nullptr;
+  uint32_t* own = nullptr;
+  uint32_t* own2 = nullptr;
+};
+
+// Overflow entries (group keys; top bit: the reduction's second level) to
+// their rows, which the owners left in the tables.
+__global__ __launch_bounds__(kBlock) void k_gen_apply(
+    Overflow ovf, RowsDev R, int nfields, const uint32_t* own,
+    const uint32_t* own2) {
+  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  int64_t cnt = (int64_t)*ovf.count;
+  if (cnt > ovf.cap) cnt = ovf.cap;
+  if (e >= cnt) return;
+  const uint32_t k = ovf.row[e];
+  const uint32_t row = k >> 31 ? own2[k & 0x7FFFFFFFu] : own[k];
+  if ((int64_t)row >= R.cap) return;
+  for (int f = 0; f < nfields; ++f)
+    atomic_field(R, f, row, ovf.val[(int64_t)f * ovf.cap + e]);
+}
+
+// Level offsets, flags and interior counts for the host (layout as
+// k_agg_offsets_fast, the interior counts of the L levels after it).
+__global__ void k_gen_offsets(int L, int64_t stride, const uint32_t* tilebase,
+                              const uint32_t* total, const uint32_t* flags,
+                              const uint32_t* interior, bool nat,
+                              bool workload, int64_t cap,
+                              int64_t* level_offset, int64_t* stage,
+                              uint32_t* status) {
+  const int t = (int)threadIdx.x;
+  const int64_t tot =
+      (int64_t)*total + (workload ? __popc(flags[1] & 3u) : 0);
+  if (t <= L) {
+    const int64_t v = t == L ? tot : (int64_t)tilebase[(int64_t)t * stride];
+    level_offset[t] = v;
+    stage[3 + t] = v;
+  }
+  if (t < L) stage[3 + L + 1 + t] = interior[t];
+  if (t < 3) stage[t] = flags[t];
+  if (t == 0 && flags[0] == 0 && !(nat && flags[2]) && tot > cap)
+    atomicOr(status, (uint32_t)CHOPPER_ST_ROWS_OVERFLOW);
+}
+
 // Piece structure of one level over a wave tile (blocked arrangement: lane
 // holds items lane * 8 + j).  Pieces are maximal runs of equal keys.  Items
 // [0, n0) and [n0, tile_n) are two separate runs of rows (the two kinds of
@@ -1428,12 +1985,17 @@ __device__ inline int64_t piece_row(const LevelTile& T, uint32_t q) {
 // Every valid item has a key here (the heads pass sends traces with unkeyed
 // items to the general path).  kNat: the natural tiles, items read in input
 // order and regrouped by kind on the way to the blocked arrangement.
-template <int MaxD, typename Src, bool kTwo, bool kNat>
+// kGen: groups of several runs (above): every piece is a head here, the
+// owners' rows are numbered by rank, and a piece's row -- or, top bit set,
+// its overflow slot -- is kept per piece in LDS.
+template <int MaxD, typename Src, bool kTwo, bool kNat, bool kGen>
 __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
     Src src, NatGeom N, int li, int D, int64_t M, const uint32_t* tilebase,
     const uint32_t* tilebase2, const int64_t* row0, RowsDev R, Overflow ovf,
-    int64_t nwt) {
+    int64_t nwt, GenRed GR) {
   __shared__ uint64_t s_v[kWavesPerBlock][kSlice];
+  __shared__ uint32_t s_row[kGen ? kWavesPerBlock : 1][kGen && kTwo ? 2 : 1]
+                           [kGen ? kWaveTile : 1];
   const int lane = lane_id();
   const int wv = (int)(threadIdx.x / kWave);
   const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + wv;
@@ -1446,7 +2008,10 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
   int64_t base;
   int tile_n;
   NatTile NT;
-  if constexpr (kNat) {
+  if constexpr (kGen) {
+    base = 0;
+    tile_n = 0;
+  } else if constexpr (kNat) {
     if (!nat_tile(N, w, NT)) {
       if (lane < 2) {
         ovf.row[2 * w + lane] = kNone;
@@ -1478,7 +2043,30 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
   uint32_t tprev[2] = {kNone, kNone}, tprev2[2] = {kNone, kNone};
   int n0 = tile_n;
   int64_t r0 = 0, r1 = 0, q0 = 0, q1 = 0;
-  if constexpr (kNat) {
+  uint32_t id[kAggIpt];            // (kGen) election positions
+  if constexpr (kGen) {
+    GenTile<MaxD> X;
+    if (!gen_load<MaxD, kNat>(src, N, w, D, lane, X)) return;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) {
+      rs[j] = X.rs[j];
+      id[j] = X.id[j];
+      gk[j] = X.gk[j];
+      dst[j] = X.dst[j];
+#pragma unroll
+      for (int l = 0; l < MaxD; ++l) p[j][l] = X.p[j][l];
+    }
+    n0 = X.n0;
+    tile_n = X.nv;
+    // (row0: the scan covers the rows' levels only, see below)
+    r0 = (row0 ? row0[0] - (int64_t)tilebase[0] : 0) + (int64_t)tilebase[X.e0];
+    r1 = kNat ? (int64_t)tilebase[X.e1] : r0;
+    if (kTwo) {
+      q0 = (row0 ? row0[-1] - (int64_t)tilebase2[0] : 0) +
+           (int64_t)tilebase2[X.e0];
+      q1 = kNat ? (int64_t)tilebase2[X.e1] : q0;
+    }
+  } else if constexpr (kNat) {
     bool valid[kAggIpt];
     uint32_t kind[kAggIpt];
 #pragma unroll
@@ -1526,19 +2114,22 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
       q0 = (row0 ? row0[-1] - (int64_t)tilebase2[0] : 0) +
            (int64_t)tilebase2[w];
   }
+  // (with kGen the items past tile_n, which the regrouping put there, have
+  // keys too; level_tile looks at the first tile_n only)
 #pragma unroll
   for (int j = 0; j < kAggIpt; ++j) {
     const int q = j * kWave + lane;
-    key[j] = q < tile_n ? level_key<MaxD>(p[j], gk[j], li, D, M) : kNone;
-    key2[j] = kTwo && q < tile_n ? level_key<MaxD>(p[j], gk[j], li2, D, M)
-                                 : kNone;
+    key[j] = kGen || q < tile_n ? level_key<MaxD>(p[j], gk[j], li, D, M)
+                                : kNone;
+    key2[j] = kTwo && (kGen || q < tile_n)
+                  ? level_key<MaxD>(p[j], gk[j], li2, D, M) : kNone;
   }
   auto blk32 = [&](uint32_t (&x)[kAggIpt]) {
-    if constexpr (kNat) wave_regroup_to_blocked(sk, x, dst, lane);
+    if constexpr (kNat || kGen) wave_regroup_to_blocked(sk, x, dst, lane);
     else wave_to_blocked(sk, x, lane);
   };
   auto blk64 = [&](uint64_t (&x)[kAggIpt]) {
-    if constexpr (kNat) wave_regroup_to_blocked(sv, x, dst, lane);
+    if constexpr (kNat || kGen) wave_regroup_to_blocked(sv, x, dst, lane);
     else wave_to_blocked(sv, x, lane);
   };
   blk32(key);
@@ -1549,20 +2140,79 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
   if (kTwo)
     level_tile(key2, tprev2[0], tprev2[1], n0, tile_n, lane, q0, q1, T2,
                slot2);
+  // (kGen) rows of the pieces: owners by rank, the others an overflow slot
+  uint32_t m_own = 0, m_own2 = 0, own_row[kAggIpt], own_row2[kAggIpt];
+  auto piece_rows = [&](const LevelTile& T, const uint32_t (&k)[kAggIpt],
+                        uint32_t mine, int which, uint32_t (&orow)[kAggIpt]) {
+    const uint32_t other = T.m_hv & ~mine;
+    const int b0 = n0 - lane * kAggIpt;
+    const uint32_t m0 = b0 <= 0 ? 0u : (b0 >= kAggIpt ? 0xFFu
+                                                      : (1u << b0) - 1u);
+    const uint32_t c0 = (uint32_t)__popc(mine & m0);
+    const uint32_t c1 = (uint32_t)__popc(mine & ~m0);
+    const uint32_t x0 = wave_prefix_small<4>(c0);
+    const uint32_t x1 = wave_prefix_small<4>(c1);
+    const uint32_t co = (uint32_t)__popc(other);
+    const uint32_t xo = wave_prefix_small<4>(co);
+    const uint32_t no =
+        (uint32_t)__builtin_amdgcn_readlane((int)(xo + co), kWave - 1);
+    uint32_t ob = 0;
+    if (no) {                      // uniform
+      if (lane == 0) ob = atomicAdd(ovf.count, no);
+      ob = (uint32_t)__builtin_amdgcn_readlane((int)ob, 0);
+    }
+    uint32_t* srow = s_row[wv][which];
+    const int64_t a0 = which ? q0 : r0, a1 = which ? q1 : r1;
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j) {
+      const uint32_t below = (1u << j) - 1u;
+      orow[j] = kNone;
+      if (!((T.m_hv >> j) & 1u)) continue;
+      const uint32_t q = T.pfx + (uint32_t)__popc(T.m_hv & below);
+      uint32_t v = kNone;
+      if ((mine >> j) & 1u) {
+        const int64_t row =
+            (m0 >> j) & 1u ? a0 + x0 + __popc(mine & m0 & below)
+                           : a1 + x1 + __popc(mine & ~m0 & below);
+        if (row < R.cap) v = (uint32_t)row;
+        orow[j] = v;
+      } else {
+        const uint32_t e = ob + xo + (uint32_t)__popc(other & below);
+        if ((int64_t)e < ovf.cap) {
+          ovf.row[e] = k[j] | ((uint32_t)which << 31);
+          v = e | 0x80000000u;
+        }
+      }
+      srow[q] = v;
+    }
+  };
+  if constexpr (kGen) {
+    m_own = GR.mask[w * kWave + lane];
+    piece_rows(T1, key, m_own, 0, own_row);
+    if (kTwo) {
+      m_own2 = GR.mask2[w * kWave + lane];
+      piece_rows(T2, key2, m_own2, 1, own_row2);
+    }
+  }
 
   // headers of the rows that start here, written from the striped items:
   // the row of every group head goes back through LDS
-  auto headers = [&](const LevelTile& T, int lv) {
+  auto headers = [&](const LevelTile& T, int lv,
+                     const uint32_t (&orow)[kAggIpt], uint32_t* own) {
     uint32_t rw[kAggIpt];
 #pragma unroll
     for (int j = 0; j < kAggIpt; ++j) {
+      if constexpr (kGen) {
+        rw[j] = orow[j];
+        continue;
+      }
       const uint32_t idx =
           T.pfx + (uint32_t)__popc(T.m_hv & ((2u << j) - 1u)) - 1u;
       const int64_t row = piece_row(T, idx);
       rw[j] = ((T.m_real >> j) & 1u) && row >= 0 && row < R.cap
                   ? (uint32_t)row : kNone;
     }
-    if constexpr (kNat) wave_blocked_to_regrouped(sk, rw, dst, lane);
+    if constexpr (kNat || kGen) wave_blocked_to_regrouped(sk, rw, dst, lane);
     else wave_to_striped(sk, rw, lane);
 #pragma unroll
     for (int j = 0; j < kAggIpt; ++j) {
@@ -1576,14 +2226,18 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
       R.gpu[wr] = (uint8_t)(gk[j] >> 1);
       R.kind[wr] = (uint8_t)(gk[j] & 1u);
       R.first[wr] = src.first_of(rs[j]);
+      if constexpr (kGen) {
+        R.firstpos[wr] = id[j];
+        own[level_key<MaxD>(p[j], gk[j], lv, D, M)] = wr;
+      }
     }
   };
-  headers(T1, li);
-  if (kTwo) headers(T2, li2);
+  headers(T1, li, own_row, GR.own);
+  if (kTwo) headers(T2, li2, own_row2, GR.own2);
   auto cont_row = [&](uint32_t c, int64_t r) -> uint32_t {
     return c && r >= 1 && r - 1 < R.cap ? (uint32_t)(r - 1) : kNone;
   };
-  if (lane == 0) {
+  if (!kGen && lane == 0) {
     if constexpr (kNat) {
       ovf.row[2 * w] = cont_row(T1.c0, T1.r0);
       ovf.row[2 * w + 1] = cont_row(T1.c1, T1.r1);
@@ -1605,12 +2259,18 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
   auto store_pieces = [&](const LevelTile& T, int64_t obase, int f,
                           bool diff) {
     uint64_t* col = row_column(R, f);
-    uint64_t* oslot = ovf.val + (int64_t)f * ovf.cap + obase +
-                      (kNat ? 2 * w : w);
+    uint64_t* oslot = ovf.val + (int64_t)f * ovf.cap +
+                      (kGen ? 0 : obase + (kNat ? 2 * w : w));
     wave_sync();
     for (uint32_t q = lane; q < T.NP; q += kWave) {
       uint64_t v = sv[q];
       if (diff && q > 0) v -= sv[q - 1];
+      if constexpr (kGen) {
+        const uint32_t r = s_row[wv][obase][q];
+        if (!(r >> 31)) col[r] = v;
+        else if (r != kNone) oslot[r & 0x7FFFFFFFu] = v;
+        continue;
+      }
       const int64_t row = piece_row(T, q);
       if (row < 0) {
         oslot[q >= T.NP0 ? 1 : 0] = v;
@@ -1624,7 +2284,7 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
 #pragma unroll
     for (int j = 0; j < kAggIpt; ++j) sv[sl[j]] = x[j];
   };
-  const int64_t ob2 = kNat ? 2 * nwt : nwt;
+  const int64_t ob2 = kGen ? 1 : kNat ? 2 * nwt : nwt;   // (kGen: s_row's)
   auto do_sum = [&](const uint64_t (&v)[kAggIpt], int f) {
     uint64_t x[kAggIpt];
 #pragma unroll
@@ -2011,6 +2671,9 @@ __global__ void k_zero_u32(uint32_t* p, int n) {
 }
 
 // ---------------------------------------------------------------------------
+// words read back by the host: flags, level offsets, interior pieces
+constexpr int kStageWords = 3 + kMaxLevels + 1 + kMaxLevels;
+
 struct AggLayout {
   int L;
   int64_t ntiles;
@@ -2068,6 +2731,10 @@ struct AggLayout {
   ClassSortLayout xsort;
   uint32_t* ipath;        // [D][n] general-path items by korder position
   uint16_t* igk;          // [n]
+  // groups of several runs
+  uint8_t* omask;         // [L][mstride] owners of every lane
+  int64_t mstride;        // 64 * (natural tiles + G)
+  uint32_t* interior;     // [kMaxLevels]
 };
 
 static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
@@ -2115,7 +2782,7 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.lp = sc.take<int32_t>(2 * L.lps);
   L.tg = sc.take<uint8_t>(L.ntiles_h + G);
   L.pair = sc.take<uint64_t>((int64_t)2 * G * kPairW);
-  L.stage = sc.take<int64_t>(3 + kMaxLevels + 1);
+  L.stage = sc.take<int64_t>(kStageWords);
   L.gs = sc.take<uint32_t>(G);
   L.ge = sc.take<uint32_t>(G);
   L.gtb = sc.take<uint32_t>(G + 1);
@@ -2131,6 +2798,9 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.xsort = class_sort_layout(sc, n, 256);
   L.ipath = sc.take<uint32_t>((int64_t)(D > 0 ? D : 1) * n);
   L.igk = sc.take<uint16_t>(n);
+  L.mstride = (int64_t)kWave * (L.ntiles_h + G);
+  L.omask = sc.take<uint8_t>((int64_t)L.L * L.mstride);
+  L.interior = sc.take<uint32_t>(kMaxLevels);
   return L;
 }
 
@@ -2180,6 +2850,35 @@ static int exact_group_ids(const AggLayout& L, const RecSrc& S, int lmax,
 
 using namespace chopper;
 
+// Geometry of the natural tiles (flag 2 set when the order does not qualify).
+static int nat_geometry(const AggLayout& L, const RecSrc& S, hipStream_t s) {
+  const int64_t Th = L.ntiles_h;
+  CHOPPER_HIP(launch("agg_nat_init", k_nat_init, dim3(1), dim3(kBlock), s,
+                     L.hflags, L.gs, L.G));
+  CHOPPER_HIP(launch("agg_nat_pre", k_nat_pre,
+                     dim3((unsigned)ceil_div(Th, (int64_t)kWavesPerBlock)),
+                     dim3(kBlock), s, S.n, L.G, S.gpu, S.cls, S.start, Th,
+                     L.lps, L.lpraw, L.gs, L.hflags + 2));
+  CHOPPER_HIP(launch("agg_nat_tiles", k_nat_tiles,
+                     dim3((unsigned)(1 + ceil_div(Th, kLpSpan))), dim3(1024), s,
+                     S.n, L.G, Th, L.lps, (const int32_t*)L.lpraw, L.lp,
+                     (const uint32_t*)L.gs, L.ge, L.gtb, L.tg,
+                     (const uint32_t*)(L.hflags + 2)));
+  return CHOPPER_OK;
+}
+
+// GPU rows and the workload rows from the level-0 rows.
+static int gpu_rows(const AggLayout& L, const RowsDev& R, int D, int nfields,
+                    const int64_t* level_offset, hipStream_t s) {
+  CHOPPER_HIP(launch("agg_gpu_rows", k_agg_gpu_sums,
+                     dim3((unsigned)(2 * L.G)), dim3(kBlock), s, level_offset,
+                     R, nfields, L.pair));
+  CHOPPER_HIP(launch("agg_workload_from_gpu", k_agg_gpu_finish, dim3(1),
+                     dim3(1024), s, level_offset, D, R, nfields, 2 * L.G,
+                     (const uint64_t*)L.pair));
+  return CHOPPER_OK;
+}
+
 // Fast path over all requested levels (MaxD >= depth); returns 1 when the
 // groups are not runs and the general path must be used.  The natural tiles
 // are tried first; when the input order does not qualify, the korder tiles
@@ -2189,7 +2888,8 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
                     const Overflow& ovf, int64_t T, int Lv, uint32_t act,
                     int D, int64_t M, int nfields, chopper_rows* rows,
                     int level, bool want_workload, uint32_t* status,
-                    hipEvent_t ready, hipStream_t s) {
+                    hipEvent_t ready, hipStream_t s, int* nat_out,
+                    bool* conflict) {
   int rc = CHOPPER_OK;
   const int64_t Th = L.ntiles_h;
   const int G = L.G;
@@ -2204,16 +2904,16 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
     const dim3 grid((unsigned)ceil_div(NW, (int64_t)kWavesPerBlock));
     if (two)
       CHOPPER_HIP(launch("agg_fast_reduce_records",
-                         k_agg_fast_reduce<kMD, FromRecords, true, true>,
+                         k_agg_fast_reduce<kMD, FromRecords, true, true, false>,
                          grid, dim3(kBlock), s, fr, NG, li, D, M, tb,
                          (const uint32_t*)(tb - L.nstride),
-                         (const int64_t*)nullptr, R, ovf, NW));
+                         (const int64_t*)nullptr, R, ovf, NW, GenRed{}));
     else
       CHOPPER_HIP(launch("agg_fast_reduce_records",
-                         k_agg_fast_reduce<kMD, FromRecords, false, true>,
+                         k_agg_fast_reduce<kMD, FromRecords, false, true, false>,
                          grid, dim3(kBlock), s, fr, NG, li, D, M, tb,
                          (const uint32_t*)nullptr, (const int64_t*)nullptr,
-                         R, ovf, NW));
+                         R, ovf, NW, GenRed{}));
     return CHOPPER_OK;
   };
   // the level the records reduce to (with li0 - 1 when two0)
@@ -2249,17 +2949,8 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
     for (int i = 0; i <= Lv; ++i) lo_h[i] = st[3 + i];
     return CHOPPER_OK;
   };
-  CHOPPER_HIP(launch("agg_nat_init", k_nat_init, dim3(1), dim3(kBlock), s,
-                     L.hflags, L.gs, G));
-  CHOPPER_HIP(launch("agg_nat_pre", k_nat_pre,
-                     dim3((unsigned)ceil_div(Th, (int64_t)kWavesPerBlock)),
-                     dim3(kBlock), s, S.n, G, S.gpu, S.cls, S.start, Th,
-                     L.lps, L.lpraw, L.gs, L.hflags + 2));
-  CHOPPER_HIP(launch("agg_nat_tiles", k_nat_tiles,
-                     dim3((unsigned)(1 + ceil_div(Th, kLpSpan))), dim3(1024), s,
-                     S.n, G, Th, L.lps, (const int32_t*)L.lpraw, L.lp,
-                     (const uint32_t*)L.gs, L.ge, L.gtb, L.tg,
-                     (const uint32_t*)(L.hflags + 2)));
+  rc = nat_geometry(L, S, s);
+  if (rc != CHOPPER_OK) return rc;
   CHOPPER_HIP(launch("agg_heads_nat", k_agg_heads_nat<kMD>,
                      dim3((unsigned)ceil_div(NW, (int64_t)kWavesPerBlock)),
                      dim3(kBlock), s, S, N, act, 0, Lv - 1, D, M, L.nstride,
@@ -2274,6 +2965,7 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
   rc = fetch_stage(true);
   if (rc != CHOPPER_OK) return rc;
   const bool nat = hf[2] == 0;
+  *nat_out = nat ? 1 : 0;
   if (!nat) {
     CHOPPER_HIP(launch("agg_zero", k_zero_u32, dim3(1), dim3(64), s,
                        L.hflags, 3));
@@ -2296,6 +2988,7 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
     if (b > rows->cap) b = rows->cap;
     return b > a ? b - a : 0;
   };
+  if (hf[0] & 2u) *conflict = true;
   if (hf[0] != 0) return 1;
   // finer < 0: from the records (two levels, li and li - 1, when `two`)
   auto fast_level = [&](int li, int finer, bool two) -> int {
@@ -2312,16 +3005,16 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
         const uint32_t* tb = L.htb + (int64_t)li * Th;
         if (two)
           CHOPPER_HIP(launch("agg_fast_reduce_records",
-                             k_agg_fast_reduce<kMD, FromRecords, true, false>,
+                             k_agg_fast_reduce<kMD, FromRecords, true, false, false>,
                              dim3((unsigned)T), dim3(kBlock), s, fr, none, li,
                              D, M, tb, (const uint32_t*)(tb - Th),
-                             (const int64_t*)nullptr, R, ovf, Th));
+                             (const int64_t*)nullptr, R, ovf, Th, GenRed{}));
         else
           CHOPPER_HIP(launch("agg_fast_reduce_records",
-                             k_agg_fast_reduce<kMD, FromRecords, false, false>,
+                             k_agg_fast_reduce<kMD, FromRecords, false, false, false>,
                              dim3((unsigned)T), dim3(kBlock), s, fr, none, li,
                              D, M, tb, (const uint32_t*)nullptr,
-                             (const int64_t*)nullptr, R, ovf, Th));
+                             (const int64_t*)nullptr, R, ovf, Th, GenRed{}));
         ns = two ? 2 * Th : Th;
       }
       CHOPPER_HIP(launch("agg_apply_overflow", k_agg_apply_overflow,
@@ -2347,16 +3040,17 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
       const int64_t* r0 = rows->level_offset + li;
       if (two)
         CHOPPER_HIP(launch("agg_fast_reduce_rows",
-                           k_agg_fast_reduce<kMD, FromRows, true, false>,
+                           k_agg_fast_reduce<kMD, FromRows, true, false, false>,
                            dim3(gr), dim3(kBlock), s, src, none, li, D, M,
                            (const uint32_t*)(L.htb2 + nw),
-                           (const uint32_t*)L.htb2, r0, R, ovf, nw));
+                           (const uint32_t*)L.htb2, r0, R, ovf, nw,
+                           GenRed{}));
       else
         CHOPPER_HIP(launch("agg_fast_reduce_rows",
-                           k_agg_fast_reduce<kMD, FromRows, false, false>,
+                           k_agg_fast_reduce<kMD, FromRows, false, false, false>,
                            dim3(gr), dim3(kBlock), s, src, none, li, D, M,
                            (const uint32_t*)L.htb2, (const uint32_t*)nullptr,
-                           r0, R, ovf, nw));
+                           r0, R, ovf, nw, GenRed{}));
       const int64_t ns = (two ? 2 : 1) * nw;
       CHOPPER_HIP(launch("agg_apply_overflow", k_agg_apply_overflow,
                          grid_for(ns, kBlock), dim3(kBlock), s, ovf, R,
@@ -2375,18 +3069,202 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
       rc = fast_level(li, li + 1, li >= 1);
       if (rc != CHOPPER_OK) return rc;
     }
-    CHOPPER_HIP(launch("agg_gpu_rows", k_agg_gpu_sums,
-                       dim3((unsigned)(2 * L.G)), dim3(kBlock), s,
-                       (const int64_t*)rows->level_offset, R, nfields,
-                       L.pair));
-    CHOPPER_HIP(launch("agg_workload_from_gpu", k_agg_gpu_finish, dim3(1),
-                       dim3(1024), s, (const int64_t*)rows->level_offset, D,
-                       R, nfields, 2 * L.G, (const uint64_t*)L.pair));
+    rc = gpu_rows(L, R, D, nfields, rows->level_offset, s);
+    if (rc != CHOPPER_OK) return rc;
   } else {
     rc = fast_level(level == CHOPPER_LEVEL_GPU ? D : level, -1, false);
     if (rc != CHOPPER_OK) return rc;
   }
   return CHOPPER_OK;
+}
+
+// Groups of several runs (k_gen_elect above) over all requested levels.
+// nat: 1 natural tiles, 0 korder tiles, -1 not known yet (the natural
+// geometry is made here, and the korder tiles taken when the order does not
+// qualify).  Returns 1 when the call must take the element-wise path: an
+// item whose marker is out of range, more pieces to add than the overflow
+// list holds, or (with *conflict set) markers that are not nested.
+template <int kMD, bool kNat>
+static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
+                         const Overflow& ovf, int Lv, uint32_t act, int D,
+                         int64_t M, int nfields, chopper_rows* rows, int level,
+                         bool want_workload, uint32_t* status,
+                         hipEvent_t ready, hipStream_t s, bool* conflict,
+                         bool* bad_order) {
+  const int64_t Th = L.ntiles_h;
+  const int64_t nwt = kNat ? Th + L.G : Th;
+  const int64_t stride = kNat ? L.nstride : Th;
+  uint32_t* tc = kNat ? L.ntc : L.htc;
+  uint32_t* tb = kNat ? L.ntb : L.htb;
+  const NatGeom N{L.gtb, L.tg, L.gs, L.ge, L.lp, L.hflags + 2, Th, L.lps, L.G};
+  const dim3 grid((unsigned)ceil_div(nwt, (int64_t)kWavesPerBlock));
+  GenTab tab;
+  int64_t maxks = 1;
+  for (int li = 0; li < kMaxLevels; ++li) {
+    tab.own[li] = li < Lv ? L.own[li] : nullptr;
+    tab.ks[li] = li < Lv && ((act >> li) & 1u) ? key_space(li, D, M) : 0;
+    if (tab.ks[li] > maxks) maxks = tab.ks[li];
+  }
+  // one table entry in sixteen bytes a thread, at most 2,048 blocks a level
+  unsigned fx = (unsigned)ceil_div(maxks, (int64_t)4 * kBlock);
+  if (fx > 2048) fx = 2048;
+  FromRecords fr{S};
+  int64_t st[kStageWords];
+  // (records out of order usually come with markers out of order)
+  bool plain = false;
+  if (!kNat) {
+    CHOPPER_HIP(launch("agg_items", k_agg_items, grid_for(S.n, kBlock),
+                       dim3(kBlock), s, S, L.ipath, L.igk));
+    fr.S.ipath = L.ipath;
+    fr.S.igk = L.igk;
+  }
+  for (;;) {
+    CHOPPER_HIP(launch("agg_gen_fill", k_gen_fill, dim3(fx, (unsigned)(D + 1)),
+                       dim3(kBlock), s, tab, act, L.hflags, L.interior,
+                       L.ovf_count));
+    if (plain)
+      CHOPPER_HIP(launch("agg_gen_elect", k_gen_elect<kMD, kNat, kNat>, grid,
+                         dim3(kBlock), s, fr, N, act, D, M, nwt, tab,
+                         L.hflags));
+    else
+      CHOPPER_HIP(launch("agg_gen_elect", k_gen_elect<kMD, kNat, false>, grid,
+                         dim3(kBlock), s, fr, N, act, D, M, nwt, tab,
+                         L.hflags));
+    CHOPPER_HIP(launch("agg_gen_count", k_gen_count<kMD, FromRecords, kNat>,
+                       grid, dim3(kBlock), s, fr, N, act, 0, Lv - 1, D, M, nwt,
+                       stride, tab, tc, L.omask, L.mstride, L.hflags,
+                       L.interior, L.ovf_count, status));
+    CHOPPER_HIP(exclusive_scan<uint32_t>(tc, tb, (int64_t)Lv * stride,
+                                         kNat ? L.nscan : L.hscan, L.htotal,
+                                         s));
+    CHOPPER_HIP(launch("agg_offsets", k_gen_offsets, dim3(1), dim3(64), s, Lv,
+                       stride, (const uint32_t*)tb, (const uint32_t*)L.htotal,
+                       (const uint32_t*)L.hflags, (const uint32_t*)L.interior,
+                       kNat, want_workload, rows->cap, rows->level_offset,
+                       L.stage, status));
+    {
+      ReadBack rb;
+      CHOPPER_HIP(read_back_start(
+          L.stage, sizeof(int64_t) * (size_t)(3 + Lv + 1 + Lv), s, &rb));
+      if (ready) CHOPPER_HIP(hipStreamWaitEvent(s, ready, 0));
+      CHOPPER_HIP(read_back_finish(&rb, st));
+    }
+    if (kNat && st[2] != 0) {
+      *bad_order = true;
+      return 1;
+    }
+    if (!(plain && st[0] == 4)) break;
+    plain = false;
+  }
+  const int64_t* lo_h = st + 3;
+  const int64_t* inner = st + 3 + Lv + 1;
+  if (st[0] & 2) *conflict = true;
+  if (st[0] != 0) return 1;
+  if (lo_h[Lv] > rows->cap) return CHOPPER_OK;     // (ROWS_OVERFLOW is set)
+  // the levels in the order they are reduced: (level, source, with the next)
+  struct Pass { int li; bool records, two; };
+  Pass ps[kMaxLevels];
+  int np = 0;
+  if (level == CHOPPER_LEVEL_ALL) {
+    ps[np++] = Pass{D > 0 ? D - 1 : D, true, D >= 2};
+    for (int li = D - (D >= 2 ? 3 : 2); li >= 0; li -= 2)
+      ps[np++] = Pass{li, false, li >= 1};
+  } else {
+    ps[np++] = Pass{level == CHOPPER_LEVEL_GPU ? D : level, true, false};
+  }
+  // pieces a pass may leave to the overflow list: those inside the tiles
+  // and the first of every run of a tile
+  auto left = [&](const Pass& q) {
+    const int64_t tiles = q.records ? (kNat ? 2 : 1) * nwt : Th;
+    return inner[q.li] + tiles + (q.two ? inner[q.li - 1] + tiles : 0);
+  };
+  for (int i = 0; i < np; ++i)
+    if (left(ps[i]) > ovf.cap) return 1;
+  for (int i = 0; i < np; ++i) {
+    const Pass& q = ps[i];
+    const int li = q.li;
+    GenRed GR;
+    GR.own = tab.own[li];
+    GR.own2 = q.two ? tab.own[li - 1] : tab.own[li];
+    if (q.records) {
+      const uint32_t* tbl = tb + (int64_t)li * stride;
+      GR.mask = L.omask + (int64_t)li * L.mstride;
+      GR.mask2 = q.two ? GR.mask - L.mstride : nullptr;
+      if (q.two)
+        CHOPPER_HIP(launch("agg_gen_reduce_records",
+                           k_agg_fast_reduce<kMD, FromRecords, true, kNat, true>,
+                           grid, dim3(kBlock), s, fr, N, li, D, M, tbl,
+                           tbl - stride, (const int64_t*)nullptr, R, ovf, nwt,
+                           GR));
+      else
+        CHOPPER_HIP(launch("agg_gen_reduce_records",
+                           k_agg_fast_reduce<kMD, FromRecords, false, kNat, true>,
+                           grid, dim3(kBlock), s, fr, N, li, D, M, tbl,
+                           (const uint32_t*)nullptr, (const int64_t*)nullptr,
+                           R, ovf, nwt, GR));
+    } else {
+      const int64_t cnt = lo_h[li + 2] - lo_h[li + 1];
+      if (cnt == 0) break;
+      const int64_t nw = ceil_div(cnt, (int64_t)kWaveTile);
+      const dim3 gr((unsigned)ceil_div(nw, (int64_t)kWavesPerBlock));
+      FromRows src{R, M, rows->level_offset, li + 1};
+      const int lv0 = q.two ? li - 1 : li;
+      const uint32_t lact = q.two ? (3u << (li - 1)) : (1u << li);
+      CHOPPER_HIP(launch("agg_gen_count_rows",
+                         k_gen_count<kMD, FromRows, false>, gr, dim3(kBlock),
+                         s, src, NatGeom{}, lact, lv0, li, D, M, nw, nw, tab,
+                         L.htc2, L.omask, L.mstride, L.hflags, L.interior,
+                         L.ovf_count, status));
+      CHOPPER_HIP(exclusive_scan<uint32_t>(L.htc2, L.htb2,
+                                           (q.two ? 2 : 1) * nw, L.hscan,
+                                           L.htotal + 1, s));
+      GR.mask = L.omask + (q.two ? L.mstride : 0);
+      GR.mask2 = L.omask;
+      const int64_t* r0 = rows->level_offset + li;
+      if (q.two)
+        CHOPPER_HIP(launch("agg_gen_reduce_rows",
+                           k_agg_fast_reduce<kMD, FromRows, true, false, true>,
+                           gr, dim3(kBlock), s, src, NatGeom{}, li, D, M,
+                           (const uint32_t*)(L.htb2 + nw),
+                           (const uint32_t*)L.htb2, r0, R, ovf, nw, GR));
+      else
+        CHOPPER_HIP(launch("agg_gen_reduce_rows",
+                           k_agg_fast_reduce<kMD, FromRows, false, false, true>,
+                           gr, dim3(kBlock), s, src, NatGeom{}, li, D, M,
+                           (const uint32_t*)L.htb2, (const uint32_t*)nullptr,
+                           r0, R, ovf, nw, GR));
+    }
+    CHOPPER_HIP(launch("agg_gen_apply", k_gen_apply,
+                       grid_for(left(q), kBlock), dim3(kBlock), s, ovf, R,
+                       nfields, (const uint32_t*)GR.own,
+                       (const uint32_t*)GR.own2));
+  }
+  if (level == CHOPPER_LEVEL_ALL)
+    return gpu_rows(L, R, D, nfields, rows->level_offset, s);
+  return CHOPPER_OK;
+}
+
+template <int kMD>
+static int agg_gen(const AggLayout& L, const RecSrc& S, const RowsDev& R,
+                   const Overflow& ovf, int Lv, uint32_t act, int D,
+                   int64_t M, int nfields, chopper_rows* rows, int level,
+                   bool want_workload, uint32_t* status, hipEvent_t ready,
+                   hipStream_t s, int nat, bool* conflict) {
+  if (nat < 0) {
+    const int rc = nat_geometry(L, S, s);
+    if (rc != CHOPPER_OK) return rc;
+  }
+  if (nat != 0) {
+    bool bad = false;
+    const int rc = agg_gen_tiles<kMD, true>(
+        L, S, R, ovf, Lv, act, D, M, nfields, rows, level, want_workload,
+        status, ready, s, conflict, &bad);
+    if (!bad) return rc;
+  }
+  bool bad = false;
+  return agg_gen_tiles<kMD, false>(L, S, R, ovf, Lv, act, D, M, nfields, rows,
+                                   level, want_workload, status, ready, s,
+                                   conflict, &bad);
 }
 
 extern "C" int chopper_aggregate(const chopper_records* rec,
@@ -2488,14 +3366,34 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
 
   // ---- fast path: every group is one run of consecutive records
   // (the fast path addresses columns with 32-bit byte offsets)
-  if (n > 0 && !filter && level != CHOPPER_LEVEL_WORKLOAD &&
-      n < ((int64_t)1 << 29) && rows->cap < ((int64_t)1 << 29)) {
+  const bool tiles = n > 0 && level != CHOPPER_LEVEL_WORKLOAD &&
+                     n < ((int64_t)1 << 29) && rows->cap < ((int64_t)1 << 29);
+  const hipEvent_t rdy = (hipEvent_t)ready;
+  int nat = -1;
+  bool conflict = false;
+  if (tiles && !filter) {
     rc = D <= 4 ? agg_fast<4>(L, S, R, ovf, T, Lv, act, D, M, nfields, rows,
-                              level, want_workload, status,
-                              (hipEvent_t)ready, s)
+                              level, want_workload, status, rdy, s, &nat,
+                              &conflict)
+       : D <= 6 ? agg_fast<6>(L, S, R, ovf, T, Lv, act, D, M, nfields, rows,
+                              level, want_workload, status, rdy, s, &nat,
+                              &conflict)
                 : agg_fast<8>(L, S, R, ovf, T, Lv, act, D, M, nfields, rows,
-                              level, want_workload, status,
-                              (hipEvent_t)ready, s);
+                              level, want_workload, status, rdy, s, &nat,
+                              &conflict);
+    if (rc != 1) return rc;
+  }
+  // ---- groups of several runs, and selections
+  if (tiles && M < kGenMaxM && !conflict) {
+    rc = D <= 4 ? agg_gen<4>(L, S, R, ovf, Lv, act, D, M, nfields, rows,
+                             level, want_workload, status, rdy, s, nat,
+                             &conflict)
+       : D <= 6 ? agg_gen<6>(L, S, R, ovf, Lv, act, D, M, nfields, rows,
+                             level, want_workload, status, rdy, s, nat,
+                             &conflict)
+                : agg_gen<8>(L, S, R, ovf, Lv, act, D, M, nfields, rows,
+                             level, want_workload, status, rdy, s, nat,
+                             &conflict);
     if (rc != 1) return rc;
   }
 
@@ -2512,9 +3410,6 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
   for (int li = 0; li < Lv; ++li) maxks = L.ks[li] > maxks ? L.ks[li] : maxks;
   unsigned fx = (unsigned)ceil_div(maxks, kBlock);
   if (fx > 4096) fx = 4096;
-  CHOPPER_HIP(launch("agg_fill_owner", k_fill_u32_many, dim3(fx, Lv),
-                     dim3(kBlock), s, L.own_tab, (const int64_t*)L.ks_dev, Lv,
-                     act));
   const uint32_t atomic_levels = (1u << D) | (1u << (D + 1));
   if (n > 0) {
     // the items once, in korder order, for the passes below
@@ -2522,24 +3417,7 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
                        dim3(kBlock), s, S, L.ipath, L.igk));
     S.ipath = L.ipath;
     S.igk = L.igk;
-    CHOPPER_HIP(launch("agg_elect", k_agg_elect, dim3((unsigned)T),
-                       dim3(kBlock), s, S, act, L.own_tab));
-    CHOPPER_HIP(launch("agg_count", k_agg_count, dim3((unsigned)T),
-                       dim3(kBlock), s, S, act, L.own_tab, T, L.tilecnt));
   }
-  CHOPPER_HIP(exclusive_scan<uint32_t>(L.tilecnt, L.tilebase, (int64_t)Lv * T,
-                                       L.scantmp, L.total, s));
-  CHOPPER_HIP(launch("agg_offsets", k_agg_offsets, dim3(1), dim3(64), s, Lv, T,
-                     (const uint32_t*)L.tilebase, (const uint32_t*)L.total,
-                     rows->cap, rows->level_offset, status));
-  if (n == 0) return CHOPPER_OK;
-  CHOPPER_HIP(launch("agg_assign", k_agg_assign, dim3((unsigned)T),
-                     dim3(kBlock), s, S, act, atomic_levels, L.own_tab,
-                     L.rowof_tab, T, (const uint32_t*)L.tilebase, R));
-  CHOPPER_HIP(launch("agg_zero", k_zero_u32, dim3(1), dim3(64), s,
-                     L.ovf_count, 2));
-  CHOPPER_HIP(launch("agg_zero", k_zero_u32, dim3(1), dim3(64), s,
-                     L.xflag, 1));
 
   // order of work: finest marker level from records, coarser marker levels
   // from the rows below, GPU rows from level-0 rows, workload from GPU rows
@@ -2595,29 +3473,16 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
     if ((act >> li) & 1u) order_levels[nl++] = li;
   if ((act >> D) & 1u) order_levels[nl++] = D;
   if ((act >> (D + 1)) & 1u) order_levels[nl++] = D + 1;
-  for (int q = 0; q < nl; ++q) {
-    const int li = order_levels[q];
-    rc = run_level(li, (atomic_levels >> li) & 1u);
-    if (rc != CHOPPER_OK) return rc;
-  }
-  // markers not nested (a record's path differed from its row's): group by
-  // the whole path, with exact group ids, and run the levels again
-  uint32_t conflict = 0;
-  CHOPPER_HIP(read_back(L.xflag, &conflict, sizeof(uint32_t), s));
-  int lmax = -1;
-  for (int li = 0; li < D; ++li)
-    if ((act >> li) & 1u) lmax = li;
-  if (conflict && lmax >= 0 && S.gk == nullptr) {
-    rc = exact_group_ids(L, S, lmax, s);
-    if (rc != CHOPPER_OK) return rc;
-    S.gk = L.gk;
+  auto run_all = [&]() -> int {
     CHOPPER_HIP(launch("agg_fill_owner", k_fill_u32_many, dim3(fx, Lv),
                        dim3(kBlock), s, L.own_tab, (const int64_t*)L.ks_dev,
                        Lv, act));
-    CHOPPER_HIP(launch("agg_elect", k_agg_elect, dim3((unsigned)T),
-                       dim3(kBlock), s, S, act, L.own_tab));
-    CHOPPER_HIP(launch("agg_count", k_agg_count, dim3((unsigned)T),
-                       dim3(kBlock), s, S, act, L.own_tab, T, L.tilecnt));
+    if (n > 0) {
+      CHOPPER_HIP(launch("agg_elect", k_agg_elect, dim3((unsigned)T),
+                         dim3(kBlock), s, S, act, L.own_tab));
+      CHOPPER_HIP(launch("agg_count", k_agg_count, dim3((unsigned)T),
+                         dim3(kBlock), s, S, act, L.own_tab, T, L.tilecnt));
+    }
     CHOPPER_HIP(exclusive_scan<uint32_t>(L.tilecnt, L.tilebase,
                                          (int64_t)Lv * T, L.scantmp, L.total,
                                          s));
@@ -2625,6 +3490,7 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
                        T, (const uint32_t*)L.tilebase,
                        (const uint32_t*)L.total, rows->cap,
                        rows->level_offset, status));
+    if (n == 0) return CHOPPER_OK;
     CHOPPER_HIP(launch("agg_assign", k_agg_assign, dim3((unsigned)T),
                        dim3(kBlock), s, S, act, atomic_levels, L.own_tab,
                        L.rowof_tab, T, (const uint32_t*)L.tilebase, R));
@@ -2632,9 +3498,33 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
                        L.ovf_count, 2));
     for (int q = 0; q < nl; ++q) {
       const int li = order_levels[q];
-      rc = run_level(li, (atomic_levels >> li) & 1u);
-      if (rc != CHOPPER_OK) return rc;
+      const int r = run_level(li, (atomic_levels >> li) & 1u);
+      if (r != CHOPPER_OK) return r;
     }
+    return CHOPPER_OK;
+  };
+  // markers not nested (a record's path differs from its row's): grouped by
+  // the whole path, with exact group ids -- at once when the tiles above
+  // met it, else after the deepest-marker pass that does
+  int lmax = -1;
+  for (int li = 0; li < D; ++li)
+    if ((act >> li) & 1u) lmax = li;
+  if (n > 0)
+    CHOPPER_HIP(launch("agg_zero", k_zero_u32, dim3(1), dim3(64), s, L.xflag,
+                       1));
+  if (!conflict) {
+    rc = run_all();
+    if (rc != CHOPPER_OK || n == 0) return rc;
+    uint32_t met = 0;
+    CHOPPER_HIP(read_back(L.xflag, &met, sizeof(uint32_t), s));
+    conflict = met != 0;
+  }
+  if (conflict && lmax >= 0) {
+    rc = exact_group_ids(L, S, lmax, s);
+    if (rc != CHOPPER_OK) return rc;
+    S.gk = L.gk;
+    rc = run_all();
+    if (rc != CHOPPER_OK) return rc;
   }
   // an overflow list that did not fit: redo the marker levels with atomics
   uint32_t lost = 0;
