@@ -35,6 +35,38 @@ __device__ inline void load8_i64(const int64_t* p, int64_t i0, int64_t n,
   }
 }
 
+// Lanes among those with v that hold the same digit as this lane.  Rows of
+// one or two distinct digits -- the usual case for classes of consecutive
+// records -- take two or three ballots; other rows match bit by bit.
+__device__ inline uint64_t digit_peers(uint32_t d, bool v, int nbits) {
+  const uint64_t vm = __ballot(v);
+  if (vm == 0) return 0;
+  // (the lanes read are uniform: a lane read, not a permute through LDS)
+  const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane(
+      (int)d, __ffsll((long long)vm) - 1);
+  const uint64_t m0 = __ballot(v && d == d0);
+  if (m0 == vm) return vm;
+  const uint64_t rest = vm & ~m0;
+  const uint32_t d1 = (uint32_t)__builtin_amdgcn_readlane(
+      (int)d, __ffsll((long long)rest) - 1);
+  const uint64_t m1 = __ballot(v && d == d1);
+  if ((m0 | m1) == vm) return d == d0 ? m0 : m1;
+  uint64_t peers = vm;
+  for (int b = 0; b < nbits; ++b) {
+    const bool bit = (d >> b) & 1u;
+    const uint64_t bb = __ballot(bit);
+    peers &= bit ? bb : ~bb;
+  }
+  return peers;
+}
+
+// number of ballots that separate c classes
+__host__ __device__ inline int class_bits(int c) {
+  int b = 0;
+  while (b < 8 && (1 << b) < c) ++b;
+  return b;
+}
+
 // Class ids of the eight items i0 .. i0 + 7 (v[j]: i0 + j < n); accessors
 // over plain columns override it with vector loads.
 template <typename Acc>

@@ -3,15 +3,20 @@
 // correlation, 25-75 % and min-max fills; Section VI duration breakdown,
 // eqs. 6-10).
 //
-// The instances (compute rows of the operation level) are partitioned by
-// (phase, operation) group into compact columns of the overlap ratio (Q30)
-// and the time (the grouping pass adds the three counters of every group in
-// LDS on the way).  Blocks of 8192 instances of one group then
-// add the exact moments in 64-bit words (halves of the products that would
-// overflow) -- integer sums do not depend on their order, so the derived
-// doubles are the same IEEE operations on the same values as anywhere else
-// -- and build the histograms of a radix selection of six order statistics
-// of the ratio per group, eight bits per pass, all groups at once.
+// The instances (compute rows of the operation level) are put in order of
+// (phase, operation) group, row order kept inside a group, as compact columns
+// of the overlap ratio (Q30), the time and the GPU: a counting pass writes
+// every block's instances per group, which one scan turns into every block's
+// first slot of each group, and a second pass writes the columns.  (The
+// counting pass adds the three counters of every group in LDS on the way.)
+// Blocks of 8192 instances of one group then add the exact moments in 64-bit
+// words (halves of the products that would overflow) -- integer sums do not
+// depend on their order, so the derived doubles are the same IEEE operations
+// on the same values as anywhere else -- and build the histograms of a radix
+// selection of six order statistics of the ratio per group, eleven bits and
+// then ten per pass, all groups at once.  The rows of a GPU follow each
+// other, so the instances of a group on one GPU are a stretch of the group's
+// column; one block selects that CDF's order statistics from it.
 #include "common.h"
 #include "sort.h"
 #include "wave.h"
@@ -25,10 +30,24 @@ namespace {
 constexpr int kMaxGroups = 16 * 128;
 constexpr int kStatT = 1024;
 constexpr int kStatIpt = 8;
-constexpr int kRowSpan = kStatT * kStatIpt;   // rows per block
+// rows per block of the two row passes: eight waves, whose 16-bit counts of
+// up to 2,048 groups take 32 KB of LDS
+constexpr int kRowT = 512;
+constexpr int kRowSpan = kRowT * kStatIpt;
 constexpr int kChunk = kStatT * kStatIpt;     // instances per block
 constexpr int kRanks = 6;                     // order statistics per group
 constexpr int kSums = 8;                      // exact moment words per group
+constexpr int kTopBits = 11;                  // digits of a ratio (31 bits)
+constexpr int kLowBits = 10;
+constexpr int kTopBins = 1 << kTopBits;
+constexpr int kLowBins = 1 << kLowBits;
+constexpr int kHistW = kRanks * kLowBins;     // histogram words of a group
+// Counter sums are kept in this many copies, by block: every block adds to
+// every group's words, and one copy would queue them all on a few lines.
+constexpr int kCopies = 32;
+constexpr uint16_t kNoGroup = 0xFFFFu;
+static_assert(kHistW >= kTopBins, "the first pass has one histogram");
+static_assert(kMaxGroups < kNoGroup, "group numbers are 16-bit");
 constexpr int kStats = 17;
 typedef __int128 i128;
 typedef unsigned __int128 u128;
@@ -78,66 +97,129 @@ __device__ inline double i128_to_double(i128 v) {
   return neg ? -d : d;
 }
 
-// add 1 for every active lane to h[bin] and return the lane's slot among
-// the adds (the old value plus its rank): one LDS atomic per wave when the
-// active lanes share the bin, else one per lane
-__device__ inline uint32_t lds_claim(uint32_t* h, uint32_t bin, bool act) {
+// add 1 for every active lane to h[bin]: one LDS add for the lanes that share
+// the first one's bin, then one per lane
+__device__ inline void lds_count(uint32_t* h, uint32_t bin, bool act) {
   const uint64_t m = __ballot(act);
-  if (m == 0) return 0;
+  if (m == 0) return;
   const int ld = __ffsll((long long)m) - 1;
   const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)bin, ld);
-  if (__ballot(act && bin == b0) == m) {
-    uint32_t base = 0;
-    if (lane_id() == ld) base = atomicAdd(&h[b0], (uint32_t)__popcll(m));
-    base = (uint32_t)__builtin_amdgcn_readlane((int)base, ld);
-    return base + lanes_below(m);
+  const uint64_t same = __ballot(act && bin == b0);
+  if (lane_id() == ld) atomicAdd(&h[b0], (uint32_t)__popcll(same));
+  if (act && bin != b0) atomicAdd(&h[bin], 1u);
+}
+
+// No overlap and full overlap: between them most instances, whose adds to
+// their two bins would queue.  A wave counts them by ballots instead and
+// adds its counts once (their digits below the first are 0).
+constexpr uint32_t kFull = 1u << 30;
+struct Ends {
+  uint32_t none = 0, full = 0;              // (the same in every lane)
+  // counts x's two, returns whether it is another instance
+  __device__ bool count(uint32_t x, bool ok) {
+    none += (uint32_t)__popcll(__ballot(ok && x == 0u));
+    full += (uint32_t)__popcll(__ballot(ok && x == kFull));
+    return ok && x != 0u && x != kFull;
   }
-  return act ? atomicAdd(&h[bin], 1u) : 0u;
+  __device__ void add_top(uint32_t* h) const {
+    if (lane_id() == 0 && none) atomicAdd(&h[0], none);
+    if (lane_id() == 1 && full) atomicAdd(&h[kFull >> (2 * kLowBits)], full);
+  }
+  __device__ void add_low(uint32_t* h, const uint32_t (&pre)[kRanks],
+                          uint32_t own, int sh) const {
+    const int hs = sh + kLowBits;
+#pragma unroll
+    for (int r = 0; r < kRanks; ++r) {
+      if (!((own >> r) & 1u) || lane_id() != 0) continue;
+      const uint32_t n = (pre[r] >> hs) == 0u             ? none
+                         : (pre[r] >> hs) == (kFull >> hs) ? full : 0u;
+      if (n) atomicAdd(&h[r * kLowBins], n);
+    }
+  }
+};
+
+// Ranks that still have the same prefix share the histogram of the first of
+// them (ranks are in ascending order, so they are neighbours): bit r of the
+// result is set for the ranks that have one of their own.
+__device__ inline uint32_t own_hist(const uint32_t (&pre)[kRanks]) {
+  uint32_t m = 1u;
+#pragma unroll
+  for (int r = 1; r < kRanks; ++r)
+    if (pre[r] != pre[r - 1]) m |= 1u << r;
+  return m;
 }
 
-__global__ void k_stats_clear_cdf(int64_t NGG, uint32_t* cnt,
-                                  uint64_t* ymin) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < NGG) {
-    cnt[i] = 0;
-    ymin[i] = ~0ull;
+// the rank whose histogram rank w uses
+__device__ inline int hist_of(const uint32_t (&pre)[kRanks], int w) {
+  const uint32_t m = own_hist(pre) & ((2u << w) - 1u);
+  return 31 - __clz((int)m);
+}
+
+// the candidates' digits of one instance into the ranks' histograms
+__device__ inline void count_digit(uint32_t* h, const uint32_t (&pre)[kRanks],
+                                   uint32_t own, uint32_t x, int sh, bool ok) {
+  const int hs = sh + kLowBits;
+  const uint32_t dig = (x >> sh) & (uint32_t)(kLowBins - 1);
+  uint32_t m = 0;
+#pragma unroll
+  for (int r = 0; r < kRanks; ++r)
+    m |= ok && (x >> hs) == (pre[r] >> hs) ? 1u << r : 0u;
+  m &= own;
+  if (__ballot(m != 0) == 0) return;
+#pragma unroll
+  for (int r = 0; r < kRanks; ++r)
+    if ((m >> r) & 1u) atomicAdd(&h[r * kLowBins + dig], 1u);
+}
+
+// CDF groups: instances, first slot and one past the last slot.
+struct Cells {
+  uint32_t* cnt;
+  uint32_t* beg;
+  uint32_t* end;
+};
+
+__global__ void k_stats_clear(int G, uint32_t* hist, int64_t nh,
+                              uint64_t* csum, Cells C, int64_t NGG) {
+  const int64_t step = (int64_t)gridDim.x * blockDim.x;
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t i = i0; i < nh; i += step) hist[i] = 0;
+  for (int64_t i = i0; i < 3 * (int64_t)G * kCopies; i += step) csum[i] = 0;
+  for (int64_t i = i0; i < NGG; i += step) {
+    C.cnt[i] = 0;
+    C.beg[i] = 0xFFFFFFFFu;
+    C.end[i] = 0;
   }
 }
 
-__global__ void k_stats_clear(uint32_t* cnt, int G, uint32_t* hist,
-                              int64_t nh, uint64_t* csum) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < G) cnt[i] = 0;
-  if (i < 3 * (int64_t)G) csum[i] = 0;
-  if (i < nh) hist[i] = 0;
-}
-
-// group of every row of the operation level (kNone when it is no
-// instance: not a compute row, zero length, or a label out of range) and
-// the instances per group
-__global__ __launch_bounds__(kStatT) void k_stats_keys(StatArgs A,
-                                                       uint32_t* key,
-                                                       uint32_t* cnt,
+// Group of every row of the operation level (kNoGroup when it is no
+// instance: not a compute row, zero length, or a label out of range) and the
+// instances per group of every block, hist[g * blocks + b].  Every column of
+// a thread's eight rows is requested before the labels are looked up, the
+// counters among them, so a thread waits twice, not eight times (0.103 to
+// 0.064 ms on 6.1M rows with counters, 0.25 GB).
+__global__ __launch_bounds__(kRowT) void k_stats_keys(StatArgs A,
+                                                       uint16_t* key,
+                                                       uint32_t* hist,
                                                        uint64_t* csum) {
-  __shared__ uint32_t s_h[kMaxGroups];
-  __shared__ uint64_t s_cs[3][kMaxGroups];   // counter sums (wrap mod 2^64)
+  extern __shared__ uint64_t s_cs[];        // [3][G] counter sums, then [G]
   const int G = A.P * A.O;
+  uint32_t* s_h = reinterpret_cast<uint32_t*>(s_cs + 3 * G);
   const bool ctr = A.nc >= 16;
-  for (int g = threadIdx.x; g < G; g += kStatT) {
+  for (int g = threadIdx.x; g < G; g += kRowT) {
     s_h[g] = 0;
-    s_cs[0][g] = s_cs[1][g] = s_cs[2][g] = 0;
+    s_cs[g] = s_cs[G + g] = s_cs[2 * G + g] = 0;
   }
   __syncthreads();
   int64_t lo, hi;
   level_range(A, lo, hi);
   const int64_t r0 = lo + (int64_t)blockIdx.x * kRowSpan + threadIdx.x;
-  // the rows' fields of all eight rows in flight at once, then the labels
   uint8_t kd[kStatIpt];
   int64_t du[kStatIpt];
   uint32_t mp[kStatIpt], mo[kStatIpt];
+  uint64_t c0[kStatIpt], c1[kStatIpt], c2[kStatIpt];
 #pragma unroll
   for (int k = 0; k < kStatIpt; ++k) {
-    const int64_t r = r0 + (int64_t)k * kStatT;
+    const int64_t r = r0 + (int64_t)k * kRowT;
     const bool ok = r < hi;
     kd[k] = ok ? A.kind[r] : (uint8_t)1;
     du[k] = ok ? A.dur[r] : 0;
@@ -146,67 +228,75 @@ __global__ __launch_bounds__(kStatT) void k_stats_keys(StatArgs A,
   }
 #pragma unroll
   for (int k = 0; k < kStatIpt; ++k) {
-    const int64_t r = r0 + (int64_t)k * kStatT;
-    uint32_t g = kNone;
-    if (kd[k] == 0 && du[k] > 0 && (int64_t)mp[k] < A.nm &&
-        (int64_t)mo[k] < A.nm) {
-      const uint32_t p = A.label[mp[k]], o = A.label[mo[k]];
-      if (p < (uint32_t)A.P && o < (uint32_t)A.O) g = p * (uint32_t)A.O + o;
-    }
-    if (r < hi) key[r - lo] = g;
-    lds_claim(s_h, g, g != kNone);
-    // GPU cycles, MFMA-busy cycles and FLOPs of the instance (eqs. 7, 8, 10)
-    if (ctr && g != kNone) {
-      atomicAdd((unsigned long long*)&s_cs[0][g],
-                (unsigned long long)A.ctr[0 * A.cap + r]);
-      atomicAdd((unsigned long long*)&s_cs[1][g],
-                (unsigned long long)A.ctr[1 * A.cap + r]);
-      atomicAdd((unsigned long long*)&s_cs[2][g],
-                (unsigned long long)A.ctr[11 * A.cap + r]);
+    // GPU cycles, MFMA-busy cycles and FLOPs of the row (eqs. 7, 8, 10)
+    const int64_t r = r0 + (int64_t)k * kRowT;
+    const bool ok = ctr && r < hi;
+    c0[k] = ok ? A.ctr[0 * A.cap + r] : 0;
+    c1[k] = ok ? A.ctr[1 * A.cap + r] : 0;
+    c2[k] = ok ? A.ctr[11 * A.cap + r] : 0;
+  }
+  uint32_t lp[kStatIpt], lo_[kStatIpt];
+  bool ok[kStatIpt];
+#pragma unroll
+  for (int k = 0; k < kStatIpt; ++k) {
+    ok[k] = kd[k] == 0 && du[k] > 0 && (int64_t)mp[k] < A.nm &&
+            (int64_t)mo[k] < A.nm;
+    lp[k] = ok[k] ? A.label[mp[k]] : 0u;
+    lo_[k] = ok[k] ? A.label[mo[k]] : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < kStatIpt; ++k) {
+    const int64_t r = r0 + (int64_t)k * kRowT;
+    ok[k] = ok[k] && lp[k] < (uint32_t)A.P && lo_[k] < (uint32_t)A.O;
+    const uint32_t g = ok[k] ? lp[k] * (uint32_t)A.O + lo_[k] : 0u;
+    if (r < hi) key[r - lo] = ok[k] ? (uint16_t)g : kNoGroup;
+    lds_count(s_h, g, ok[k]);
+    if (ctr && ok[k]) {
+      atomicAdd((unsigned long long*)&s_cs[g], (unsigned long long)c0[k]);
+      atomicAdd((unsigned long long*)&s_cs[G + g], (unsigned long long)c1[k]);
+      atomicAdd((unsigned long long*)&s_cs[2 * G + g],
+                (unsigned long long)c2[k]);
     }
   }
   __syncthreads();
-  for (int g = threadIdx.x; g < G; g += kStatT)
-    if (s_h[g]) {
-      atomicAdd(&cnt[g], s_h[g]);
-      if (ctr)
-        for (int f = 0; f < 3; ++f)
-          atomicAdd((unsigned long long*)&csum[3 * g + f],
-                    (unsigned long long)s_cs[f][g]);
-    }
+  for (int g = threadIdx.x; g < G; g += kRowT) {
+    hist[(int64_t)g * gridDim.x + blockIdx.x] = s_h[g];
+    if (ctr && s_h[g])
+      for (int f = 0; f < 3; ++f)
+        atomicAdd((unsigned long long*)&csum[(blockIdx.x % kCopies * 3 + f) *
+                                                 (int64_t)G + g],
+                  (unsigned long long)s_cs[f * G + g]);
+  }
 }
 
-// group offsets, fill cursors, chunk offsets and the ranks to select (one
-// block)
+// group offsets and counts from the scanned table, chunk offsets and the
+// ranks to select (one block)
 __global__ __launch_bounds__(kStatT) void k_stats_offsets(
-    const uint32_t* cnt, int G, uint32_t* off, uint32_t* cur, uint32_t* coff,
-    uint32_t* spre, int64_t* srank) {
-  __shared__ uint32_t s_w[2][kStatT / kWave];
+    const uint32_t* tab, int64_t nb, const uint32_t* total, int G,
+    uint32_t* cnt, uint32_t* off, uint32_t* coff, uint32_t* spre,
+    int64_t* srank) {
+  __shared__ uint32_t s_w[kStatT / kWave];
   const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
-  uint32_t carry = 0, ccarry = 0;
+  uint32_t ccarry = 0;
   for (int b0 = 0; b0 < G; b0 += kStatT) {
     const int g = b0 + t;
-    const uint32_t v = g < G ? cnt[g] : 0u;
-    const uint32_t c = (uint32_t)ceil_div(v, kChunk);
-    const uint32_t incl = wave_incl(v, OpAdd(), 0u);
-    const uint32_t cincl = wave_incl(c, OpAdd(), 0u);
-    if (lane == kWave - 1) {
-      s_w[0][w] = incl;
-      s_w[1][w] = cincl;
+    uint32_t v = 0;
+    if (g < G) {
+      const uint32_t a = tab[(int64_t)g * nb];
+      v = (g + 1 < G ? tab[(int64_t)(g + 1) * nb] : *total) - a;
+      off[g] = a;
+      cnt[g] = v;
     }
+    const uint32_t c = (uint32_t)ceil_div(v, kChunk);
+    const uint32_t cincl = wave_incl(c, OpAdd(), 0u);
+    if (lane == kWave - 1) s_w[w] = cincl;
     __syncthreads();
-    uint32_t pre = carry, tot = carry, cpre = ccarry, ctot = ccarry;
+    uint32_t cpre = ccarry, ctot = ccarry;
     for (int q = 0; q < kStatT / kWave; ++q) {
-      if (q < w) {
-        pre += s_w[0][q];
-        cpre += s_w[1][q];
-      }
-      tot += s_w[0][q];
-      ctot += s_w[1][q];
+      if (q < w) cpre += s_w[q];
+      ctot += s_w[q];
     }
     if (g < G) {
-      off[g] = pre + incl - v;
-      cur[g] = pre + incl - v;
       coff[g] = cpre + cincl - c;
       // v[0], v[(m-1)/4], v[(m-1)/2], v[m/2], v[3(m-1)/4], v[m-1]
       const int64_t m = v;
@@ -218,64 +308,100 @@ __global__ __launch_bounds__(kStatT) void k_stats_offsets(
         srank[g * kRanks + r] = want[r];
       }
     }
-    carry = tot;
     ccarry = ctot;
     __syncthreads();
   }
   if (t == 0) {
-    off[G] = carry;
+    off[G] = *total;
     coff[G] = ccarry;
   }
 }
 
-// every instance into its group's slots with its ratio x (Q30), its time y
-// and three counters: a block claims its slots of a group with one atomic
-// (the order inside a group is immaterial: sums are exact and quantiles are
-// order statistics)
-__global__ __launch_bounds__(kStatT) void k_stats_scatter(
-    StatArgs A, const uint32_t* key, uint32_t* cur, uint32_t* xs,
-    uint64_t* ys, uint32_t* status) {
-  __shared__ uint32_t s_n[kMaxGroups];
-  __shared__ uint32_t s_base[kMaxGroups];
+// Every instance into its slot of its group, row order kept, with its ratio
+// x (Q30), its time y and its GPU.  A wave takes 512 consecutive rows and
+// ranks them row by row (lanes of equal groups find each other by ballots;
+// the wave's running counts are in LDS); the block's table entry and the
+// waves before give the slot.  A block whose rows are all on one GPU --
+// every block but the few where one GPU's rows end -- notes the GPU, and the
+// CDF groups get its instances from the table; another block adds them one
+// by one.
+__global__ __launch_bounds__(kRowT) void k_stats_scatter(
+    StatArgs A, const uint8_t* gpu, int NG, const uint16_t* key,
+    const uint32_t* tab, uint32_t* xs, uint64_t* ys, uint8_t* hs,
+    uint16_t* bgpu, Cells C, uint32_t* status) {
+  extern __shared__ uint32_t s_base[];      // [G], then u16 [waves][G]
+  constexpr int kWaves = kRowT / kWave;
   const int G = A.P * A.O;
-  for (int g = threadIdx.x; g < G; g += kStatT) s_n[g] = 0;
-  __syncthreads();
+  uint16_t* s_cnt = reinterpret_cast<uint16_t*>(s_base + G);
+  for (int g = threadIdx.x; g < kWaves * G; g += kRowT) s_cnt[g] = 0;
   int64_t lo, hi;
   level_range(A, lo, hi);
-  const int64_t r0 = lo + (int64_t)blockIdx.x * kRowSpan + threadIdx.x;
-  uint32_t g[kStatIpt], slot[kStatIpt];
+  const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
+  const int64_t b0 = lo + (int64_t)blockIdx.x * kRowSpan;
+  const int64_t r0 = b0 + (int64_t)w * (kStatIpt * kWave) + lane;
+  uint32_t g[kStatIpt], rank[kStatIpt], h[kStatIpt];
   int64_t du[kStatIpt], ol[kStatIpt], gp[kStatIpt];
 #pragma unroll
   for (int k = 0; k < kStatIpt; ++k) {
-    const int64_t r = r0 + (int64_t)k * kStatT;
+    const int64_t r = r0 + (int64_t)k * kWave;
     const bool ok = r < hi;
-    g[k] = ok ? key[r - lo] : kNone;
+    g[k] = ok ? key[r - lo] : kNoGroup;
+    h[k] = ok ? gpu[r] : 0u;
     du[k] = ok ? A.dur[r] : 1;
     ol[k] = ok ? A.ovl[r] : 0;
     gp[k] = ok ? A.gap[r] : 0;
   }
-#pragma unroll
-  for (int k = 0; k < kStatIpt; ++k)
-    slot[k] = lds_claim(s_n, g[k], g[k] != kNone);
+  const uint32_t h0 = b0 < hi ? (uint32_t)gpu[b0] : 0u;
   __syncthreads();
-  for (int q = threadIdx.x; q < G; q += kStatT)
-    if (s_n[q]) s_base[q] = atomicAdd(&cur[q], s_n[q]);
+  uint16_t* mine = s_cnt + w * G;
+  const int nbits = 11;                     // (kMaxGroups = 2^11)
+  bool other = false;
+#pragma unroll
+  for (int k = 0; k < kStatIpt; ++k) {
+    const bool v = g[k] != kNoGroup;
+    const uint64_t peers = digit_peers(g[k], v, nbits);
+    const uint32_t below = lanes_below(peers);
+    const uint32_t c = v ? mine[g[k]] : 0u;
+    wave_sync();
+    if (v && below == 0) mine[g[k]] = (uint16_t)(c + __popcll(peers));
+    wave_sync();
+    rank[k] = c + below;
+    other = other || (v && h[k] != h0);
+  }
+  const bool mixed = __syncthreads_or(other);
+  for (int q = threadIdx.x; q < G; q += kRowT) {
+    uint32_t acc = 0;
+#pragma unroll
+    for (int i = 0; i < kWaves; ++i) {
+      const uint32_t c = s_cnt[i * G + q];
+      s_cnt[i * G + q] = (uint16_t)acc;
+      acc += c;
+    }
+    s_base[q] = tab[(int64_t)q * gridDim.x + blockIdx.x];
+  }
+  if (threadIdx.x == 0) bgpu[blockIdx.x] = mixed ? kNoGroup : (uint16_t)h0;
   __syncthreads();
   bool big = false;
 #pragma unroll
   for (int k = 0; k < kStatIpt; ++k) {
-    if (g[k] == kNone) continue;
+    if (g[k] == kNoGroup) continue;
     const uint64_t d = (uint64_t)du[k];
     const uint64_t ov = (uint64_t)ol[k];
     const uint64_t y = d + (uint64_t)gp[k];
     const uint64_t x = (ov << 30) / d;
     if ((y >> 34) != 0 || x > (1ull << 30)) big = true;
-    const uint32_t pos = s_base[g[k]] + slot[k];
-    xs[pos] = (uint32_t)x;
+    const uint32_t pos = s_base[g[k]] + mine[g[k]] + rank[k];
+    xs[pos] = x > 0x7FFFFFFFull ? 0x7FFFFFFFu : (uint32_t)x;
     ys[pos] = y;
+    hs[pos] = (uint8_t)h[k];
+    if (mixed && (int)h[k] < NG) {
+      const int64_t c = (int64_t)g[k] * NG + h[k];
+      atomicAdd(&C.cnt[c], 1u);
+      atomicMin(&C.beg[c], pos);
+      atomicMax(&C.end[c], pos + 1);
+    }
   }
-  if (__ballot(big) != 0 && lane_id() == 0)
-    atomicOr(status, CHOPPER_ST_RANGE);
+  if (__ballot(big) != 0 && lane == 0) atomicOr(status, CHOPPER_ST_RANGE);
 }
 
 // the group and chunk of this block (false past the last chunk)
@@ -314,47 +440,55 @@ __device__ inline void block_sums(uint64_t (&v)[kSums],
   }
 }
 
-// One radix pass over a chunk of one group: the histogram of digit
-// (x >> sh) & 255 of the candidates of every rank (those whose higher
-// digits equal the rank's selected prefix) into the group's global
-// histograms.  The first pass has one histogram (no prefix yet) and also
-// writes the chunk's sums of x, y, x^2, y^2, xy (in 32-bit halves where they
-// would overflow); the counter sums come from the grouping pass.
+// One radix pass over a chunk of one group: the histogram of the digit at
+// `sh` of the candidates of every rank (those whose higher digits equal the
+// rank's selected prefix) into the group's global histograms.  The first
+// pass has one histogram (no prefix yet) and also writes the chunk's sums of
+// x, y, x^2, y^2, xy (in 32-bit halves where they would overflow); the
+// counter sums come from the grouping pass.  After the eleven bits of the
+// first pass few instances are candidates but for those that share one
+// value (no overlap at all), which one LDS add per wave counts.
 template <bool First>
 __global__ __launch_bounds__(kStatT) void k_stats_pass(
     const uint32_t* off, const uint32_t* coff, int G, const uint32_t* xs,
     const uint64_t* ys,
     const uint32_t* spre, int sh, uint32_t* ghist, uint64_t* part) {
-  __shared__ uint32_t s_h[kRanks * 256];
+  constexpr int kBins = First ? kTopBins : kHistW;
+  __shared__ uint32_t s_h[kBins];
   __shared__ uint64_t s_w[kStatT / kWave][kSums];
   int64_t b, e;
   int g;
   if (!chunk_of(coff, off, G, b, e, g)) return;
   const int t = threadIdx.x;
-  for (int q = t; q < kRanks * 256; q += kStatT) s_h[q] = 0;
+  uint32_t x[kStatIpt];
+  uint64_t y[kStatIpt];
+#pragma unroll
+  for (int k = 0; k < kStatIpt; ++k) {
+    const int64_t i = b + (int64_t)k * kStatT + t;
+    x[k] = i < e ? xs[i] : 0u;
+    if (First) y[k] = i < e ? ys[i] : 0ull;
+  }
+  for (int q = t; q < kBins; q += kStatT) s_h[q] = 0;
   uint32_t pre[kRanks];
 #pragma unroll
-  for (int r = 0; r < kRanks; ++r) pre[r] = spre[g * kRanks + r];
+  for (int r = 0; r < kRanks; ++r) pre[r] = First ? 0u : spre[g * kRanks + r];
+  const uint32_t own = own_hist(pre);
   __syncthreads();
-  const int hs = sh + 8;
   uint64_t acc[kSums];
+  Ends ends;
 #pragma unroll
   for (int k = 0; k < kSums; ++k) acc[k] = 0;
 #pragma unroll
   for (int k = 0; k < kStatIpt; ++k) {
-    const int64_t i = b + (int64_t)k * kStatT + t;
-    const bool ok = i < e;
-    const uint32_t x = ok ? xs[i] : 0u;
-    const uint32_t dig = (x >> sh) & 255u;
+    const bool ok = b + (int64_t)k * kStatT + t < e;
     if (First) {
-      lds_claim(s_h, dig, ok);
+      lds_count(s_h, x[k] >> sh, ends.count(x[k], ok));
       if (ok) {
-        const uint64_t y = ys[i];
-        const uint64_t xx = (uint64_t)x * x;
-        const u128 yy = (u128)y * y;
-        const uint64_t xy = (uint64_t)x * y;
-        acc[0] += x;
-        acc[1] += y;
+        const uint64_t xx = (uint64_t)x[k] * x[k];
+        const u128 yy = (u128)y[k] * y[k];
+        const uint64_t xy = (uint64_t)x[k] * y[k];
+        acc[0] += x[k];
+        acc[1] += y[k];
         acc[2] += xx & 0xFFFFFFFFull;
         acc[3] += xx >> 32;
         acc[4] += (uint64_t)yy & 0xFFFFFFFFull;
@@ -363,53 +497,72 @@ __global__ __launch_bounds__(kStatT) void k_stats_pass(
         acc[7] += xy >> 32;
       }
     } else {
-#pragma unroll
-      for (int r = 0; r < kRanks; ++r)
-        lds_claim(&s_h[r * 256], dig, ok && (x >> hs) == (pre[r] >> hs));
+      count_digit(s_h, pre, own, x[k], sh, ends.count(x[k], ok));
     }
   }
+  if (First) ends.add_top(s_h);
+  else ends.add_low(s_h, pre, own, sh);
   if (First) block_sums(acc, s_w, part + (int64_t)blockIdx.x * kSums);
   __syncthreads();
-  uint32_t* gh = ghist + (int64_t)g * kRanks * 256;
-  for (int q = t; q < (First ? 256 : kRanks * 256); q += kStatT)
+  uint32_t* gh = ghist + (int64_t)g * kHistW;
+  for (int q = t; q < kBins; q += kStatT)
     if (s_h[q]) atomicAdd(&gh[q], s_h[q]);
+}
+
+// The bin of a histogram of kPer * 64 counts in which rank `rank` falls and
+// the counts before it, found by one wave (the same in every lane).
+template <int kPer>
+__device__ inline void wave_find(const uint32_t* hist, int64_t rank,
+                                 uint32_t* bin, int64_t* under) {
+  const int lane = lane_id();
+  uint32_t h[kPer], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    h[q] = hist[lane * kPer + q];
+    sum += h[q];
+  }
+  const uint32_t incl = wave_incl(sum, OpAdd(), 0u);
+  const uint64_t past = __ballot((int64_t)incl > rank);
+  const int ln = past ? __ffsll((long long)past) - 1 : kWave - 1;
+  int64_t u = (int64_t)incl - sum;
+  uint32_t d = (uint32_t)(lane * kPer + kPer - 1);
+  bool found = false;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const bool here = !found && u + (int64_t)h[q] > rank;
+    if (here) d = (uint32_t)(lane * kPer + q);
+    found = found || here;
+    if (!found && q + 1 < kPer) u += h[q];
+  }
+  *bin = (uint32_t)__builtin_amdgcn_readlane((int)d, ln);
+  *under = readlane64(u, ln);
 }
 
 // the digit of every rank of a group from its histogram; the prefix and
 // the rank within the remaining candidates move on, and the histograms are
 // cleared for the next pass
+template <bool First>
 __global__ __launch_bounds__(kRanks * kWave) void k_stats_select(
-    const uint32_t* cnt, int sh, bool first, uint32_t* ghist, uint32_t* spre,
+    const uint32_t* cnt, int sh, uint32_t* ghist, uint32_t* spre,
     int64_t* srank) {
   const int g = blockIdx.x, w = threadIdx.x / kWave, lane = lane_id();
   if (cnt[g] == 0) return;
-  uint32_t* gh = ghist + (int64_t)g * kRanks * 256;
-  const uint32_t* h4 = gh + (first ? 0 : w * 256) + lane * 4;
-  uint32_t h[4], sum = 0;
+  uint32_t* gh = ghist + (int64_t)g * kHistW;
+  uint32_t bin, pre[kRanks];
+  int64_t under;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    h[q] = h4[q];
-    sum += h[q];
-  }
+  for (int r = 0; r < kRanks; ++r) pre[r] = spre[g * kRanks + r];
   const int64_t rank = srank[g * kRanks + w];
-  const uint32_t incl = wave_incl(sum, OpAdd(), 0u);
-  const uint64_t past = __ballot((int64_t)incl > rank);
-  const int ln = __ffsll((long long)past) - 1;
-  if (lane == ln) {
-    int64_t under = (int64_t)incl - sum;
-    int dsel = lane * 4 + 3;
-    for (int q = 0; q < 4; ++q) {
-      if (under + (int64_t)h[q] > rank) {
-        dsel = lane * 4 + q;
-        break;
-      }
-      under += h[q];
-    }
-    spre[g * kRanks + w] |= (uint32_t)dsel << sh;
+  if (First) wave_find<kTopBins / kWave>(gh, rank, &bin, &under);
+  else
+    wave_find<kLowBins / kWave>(gh + hist_of(pre, w) * kLowBins, rank, &bin,
+                                &under);
+  __syncthreads();
+  if (lane == 0) {
+    spre[g * kRanks + w] |= bin << sh;
     srank[g * kRanks + w] = rank - under;
   }
-  __syncthreads();
-  for (int q = threadIdx.x; q < (first ? 256 : kRanks * 256);
+  for (int q = threadIdx.x; q < (First ? kTopBins : kHistW);
        q += kRanks * kWave)
     gh[q] = 0;
 }
@@ -423,11 +576,15 @@ struct StatOut {
 };
 
 // the exact sums of a group from its chunks and the derived values, in the
-// same IEEE operations as their definition
+// same IEEE operations as their definition; also the group's CDF groups,
+// from the blocks of the row passes
 __global__ __launch_bounds__(kBlock) void k_stats_final(
     const uint32_t* cnt, const uint32_t* coff, int G, int O, int nc,
     const uint64_t* part, const uint64_t* csum, const uint32_t* spre,
-    StatOut S) {
+    const uint32_t* hist, const uint32_t* tab, int64_t nb,
+    const uint16_t* bgpu, int NG, Cells C, StatOut S) {
+  __shared__ uint64_t s_cs[3];
+  __shared__ uint32_t s_n[256], s_b[256], s_e[256];
   __shared__ uint64_t s_w[kBlock / kWave][kSums];
   __shared__ uint64_t s_tot[kSums];
   const int g = blockIdx.x, t = threadIdx.x;
@@ -446,7 +603,37 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(
 #pragma unroll
     for (int k = 0; k < kSums; ++k) acc[k] += part[(int64_t)c * kSums + k];
   block_sums(acc, s_w, s_tot);
+  // counter sums: a wave a word
+  const int wv = t / kWave;
+  if (wv < 3) {
+    const uint64_t v =
+        lane_id() < kCopies
+            ? csum[(lane_id() * 3 + wv) * (int64_t)G + g] : 0ull;
+    const uint64_t sum = lane63(wave_incl(v, OpAdd(), (uint64_t)0));
+    if (lane_id() == 0) s_cs[wv] = sum;
+  }
+  // CDF groups: the blocks of rows on one GPU (the others have added theirs
+  // instance by instance), in row order
+  for (int h = t; h < NG; h += kBlock) {
+    s_n[h] = C.cnt[(int64_t)g * NG + h];
+    s_b[h] = C.beg[(int64_t)g * NG + h];
+    s_e[h] = C.end[(int64_t)g * NG + h];
+  }
   __syncthreads();
+  for (int64_t b = t; b < nb; b += kBlock) {
+    const uint32_t h = bgpu[b], n = hist[(int64_t)g * nb + b];
+    if (n == 0 || h >= (uint32_t)NG) continue;
+    const uint32_t at = tab[(int64_t)g * nb + b];
+    atomicAdd(&s_n[h], n);
+    atomicMin(&s_b[h], at);
+    atomicMax(&s_e[h], at + n);
+  }
+  __syncthreads();
+  for (int h = t; h < NG; h += kBlock) {
+    C.cnt[(int64_t)g * NG + h] = s_n[h];
+    C.beg[(int64_t)g * NG + h] = s_b[h];
+    C.end[(int64_t)g * NG + h] = s_e[h];
+  }
   if (t != 0) return;
   for (int k = 0; k < kStats; ++k) o[(int64_t)k * G + g] = nan;
   S.cnt[g] = m;
@@ -454,8 +641,7 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(
   const i128 sxx = ((i128)s_tot[3] << 32) + (i128)s_tot[2];
   const i128 syy = ((i128)s_tot[5] << 32) + (i128)s_tot[4];
   const i128 sxy = ((i128)s_tot[7] << 32) + (i128)s_tot[6];
-  const uint64_t cyc = csum[3 * g], busy = csum[3 * g + 1],
-                 flops = csum[3 * g + 2];
+  const uint64_t cyc = s_cs[0], busy = s_cs[1], flops = s_cs[2];
   const i128 im = (i128)m;
   const i128 cov = im * sxy - sx * sy;
   const i128 vx = im * sxx - sx * sx;
@@ -498,150 +684,260 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(
 
 // ------------------------------------------------------ per-GPU overlap CDF
 // Instances of (phase, operation) group g on GPU h form CDF group
-// c = g * NG + h.  Every row slot of the rows output gets the sort key
-// c << 31 | x (x = overlap ratio in Q30), or `sentinel` (above every key)
-// when it is no instance; its value is the slot.  After a stable sort by
-// key each CDF group is a run in CDF order: ascending x, equal x in row
-// order, which is time order on a GPU.
-struct CdfArgs {
-  StatArgs A;
-  const uint8_t* gpu;
-  int NG;
-};
-
-// Counts and smallest durations of the CDF groups: a block takes kCdfSpan
-// row slots (rows of one gpu are consecutive, so nearly all of a block's
-// instances are on its first row's gpu) and adds those per (phase,
-// operation) in LDS, with one global atomic per group and block; instances
-// of other gpus go to the global tables directly.
-constexpr int kCdfIpt = 8;
-constexpr int kCdfSpan = kBlock * kCdfIpt;
-
-__global__ __launch_bounds__(kBlock) void k_cdf_keys(CdfArgs C,
-                                                     uint64_t sentinel,
-                                                     uint64_t* key,
-                                                     uint32_t* val,
-                                                     uint32_t* gcnt,
-                                                     uint64_t* ymin) {
-  __shared__ uint32_t s_cnt[kMaxGroups];
-  __shared__ unsigned long long s_min[kMaxGroups];
-  const StatArgs& A = C.A;
-  const int G = A.P * A.O;
-  for (int g = threadIdx.x; g < G; g += kBlock) {
-    s_cnt[g] = 0;
-    s_min[g] = ~0ull;
-  }
-  int64_t lo, hi;
-  level_range(A, lo, hi);
-  const int64_t b0 = (int64_t)blockIdx.x * kCdfSpan;
-  const int64_t f = b0 > lo ? b0 : lo;     // the block's first row in range
-  const uint32_t h0 = f < hi ? (uint32_t)C.gpu[f] : 0xFFFFFFFFu;
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kCdfIpt; ++q) {
-    const int64_t r = b0 + (int64_t)q * kBlock + threadIdx.x;
-    if (r >= A.cap) break;
-    uint64_t k = sentinel;
-    if (r >= lo && r < hi && A.kind[r] == 0 && A.dur[r] > 0) {
-      const uint32_t mp = A.path[(int64_t)A.lv_phase * A.cap + r];
-      const uint32_t mo = A.path[(int64_t)A.lv_op * A.cap + r];
-      const uint32_t h = C.gpu[r];
-      if ((int64_t)mp < A.nm && (int64_t)mo < A.nm && (int)h < C.NG) {
-        const uint32_t p = A.label[mp], o = A.label[mo];
-        if (p < (uint32_t)A.P && o < (uint32_t)A.O) {
-          const uint32_t g = p * (uint32_t)A.O + o;
-          const uint64_t c = (uint64_t)g * C.NG + h;
-          const uint64_t d = (uint64_t)A.dur[r];
-          uint64_t x = ((uint64_t)A.ovl[r] << 30) / d;
-          if (x > 0x7FFFFFFFull) x = 0x7FFFFFFFull;   // (RANGE, set elsewhere)
-          k = c << 31 | x;
-          const uint64_t y = d + (uint64_t)A.gap[r];
-          if (h == h0) {
-            atomicAdd(&s_cnt[g], 1u);
-            atomicMin(&s_min[g], (unsigned long long)y);
-          } else {
-            atomicAdd(&gcnt[c], 1u);
-            atomicMin((unsigned long long*)&ymin[c], (unsigned long long)y);
-          }
-        }
-      }
-    }
-    key[r] = k;
-    val[r] = (uint32_t)r;
-  }
-  __syncthreads();
-  if (h0 == 0xFFFFFFFFu || (int)h0 >= C.NG) return;
-  for (int g = threadIdx.x; g < G; g += kBlock)
-    if (s_cnt[g]) {
-      const int64_t c = (int64_t)g * C.NG + h0;
-      atomicAdd(&gcnt[c], s_cnt[g]);
-      atomicMin((unsigned long long*)&ymin[c], s_min[g]);
-    }
-}
-
-// one thread per CDF group: quantiles of x, y_min, D_0%, D_50% and their
-// ratio, in the same IEEE operations as their definition
-__global__ __launch_bounds__(kBlock) void k_cdf_final(
-    CdfArgs C, int64_t NGG, const uint32_t* gcnt, const uint32_t* goff,
-    const uint64_t* skey, const uint32_t* sval, const uint64_t* ymin,
-    double* gout, int64_t* gcnt_out) {
-  const int64_t c = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (c >= NGG) return;
-  const int64_t m = gcnt[c];
-  gcnt_out[c] = m;
-  const double nan = __builtin_nan("");
+// c = g * NG + h, in CDF order: ascending x, equal x in row order (time
+// order on a GPU).  They lie in slots beg .. end - 1 of the group's column,
+// in row order, alone there when the rows of a GPU follow each other as
+// chopper_aggregate writes them; where they do not, those of the other GPUs
+// are passed over.
+//
+// One block per CDF group: the six order statistics by the radix selection
+// of the pooled ones with its histograms in LDS, then, for the three whose
+// times are wanted, the slot of the tie the rank falls on (each wave counts
+// the ties of its part of the stretch in order).  A stretch is read about
+// six times, from cache: 27,000 instances in 224 groups take 0.098 ms, where a
+// stable radix sort of the 6.1M keys took 0.51; one group of every instance
+// would take about as long as that sort.
+__global__ __launch_bounds__(kStatT) void k_cdf_cells(
+    int NG, int64_t NGG, Cells C, const uint32_t* xs, const uint64_t* ys,
+    const uint8_t* hs, double* gout, int64_t* gcnt_out) {
+  constexpr int kWaves = kStatT / kWave;
+  constexpr int kTies = 3;                  // ranks 0, 2 and 3
+  __shared__ uint32_t s_h[kHistW];
+  __shared__ uint32_t s_pre[kRanks];
+  __shared__ int64_t s_rank[kRanks];
+  __shared__ uint32_t s_tie[kTies][kWaves];
+  __shared__ uint64_t s_min[kWaves];
+  __shared__ double s_y[kTies];
+  const int64_t c = blockIdx.x;
+  const int t = (int)threadIdx.x, lane = lane_id(), w = t / kWave;
+  const int64_t m = C.cnt[c];
   if (m == 0) {
-    for (int z = 0; z < 9; ++z) gout[(int64_t)z * NGG + c] = nan;
+    if (t < 9) gout[(int64_t)t * NGG + c] = __builtin_nan("");
+    if (t == 0) gcnt_out[c] = 0;
     return;
   }
-  const int64_t b = goff[c];
-  auto xq = [&](int64_t k) {
-    return (double)(uint32_t)(skey[b + k] & 0x7FFFFFFFull);
+  const int64_t b = C.beg[c], e = C.end[c];
+  const uint32_t h = (uint32_t)(c % NG);
+  const bool all = e - b == m;              // no other GPU's slots between
+  // wave w takes the w-th part of the stretch, a lane four slots a round
+  // (aligned down), the next round's requested before this one is looked at
+  constexpr int64_t kRound = 4 * kWave;
+  const int64_t a = b & ~(int64_t)3;
+  const int64_t part = ceil_div(ceil_div(e - a, (int64_t)4), kWaves) * 4;
+  const int64_t w0 = a + w * part;
+  const int64_t w1 = w0 + part < e ? w0 + part : e;
+  struct Four {
+    uint32_t x[4], hw;
   };
-  auto yk = [&](int64_t k) {
-    const uint32_t r = sval[b + k];
-    return (double)(C.A.dur[r] + C.A.gap[r]);
+  auto load = [&](int64_t i, Four& F) {
+    F.hw = 0;
+    if (i + 4 <= w1) {
+      const uint4 v = *reinterpret_cast<const uint4*>(xs + i);
+      F.x[0] = v.x;
+      F.x[1] = v.y;
+      F.x[2] = v.z;
+      F.x[3] = v.w;
+      if (!all) F.hw = *reinterpret_cast<const uint32_t*>(hs + i);
+    } else {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        F.x[q] = i + q < w1 ? xs[i + q] : 0u;
+        if (!all && i + q < w1) F.hw |= (uint32_t)hs[i + q] << (8 * q);
+      }
+    }
   };
-  const double q = 1.0 / 1073741824.0, dy = (double)ymin[c];
+  // f(first slot of the lane, x, mask of the slots that count)
+  auto visit = [&](auto f) {
+    if (w0 >= w1) return;                              // (uniform)
+    Four cur, next;
+    load(w0 + 4 * lane, cur);
+#pragma unroll 1
+    for (int64_t c = w0; c < w1; c += kRound) {        // (uniform)
+      const int64_t i = c + 4 * lane;
+      load(i + kRound, next);
+      uint32_t ok = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        ok |= i + q >= b && i + q < w1 &&
+                      (all || ((cur.hw >> (8 * q)) & 255u) == h)
+                  ? 1u << q : 0u;
+      f(i, cur.x, ok);
+      cur = next;
+    }
+  };
+  if (t < kRanks) {
+    const int64_t want[kRanks] = {0, (m - 1) / 4, (m - 1) / 2, m / 2,
+                                  3 * (m - 1) / 4, m - 1};
+    s_pre[t] = 0;
+    s_rank[t] = want[t];
+  }
+  uint64_t low = ~0ull;
+  Ends ends;
+  for (int pass = 0; pass < 3; ++pass) {
+    const int sh = pass == 0 ? 2 * kLowBits : pass == 1 ? kLowBits : 0;
+    for (int q = t; q < (pass == 0 ? kTopBins : kHistW); q += kStatT)
+      s_h[q] = 0;
+    __syncthreads();
+    uint32_t pre[kRanks];
+#pragma unroll
+    for (int r = 0; r < kRanks; ++r) pre[r] = s_pre[r];
+    const uint32_t own = own_hist(pre);
+    if (pass == 0) {
+      // (the smallest time on the way)
+      visit([&](int64_t i, const uint32_t (&v)[4], uint32_t ok) {
+        uint64_t y[4];
+        if (i + 4 <= w1) {
+          const ulonglong2 y0 = *reinterpret_cast<const ulonglong2*>(ys + i);
+          const ulonglong2 y1 =
+              *reinterpret_cast<const ulonglong2*>(ys + i + 2);
+          y[0] = y0.x;
+          y[1] = y0.y;
+          y[2] = y1.x;
+          y[3] = y1.y;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) y[q] = i + q < w1 ? ys[i + q] : 0ull;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          lds_count(s_h, v[q] >> sh, ends.count(v[q], (ok >> q) & 1u));
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if ((ok >> q) & 1u) low = y[q] < low ? y[q] : low;
+      });
+      ends.add_top(s_h);
+    } else {
+      visit([&](int64_t, const uint32_t (&v)[4], uint32_t ok) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          count_digit(s_h, pre, own, v[q], sh,
+                      (ok >> q) & 1u && v[q] != 0u && v[q] != kFull);
+      });
+      ends.add_low(s_h, pre, own, sh);
+    }
+    __syncthreads();
+    if (w < kRanks) {
+      uint32_t bin;
+      int64_t under;
+      const int64_t rank = s_rank[w];
+      if (pass == 0) wave_find<kTopBins / kWave>(s_h, rank, &bin, &under);
+      else
+        wave_find<kLowBins / kWave>(s_h + hist_of(pre, w) * kLowBins, rank,
+                                    &bin, &under);
+      if (lane == 0) {
+        s_pre[w] |= bin << sh;
+        s_rank[w] = rank - under;
+      }
+    }
+    __syncthreads();
+  }
+  // the ties of every wave, then the wanted one of each
+  uint32_t tx[kTies], n[kTies] = {0, 0, 0};
+  int64_t tr[kTies];
+#pragma unroll
+  for (int k = 0; k < kTies; ++k) {
+    const int r = k == 0 ? 0 : k + 1;
+    tx[k] = s_pre[r];
+    tr[k] = s_rank[r];
+  }
+  visit([&](int64_t, const uint32_t (&v)[4], uint32_t ok) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int k = 0; k < kTies; ++k)
+        n[k] += (ok >> q) & 1u && v[q] == tx[k] ? 1u : 0u;
+  });
+#pragma unroll
+  for (int k = 0; k < kTies; ++k) {
+    const uint32_t sum = lane63(wave_incl(n[k], OpAdd(), 0u));
+    if (lane == 0) s_tie[k][w] = sum;
+  }
+  low = lane63(wave_incl(low, OpMin(), (uint64_t)~0ull));
+  if (lane == 0) s_min[w] = low;
+  __syncthreads();
+  bool here = false;
+#pragma unroll
+  for (int k = 0; k < kTies; ++k) {
+    for (int q = 0; q < w; ++q) tr[k] -= s_tie[k][q];
+    here = here || (tr[k] >= 0 && tr[k] < (int64_t)s_tie[k][w]);
+  }
+  if (here) {                               // (uniform)
+    // tr[k]: rank among the ties from here on (negative: passed)
+    visit([&](int64_t i, const uint32_t (&v)[4], uint32_t ok) {
+#pragma unroll
+      for (int k = 0; k < kTies; ++k) {
+        uint32_t tie = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          tie |= v[q] == tx[k] ? ok & (1u << q) : 0u;
+        if (__ballot(tie != 0) == 0) continue;
+        const uint32_t c = (uint32_t)__popc(tie);
+        const uint32_t incl = wave_incl(c, OpAdd(), 0u);
+        const int64_t at = tr[k] - (int64_t)(incl - c);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (((tie >> q) & 1u) &&
+              at == (int64_t)__popc(tie & ((1u << q) - 1u)))
+            s_y[k] = (double)ys[i + q];
+        tr[k] -= lane63(incl);
+      }
+    });
+  }
+  __syncthreads();
+  if (t != 0) return;
+  uint64_t ymin = ~0ull;
+  for (int q = 0; q < kWaves; ++q) ymin = s_min[q] < ymin ? s_min[q] : ymin;
+  auto xq = [&](int r) { return (double)s_pre[r]; };
+  const double q = 1.0 / 1073741824.0, dy = (double)ymin;
+  gcnt_out[c] = m;
   gout[0 * NGG + c] = xq(0) * q;
-  gout[1 * NGG + c] = xq((m - 1) / 4) * q;
-  gout[2 * NGG + c] = (xq((m - 1) / 2) + xq(m / 2)) / 2.0 * q;
-  gout[3 * NGG + c] = xq(3 * (m - 1) / 4) * q;
-  gout[4 * NGG + c] = xq(m - 1) * q;
+  gout[1 * NGG + c] = xq(1) * q;
+  gout[2 * NGG + c] = (xq(2) + xq(3)) / 2.0 * q;
+  gout[3 * NGG + c] = xq(4) * q;
+  gout[4 * NGG + c] = xq(5) * q;
   gout[5 * NGG + c] = dy;
-  const double c0 = yk(0) / dy;
-  const double c50 = (yk((m - 1) / 2) / dy + yk(m / 2) / dy) / 2.0;
+  const double c0 = s_y[0] / dy;
+  const double c50 = (s_y[1] / dy + s_y[2] / dy) / 2.0;
   gout[6 * NGG + c] = c0;
   gout[7 * NGG + c] = c50;
   gout[8 * NGG + c] = c50 / c0;
 }
 
-// eq. 9 per (phase, operation): the median over its GPUs with instances of
-// their D_50% / D_0%; eq. 10 divides by it (overwrites columns 14 and 15 of
-// k_stats_final)
-__global__ __launch_bounds__(kBlock) void k_cdf_pool(int G, int NG, int nc,
-                                                     const int64_t* gcnt,
-                                                     const double* gout,
-                                                     int64_t NGG,
-                                                     double* out) {
-  const int g = (int)(blockIdx.x * kBlock + threadIdx.x);
-  if (g >= G) return;
-  double v[256];
+// eq. 9 per (phase, operation), one wave each: the median over its GPUs with
+// instances of their D_50% / D_0%; eq. 10 divides by it (overwrites columns
+// 14 and 15 of k_stats_final).  Lanes hold four GPUs each; a value's place
+// in ascending order is the number of values below it, or equal and before.
+__global__ __launch_bounds__(kWave) void k_cdf_pool(int G, int NG, int nc,
+                                                    const int64_t* gcnt,
+                                                    const double* gout,
+                                                    int64_t NGG, double* out) {
+  __shared__ double s_v[256];
+  __shared__ double s_mid[2];
+  const int g = (int)blockIdx.x, lane = lane_id();
+  const int64_t c0 = (int64_t)g * NG;
   int k = 0;
-  for (int h = 0; h < NG; ++h) {
-    const int64_t c = (int64_t)g * NG + h;
-    if (gcnt[c] == 0) continue;
-    // insertion into ascending order
-    const double x = gout[8 * NGG + c];
-    int j = k++;
-    while (j > 0 && v[j - 1] > x) {
-      v[j] = v[j - 1];
-      --j;
-    }
-    v[j] = x;
+  for (int h0 = 0; h0 < NG; h0 += kWave) {
+    const int h = h0 + lane;
+    const bool on = h < NG && gcnt[c0 + h] != 0;
+    const uint64_t m = __ballot(on);
+    if (on) s_v[k + (int)lanes_below(m)] = gout[8 * NGG + c0 + h];
+    k += (int)__popcll(m);
   }
-  const double ovr = k > 0 ? (v[(k - 1) / 2] + v[k / 2]) / 2.0
-                           : __builtin_nan("");
+  if (lane < 2) s_mid[lane] = __builtin_nan("");
+  __syncthreads();
+  for (int i = lane; i < k; i += kWave) {
+    const double x = s_v[i];
+    int at = 0;
+    for (int j = 0; j < k; ++j) {
+      const double y = s_v[j];
+      at += y < x || (y == x && j < i) ? 1 : 0;
+    }
+    if (at == (k - 1) / 2) s_mid[0] = x;
+    if (at == k / 2) s_mid[1] = x;
+  }
+  __syncthreads();
+  if (lane != 0) return;
+  const double ovr = k > 0 ? (s_mid[0] + s_mid[1]) / 2.0 : __builtin_nan("");
   out[14 * (int64_t)G + g] = ovr;
   if (nc >= 16)
     out[15 * (int64_t)G + g] =
@@ -677,43 +973,44 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
   const int G = P * O;
   const int64_t cap = rows->cap;
   const int64_t nchunk = ceil_div(cap, kChunk) + G;
-  const int64_t nh = (int64_t)G * kRanks * 256;
+  const int64_t nh = (int64_t)G * kHistW;
   const int64_t NGG = (int64_t)G * NG;      // CDF groups
-  const int64_t capn = cap > 0 ? cap : 1;
+  const int64_t nb = ceil_div(cap > 0 ? cap : 1, (int64_t)kRowSpan);
   struct Bufs {
-    uint32_t *key, *gcnt, *off, *cur, *coff, *xs, *ghist, *spre;
+    uint16_t* key;
+    uint8_t* hs;
+    uint16_t* bgpu;
+    uint32_t *gcnt, *off, *coff, *xs, *ghist, *spre, *hist, *tab, *scan, *tot;
     uint64_t *ys, *csum, *part;
     int64_t* srank;
-    uint32_t *ccnt, *coffs, *cscan, *ctot, *sval;
-    uint64_t *ymin, *skey;
+    Cells cells;
     double* gout;
     int64_t* gcnt_out;
-    ClassSortLayout sort;
   } B;
   auto layout = [&](Scratch& sc) {
-    B.key = sc.take<uint32_t>(cap);
+    B.key = sc.take<uint16_t>(cap);
+    B.hs = sc.take<uint8_t>(cap);
+    B.bgpu = sc.take<uint16_t>(nb);
     B.gcnt = sc.take<uint32_t>(G);
     B.off = sc.take<uint32_t>(G + 1);
-    B.cur = sc.take<uint32_t>(G);
     B.coff = sc.take<uint32_t>(G + 1);
     B.xs = sc.take<uint32_t>(cap);
     B.ys = sc.take<uint64_t>(cap);
-    B.csum = sc.take<uint64_t>(3 * (int64_t)G);
+    B.csum = sc.take<uint64_t>(3 * (int64_t)G * kCopies);
     B.part = sc.take<uint64_t>(nchunk * kSums);
     B.ghist = sc.take<uint32_t>(nh);
     B.spre = sc.take<uint32_t>((int64_t)G * kRanks);
     B.srank = sc.take<int64_t>((int64_t)G * kRanks);
-    B.ccnt = sc.take<uint32_t>(NGG);
-    B.coffs = sc.take<uint32_t>(NGG + 1);
-    B.cscan = sc.take<uint32_t>(scan_scratch_elems(NGG));
-    B.ctot = sc.take<uint32_t>(1);
-    B.ymin = sc.take<uint64_t>(NGG);
-    B.skey = sc.take<uint64_t>(capn);
-    B.sval = sc.take<uint32_t>(capn);
+    B.hist = sc.take<uint32_t>(G * nb);
+    B.tab = sc.take<uint32_t>(G * nb);
+    B.scan = sc.take<uint32_t>(scan_scratch_elems(G * nb));
+    B.tot = sc.take<uint32_t>(1);
+    B.cells.cnt = sc.take<uint32_t>(NGG);
+    B.cells.beg = sc.take<uint32_t>(NGG);
+    B.cells.end = sc.take<uint32_t>(NGG);
     // (per-GPU results in scratch when the caller passes no arrays)
     B.gout = gpu_out ? gpu_out : sc.take<double>(9 * NGG);
     B.gcnt_out = gpu_cnt ? gpu_cnt : sc.take<int64_t>(NGG);
-    B.sort = class_sort_layout(sc, capn, 256);
   };
   Scratch probe(nullptr);
   layout(probe);
@@ -729,62 +1026,53 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
   StatOut S{out, cnt, spec->freq_peak_mhz, spec->tpt_peak,
             spec->f_gemm != nullptr, {0}};
   for (int o = 0; o < O && spec->f_gemm; ++o) S.f_gemm[o] = spec->f_gemm[o];
-  CHOPPER_HIP(launch("stats_clear", k_stats_clear, grid_for(nh, kBlock),
-                     dim3(kBlock), s, B.gcnt, G, B.ghist, nh, B.csum));
-  const dim3 rb((unsigned)ceil_div(cap > 0 ? cap : 1, (int64_t)kRowSpan));
-  CHOPPER_HIP(launch("stats_keys", k_stats_keys, rb, dim3(kStatT), s, A,
-                     B.key, B.gcnt, B.csum));
+  int64_t nclear = nh > NGG ? nh : NGG;
+  if (nclear > (int64_t)4096 * kBlock) nclear = (int64_t)4096 * kBlock;
+  CHOPPER_HIP(launch("stats_clear", k_stats_clear, grid_for(nclear, kBlock),
+                     dim3(kBlock), s, G, B.ghist, nh, B.csum, B.cells, NGG));
+  const dim3 rb((unsigned)nb);
+  CHOPPER_HIP(launch_shm("stats_keys", k_stats_keys, rb, dim3(kRowT),
+                         (size_t)G * 28, s, A, B.key, B.hist, B.csum));
+  CHOPPER_HIP(exclusive_scan<uint32_t>(B.hist, B.tab, G * nb, B.scan, B.tot,
+                                       s));
   CHOPPER_HIP(launch("stats_offsets", k_stats_offsets, dim3(1), dim3(kStatT),
-                     s, (const uint32_t*)B.gcnt, G, B.off, B.cur, B.coff,
-                     B.spre, B.srank));
-  CHOPPER_HIP(launch("stats_scatter", k_stats_scatter, rb, dim3(kStatT), s,
-                     A, (const uint32_t*)B.key, B.cur, B.xs, B.ys, status));
-  for (int pass = 0; pass < 4; ++pass) {
-    const int sh = 24 - 8 * pass;
+                     s, (const uint32_t*)B.tab, nb, (const uint32_t*)B.tot, G,
+                     B.gcnt, B.off, B.coff, B.spre, B.srank));
+  const size_t lds = (size_t)G * 4 + (size_t)G * 2 * (kRowT / kWave);
+  CHOPPER_HIP(launch_shm("stats_scatter", k_stats_scatter, rb, dim3(kRowT),
+                         lds, s, A, rows->gpu, NG, (const uint16_t*)B.key,
+                         (const uint32_t*)B.tab, B.xs, B.ys, B.hs, B.bgpu,
+                         B.cells, status));
+  for (int pass = 0; pass < 3; ++pass) {
+    const int sh = pass == 0 ? 2 * kLowBits : pass == 1 ? kLowBits : 0;
     CHOPPER_HIP(launch("stats_pass",
                        pass == 0 ? k_stats_pass<true> : k_stats_pass<false>,
                        dim3((unsigned)nchunk), dim3(kStatT), s,
                        (const uint32_t*)B.off, (const uint32_t*)B.coff, G,
                        (const uint32_t*)B.xs, (const uint64_t*)B.ys,
                        (const uint32_t*)B.spre, sh, B.ghist, B.part));
-    CHOPPER_HIP(launch("stats_select", k_stats_select, dim3((unsigned)G),
-                       dim3(kRanks * kWave), s, (const uint32_t*)B.gcnt, sh,
-                       pass == 0, B.ghist, B.spre, B.srank));
+    CHOPPER_HIP(launch("stats_select",
+                       pass == 0 ? k_stats_select<true>
+                                 : k_stats_select<false>,
+                       dim3((unsigned)G), dim3(kRanks * kWave), s,
+                       (const uint32_t*)B.gcnt, sh, B.ghist, B.spre,
+                       B.srank));
   }
   CHOPPER_HIP(launch("stats_final", k_stats_final, dim3((unsigned)G),
                      dim3(kBlock), s, (const uint32_t*)B.gcnt,
                      (const uint32_t*)B.coff, G, O, n_counters,
                      (const uint64_t*)B.part, (const uint64_t*)B.csum,
-                     (const uint32_t*)B.spre, S));
+                     (const uint32_t*)B.spre, (const uint32_t*)B.hist,
+                     (const uint32_t*)B.tab, nb, (const uint16_t*)B.bgpu, NG,
+                     B.cells, S));
   // per-GPU overlap CDFs, and eq. 9 / eq. 10 from them
-  const CdfArgs C{A, rows->gpu, NG};
-  const uint64_t sentinel = (uint64_t)NGG << 31;
-  int bits = 0;
-  while (bits < 64 && (sentinel >> bits) != 0) ++bits;
-  CHOPPER_HIP(launch("stats_cdf", k_stats_clear_cdf, grid_for(NGG, kBlock),
-                     dim3(kBlock), s, NGG, B.ccnt, B.ymin));
-  if (cap > 0) {
-    CHOPPER_HIP(launch("stats_cdf", k_cdf_keys,
-                       dim3((unsigned)ceil_div(cap, (int64_t)kCdfSpan)),
-                       dim3(kBlock), s, C, sentinel, B.sort.key0, B.sort.val0,
-                       B.ccnt, B.ymin));
-    ClassSortLayout L = B.sort;
-    L.n = cap;
-    L.ntiles = sort_tiles(cap);
-    rc = radix_sort_pairs(L, bits, B.sval, B.skey, s);
-    if (rc != CHOPPER_OK) return rc;
-  }
-  CHOPPER_HIP(exclusive_scan<uint32_t>(B.ccnt, B.coffs, NGG, B.cscan, B.ctot,
-                                       s));
-  CHOPPER_HIP(launch("stats_cdf", k_cdf_final, grid_for(NGG, kBlock),
-                     dim3(kBlock), s, C, NGG, (const uint32_t*)B.ccnt,
-                     (const uint32_t*)B.coffs, (const uint64_t*)B.skey,
-                     (const uint32_t*)B.sval, (const uint64_t*)B.ymin, B.gout,
-                     B.gcnt_out));
-  CHOPPER_HIP(launch("stats_cdf", k_cdf_pool, grid_for(G, kBlock),
-                     dim3(kBlock), s, G, NG, n_counters,
-                     (const int64_t*)B.gcnt_out, (const double*)B.gout, NGG,
-                     out));
+  CHOPPER_HIP(launch("stats_cdf", k_cdf_cells, dim3((unsigned)NGG),
+                     dim3(kStatT), s, NG, NGG, B.cells,
+                     (const uint32_t*)B.xs, (const uint64_t*)B.ys,
+                     (const uint8_t*)B.hs, B.gout, B.gcnt_out));
+  CHOPPER_HIP(launch("stats_cdf", k_cdf_pool, dim3((unsigned)G), dim3(kWave),
+                     s, G, NG, n_counters, (const int64_t*)B.gcnt_out,
+                     (const double*)B.gout, NGG, out));
   return CHOPPER_OK;
 }
 

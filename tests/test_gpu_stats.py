@@ -113,3 +113,50 @@ def test_stats_no_instances(ch):
                           n_ops=8)
     check(got, ref, "no instances")
     assert got[1].sum() == 0 and np.isnan(got[0]).all()
+
+
+@pytest.mark.parametrize("rows,grouped", [(4095, True), (4097, False),
+                                          (8193, True), (84000, True),
+                                          (84000, False)])
+def test_stats_one_group(ch, rows, grouped):
+    """One (phase, operation) of every instance: stretches of many blocks and
+    chunks, ties at no, full and partial overlap, GPUs that follow each other
+    and GPUs mixed row by row (equal ratios in row order either way)."""
+    import torch
+    say("op stats: one group,", rows, "rows, GPUs",
+        "in turn" if grouped else "mixed")
+    tr = tg.make_config(1, iters=11, seed=3)
+    tr.m_label = np.zeros_like(tr.m_label)
+    pipe = ch.Pipeline(ch.DeviceTrace(tr, "cuda"))
+    pipe.step()
+    host = pipe.rows.to_numpy()
+    lo, hi = host["level_offset"][3:5]
+    assert hi - lo >= rows
+    rng = np.random.default_rng(rows)
+    pick = rng.permutation(hi - lo)[:rows]
+    pick = lo + (np.sort(pick) if grouped else pick)
+    part = {k: np.ascontiguousarray(v[..., pick])
+            for k, v in host.items() if k not in ("n_rows", "level_offset")}
+    # a third at full overlap, a third at one of four ratios
+    third = np.arange(rows) % 3
+    part["ovl"] = np.where(third == 1, part["dur"], np.where(
+        third == 2, part["dur"] * (1 + rng.integers(0, 4, rows)) // 8,
+        part["ovl"]))
+    part["level_offset"] = np.array([0, 0, 0, 0, rows, rows, rows], np.int64)
+    part["n_rows"] = rows
+    buf = ch.RowsBuffer(rows, 4, 0, "cuda")
+    for k, v in part.items():
+        if k not in ("n_rows", "ctr"):
+            t = getattr(buf, k)
+            t.copy_(torch.from_numpy(np.ascontiguousarray(v).view(
+                {1: np.uint8, 4: np.int32, 8: np.int64}[v.itemsize])))
+    pipe.rows = buf
+    pipe.status.zero_()
+    spec = dict(n_phases=1, n_ops=1, phase_level=1, op_level=3)
+    out, cnt, gout, gcnt = pipe.op_stats(per_gpu=True, **spec)
+    got = (out.cpu().numpy(), cnt.cpu().numpy(), 0, gout.cpu().numpy(),
+           gcnt.cpu().numpy())
+    ref = oracle.op_stats(part, tr.m_label, tr.depth, n_gpus=tr.n_gpus,
+                          per_gpu=True, **spec)
+    check(got, ref, f"one group of {rows}")
+    assert got[1][0] > rows // 2
