@@ -240,7 +240,7 @@ __global__ __launch_bounds__(kBlock) void k_agg_count(RecSrc S, uint32_t act,
   }
 }
 
-__global__ void k_agg_offsets(int L, int64_t ntiles, const uint32_t* tilebase,
+__global__ void k_agg_offsets_all(int L, int64_t ntiles, const uint32_t* tilebase,
                               const uint32_t* total, int64_t cap,
                               int64_t* level_offset, uint32_t* status) {
   const int li = threadIdx.x;
@@ -750,9 +750,9 @@ __device__ inline void gather_item(const Src& src, int64_t i, int D,
 // path.  Items are striped (item j * 64 + lane of the tile in lane `lane`);
 // the previous item comes from the lane below by a DPP rotate.
 template <int MaxD, typename Src>
-__global__ __launch_bounds__(kBlock) void k_agg_heads(
-    Src src, uint32_t act, int lv0, int lv1, int D, int64_t M, int64_t nwt,
-    uint32_t* tilecnt, uint32_t* flags, uint32_t* status) {
+__device__ inline void agg_heads(
+    const Src& src, uint32_t act, int lv0, int lv1, int D, int64_t M,
+    int64_t nwt, uint32_t* tilecnt, uint32_t* flags, uint32_t* status) {
   const int lane = lane_id();
   const int64_t w =
       (int64_t)blockIdx.x * kWavesPerBlock + (int64_t)(threadIdx.x / kWave);
@@ -851,31 +851,77 @@ __global__ __launch_bounds__(kBlock) void k_agg_heads(
     atomicOr(&flags[1], kk);
 }
 
-// Fast-path level offsets: the level-major scan gives every level but the
-// workload level, whose rows are the kinds present.
-// `stage` receives the three flags and the L + 1 offsets, so that the host
-// reads them with one copy.
-__global__ void k_agg_offsets_fast(int L, int64_t ntiles,
-                                   const uint32_t* tilebase,
-                                   const uint32_t* total, const uint32_t* flags,
-                                   bool workload, int64_t cap,
-                                   int64_t* level_offset, int64_t* stage,
-                                   uint32_t* status) {
-  if (threadIdx.x != 0) return;
-  for (int li = 0; li < L; ++li) {
-    const int64_t v = ntiles > 0 ? tilebase[(int64_t)li * ntiles] : 0;
-    level_offset[li] = v;
-    stage[3 + li] = v;
-  }
+// Level offsets and what the host reads: the level-major scan of the head
+// counts gives every level but the workload level, whose rows are the kinds
+// present.  `stage`, and `host` (a read-back slot or null) beside it,
+// receive the three flags, the L + 1 offsets and, with `interior`, L more
+// counts.  The last block of a heads pass does this itself for a small table
+// (it scans it first), else one wave of its own.
+struct StageOut {
+  int L;
+  int64_t stride;          // counts per level
+  uint32_t* tilecnt;
+  uint32_t* tilebase;      // scanned
+  uint32_t* total;
+  const uint32_t* interior;
+  bool nat;                // flags[2] rules the counts out
+  bool workload;
+  int64_t cap;
+  int64_t* level_offset;
+  int64_t* stage;
+  uint32_t* host;
+  uint32_t* status;
+  uint32_t* count;         // of the blocks that are done; null: not here
+};
+
+__device__ inline void stage_out(const StageOut& O, const uint32_t* flags,
+                                 uint32_t total) {
+  const int t = (int)threadIdx.x;
+  const uint32_t f0 = flag_read(&flags[0]), f1 = flag_read(&flags[1]),
+                 f2 = flag_read(&flags[2]);
   const int64_t tot =
-      (int64_t)*total + (workload ? __popc(flags[1] & 3u) : 0);
-  level_offset[L] = tot;
-  stage[3 + L] = tot;
-  for (int i = 0; i < 3; ++i) stage[i] = flags[i];
-  // the counts are the row counts only when the fast path applies (and,
-  // for the natural tiles, when the input order qualified)
-  if (flags[0] == 0 && flags[2] == 0 && tot > cap)
-    atomicOr(status, (uint32_t)CHOPPER_ST_ROWS_OVERFLOW);
+      (int64_t)total + (O.workload ? __popc(f1 & 3u) : 0);
+  auto put = [&](int i, int64_t v) {
+    O.stage[i] = v;
+    store_host(O.host, i, v);
+  };
+  if (t <= O.L) {
+    const int64_t v =
+        t == O.L ? tot : (int64_t)O.tilebase[(int64_t)t * O.stride];
+    O.level_offset[t] = v;
+    put(3 + t, v);
+  }
+  if (O.interior && t < O.L)
+    put(3 + O.L + 1 + t, (int64_t)flag_read(&O.interior[t]));
+  if (t < 3) put(t, (int64_t)(t == 0 ? f0 : t == 1 ? f1 : f2));
+  // the counts are the row counts only when the path applies (and, for the
+  // natural tiles, when the input order qualified)
+  if (t == 0 && f0 == 0 && !(O.nat && f2) && tot > O.cap)
+    atomicOr(O.status, (uint32_t)CHOPPER_ST_ROWS_OVERFLOW);
+}
+
+__global__ void k_agg_offsets(StageOut O, const uint32_t* flags) {
+  stage_out(O, flags, *O.total);
+}
+
+// the end of a heads pass over `blocks` blocks: see StageOut
+__device__ inline void heads_end(const StageOut& O, const uint32_t* flags,
+                                 uint32_t blocks) {
+  if (!O.count || !last_block(O.count, blocks)) return;
+  const uint32_t tot =
+      block_scan_array(O.tilecnt, O.tilebase, (int64_t)O.L * O.stride);
+  if (threadIdx.x == 0) *O.total = tot;
+  __syncthreads();
+  stage_out(O, flags, tot);
+}
+
+template <int MaxD>
+__global__ __launch_bounds__(kBlock) void k_agg_heads(
+    FromRecords src, uint32_t act, int lv0, int lv1, int D, int64_t M,
+    int64_t nwt, uint32_t* tilecnt, uint32_t* flags, uint32_t* status,
+    StageOut O) {
+  agg_heads<MaxD>(src, act, lv0, lv1, D, M, nwt, tilecnt, flags, status);
+  heads_end(O, flags, gridDim.x);
 }
 
 // ------------------------------------------------------------ input order
@@ -1193,9 +1239,10 @@ __device__ inline void nat_item(const RecSrc& S, int64_t i, uint32_t g, int D,
 // start in the tile, at tilecnt[(li - lv0) * stride + 2 * tbg + k * cg + tl];
 // entries past the last tile are zeroed.  Flags as in k_agg_heads.
 template <int MaxD>
-__global__ __launch_bounds__(kBlock) void k_agg_heads_nat(
-    RecSrc S, NatGeom N, uint32_t act, int lv0, int lv1, int D, int64_t M,
-    int64_t stride, uint32_t* tilecnt, uint32_t* flags, uint32_t* status) {
+__device__ inline void agg_heads_nat(
+    const RecSrc& S, const NatGeom& N, uint32_t act, int lv0, int lv1, int D,
+    int64_t M, int64_t stride, uint32_t* tilecnt, uint32_t* flags,
+    uint32_t* status) {
   __shared__ uint32_t s_k[kWavesPerBlock][kSlice];
   if (*N.bad) return;
   const int lane = lane_id();
@@ -1328,6 +1375,16 @@ __global__ __launch_bounds__(kBlock) void k_agg_heads_nat(
     atomicOr(&flags[1], kk);
 }
 
+template <int MaxD>
+__global__ __launch_bounds__(kBlock) void k_agg_heads_nat(
+    RecSrc S, NatGeom N, uint32_t act, int lv0, int lv1, int D, int64_t M,
+    int64_t stride, uint32_t* tilecnt, uint32_t* flags, uint32_t* status,
+    StageOut O) {
+  agg_heads_nat<MaxD>(S, N, act, lv0, lv1, D, M, stride, tilecnt, flags,
+                      status);
+  heads_end(O, flags, gridDim.x);
+}
+
 // ---------------------------------------------------- groups of several runs
 // With a filter, or when groups are not runs (a marker that was lost leaves
 // its records to the marker around it, whose group then comes back after
@@ -1372,7 +1429,8 @@ __global__ __launch_bounds__(kBlock) void k_gen_fill(GenTab tab, uint32_t act,
   const int li = (int)blockIdx.y;
   if (blockIdx.x == 0 && li == 0) {
     if (threadIdx.x < 2) flags[threadIdx.x] = 0;
-    if (threadIdx.x < kMaxLevels) interior[threadIdx.x] = 0;
+    // (the counter of finished blocks after the levels)
+    if (threadIdx.x <= kMaxLevels) interior[threadIdx.x] = 0;
     if (threadIdx.x == 0) *ovf_count = 0;
   }
   if (!((act >> li) & 1u)) return;
@@ -1683,17 +1741,15 @@ __global__ __launch_bounds__(kBlock) void k_gen_elect(
 // their run of the tile (interior[li]), and PATH_CONFLICT when two items of
 // a key hold different paths.
 template <int MaxD, typename Src, bool kNat>
-__global__ __launch_bounds__(kBlock) void k_gen_count(
-    Src src, NatGeom N, uint32_t act, int lv0, int lv1, int D, int64_t M,
-    int64_t nwt, int64_t stride, GenTab tab, uint32_t* tilecnt,
-    uint8_t* omask, int64_t mstride, uint32_t* flags, uint32_t* interior,
-    uint32_t* ovf_count, uint32_t* status) {
+__device__ inline void gen_count(
+    const Src& src, const NatGeom& N, uint32_t act, int lv0, int lv1, int D,
+    int64_t M, int64_t nwt, int64_t stride, const GenTab& tab,
+    uint32_t* tilecnt, uint8_t* omask, int64_t mstride, uint32_t* flags,
+    uint32_t* interior, uint32_t* status) {
   __shared__ uint32_t s_k[kWavesPerBlock][kSlice];
   if constexpr (kNat) {
     if (*N.bad) return;
   }
-  // (from rows: the overflow list of the level below has been applied)
-  if (!Src::kRecords && blockIdx.x == 0 && threadIdx.x == 0) *ovf_count = 0;
   const int lane = lane_id();
   const int wv = (int)(threadIdx.x / kWave);
   const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + wv;
@@ -1837,6 +1893,34 @@ __global__ __launch_bounds__(kBlock) void k_gen_count(
   }
 }
 
+template <int MaxD, bool kNat>
+__global__ __launch_bounds__(kBlock) void k_gen_count(
+    FromRecords src, NatGeom N, uint32_t act, int lv0, int lv1, int D,
+    int64_t M, int64_t nwt, int64_t stride, GenTab tab, uint32_t* tilecnt,
+    uint8_t* omask, int64_t mstride, uint32_t* flags, uint32_t* interior,
+    uint32_t* status, StageOut O) {
+  gen_count<MaxD, FromRecords, kNat>(src, N, act, lv0, lv1, D, M, nwt, stride,
+                                     tab, tilecnt, omask, mstride, flags,
+                                     interior, status);
+  heads_end(O, flags, gridDim.x);
+}
+
+// over rows (the overflow list of the level below has been applied); the
+// last block scans a table of at most kTailScan counts
+template <int MaxD>
+__global__ __launch_bounds__(kBlock) void k_gen_count_rows(
+    FromRows src, uint32_t act, int lv0, int lv1, int D, int64_t M,
+    int64_t nwt, GenTab tab, uint32_t* tilecnt, uint32_t* tilebase,
+    uint8_t* omask, int64_t mstride, uint32_t* count, uint32_t* ovf_count) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) *ovf_count = 0;
+  const NatGeom none{};
+  gen_count<MaxD, FromRows, false>(src, none, act, lv0, lv1, D, M, nwt, nwt,
+                                   tab, tilecnt, omask, mstride, nullptr,
+                                   nullptr, nullptr);
+  if (!count || !last_block(count, gridDim.x)) return;
+  block_scan_array(tilecnt, tilebase, (int64_t)(lv1 - lv0 + 1) * nwt);
+}
+
 // What the reduction needs of this path: the owner masks and tables of the
 // level and the next coarser one, and whether later passes read firstpos.
 struct GenRed {
@@ -1860,28 +1944,6 @@ __global__ __launch_bounds__(kBlock) void k_gen_apply(
   if ((int64_t)row >= R.cap) return;
   for (int f = 0; f < nfields; ++f)
     atomic_field(R, f, row, ovf.val[(int64_t)f * ovf.cap + e]);
-}
-
-// Level offsets, flags and interior counts for the host (layout as
-// k_agg_offsets_fast, the interior counts of the L levels after it).
-__global__ void k_gen_offsets(int L, int64_t stride, const uint32_t* tilebase,
-                              const uint32_t* total, const uint32_t* flags,
-                              const uint32_t* interior, bool nat,
-                              bool workload, int64_t cap,
-                              int64_t* level_offset, int64_t* stage,
-                              uint32_t* status) {
-  const int t = (int)threadIdx.x;
-  const int64_t tot =
-      (int64_t)*total + (workload ? __popc(flags[1] & 3u) : 0);
-  if (t <= L) {
-    const int64_t v = t == L ? tot : (int64_t)tilebase[(int64_t)t * stride];
-    level_offset[t] = v;
-    stage[3 + t] = v;
-  }
-  if (t < L) stage[3 + L + 1 + t] = interior[t];
-  if (t < 3) stage[t] = flags[t];
-  if (t == 0 && flags[0] == 0 && !(nat && flags[2]) && tot > cap)
-    atomicOr(status, (uint32_t)CHOPPER_ST_ROWS_OVERFLOW);
 }
 
 // Piece structure of one level over a wave tile (blocked arrangement: lane
@@ -1985,10 +2047,15 @@ __device__ inline int64_t piece_row(const LevelTile& T, uint32_t q) {
 // Every valid item has a key here (the heads pass sends traces with unkeyed
 // items to the general path).  kNat: the natural tiles, items read in input
 // order and regrouped by kind on the way to the blocked arrangement.
+// Where there are fewer tiles than wave slots, blockIdx.y splits a tile's
+// fields over several waves, each of which finds the tile's pieces again
+// (kSplit; reduce_parts below).
 // kGen: groups of several runs (above): every piece is a head here, the
 // owners' rows are numbered by rank, and a piece's row -- or, top bit set,
 // its overflow slot -- is kept per piece in LDS.
-template <int MaxD, typename Src, bool kTwo, bool kNat, bool kGen>
+constexpr int kSpecial = 5;
+constexpr int64_t kReduceWaves = 3072;
+template <int MaxD, typename Src, bool kTwo, bool kNat, bool kGen, bool kSplit>
 __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
     Src src, NatGeom N, int li, int D, int64_t M, const uint32_t* tilebase,
     const uint32_t* tilebase2, const int64_t* row0, RowsDev R, Overflow ovf,
@@ -2232,12 +2299,15 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
       }
     }
   };
-  headers(T1, li, own_row, GR.own);
-  if (kTwo) headers(T2, li2, own_row2, GR.own2);
+  const bool first = !kSplit || blockIdx.y == 0;  // part with the headers
+  if (first) {
+    headers(T1, li, own_row, GR.own);
+    if (kTwo) headers(T2, li2, own_row2, GR.own2);
+  }
   auto cont_row = [&](uint32_t c, int64_t r) -> uint32_t {
     return c && r >= 1 && r - 1 < R.cap ? (uint32_t)(r - 1) : kNone;
   };
-  if (!kGen && lane == 0) {
+  if (!kGen && first && lane == 0) {
     if constexpr (kNat) {
       ovf.row[2 * w] = cont_row(T1.c0, T1.r0);
       ovf.row[2 * w + 1] = cont_row(T1.c1, T1.r1);
@@ -2336,11 +2406,24 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
       v[j] = *(const uint64_t*)((const char*)col + off[j]);
   };
 
-  const int ns = src.nsum();
+  // this part's plain sums: is .. ns - 1 (the special fields, which come to
+  // about kSpecial sums, are the first part's)
+  int is = 0, ns = src.nsum();
+  if constexpr (kSplit) {
+    const int units = kSpecial + ns, P = (int)gridDim.y, q = (int)blockIdx.y;
+    const int u0 = units * q / P - kSpecial;
+    const int u1 = units * (q + 1) / P - kSpecial;
+    is = u0 > 0 ? u0 : 0;
+    ns = u1 > 0 ? u1 : 0;
+  }
   // three plain-sum columns in flight: each is loaded three fields ahead of
   // its use (the first ones staggered between the special fields)
   uint64_t va[kAggIpt], vb[kAggIpt], vc[kAggIpt];
-  {
+  if (kSplit && !first) {
+    if (ns > is) load(src.sum_col(is), va);
+    if (ns > is + 1) load(src.sum_col(is + 1), vb);
+    if (ns > is + 2) load(src.sum_col(is + 2), vc);
+  } else {
     uint64_t ts[kAggIpt], te[kAggIpt];
     load((const uint64_t*)src.start_col(), ts);
     load((const uint64_t*)src.end_col(), te);
@@ -2369,7 +2452,7 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
     if (ns > 2) load(src.sum_col(2), vc);
     do_seg(te, 5, CMax());
   }
-  for (int i = 0; i < ns; i += 3) {
+  for (int i = is; i < ns; i += 3) {
     do_sum(va, src.sum_dst(i));
     if (i + 3 < ns) load(src.sum_col(i + 3), va);
     if (i + 1 < ns) {
@@ -2419,8 +2502,9 @@ __device__ inline int64_t block_pair_lower(const RowsDev& R, int64_t a0,
   return lo;
 }
 
-__global__ __launch_bounds__(kBlock) void k_agg_gpu_sums(
-    const int64_t* level_offset, RowsDev R, int nfields, uint64_t* pair) {
+__device__ inline void agg_gpu_sums(const int64_t* level_offset,
+                                    const RowsDev& R, int nfields,
+                                    uint64_t* pair) {
   __shared__ uint32_t s_cnt[kWavesPerBlock];
   __shared__ uint64_t s_f[kWavesPerBlock][kMaxFields];
   const uint32_t b = blockIdx.x;
@@ -2447,13 +2531,13 @@ __global__ __launch_bounds__(kBlock) void k_agg_gpu_sums(
                       : acc[f] + x;
     }
   }
+  // (lane moves without LDS; the fields that are there)
 #pragma unroll
   for (int f = 0; f < kMaxFields; ++f) {
-    uint64_t v = acc[f];
-    for (int d = kWave / 2; d > 0; d >>= 1) {
-      const uint64_t o = __shfl_xor(v, d, kWave);
-      v = f == 5 ? ((int64_t)o > (int64_t)v ? o : v) : v + o;
-    }
+    if (f == 4 || f >= nfields) continue;
+    const uint64_t v =
+        f == 5 ? (uint64_t)lane63(wave_incl((int64_t)acc[f], OpMax(), kI64Min))
+               : lane63(wave_incl(acc[f], OpAdd(), (uint64_t)0));
     if (lane_id() == 0) s_f[threadIdx.x / kWave][f] = v;
   }
   __syncthreads();
@@ -2474,23 +2558,29 @@ __global__ __launch_bounds__(kBlock) void k_agg_gpu_sums(
   }
 }
 
-__global__ __launch_bounds__(1024) void k_agg_gpu_finish(
-    const int64_t* level_offset, int D, RowsDev R, int nfields, int npairs,
-    const uint64_t* pair) {
+// (one block of kBlock threads)
+__device__ inline void agg_gpu_finish(const int64_t* level_offset, int D,
+                                      const RowsDev& R, int nfields,
+                                      int npairs, const uint64_t* pair) {
   __shared__ uint32_t s_rank[513];
   const int t = (int)threadIdx.x;
-  if (t == 0) {
-    uint32_t c = 0;
-    for (int q = 0; q < npairs; ++q) {
-      s_rank[q] = c;
-      c += (uint32_t)pair[(int64_t)q * kPairW + kMaxFields + 2];
-    }
-    s_rank[npairs] = c;
+  {
+    // two consecutive pairs a thread (at most 512)
+    const int q0 = 2 * t;
+    uint32_t p0 = 0, p1 = 0, tot;
+    if (q0 < npairs)
+      p0 = (uint32_t)pair[(int64_t)q0 * kPairW + kMaxFields + 2];
+    if (q0 + 1 < npairs)
+      p1 = (uint32_t)pair[(int64_t)(q0 + 1) * kPairW + kMaxFields + 2];
+    const uint32_t pre = block_exclusive(p0 + p1, OpAdd(), 0u, &tot);
+    s_rank[q0] = pre;
+    s_rank[q0 + 1] = pre + p0;
+    if (t == 0) s_rank[512] = tot;
   }
   __syncthreads();
   const int64_t g0 = level_offset[D];
   // GPU rows: one thread per (pair, field) of the pairs present
-  for (int i = t; i < npairs * kPairW; i += 1024) {
+  for (int i = t; i < npairs * kPairW; i += kBlock) {
     const int q = i / kPairW, f = i % kPairW;
     const uint64_t* slot = pair + (int64_t)q * kPairW;
     if (!slot[kMaxFields + 2]) continue;
@@ -2507,7 +2597,7 @@ __global__ __launch_bounds__(1024) void k_agg_gpu_finish(
   }
   // workload rows: kind 0 first when present
   const int64_t w0 = level_offset[D + 1], w1 = level_offset[D + 2];
-  for (int i = t; i < 2 * kPairW; i += 1024) {
+  for (int i = t; i < 2 * kPairW; i += kBlock) {
     const uint32_t kd = (uint32_t)(i / kPairW);
     const int f = i % kPairW;
     bool any = false;
@@ -2543,6 +2633,15 @@ __global__ __launch_bounds__(1024) void k_agg_gpu_finish(
   }
 }
 
+// GPU rows, then the workload rows by the last block.
+__global__ __launch_bounds__(kBlock) void k_agg_gpu_rows(
+    const int64_t* level_offset, int D, RowsDev R, int nfields, int npairs,
+    uint64_t* pair, uint32_t* count) {
+  agg_gpu_sums(level_offset, R, nfields, pair);
+  if (last_block(count, gridDim.x))
+    agg_gpu_finish(level_offset, D, R, nfields, npairs, pair);
+}
+
 // first record of a workload row: the smallest input index among the records
 // (or GPU rows) whose start equals the row's tmin
 template <typename Src>
@@ -2561,13 +2660,10 @@ __global__ __launch_bounds__(kBlock) void k_agg_workload_first(
     atomicMin(&R.first[row], src.first_of(r));
 }
 
-// Entries [0, nslots), or [0, *count) when nslots < 0; a slot holding
+// Entry e of [0, nslots), or of [0, *count) when nslots < 0; a slot holding
 // kNone is empty.
-// `clear` (optional): three flag words zeroed for the next heads pass
-__global__ __launch_bounds__(kBlock) void k_agg_apply_overflow(
-    Overflow ovf, RowsDev R, int nfields, int64_t nslots, uint32_t* clear) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (clear && e < 3) clear[e] = 0;
+__device__ inline void apply_overflow(const Overflow& ovf, RowsDev R,
+                                      int nfields, int64_t nslots, int64_t e) {
   int64_t cnt = nslots >= 0 ? nslots : (int64_t)*ovf.count;
   if (cnt > ovf.cap) cnt = ovf.cap;
   if (e >= cnt) return;
@@ -2575,6 +2671,32 @@ __global__ __launch_bounds__(kBlock) void k_agg_apply_overflow(
   if (row == kNone || (int64_t)row >= R.cap) return;
   for (int f = 0; f < nfields; ++f)
     atomic_field(R, f, row, ovf.val[(int64_t)f * ovf.cap + e]);
+}
+
+__global__ __launch_bounds__(kBlock) void k_agg_apply_overflow(
+    Overflow ovf, RowsDev R, int nfields, int64_t nslots) {
+  apply_overflow(ovf, R, nfields, nslots,
+                 (int64_t)blockIdx.x * kBlock + threadIdx.x);
+}
+
+// The heads pass over rows (its first `hblocks` blocks; it reads headers
+// only) and beside it the finer levels' overflow slots (the blocks after
+// them, null ovf.row: none).  The last heads block scans a table of at most
+// kTailScan counts.
+template <int MaxD>
+__global__ __launch_bounds__(kBlock) void k_agg_heads_rows(
+    FromRows src, uint32_t act, int lv0, int lv1, int D, int64_t M,
+    int64_t nwt, uint32_t* tilecnt, uint32_t* tilebase, uint32_t* flags,
+    uint32_t* status, uint32_t* count, uint32_t hblocks, Overflow ovf,
+    RowsDev R, int nfields, int64_t nslots) {
+  if (blockIdx.x >= hblocks) {
+    apply_overflow(ovf, R, nfields, nslots,
+                   (int64_t)(blockIdx.x - hblocks) * kBlock + threadIdx.x);
+    return;
+  }
+  agg_heads<MaxD>(src, act, lv0, lv1, D, M, nwt, tilecnt, flags, status);
+  if (!count || !last_block(count, hblocks)) return;
+  block_scan_array(tilecnt, tilebase, (int64_t)(lv1 - lv0 + 1) * nwt);
 }
 
 // zero the sums of rows [level_offset[a], level_offset[b]) (atomic re-run)
@@ -2659,9 +2781,17 @@ __global__ void k_fill_u32_many(uint32_t** p, const int64_t* counts, int L,
     p[li][i] = 0xFFFFFFFFu;
 }
 
-__global__ void k_nat_init(uint32_t* flags, uint32_t* gs, int G) {
+// Counters of finished blocks (last_block), one per launch of a call that
+// uses one: the heads passes, the GPU rows, the row passes.
+constexpr int kDoneHeads = 0, kDoneHeads2 = 1, kDoneGpu = 2, kDoneRows = 3,
+              kDone = kDoneRows + kMaxLevels;
+
+// flags, the counters of finished blocks and the GPUs' first positions
+__global__ void k_nat_init(uint32_t* flags, uint32_t* flags2, uint32_t* done,
+                           uint32_t* gs, int G) {
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i < 3) flags[i] = 0;
+  if (i < 3) flags[i] = flags2[i] = 0;
+  if (i < kDone) done[i] = 0;
   if (i < G) gs[i] = kNone;
 }
 
@@ -2673,6 +2803,7 @@ __global__ void k_zero_u32(uint32_t* p, int n) {
 // ---------------------------------------------------------------------------
 // words read back by the host: flags, level offsets, interior pieces
 constexpr int kStageWords = 3 + kMaxLevels + 1 + kMaxLevels;
+static_assert(kStageWords * sizeof(int64_t) <= kReadBackMax, "one read-back");
 
 struct AggLayout {
   int L;
@@ -2703,6 +2834,7 @@ struct AggLayout {
   uint32_t* htc2;         // one or two levels over rows
   uint32_t* htb2;
   uint32_t* hflags2;
+  uint32_t* done;         // [kDone] counters of finished blocks
   // natural tiles
   int G;
   int64_t nstride;        // 2 * (natural tiles + G): counts per level
@@ -2734,7 +2866,7 @@ struct AggLayout {
   // groups of several runs
   uint8_t* omask;         // [L][mstride] owners of every lane
   int64_t mstride;        // 64 * (natural tiles + G)
-  uint32_t* interior;     // [kMaxLevels]
+  uint32_t* interior;     // [kMaxLevels] and a counter of finished blocks
 };
 
 static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
@@ -2773,6 +2905,7 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.htc2 = sc.take<uint32_t>(2 * L.ntiles_h);
   L.htb2 = sc.take<uint32_t>(2 * L.ntiles_h);
   L.hflags2 = sc.take<uint32_t>(3);
+  L.done = sc.take<uint32_t>(kDone);
   L.G = G;
   L.ntc = sc.take<uint32_t>((int64_t)L.L * L.nstride);
   L.ntb = sc.take<uint32_t>((int64_t)L.L * L.nstride);
@@ -2800,7 +2933,7 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.igk = sc.take<uint16_t>(n);
   L.mstride = (int64_t)kWave * (L.ntiles_h + G);
   L.omask = sc.take<uint8_t>((int64_t)L.L * L.mstride);
-  L.interior = sc.take<uint32_t>(kMaxLevels);
+  L.interior = sc.take<uint32_t>(kMaxLevels + 1);
   return L;
 }
 
@@ -2850,11 +2983,24 @@ static int exact_group_ids(const AggLayout& L, const RecSrc& S, int lmax,
 
 using namespace chopper;
 
+// Parts of the reduction's fields.  A wave takes about 1 us a field, and the
+// chip holds 3,072 of them, so that below as many tiles most of it would
+// idle: 262 tiles of 134,000 rows with 16 counters 43 to 23 us, the 480 of
+// 245,760 records without counters 27 to 24.  Above, finding the pieces again
+// costs what the fuller chip gives (4,808 tiles in two parts: no change, in
+// three 5 % slower).
+static unsigned reduce_parts(int64_t tiles, int nsum) {
+  const int64_t most = (kSpecial + nsum) / 3;
+  int64_t p = ceil_div(kReduceWaves, tiles > 0 ? tiles : 1);
+  if (p > most) p = most;
+  return (unsigned)(p > 0 ? p : 1);
+}
+
 // Geometry of the natural tiles (flag 2 set when the order does not qualify).
 static int nat_geometry(const AggLayout& L, const RecSrc& S, hipStream_t s) {
   const int64_t Th = L.ntiles_h;
   CHOPPER_HIP(launch("agg_nat_init", k_nat_init, dim3(1), dim3(kBlock), s,
-                     L.hflags, L.gs, L.G));
+                     L.hflags, L.hflags2, L.done, L.gs, L.G));
   CHOPPER_HIP(launch("agg_nat_pre", k_nat_pre,
                      dim3((unsigned)ceil_div(Th, (int64_t)kWavesPerBlock)),
                      dim3(kBlock), s, S.n, L.G, S.gpu, S.cls, S.start, Th,
@@ -2870,12 +3016,9 @@ static int nat_geometry(const AggLayout& L, const RecSrc& S, hipStream_t s) {
 // GPU rows and the workload rows from the level-0 rows.
 static int gpu_rows(const AggLayout& L, const RowsDev& R, int D, int nfields,
                     const int64_t* level_offset, hipStream_t s) {
-  CHOPPER_HIP(launch("agg_gpu_rows", k_agg_gpu_sums,
+  CHOPPER_HIP(launch("agg_gpu_rows", k_agg_gpu_rows,
                      dim3((unsigned)(2 * L.G)), dim3(kBlock), s, level_offset,
-                     R, nfields, L.pair));
-  CHOPPER_HIP(launch("agg_workload_from_gpu", k_agg_gpu_finish, dim3(1),
-                     dim3(1024), s, level_offset, D, R, nfields, 2 * L.G,
-                     (const uint64_t*)L.pair));
+                     D, R, nfields, 2 * L.G, L.pair, L.done + kDoneGpu));
   return CHOPPER_OK;
 }
 
@@ -2901,16 +3044,19 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
   // li - 1
   auto nat_records = [&](const NatGeom& NG, int li, bool two) -> int {
     const uint32_t* tb = L.ntb + (int64_t)li * L.nstride;
-    const dim3 grid((unsigned)ceil_div(NW, (int64_t)kWavesPerBlock));
+    const unsigned parts = reduce_parts(NW, fr.S.nc + 2);
+    const dim3 grid((unsigned)ceil_div(NW, (int64_t)kWavesPerBlock), parts);
     if (two)
       CHOPPER_HIP(launch("agg_fast_reduce_records",
-                         k_agg_fast_reduce<kMD, FromRecords, true, true, false>,
+                         parts > 1 ? k_agg_fast_reduce<kMD, FromRecords, true, true, false, true>
+                                   : k_agg_fast_reduce<kMD, FromRecords, true, true, false, false>,
                          grid, dim3(kBlock), s, fr, NG, li, D, M, tb,
                          (const uint32_t*)(tb - L.nstride),
                          (const int64_t*)nullptr, R, ovf, NW, GenRed{}));
     else
       CHOPPER_HIP(launch("agg_fast_reduce_records",
-                         k_agg_fast_reduce<kMD, FromRecords, false, true, false>,
+                         parts > 1 ? k_agg_fast_reduce<kMD, FromRecords, false, true, false, true>
+                                   : k_agg_fast_reduce<kMD, FromRecords, false, true, false, false>,
                          grid, dim3(kBlock), s, fr, NG, li, D, M, tb,
                          (const uint32_t*)nullptr, (const int64_t*)nullptr,
                          R, ovf, NW, GenRed{}));
@@ -2928,12 +3074,39 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
   // and exits on the device unless the flags let it run
   uint32_t hf[3] = {1u, 0u, 1u};
   int64_t lo_h[kMaxLevels + 1];
+  // opened before the kernel that stores the words, finished here
+  ReadBack rb;
+  auto stage_of = [&](int64_t stride, uint32_t* tc, uint32_t* tb, bool isnat,
+                      int done) -> StageOut {
+    StageOut O;
+    O.L = Lv;
+    O.stride = stride;
+    O.tilecnt = tc;
+    O.tilebase = tb;
+    O.total = L.htotal;
+    O.interior = nullptr;
+    O.nat = isnat;
+    O.workload = want_workload;
+    O.cap = rows->cap;
+    O.level_offset = rows->level_offset;
+    O.stage = L.stage;
+    O.host = read_back_open(sizeof(int64_t) * (size_t)(3 + Lv + 1), &rb);
+    O.status = status;
+    O.count = (int64_t)Lv * stride <= kTailScan ? L.done + done : nullptr;
+    return O;
+  };
+  auto scan_of = [&](const StageOut& O, uint32_t* tmp) -> int {
+    if (O.count) return CHOPPER_OK;       // done by the heads pass
+    CHOPPER_HIP(exclusive_scan<uint32_t>(O.tilecnt, O.tilebase,
+                                         (int64_t)Lv * O.stride, tmp, O.total,
+                                         s));
+    CHOPPER_HIP(launch("agg_offsets", k_agg_offsets, dim3(1), dim3(64), s, O,
+                       (const uint32_t*)L.hflags));
+    return CHOPPER_OK;
+  };
   auto fetch_stage = [&](bool speculate) -> int {
     int64_t st[3 + kMaxLevels + 1];
-    ReadBack rb;
-    CHOPPER_HIP(read_back_start(L.stage,
-                                sizeof(int64_t) * (size_t)(3 + Lv + 1), s,
-                                &rb));
+    CHOPPER_HIP(read_back_close(L.stage, s, &rb));
     // gap and ovl are read from here on: the caller's event first (the
     // read-back above does not wait for it)
     if (ready) CHOPPER_HIP(hipStreamWaitEvent(s, ready, 0));
@@ -2951,17 +3124,15 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
   };
   rc = nat_geometry(L, S, s);
   if (rc != CHOPPER_OK) return rc;
-  CHOPPER_HIP(launch("agg_heads_nat", k_agg_heads_nat<kMD>,
-                     dim3((unsigned)ceil_div(NW, (int64_t)kWavesPerBlock)),
-                     dim3(kBlock), s, S, N, act, 0, Lv - 1, D, M, L.nstride,
-                     L.ntc, L.hflags, status));
-  CHOPPER_HIP(exclusive_scan<uint32_t>(L.ntc, L.ntb, (int64_t)Lv * L.nstride,
-                                       L.nscan, L.htotal, s));
-  CHOPPER_HIP(launch("agg_offsets", k_agg_offsets_fast, dim3(1), dim3(64),
-                     s, Lv, L.nstride, (const uint32_t*)L.ntb,
-                     (const uint32_t*)L.htotal, (const uint32_t*)L.hflags,
-                     want_workload, rows->cap, rows->level_offset, L.stage,
-                     status));
+  {
+    const StageOut O = stage_of(L.nstride, L.ntc, L.ntb, true, kDoneHeads);
+    CHOPPER_HIP(launch("agg_heads_nat", k_agg_heads_nat<kMD>,
+                       dim3((unsigned)ceil_div(NW, (int64_t)kWavesPerBlock)),
+                       dim3(kBlock), s, S, N, act, 0, Lv - 1, D, M, L.nstride,
+                       L.ntc, L.hflags, status, O));
+    rc = scan_of(O, L.nscan);
+    if (rc != CHOPPER_OK) return rc;
+  }
   rc = fetch_stage(true);
   if (rc != CHOPPER_OK) return rc;
   const bool nat = hf[2] == 0;
@@ -2969,17 +3140,13 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
   if (!nat) {
     CHOPPER_HIP(launch("agg_zero", k_zero_u32, dim3(1), dim3(64), s,
                        L.hflags, 3));
-    CHOPPER_HIP(launch("agg_heads_records", k_agg_heads<kMD, FromRecords>,
+    const StageOut O = stage_of(Th, L.htc, L.htb, false, kDoneHeads2);
+    CHOPPER_HIP(launch("agg_heads_records", k_agg_heads<kMD>,
                        dim3((unsigned)ceil_div(Th, (int64_t)kWavesPerBlock)),
                        dim3(kBlock), s, fr, act, 0, Lv - 1, D, M, Th, L.htc,
-                       L.hflags, status));
-    CHOPPER_HIP(exclusive_scan<uint32_t>(L.htc, L.htb, (int64_t)Lv * Th,
-                                         L.hscan, L.htotal, s));
-    CHOPPER_HIP(launch("agg_offsets", k_agg_offsets_fast, dim3(1), dim3(64),
-                       s, Lv, Th, (const uint32_t*)L.htb,
-                       (const uint32_t*)L.htotal, (const uint32_t*)L.hflags,
-                       want_workload, rows->cap, rows->level_offset, L.stage,
-                       status));
+                       L.hflags, status, O));
+    rc = scan_of(O, L.hscan);
+    if (rc != CHOPPER_OK) return rc;
     rc = fetch_stage(false);
     if (rc != CHOPPER_OK) return rc;
   }
@@ -2990,71 +3157,88 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
   };
   if (hf[0] & 2u) *conflict = true;
   if (hf[0] != 0) return 1;
+  // overflow slots of the pass before, applied beside the next heads pass
+  // over rows (which reads headers only) or, after the last pass, alone
+  int64_t slots = 0;
+  auto apply = [&]() -> int {
+    if (slots == 0) return CHOPPER_OK;
+    CHOPPER_HIP(launch("agg_apply_overflow", k_agg_apply_overflow,
+                       grid_for(slots, kBlock), dim3(kBlock), s, ovf, R,
+                       nfields, slots));
+    slots = 0;
+    return CHOPPER_OK;
+  };
   // finer < 0: from the records (two levels, li and li - 1, when `two`)
   auto fast_level = [&](int li, int finer, bool two) -> int {
     if (finer < 0) {
-      int64_t ns;
       if (nat) {
         // (queued before the flags were read, when they allowed it)
         if (!(spec && li == li0 && two == two0)) {
           const int r = nat_records(N, li, two);
           if (r != CHOPPER_OK) return r;
         }
-        ns = (two ? 4 : 2) * NW;
+        slots = (two ? 4 : 2) * NW;
       } else {
         const uint32_t* tb = L.htb + (int64_t)li * Th;
+        const unsigned parts = reduce_parts(Th, fr.S.nc + 2);
         if (two)
           CHOPPER_HIP(launch("agg_fast_reduce_records",
-                             k_agg_fast_reduce<kMD, FromRecords, true, false, false>,
-                             dim3((unsigned)T), dim3(kBlock), s, fr, none, li,
+                             parts > 1 ? k_agg_fast_reduce<kMD, FromRecords, true, false, false, true>
+                                       : k_agg_fast_reduce<kMD, FromRecords, true, false, false, false>,
+                             dim3((unsigned)T, parts),
+                             dim3(kBlock), s, fr, none, li,
                              D, M, tb, (const uint32_t*)(tb - Th),
                              (const int64_t*)nullptr, R, ovf, Th, GenRed{}));
         else
           CHOPPER_HIP(launch("agg_fast_reduce_records",
-                             k_agg_fast_reduce<kMD, FromRecords, false, false, false>,
-                             dim3((unsigned)T), dim3(kBlock), s, fr, none, li,
+                             parts > 1 ? k_agg_fast_reduce<kMD, FromRecords, false, false, false, true>
+                                       : k_agg_fast_reduce<kMD, FromRecords, false, false, false, false>,
+                             dim3((unsigned)T, parts),
+                             dim3(kBlock), s, fr, none, li,
                              D, M, tb, (const uint32_t*)nullptr,
                              (const int64_t*)nullptr, R, ovf, Th, GenRed{}));
-        ns = two ? 2 * Th : Th;
+        slots = two ? 2 * Th : Th;
       }
-      CHOPPER_HIP(launch("agg_apply_overflow", k_agg_apply_overflow,
-                         grid_for(ns, kBlock), dim3(kBlock), s, ovf, R,
-                         nfields, ns, L.hflags2));
     } else {
       // launches sized by the finer level's row count; with `two` also the
       // level li - 1 (heads of li - 1 first in the table, then li)
       const int64_t cnt = level_rows(finer);
-      if (cnt == 0) return CHOPPER_OK;
+      if (cnt == 0) return apply();
       const int64_t nw = ceil_div(cnt, (int64_t)kWaveTile);
       const unsigned gr = (unsigned)ceil_div(nw, (int64_t)kWavesPerBlock);
       FromRows src{R, M, rows->level_offset, finer};
       const int lv0 = two ? li - 1 : li;
       const uint32_t lact = two ? (3u << (li - 1)) : (1u << li);
-      // (the flags were zeroed by the previous overflow pass)
-      CHOPPER_HIP(launch("agg_heads_rows", k_agg_heads<kMD, FromRows>,
-                         dim3(gr), dim3(kBlock), s, src, lact, lv0, li, D, M,
-                         nw, L.htc2, L.hflags2, status));
-      CHOPPER_HIP(exclusive_scan<uint32_t>(L.htc2, L.htb2,
-                                           (two ? 2 : 1) * nw, L.hscan,
-                                           L.htotal + 1, s));
+      const int64_t tab = (two ? 2 : 1) * nw;
+      uint32_t* done = tab <= kTailScan ? L.done + kDoneRows + li : nullptr;
+      CHOPPER_HIP(launch("agg_heads_rows", k_agg_heads_rows<kMD>,
+                         dim3(gr + (unsigned)ceil_div(slots, (int64_t)kBlock)),
+                         dim3(kBlock), s, src, lact, lv0, li, D, M, nw,
+                         L.htc2, L.htb2, L.hflags2, status, done, gr, ovf, R,
+                         nfields, slots));
+      if (!done)
+        CHOPPER_HIP(exclusive_scan<uint32_t>(L.htc2, L.htb2, tab, L.hscan,
+                                             L.htotal + 1, s));
       const int64_t* r0 = rows->level_offset + li;
+      const unsigned parts = reduce_parts(nw, R.nc + 4);
       if (two)
         CHOPPER_HIP(launch("agg_fast_reduce_rows",
-                           k_agg_fast_reduce<kMD, FromRows, true, false, false>,
-                           dim3(gr), dim3(kBlock), s, src, none, li, D, M,
+                           parts > 1 ? k_agg_fast_reduce<kMD, FromRows, true, false, false, true>
+                                     : k_agg_fast_reduce<kMD, FromRows, true, false, false, false>,
+                           dim3(gr, parts), dim3(kBlock), s,
+                           src, none, li, D, M,
                            (const uint32_t*)(L.htb2 + nw),
                            (const uint32_t*)L.htb2, r0, R, ovf, nw,
                            GenRed{}));
       else
         CHOPPER_HIP(launch("agg_fast_reduce_rows",
-                           k_agg_fast_reduce<kMD, FromRows, false, false, false>,
-                           dim3(gr), dim3(kBlock), s, src, none, li, D, M,
+                           parts > 1 ? k_agg_fast_reduce<kMD, FromRows, false, false, false, true>
+                                     : k_agg_fast_reduce<kMD, FromRows, false, false, false, false>,
+                           dim3(gr, parts), dim3(kBlock), s,
+                           src, none, li, D, M,
                            (const uint32_t*)L.htb2, (const uint32_t*)nullptr,
                            r0, R, ovf, nw, GenRed{}));
-      const int64_t ns = (two ? 2 : 1) * nw;
-      CHOPPER_HIP(launch("agg_apply_overflow", k_agg_apply_overflow,
-                         grid_for(ns, kBlock), dim3(kBlock), s, ovf, R,
-                         nfields, ns, L.hflags2));
+      slots = tab;
     }
     return CHOPPER_OK;
   };
@@ -3069,10 +3253,14 @@ static int agg_fast(const AggLayout& L, const RecSrc& S, const RowsDev& R,
       rc = fast_level(li, li + 1, li >= 1);
       if (rc != CHOPPER_OK) return rc;
     }
+    rc = apply();
+    if (rc != CHOPPER_OK) return rc;
     rc = gpu_rows(L, R, D, nfields, rows->level_offset, s);
     if (rc != CHOPPER_OK) return rc;
   } else {
     rc = fast_level(level == CHOPPER_LEVEL_GPU ? D : level, -1, false);
+    if (rc != CHOPPER_OK) return rc;
+    rc = apply();
     if (rc != CHOPPER_OK) return rc;
   }
   return CHOPPER_OK;
@@ -3130,25 +3318,37 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
       CHOPPER_HIP(launch("agg_gen_elect", k_gen_elect<kMD, kNat, false>, grid,
                          dim3(kBlock), s, fr, N, act, D, M, nwt, tab,
                          L.hflags));
-    CHOPPER_HIP(launch("agg_gen_count", k_gen_count<kMD, FromRecords, kNat>,
-                       grid, dim3(kBlock), s, fr, N, act, 0, Lv - 1, D, M, nwt,
+    ReadBack rb;
+    StageOut O;
+    O.L = Lv;
+    O.stride = stride;
+    O.tilecnt = tc;
+    O.tilebase = tb;
+    O.total = L.htotal;
+    O.interior = L.interior;
+    O.nat = kNat;
+    O.workload = want_workload;
+    O.cap = rows->cap;
+    O.level_offset = rows->level_offset;
+    O.stage = L.stage;
+    O.host = read_back_open(sizeof(int64_t) * (size_t)(3 + Lv + 1 + Lv), &rb);
+    O.status = status;
+    O.count = (int64_t)Lv * stride <= kTailScan ? L.interior + kMaxLevels
+                                                : nullptr;
+    CHOPPER_HIP(launch("agg_gen_count", k_gen_count<kMD, kNat>, grid,
+                       dim3(kBlock), s, fr, N, act, 0, Lv - 1, D, M, nwt,
                        stride, tab, tc, L.omask, L.mstride, L.hflags,
-                       L.interior, L.ovf_count, status));
-    CHOPPER_HIP(exclusive_scan<uint32_t>(tc, tb, (int64_t)Lv * stride,
-                                         kNat ? L.nscan : L.hscan, L.htotal,
-                                         s));
-    CHOPPER_HIP(launch("agg_offsets", k_gen_offsets, dim3(1), dim3(64), s, Lv,
-                       stride, (const uint32_t*)tb, (const uint32_t*)L.htotal,
-                       (const uint32_t*)L.hflags, (const uint32_t*)L.interior,
-                       kNat, want_workload, rows->cap, rows->level_offset,
-                       L.stage, status));
-    {
-      ReadBack rb;
-      CHOPPER_HIP(read_back_start(
-          L.stage, sizeof(int64_t) * (size_t)(3 + Lv + 1 + Lv), s, &rb));
-      if (ready) CHOPPER_HIP(hipStreamWaitEvent(s, ready, 0));
-      CHOPPER_HIP(read_back_finish(&rb, st));
+                       L.interior, status, O));
+    if (!O.count) {
+      CHOPPER_HIP(exclusive_scan<uint32_t>(tc, tb, (int64_t)Lv * stride,
+                                           kNat ? L.nscan : L.hscan,
+                                           L.htotal, s));
+      CHOPPER_HIP(launch("agg_offsets", k_agg_offsets, dim3(1), dim3(64), s,
+                         O, (const uint32_t*)L.hflags));
     }
+    CHOPPER_HIP(read_back_close(L.stage, s, &rb));
+    if (ready) CHOPPER_HIP(hipStreamWaitEvent(s, ready, 0));
+    CHOPPER_HIP(read_back_finish(&rb, st));
     if (kNat && st[2] != 0) {
       *bad_order = true;
       return 1;
@@ -3192,13 +3392,13 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
       GR.mask2 = q.two ? GR.mask - L.mstride : nullptr;
       if (q.two)
         CHOPPER_HIP(launch("agg_gen_reduce_records",
-                           k_agg_fast_reduce<kMD, FromRecords, true, kNat, true>,
+                           k_agg_fast_reduce<kMD, FromRecords, true, kNat, true, false>,
                            grid, dim3(kBlock), s, fr, N, li, D, M, tbl,
                            tbl - stride, (const int64_t*)nullptr, R, ovf, nwt,
                            GR));
       else
         CHOPPER_HIP(launch("agg_gen_reduce_records",
-                           k_agg_fast_reduce<kMD, FromRecords, false, kNat, true>,
+                           k_agg_fast_reduce<kMD, FromRecords, false, kNat, true, false>,
                            grid, dim3(kBlock), s, fr, N, li, D, M, tbl,
                            (const uint32_t*)nullptr, (const int64_t*)nullptr,
                            R, ovf, nwt, GR));
@@ -3210,26 +3410,27 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
       FromRows src{R, M, rows->level_offset, li + 1};
       const int lv0 = q.two ? li - 1 : li;
       const uint32_t lact = q.two ? (3u << (li - 1)) : (1u << li);
-      CHOPPER_HIP(launch("agg_gen_count_rows",
-                         k_gen_count<kMD, FromRows, false>, gr, dim3(kBlock),
-                         s, src, NatGeom{}, lact, lv0, li, D, M, nw, nw, tab,
-                         L.htc2, L.omask, L.mstride, L.hflags, L.interior,
-                         L.ovf_count, status));
-      CHOPPER_HIP(exclusive_scan<uint32_t>(L.htc2, L.htb2,
-                                           (q.two ? 2 : 1) * nw, L.hscan,
-                                           L.htotal + 1, s));
+      const int64_t tab_n = (q.two ? 2 : 1) * nw;
+      uint32_t* done = tab_n <= kTailScan ? L.done + kDoneRows + li : nullptr;
+      CHOPPER_HIP(launch("agg_gen_count_rows", k_gen_count_rows<kMD>, gr,
+                         dim3(kBlock), s, src, lact, lv0, li, D, M, nw, tab,
+                         L.htc2, L.htb2, L.omask, L.mstride, done,
+                         L.ovf_count));
+      if (!done)
+        CHOPPER_HIP(exclusive_scan<uint32_t>(L.htc2, L.htb2, tab_n, L.hscan,
+                                             L.htotal + 1, s));
       GR.mask = L.omask + (q.two ? L.mstride : 0);
       GR.mask2 = L.omask;
       const int64_t* r0 = rows->level_offset + li;
       if (q.two)
         CHOPPER_HIP(launch("agg_gen_reduce_rows",
-                           k_agg_fast_reduce<kMD, FromRows, true, false, true>,
+                           k_agg_fast_reduce<kMD, FromRows, true, false, true, false>,
                            gr, dim3(kBlock), s, src, NatGeom{}, li, D, M,
                            (const uint32_t*)(L.htb2 + nw),
                            (const uint32_t*)L.htb2, r0, R, ovf, nw, GR));
       else
         CHOPPER_HIP(launch("agg_gen_reduce_rows",
-                           k_agg_fast_reduce<kMD, FromRows, false, false, true>,
+                           k_agg_fast_reduce<kMD, FromRows, false, false, true, false>,
                            gr, dim3(kBlock), s, src, NatGeom{}, li, D, M,
                            (const uint32_t*)L.htb2, (const uint32_t*)nullptr,
                            r0, R, ovf, nw, GR));
@@ -3450,7 +3651,7 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
     if (!atomic_mode)
       CHOPPER_HIP(launch("agg_apply_overflow", k_agg_apply_overflow,
                          grid_for(L.ovf_cap, kBlock), dim3(kBlock), s, ovf, R,
-                         nfields, (int64_t)-1, (uint32_t*)nullptr));
+                         nfields, (int64_t)-1));
     if (li == D + 1) {
       if (finer < 0) {
         FromRecords src{S};
@@ -3486,8 +3687,8 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
     CHOPPER_HIP(exclusive_scan<uint32_t>(L.tilecnt, L.tilebase,
                                          (int64_t)Lv * T, L.scantmp, L.total,
                                          s));
-    CHOPPER_HIP(launch("agg_offsets", k_agg_offsets, dim3(1), dim3(64), s, Lv,
-                       T, (const uint32_t*)L.tilebase,
+    CHOPPER_HIP(launch("agg_offsets", k_agg_offsets_all, dim3(1), dim3(64), s,
+                       Lv, T, (const uint32_t*)L.tilebase,
                        (const uint32_t*)L.total, rows->cap,
                        rows->level_offset, status));
     if (n == 0) return CHOPPER_OK;

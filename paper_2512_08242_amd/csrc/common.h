@@ -189,6 +189,91 @@ struct ReadBack {
 hipError_t read_back_start(const void* dev, size_t bytes, hipStream_t s,
                            ReadBack* rb);
 hipError_t read_back_finish(ReadBack* rb, void* host);
+// The first half without a launch of its own, for a kernel that stores the
+// words itself: read_back_open hands out the slot's device address (null
+// when there is none), which the kernel writes beside `dev` (store_host
+// below); read_back_close after the launch records the event, or reads
+// `dev` at once when there was no slot.
+uint32_t* read_back_open(size_t bytes, ReadBack* rb);
+hipError_t read_back_close(const void* dev, hipStream_t s, ReadBack* rb);
+
+// One word of a read-back into the slot (host memory), visible to the host
+// before the kernel, and the event after it, ends.
+__device__ inline void store_host(uint32_t* slot, int i, uint32_t v) {
+  if (slot) {
+    slot[i] = v;
+    __threadfence_system();
+  }
+}
+__device__ inline void store_host(uint32_t* slot, int i, int64_t v) {
+  if (slot) {
+    reinterpret_cast<int64_t*>(slot)[i] = v;
+    __threadfence_system();
+  }
+}
+
+// Is this the last block of a launch of `blocks` blocks to get here (the
+// same in every thread)?  Everything the other blocks stored before is then
+// visible.  `count` is zero before the launch.  A kernel whose blocks each
+// leave a small result ends this way with the steps that combine them,
+// which saves a launch or more.  It costs the fence, 3 us beside 120 blocks,
+// so it pays where it stands for two launches, not for one.
+// Every thread of every block comes here.
+__device__ inline bool last_block(uint32_t* count, uint32_t blocks) {
+  __shared__ uint32_t s_last;
+  // (every wave's stores have reached the L2 before one wave writes it back)
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    __threadfence();
+    s_last = atomicAdd(count, 1u) == blocks - 1u;
+  }
+  __syncthreads();
+  const bool last = s_last != 0;
+  if (last) __threadfence();
+  return last;
+}
+
+// Exclusive prefix sums of in[0 .. n) by one block of kBlock threads, for
+// small n (16-byte loads and stores; in and out 16-byte aligned and readable
+// and writable up to a multiple of four); returns the total in every thread.
+__device__ inline uint32_t block_scan_array(const uint32_t* in, uint32_t* out,
+                                            int64_t n) {
+  constexpr int kQ = 4;
+  uint32_t carry = 0;
+  for (int64_t b = 0; b < n; b += (int64_t)kBlock * kQ * 4) {
+    const int64_t i0 = b + (int64_t)threadIdx.x * (kQ * 4);
+    uint32_t v[kQ * 4], acc = 0;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q) {
+      uint4 x = make_uint4(0u, 0u, 0u, 0u);
+      if (i0 + 4 * q < n) x = *reinterpret_cast<const uint4*>(in + i0 + 4 * q);
+      v[4 * q] = x.x;
+      v[4 * q + 1] = i0 + 4 * q + 1 < n ? x.y : 0u;
+      v[4 * q + 2] = i0 + 4 * q + 2 < n ? x.z : 0u;
+      v[4 * q + 3] = i0 + 4 * q + 3 < n ? x.w : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < kQ * 4; ++q) {
+      const uint32_t x = v[q];
+      v[q] = acc;
+      acc += x;
+    }
+    uint32_t tot;
+    const uint32_t pre = block_exclusive(acc, OpAdd(), 0u, &tot) + carry;
+#pragma unroll
+    for (int q = 0; q < kQ; ++q)
+      if (i0 + 4 * q < n)
+        *reinterpret_cast<uint4*>(out + i0 + 4 * q) =
+            make_uint4(pre + v[4 * q], pre + v[4 * q + 1], pre + v[4 * q + 2],
+                       pre + v[4 * q + 3]);
+    carry += tot;
+  }
+  return carry;
+}
+// the largest table a kernel's last block scans itself: three rounds of the
+// loop above, which is what the scan's launches take
+constexpr int64_t kTailScan = 12288;
 
 // the same as launch() with `shm` bytes of dynamic LDS
 template <typename Kern, typename... Args>

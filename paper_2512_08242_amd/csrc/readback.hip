@@ -105,31 +105,54 @@ __global__ __launch_bounds__(kWave) void k_put_host(const uint32_t* src,
 
 }  // namespace
 
-hipError_t read_back_start(const void* dev, size_t bytes, hipStream_t s,
-                           ReadBack* rb) {
-  rb->slot = nullptr;
+uint32_t* read_back_open(size_t bytes, ReadBack* rb) {
   rb->bytes = bytes;
   rb->err = hipSuccess;
-  if (bytes == 0) return hipSuccess;
-  if (bytes > kReadBackMax) return hipErrorInvalidValue;
-  // whole aligned words only (every caller's case); others read now
-  RbSlot* q = (bytes % 4 == 0 && ((uintptr_t)dev & 3) == 0) ? take_slot()
-                                                              : nullptr;
+  // whole words only (every caller's case)
+  RbSlot* q = bytes > 0 && bytes <= kReadBackMax && bytes % 4 == 0
+                  ? take_slot() : nullptr;
+  rb->slot = q;
+  return q ? q->dpin : nullptr;
+}
+
+hipError_t read_back_close(const void* dev, hipStream_t s, ReadBack* rb) {
+  if (rb->bytes == 0) return hipSuccess;
+  RbSlot* q = static_cast<RbSlot*>(rb->slot);
   if (!q) {
     // no slot: read now into the inline buffer
-    rb->err = read_now(dev, rb->now, bytes, s);
+    rb->err = rb->bytes > kReadBackMax ? hipErrorInvalidValue
+                                       : read_now(dev, rb->now, rb->bytes, s);
     return rb->err;
   }
-  hipError_t e = launch("read_back", k_put_host, dim3(1), dim3(kWave), s,
-                        static_cast<const uint32_t*>(dev), q->dpin,
-                        (int)(bytes / 4));
-  if (e == hipSuccess) e = hipEventRecord(q->ev, s);
+  const hipError_t e = hipEventRecord(q->ev, s);
   if (e != hipSuccess) {
+    // (the kernel before may still store into the slot)
+    (void)poll([&] { return hipStreamQuery(s); });
+    rb->slot = nullptr;
     give_slot(q);
+  }
+  return e;
+}
+
+hipError_t read_back_start(const void* dev, size_t bytes, hipStream_t s,
+                           ReadBack* rb) {
+  if (bytes > kReadBackMax) return hipErrorInvalidValue;
+  uint32_t* slot = ((uintptr_t)dev & 3) == 0 ? read_back_open(bytes, rb)
+                                             : nullptr;
+  if (!slot) {
+    rb->slot = nullptr;
+    rb->bytes = bytes;
+    return read_back_close(dev, s, rb);
+  }
+  const hipError_t e = launch("read_back", k_put_host, dim3(1), dim3(kWave),
+                              s, static_cast<const uint32_t*>(dev), slot,
+                              (int)(bytes / 4));
+  if (e != hipSuccess) {
+    give_slot(static_cast<RbSlot*>(rb->slot));
+    rb->slot = nullptr;
     return e;
   }
-  rb->slot = q;
-  return hipSuccess;
+  return read_back_close(dev, s, rb);
 }
 
 hipError_t read_back_finish(ReadBack* rb, void* host) {
@@ -150,7 +173,8 @@ ReadBack::~ReadBack() {
   if (!slot) return;
   RbSlot* q = static_cast<RbSlot*>(slot);
   // the copy into the slot may still be queued: wait for it before the
-  // slot can be taken again
+  // slot can be taken again (a slot that was opened and not closed, its
+  // launch having failed, has only its earlier event, already past)
   (void)poll([&] { return hipEventQuery(q->ev); });
   give_slot(q);
 }
