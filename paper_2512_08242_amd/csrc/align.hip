@@ -124,9 +124,11 @@ __device__ inline void mark_present(uint8_t* flags, uint32_t idx) {
 __global__ __launch_bounds__(kBlock) void k_transform_records(
     int64_t n, int n_gpus, const uint8_t* gpu, const uint8_t* stream,
     const uint8_t* cls, const int64_t* start, const int64_t* end,
-    const ClockDev* clk, int64_t* s_out, int64_t* e_out, uint8_t* pres_s,
+    ClockArgs clocks, int64_t* s_out, int64_t* e_out, uint8_t* pres_s,
     uint8_t* pres_k, uint32_t* unsorted, uint32_t* status,
     WaveClasses* wcls) {
+  __shared__ ClockDev clk[kMaxClocks];
+  clocks_to_lds(clocks, n_gpus, clk);
   // each lane owns eight consecutive records (a wave 512)
   const int lane = lane_id(), wv = (int)(threadIdx.x / kWave);
   const int64_t base =
@@ -283,8 +285,10 @@ __global__ __launch_bounds__(kBlock) void k_transform_records(
 
 __global__ __launch_bounds__(kBlock) void k_transform_markers(
     int64_t n, int n_gpus, int depth, const uint8_t* gpu, const uint8_t* level,
-    const int64_t* start, const int64_t* end, const ClockDev* clk,
+    const int64_t* start, const int64_t* end, ClockArgs clocks,
     int64_t* s_out, int64_t* e_out, uint32_t* status) {
+  __shared__ ClockDev clk[kMaxClocks];
+  clocks_to_lds(clocks, n_gpus, clk);
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   uint32_t st = 0;
   if (i < n) {
@@ -308,8 +312,8 @@ __global__ __launch_bounds__(kBlock) void k_transform_markers(
 // Dense class ids in (gpu, stream) and (gpu, kind) order from the presence
 // flags (65536 + 512 bytes), one block of 1024 threads: every thread counts
 // 64 consecutive (gpu, stream) flags (and at most one (gpu, kind) flag), a
-// block scan numbers them, and every thread writes its own ids with
-// 16-byte stores.
+// block scan numbers them, and every thread writes its own ids; the counts
+// (and the order flag after them) also go to the host's slot.
 constexpr int kDenseThreads = 1024;
 
 __device__ inline uint32_t block1024_exclusive(uint32_t v, uint32_t* s_w,
@@ -330,36 +334,51 @@ __device__ inline uint32_t block1024_exclusive(uint32_t v, uint32_t* s_w,
 
 __global__ __launch_bounds__(kDenseThreads) void k_dense_classes(
     const uint8_t* pres_s, uint16_t* cmap_s, const uint8_t* pres_k,
-    uint16_t* cmap_k, uint32_t* counts) {
+    uint16_t* cmap_k, uint32_t* counts, uint32_t* host) {
   __shared__ uint32_t s_w[kDenseThreads / kWave];
   const int t = threadIdx.x;
   uint4 f[4];
   const uint4* src = reinterpret_cast<const uint4*>(pres_s) + t * 4;
 #pragma unroll
   for (int q = 0; q < 4; ++q) f[q] = src[q];
-  const uint8_t* fb = reinterpret_cast<const uint8_t*>(f);
-  uint32_t c = 0;
+  // (flags are 0 or 1, and nearly every thread's are all 0; only pairs that
+  // occur are ever looked up, so only their ids are written)
+  uint32_t w[16], c = 0;
 #pragma unroll
-  for (int b = 0; b < 64; ++b) c += fb[b] ? 1u : 0u;
+  for (int q = 0; q < 4; ++q) {
+    w[4 * q] = f[q].x;
+    w[4 * q + 1] = f[q].y;
+    w[4 * q + 2] = f[q].z;
+    w[4 * q + 3] = f[q].w;
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) c += (uint32_t)__popc(w[q]);
   uint32_t tot;
   uint32_t id = block1024_exclusive(c, s_w, &tot);
-  uint16_t ids[64];
+  if (c) {
 #pragma unroll
-  for (int b = 0; b < 64; ++b) {
-    ids[b] = (uint16_t)(fb[b] ? id : 0u);
-    id += fb[b] ? 1u : 0u;
+    for (int q = 0; q < 16; ++q) {
+      uint32_t m = w[q];
+      while (m) {
+        cmap_s[t * 64 + q * 4 + ((__ffs((int)m) - 1) >> 3)] = (uint16_t)id++;
+        m &= m - 1u;
+      }
+    }
   }
-  uint4* dst = reinterpret_cast<uint4*>(cmap_s) + t * 8;
-  const uint4* iv = reinterpret_cast<const uint4*>(ids);
-#pragma unroll
-  for (int q = 0; q < 8; ++q) dst[q] = iv[q];
-  if (t == 0) counts[0] = tot;
+  if (t == 0) {
+    counts[0] = tot;
+    store_host(host, 0, tot);
+  }
   // (gpu, kind) flags: one per thread
   const uint32_t on = t < 512 && pres_k[t] ? 1u : 0u;
   uint32_t totk;
   const uint32_t k = block1024_exclusive(on, s_w, &totk);
   if (t < 512) cmap_k[t] = (uint16_t)(on ? k : 0u);
-  if (t == 0) counts[1] = totk;
+  if (t == 0) {
+    counts[1] = totk;
+    store_host(host, 1, totk);
+    store_host(host, 2, counts[2]);      // input not in order
+  }
 }
 
 // presence flags (65536 + 512 bytes) and the class counts to zero
@@ -460,18 +479,14 @@ extern "C" int chopper_align(const chopper_records* rec,
   hipStream_t s = (hipStream_t)stream;
   Scratch sc(scratch);
   AlignLayout L = align_layout(sc, n, G);
-  std::vector<ClockDev> cd(G);
-  for (int g = 0; g < G; ++g)
-    cd[g] = ClockDev{clocks[g].x0, clocks[g].c, clocks[g].d_q48};
-  CHOPPER_HIP(hipMemcpyAsync(L.clk, cd.data(), sizeof(ClockDev) * G,
-                             hipMemcpyHostToDevice, s));
+  ClockArgs ca;
+  CHOPPER_HIP(clock_args(clocks.data(), G, L.clk, s, &ca));
   auto markers = [&]() -> int {
     if (nm > 0)
       CHOPPER_HIP(launch("align_transform_markers", k_transform_markers,
                          grid_for(nm, kBlock), dim3(kBlock), s, nm, G,
                          mk->depth, mk->gpu, mk->level, mk->start_ns,
-                         mk->end_ns, (const ClockDev*)L.clk, mstart_out,
-                         mend_out, status));
+                         mk->end_ns, ca, mstart_out, mend_out, status));
     return CHOPPER_OK;
   };
   if (n == 0) return markers();
@@ -483,15 +498,15 @@ extern "C" int chopper_align(const chopper_records* rec,
                                                     kWavesPerBlock)),
                      dim3(kBlock), s, n, G, rec->gpu,
                      rec->stream, rec->cls, rec->start_ns, rec->end_ns,
-                     (const ClockDev*)L.clk, start_out, end_out, L.pres_s,
-                     L.pres_k, L.counts + 2, status, L.wcls));
-  CHOPPER_HIP(launch("align_dense_classes", k_dense_classes, dim3(1),
-                     dim3(kDenseThreads), s, (const uint8_t*)L.pres_s, L.cmap_s,
-                     (const uint8_t*)L.pres_k, L.cmap_k, L.counts));
+                     ca, start_out, end_out, L.pres_s, L.pres_k, L.counts + 2, status, L.wcls));
   // the markers are transformed while the host waits for the class counts
   uint32_t counts[3];
   ReadBack rb;
-  CHOPPER_HIP(read_back_start(L.counts, sizeof(counts), s, &rb));
+  uint32_t* host = read_back_open(sizeof(counts), &rb);
+  CHOPPER_HIP(launch("align_dense_classes", k_dense_classes, dim3(1),
+                     dim3(kDenseThreads), s, (const uint8_t*)L.pres_s, L.cmap_s,
+                     (const uint8_t*)L.pres_k, L.cmap_k, L.counts, host));
+  CHOPPER_HIP(read_back_close(L.counts, s, &rb));
   rc = markers();
   if (rc != CHOPPER_OK) {
     (void)read_back_finish(&rb, counts);

@@ -9,7 +9,6 @@
 // across the lanes and all issued before any use; the clock table sits in
 // LDS.
 #include <mutex>
-#include <vector>
 
 #include "clock.h"
 #include "wave.h"
@@ -32,12 +31,11 @@ static_assert(sizeof(::scratch) == kMaxGpus * sizeof(ClockDev),
               "the static clock table holds kMaxGpus entries");
 
 __global__ __launch_bounds__(kBlock) void k_launch_split(
-    int64_t n, int G, const uint8_t* gpu, const ClockDev* clk,
+    int64_t n, int G, const uint8_t* gpu, ClockArgs clk,
     const int64_t* launch, const int64_t* start, const int64_t* gap,
     int64_t* prep, int64_t* call, uint32_t* status) {
   __shared__ ClockDev s_clk[kMaxGpus];
-  for (int g = (int)threadIdx.x; g < G; g += kBlock) s_clk[g] = clk[g];
-  __syncthreads();
+  clocks_to_lds(clk, G, s_clk);
   const int lane = lane_id(), wv = (int)(threadIdx.x / kWave);
   const int64_t base =
       ((int64_t)blockIdx.x * kWavesPerBlock + wv) * (int64_t)kWaveTile;
@@ -134,16 +132,12 @@ extern "C" int chopper_launch_split(const chopper_records* rec,
   hipStream_t s = (hipStream_t)stream;
   Scratch sc(scratch);
   ClockDev* clk = sc.take<ClockDev>(G);
-  std::vector<ClockDev> cd(G);
-  for (int g = 0; g < G; ++g)
-    cd[g] = ClockDev{clocks[g].x0, clocks[g].c, clocks[g].d_q48};
-  // (a copy from pageable memory is staged before the call returns)
-  CHOPPER_HIP(hipMemcpyAsync(clk, cd.data(), sizeof(ClockDev) * G,
-                             hipMemcpyHostToDevice, s));
+  ClockArgs A;
+  CHOPPER_HIP(clock_args(clocks, G, clk, s, &A));
   CHOPPER_HIP(launch("launch_split", k_launch_split,
                      dim3((unsigned)ceil_div(n, (int64_t)kWaveTile *
                                                     kWavesPerBlock)),
-                     dim3(kBlock), s, n, G, rec->gpu, (const ClockDev*)clk,
+                     dim3(kBlock), s, n, G, rec->gpu, A,
                      launch_ns, start_al, gap, prep_out, call_out, status));
   return CHOPPER_OK;
 }
@@ -170,20 +164,18 @@ extern "C" int chopper_launch_split_noalloc(const chopper_records* rec,
   if (G < 1 || G > kMaxGpus) return CHOPPER_ESCRATCH;
   if (n == 0) return CHOPPER_OK;
   hipStream_t s = (hipStream_t)stream;
+  // (looked up, and the stream's device checked, also when the clocks travel
+  // with the launch)
   ClockDev* clk = nullptr;
   CHOPPER_HIP(static_scratch(s, &clk));
-  ClockDev cd[kMaxGpus];
-  for (int g = 0; g < G; ++g)
-    cd[g] = ClockDev{clocks[g].x0, clocks[g].c, clocks[g].d_q48};
   // every entry the kernel reads (0 .. G-1) is written here, so nothing left
-  // by an earlier call is read; a copy from pageable memory is staged before
-  // the call returns
-  CHOPPER_HIP(hipMemcpyAsync(clk, cd, sizeof(ClockDev) * G,
-                             hipMemcpyHostToDevice, s));
+  // by an earlier call is read
+  ClockArgs A;
+  CHOPPER_HIP(clock_args(clocks, G, clk, s, &A));
   CHOPPER_HIP(launch("launch_split", k_launch_split,
                      dim3((unsigned)ceil_div(n, (int64_t)kWaveTile *
                                                     kWavesPerBlock)),
-                     dim3(kBlock), s, n, G, rec->gpu, (const ClockDev*)clk,
+                     dim3(kBlock), s, n, G, rec->gpu, A,
                      launch_ns, start_al, gap, prep_out, call_out, status));
   return CHOPPER_OK;
 }
