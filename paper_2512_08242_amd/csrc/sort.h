@@ -344,6 +344,21 @@ int class_sort2(const AccA& a, const AccB& b, const ClassSortLayout& L,
                 uint32_t* outA, uint32_t* coffA, uint32_t* outB,
                 uint32_t* coffB, hipStream_t s, const WaveClasses* wcls);
 
+// Are both permutations of class_sort2, made of input in any order, the
+// stable sorts by (class, time)?  *sorted says; waits for `s`.
+template <typename AccA, typename AccB>
+int class_verify2(const AccA& a, const AccB& b, const ClassSortLayout& L,
+                  const uint32_t* outA, const uint32_t* outB, bool* sorted,
+                  hipStream_t s);
+
+// Both stable sorts by (class, time) of the same n > 0 items in any order:
+// one radix sort by time, carrying both class ids above the time's bits,
+// then a partition by either class.  *fits: false (and nothing sorted) when
+// a class count is above 256 or the times span 2^48 or more.  Waits for `s`.
+template <typename AccA, typename AccB>
+int time_sort2(const AccA& a, const AccB& b, const ClassSortLayout& L,
+               uint32_t* outA, uint32_t* outB, bool* fits, hipStream_t s);
+
 // Stable LSD radix sort of the (L.key0, L.val0) pairs of L.n items by the
 // low `bits` bits of the keys (8 bits per pass, through key1 / val1): the
 // values in key order go to out, the keys (optional) to keys_out.

@@ -203,7 +203,7 @@ __global__ __launch_bounds__(kBlock) void k_class_partition(
   }
 }
 
-// (both checks stop reading once some wave has found the answer)
+// (stops reading once some wave has found the answer)
 template <typename Acc>
 __global__ __launch_bounds__(kBlock) void k_class_verify(Acc acc, int64_t n,
                                                          const uint32_t* perm,
@@ -747,6 +747,100 @@ int class_sort2(const AccA& a, const AccB& b, const ClassSortLayout& L,
   return CHOPPER_OK;
 }
 
+template <typename AccA, typename AccB>
+__global__ __launch_bounds__(kBlock) void k_class_verify2(
+    AccA a, AccB b, int64_t n, const uint32_t* pa, const uint32_t* pb,
+    uint32_t* unsorted) {
+  // (stops reading once some wave has found the answer)
+  if (__builtin_amdgcn_readfirstlane((int)flag_read(unsorted)) != 0) return;
+  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  bool bad = false;
+  if (p + 1 < n) {
+    const uint32_t x = pa[p], y = pa[p + 1], u = pb[p], v = pb[p + 1];
+    bad = (a.cls(x) == a.cls(y) && a.time(y) < a.time(x)) ||
+          (b.cls(u) == b.cls(v) && b.time(v) < b.time(u));
+  }
+  wave_flag_or(unsorted, bad, 1u);
+}
+
+template <typename AccA, typename AccB>
+int class_verify2(const AccA& a, const AccB& b, const ClassSortLayout& L,
+                  const uint32_t* outA, const uint32_t* outB, bool* sorted,
+                  hipStream_t s) {
+  CHOPPER_HIP(launch("sort_fill", k_fill_u32, dim3(1), dim3(kBlock), s, L.flag,
+                     (int64_t)1, 0u));
+  CHOPPER_HIP(launch("sort_class_verify", k_class_verify2<AccA, AccB>,
+                     grid_for(L.n, kBlock), dim3(kBlock), s, a, b, L.n, outA,
+                     outB, L.flag));
+  uint32_t unsorted = 1;
+  CHOPPER_HIP(read_back(L.flag, &unsorted, sizeof(uint32_t), s));
+  *sorted = unsorted == 0;
+  return CHOPPER_OK;
+}
+
+// time - tmin in the low bits, A's class at bit `tbits`, B's above it
+template <typename AccA, typename AccB>
+__global__ __launch_bounds__(kBlock) void k_make_keys2(
+    AccA a, AccB b, int64_t n, const int64_t* mm, int tbits, uint64_t* key,
+    uint32_t* val) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  key[i] = (uint64_t)(a.time(i) - mm[0]) | (uint64_t)a.cls(i) << tbits |
+           (uint64_t)b.cls(i) << (tbits + 8);
+  val[i] = (uint32_t)i;
+}
+
+template <typename AccA, typename AccB>
+int time_sort2(const AccA& a, const AccB& b, const ClassSortLayout& L,
+               uint32_t* outA, uint32_t* outB, bool* fits, hipStream_t s) {
+  const int64_t n = L.n, T = L.ntiles;
+  *fits = false;
+  if (n == 0 || a.nclass() > 256 || b.nclass() > 256) return CHOPPER_OK;
+  CHOPPER_HIP(launch("sort_init_minmax", k_init_minmax, dim3(1), dim3(1), s,
+                     L.mm));
+  CHOPPER_HIP(launch("sort_time_minmax", k_time_minmax<AccA>,
+                     dim3((unsigned)(T < 1024 ? T : 1024)), dim3(kBlock), s,
+                     a, n, L.mm));
+  int64_t mm[2];
+  CHOPPER_HIP(read_back(L.mm, mm, sizeof(mm), s));
+  const int passes = (bitlen_u64((uint64_t)mm[1] - (uint64_t)mm[0]) + 7) / 8;
+  if (passes > 6) return CHOPPER_OK;
+  *fits = true;
+  const int tbits = 8 * passes;
+  CHOPPER_HIP(launch("sort_make_keys", k_make_keys2<AccA, AccB>,
+                     grid_for(n, kBlock), dim3(kBlock), s, a, b, n,
+                     (const int64_t*)L.mm, tbits, L.key0, L.val0));
+  uint64_t *kin = L.key0, *kout = L.key1;
+  uint32_t *vin = L.val0, *vout = L.val1;
+  auto pass = [&](int shift, uint64_t* ko, uint32_t* vo) -> int {
+    CHOPPER_HIP(launch("sort_digit_hist", k_digit_hist, dim3((unsigned)T),
+                       dim3(kBlock), s, (const uint64_t*)kin, n, shift, T,
+                       L.tilehist));
+    CHOPPER_HIP(exclusive_scan<uint32_t>(L.tilehist, L.tileoff, 256 * T,
+                                         L.scantmp, L.total, s));
+    CHOPPER_HIP(launch("sort_digit_scatter", k_digit_scatter,
+                       dim3((unsigned)T), dim3(kBlock), s,
+                       (const uint64_t*)kin, (const uint32_t*)vin, n, shift, T,
+                       (const uint32_t*)L.tileoff, ko, vo));
+    return CHOPPER_OK;
+  };
+  for (int p = 0; p < passes; ++p) {
+    const int rc = pass(8 * p, kout, vout);
+    if (rc != CHOPPER_OK) return rc;
+    uint64_t* tk = kin; kin = kout; kout = tk;
+    uint32_t* tv = vin; vin = vout; vout = tv;
+  }
+  int rc = pass(tbits, nullptr, outA);
+  if (rc == CHOPPER_OK) rc = pass(tbits + 8, nullptr, outB);
+  return rc;
+}
+
+template int class_verify2<KeyRecStream, KeyRecKind>(
+    const KeyRecStream&, const KeyRecKind&, const ClassSortLayout&,
+    const uint32_t*, const uint32_t*, bool*, hipStream_t);
+template int time_sort2<KeyRecStream, KeyRecKind>(
+    const KeyRecStream&, const KeyRecKind&, const ClassSortLayout&, uint32_t*,
+    uint32_t*, bool*, hipStream_t);
 template int class_sort2<KeyRecStream, KeyRecKind>(
     const KeyRecStream&, const KeyRecKind&, const ClassSortLayout&, uint32_t*,
     uint32_t*, uint32_t*, uint32_t*, hipStream_t, const WaveClasses*);
