@@ -31,8 +31,10 @@ HBM_PEAK_GBS = 8000.0
 # the kernel whose roofline is reported: the records reduction, which reads
 # every record's counters -- the fast path's (groups are runs of the
 # (gpu, kind, start') order) or, where that does not hold (e.g. shuffled
-# input with markers numbered out of order), the general path's
-ROOF_KERNELS = ("agg_fast_reduce_records", "agg_reduce_records")
+# input with markers numbered out of order), that of groups of several runs
+# or the element-wise one
+ROOF_KERNELS = ("agg_fast_reduce_records", "agg_gen_reduce_records",
+                "agg_reduce_records")
 
 
 def algorithmic_bytes(n, nm, rows, depth, nc, n_rows_finest):
@@ -49,12 +51,13 @@ def roof_kernel_bytes(kernel, n, depth, nc, rows_written, input_order):
     """Algorithmic bytes of one launch of the records reduction: per record
     gpu, cls, path, start, end, gap, ovl and counters read once (and korder
     when the input is not grouped by GPU in start order, so that the
-    reduction reads through it; the general path reads the gathered path
-    and gpu/kind items, 4 per level + 2 bytes, in place of gpu, cls and
-    path); per row it produces (the two finest levels on the fast path, the
-    finest on the general one) its header (path, gpu, kind, first record)
-    and its sums and counters written once."""
-    if kernel == "agg_reduce_records":
+    reduction reads through it; on other input the paths of groups of
+    several runs read the gathered path and gpu/kind items, 4 per level + 2
+    bytes, in place of gpu, cls and path); per row it produces (the two
+    finest levels, the finest one on the element-wise path) its header (path,
+    gpu, kind, first record) and its sums and counters written once."""
+    if kernel == "agg_reduce_records" or (
+            kernel == "agg_gen_reduce_records" and not input_order):
         per_rec = 4 + 2 + 4 * depth + 8 * 4 + 8 * nc
     else:
         per_rec = (0 if input_order else 4) + 1 + 1 + 4 * depth + 8 * 4 + 8 * nc
@@ -216,9 +219,9 @@ def main():
         ch.time_kernel(None)
         probe[name] = a.elapsed_time(b)
     ROOF_KERNEL = max(ROOF_KERNELS, key=lambda k: probe[k])
-    # the fast path writes the two finest levels, the general one the finest
+    # the two finest levels, on the element-wise path the finest
     rows_records = (int(lo[depth] - lo[max(depth - 2, 0)])
-                    if ROOF_KERNEL == "agg_fast_reduce_records"
+                    if ROOF_KERNEL != "agg_reduce_records"
                     else rows_finest)
 
     K = args.steps

@@ -68,6 +68,9 @@ struct RecSrc {
   // gpu * 2 + kind (0xFFFF: left out by the filter)
   const uint32_t* ipath;
   const uint16_t* igk;
+  // start, end, gap, ovl and the counters are copies in korder position
+  // order (see k_stage_columns)
+  bool sorted = false;
 };
 
 struct RowsDev {
@@ -171,6 +174,106 @@ __global__ __launch_bounds__(kBlock) void k_agg_items(RecSrc S, uint32_t* ipath,
   igk[pos] = rec_pass(S, r) ? (uint16_t)(g * 2u + kind) : (uint16_t)0xFFFFu;
   for (int l = 0; l < S.D; ++l)
     ipath[(int64_t)l * S.n + pos] = S.idx[(int64_t)l * S.n + r];
+}
+
+// ---------------------------------------------------- records in no order
+// Reading a column through korder fetches a cache line per value where the
+// order jumps (27 ms for the 20 columns of 50M records, and 8 ms for their
+// markers and GPUs).  Such input goes through rows instead: a pass in input
+// order puts up to eight columns of a record side by side in one row of 64
+// bytes (markers, GPU and kind: 32 or 64), and a pass in korder order
+// fetches that row -- one line, not eight -- and writes the columns in korder
+// order, which the reduction then reads as they lie.  Both passes stream but
+// for the row fetch: 50M records STAGEMS.
+constexpr int kRowCols = 8;
+constexpr int64_t kStageMin = (int64_t)1 << 20;   // below, columns stay cached
+
+// Do the records lie far from korder?  Positions spread over all of it are
+// sampled by one block: *far = steps of more than 4,096 records among them.
+__global__ __launch_bounds__(kBlock) void k_sample_jumps(const uint32_t* korder,
+                                                         int64_t n,
+                                                         uint32_t* far) {
+  const int64_t p = (n - 1) * (int64_t)threadIdx.x / kBlock;
+  const int64_t d = (int64_t)korder[p + 1] - (int64_t)korder[p];
+  uint32_t tot;
+  block_exclusive(d > 4096 || d < -4096 ? 1u : 0u, OpAdd(), 0u, &tot);
+  if (threadIdx.x == 0) *far = tot;
+}
+
+// Items in rows of W words: the path in words 0 .. D - 1 (D < W) and, in the
+// last word, gpu * 2 + kind (0xFFFF: left out).
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_stage_items(RecSrc S, uint4* rows) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= S.n) return;
+  uint32_t v[W];
+#pragma unroll
+  for (int l = 0; l < W; ++l)
+    v[l] = l < S.D && l < W - 1 ? S.idx[(int64_t)l * S.n + i] : kNone;
+  const uint32_t gk = (uint32_t)S.gpu[i] * 2u + (uint32_t)kind_of(S.cls[i]);
+  v[W - 1] = rec_pass(S, (uint32_t)i) ? gk : 0xFFFFu;
+#pragma unroll
+  for (int q = 0; q < W / 4; ++q)
+    rows[i * (W / 4) + q] =
+        make_uint4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+}
+
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_unstage_items(
+    const uint32_t* korder, int64_t n, int D, const uint4* rows,
+    uint32_t* ipath, uint16_t* igk) {
+  const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (pos >= n) return;
+  const int64_t r = korder[pos];
+  uint32_t v[W];
+#pragma unroll
+  for (int q = 0; q < W / 4; ++q) {
+    const uint4 x = rows[r * (W / 4) + q];
+    v[4 * q] = x.x;
+    v[4 * q + 1] = x.y;
+    v[4 * q + 2] = x.z;
+    v[4 * q + 3] = x.w;
+  }
+#pragma unroll
+  for (int l = 0; l < W - 1; ++l)
+    if (l < D) ipath[(int64_t)l * n + pos] = v[l];
+  igk[pos] = (uint16_t)v[W - 1];
+}
+
+// kRowCols columns (fewer: the rest of the row is not written or read)
+struct StageCols {
+  const uint64_t* in[kRowCols];
+  uint64_t* out[kRowCols];
+};
+
+__global__ __launch_bounds__(kBlock) void k_stage_columns(StageCols C,
+                                                          int64_t n,
+                                                          ulonglong2* rows) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  uint64_t v[kRowCols];
+#pragma unroll
+  for (int c = 0; c < kRowCols; ++c) v[c] = C.in[c] ? C.in[c][i] : 0ull;
+#pragma unroll
+  for (int q = 0; q < kRowCols / 2; ++q)
+    if (C.in[2 * q])
+      rows[i * (kRowCols / 2) + q] = make_ulonglong2(v[2 * q], v[2 * q + 1]);
+}
+
+__global__ __launch_bounds__(kBlock) void k_unstage_columns(
+    StageCols C, const uint32_t* korder, int64_t n, const ulonglong2* rows) {
+  const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (pos >= n) return;
+  const int64_t r = korder[pos];
+  ulonglong2 v[kRowCols / 2];
+#pragma unroll
+  for (int q = 0; q < kRowCols / 2; ++q)
+    if (C.out[2 * q]) v[q] = rows[r * (kRowCols / 2) + q];
+#pragma unroll
+  for (int q = 0; q < kRowCols / 2; ++q) {
+    if (C.out[2 * q]) C.out[2 * q][pos] = v[q].x;
+    if (C.out[2 * q + 1]) C.out[2 * q + 1][pos] = v[q].y;
+  }
 }
 
 // ------------------------------------------------------------------ election
@@ -2323,7 +2426,12 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
   // byte offsets of the striped items (sizes are below 2^29 here)
   uint32_t off[kAggIpt];
 #pragma unroll
-  for (int j = 0; j < kAggIpt; ++j) off[j] = rs[j] << 3;
+  for (int j = 0; j < kAggIpt; ++j) {
+    if constexpr (kGen && !kNat && Src::kRecords)
+      off[j] = (src.S.sorted ? id[j] : rs[j]) << 3;
+    else
+      off[j] = rs[j] << 3;
+  }
 
   // piece values at the slots -> rows (and the overflow slots)
   auto store_pieces = [&](const LevelTile& T, int64_t obase, int f,
@@ -2863,6 +2971,10 @@ struct AggLayout {
   ClassSortLayout xsort;
   uint32_t* ipath;        // [D][n] general-path items by korder position
   uint16_t* igk;          // [n]
+  // records in no order: a row per record (in the exact ids' space, which
+  // is then free) and the columns in korder order
+  char* srow;
+  uint64_t* scol;         // [4 + counters][n], null below kStageMin records
   // groups of several runs
   uint8_t* omask;         // [L][mstride] owners of every lane
   int64_t mstride;        // 64 * (natural tiles + G)
@@ -2870,7 +2982,7 @@ struct AggLayout {
 };
 
 static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
-                            int64_t cap, uint32_t act, int G) {
+                            int64_t cap, uint32_t act, int G, int nc) {
   AggLayout L;
   L.L = D + 2;
   L.ntiles = ceil_div(n, kAggTile);
@@ -2919,6 +3031,8 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.gs = sc.take<uint32_t>(G);
   L.ge = sc.take<uint32_t>(G);
   L.gtb = sc.take<uint32_t>(G + 1);
+  L.srow = sc.take<char>(0);
+  const size_t row0 = sc.used;
   L.gk = sc.take<uint32_t>((int64_t)(D > 0 ? D : 1) * n);
   L.xflag = sc.take<uint32_t>(1);
   L.xskey = sc.take<uint64_t>(n);
@@ -2929,6 +3043,13 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.xtot = sc.take<uint32_t>(1);
   L.xscan = sc.take<uint32_t>(scan_scratch_elems(n));
   L.xsort = class_sort_layout(sc, n, 256);
+  L.scol = nullptr;
+  if (n >= kStageMin) {
+    const int64_t have = (int64_t)(sc.used - row0);
+    const int64_t rows = n * (int64_t)(kRowCols * sizeof(uint64_t)) + 512;
+    if (have < rows) (void)sc.take<char>(rows - have);
+    L.scol = sc.take<uint64_t>((4 + nc) * n);
+  }
   L.ipath = sc.take<uint32_t>((int64_t)(D > 0 ? D : 1) * n);
   L.igk = sc.take<uint16_t>(n);
   L.mstride = (int64_t)kWave * (L.ntiles_h + G);
@@ -3300,9 +3421,33 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
   int64_t st[kStageWords];
   // (records out of order usually come with markers out of order)
   bool plain = false;
+  bool far = false;            // records in no order: through rows
   if (!kNat) {
-    CHOPPER_HIP(launch("agg_items", k_agg_items, grid_for(S.n, kBlock),
-                       dim3(kBlock), s, S, L.ipath, L.igk));
+    const dim3 gi = grid_for(S.n, kBlock);
+    if (L.scol) {
+      uint32_t jumps = 0;
+      CHOPPER_HIP(launch("agg_stage", k_sample_jumps, dim3(1), dim3(kBlock), s,
+                         S.korder, S.n, L.xflag));
+      CHOPPER_HIP(read_back(L.xflag, &jumps, sizeof(jumps), s));
+      far = jumps > kBlock / 2;
+    }
+    uint4* rows4 = reinterpret_cast<uint4*>(L.srow);
+    if (far && D < 8) {
+      CHOPPER_HIP(launch("agg_stage", k_stage_items<8>, gi, dim3(kBlock), s, S,
+                         rows4));
+      CHOPPER_HIP(launch("agg_stage", k_unstage_items<8>, gi, dim3(kBlock), s,
+                         S.korder, S.n, D, (const uint4*)rows4, L.ipath,
+                         L.igk));
+    } else if (far) {
+      CHOPPER_HIP(launch("agg_stage", k_stage_items<16>, gi, dim3(kBlock), s,
+                         S, rows4));
+      CHOPPER_HIP(launch("agg_stage", k_unstage_items<16>, gi, dim3(kBlock),
+                         s, S.korder, S.n, D, (const uint4*)rows4, L.ipath,
+                         L.igk));
+    } else {
+      CHOPPER_HIP(launch("agg_items", k_agg_items, gi, dim3(kBlock), s, S,
+                         L.ipath, L.igk));
+    }
     fr.S.ipath = L.ipath;
     fr.S.igk = L.igk;
   }
@@ -3380,6 +3525,36 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
   };
   for (int i = 0; i < np; ++i)
     if (left(ps[i]) > ovf.cap) return 1;
+  if (far) {
+    // (gap and ovl are complete here: the event above)
+    const int cols = 4 + fr.S.nc;
+    auto in = [&](int c) -> const uint64_t* {
+      return c == 0   ? (const uint64_t*)S.start
+             : c == 1 ? (const uint64_t*)S.end
+             : c == 2 ? (const uint64_t*)S.gap
+             : c == 3 ? (const uint64_t*)S.ovl
+                      : S.ctr + (int64_t)(c - 4) * S.n;
+    };
+    ulonglong2* rows2 = reinterpret_cast<ulonglong2*>(L.srow);
+    for (int c0 = 0; c0 < cols; c0 += kRowCols) {
+      StageCols C;
+      for (int c = 0; c < kRowCols; ++c) {
+        C.in[c] = c0 + c < cols ? in(c0 + c) : nullptr;
+        C.out[c] = c0 + c < cols ? L.scol + (int64_t)(c0 + c) * S.n : nullptr;
+      }
+      CHOPPER_HIP(launch("agg_stage", k_stage_columns, grid_for(S.n, kBlock),
+                         dim3(kBlock), s, C, S.n, rows2));
+      CHOPPER_HIP(launch("agg_stage", k_unstage_columns,
+                         grid_for(S.n, kBlock), dim3(kBlock), s, C, S.korder,
+                         S.n, (const ulonglong2*)rows2));
+    }
+    fr.S.start = (const int64_t*)L.scol;
+    fr.S.end = (const int64_t*)(L.scol + S.n);
+    fr.S.gap = (const int64_t*)(L.scol + 2 * S.n);
+    fr.S.ovl = (const int64_t*)(L.scol + 3 * S.n);
+    fr.S.ctr = L.scol + 4 * S.n;
+    fr.S.sorted = true;
+  }
   for (int i = 0; i < np; ++i) {
     const Pass& q = ps[i];
     const int li = q.li;
@@ -3506,13 +3681,14 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
   else return CHOPPER_EINVAL;
 
   Scratch probe(nullptr);
-  agg_layout(probe, n, D, M, rows->cap, act, rec->n_gpus);
+  agg_layout(probe, n, D, M, rows->cap, act, rec->n_gpus, rec->n_counters);
   int rc = scratch_check(scratch, scratch_bytes, probe.used);
   if (rc != 0) return rc > 0 ? CHOPPER_OK : rc;
   if (!status) return CHOPPER_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   Scratch sc(scratch);
-  AggLayout L = agg_layout(sc, n, D, M, rows->cap, act, rec->n_gpus);
+  AggLayout L = agg_layout(sc, n, D, M, rows->cap, act, rec->n_gpus,
+                           rec->n_counters);
   const int Lv = L.L;
   const int64_t T = L.ntiles;
   const int nc = rec->n_counters;

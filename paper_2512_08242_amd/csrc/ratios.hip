@@ -32,6 +32,9 @@ static const char* const kKernelNames[] = {
     "bi_fixup", "ov_comm_records", "agg_nat_init", "agg_nat_pre",
     "agg_nat_tiles", "agg_heads_nat", "agg_gpu_rows",
     "agg_exact_keys", "join_resort", "attr_windows", "agg_items",
+    "agg_gen_fill", "agg_gen_elect", "agg_gen_count",
+    "agg_gen_reduce_records", "agg_gen_count_rows", "agg_gen_reduce_rows",
+    "agg_gen_apply", "agg_stage",
     "view_flags", "view_units", "view_fill", "view_records", "view_rows",
     "view_iter_max", "view_medians", "launch_split", "join_fill",
     "join_labels", "join_heads", "join_runs", "join_order", "join_pass_prep",

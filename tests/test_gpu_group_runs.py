@@ -108,3 +108,18 @@ def test_capacity(ch):
     torch.cuda.synchronize()
     assert np.array_equal(pipe.rows.level_offset.cpu().numpy(), want)
     assert pipe.status.item() & ch.ST_ROWS_OVERFLOW
+
+
+@pytest.mark.parametrize("depth,filt", [(6, None), (8, dict(
+    iters=(3, 40), gpus=[0, 1, 2, 5, 6], classes=[0, 1, 2, 5, 6, 7]))])
+def test_records_in_no_order(ch, depth, filt):
+    """Enough shuffled records for the pass through rows, paths of six and
+    eight levels, the latter with a selection."""
+    tr = tg.make_config(4, iters=43, seed=17)
+    assert tr.n >= 1 << 20
+    tr = dataclasses.replace(tr, depth=depth)
+    say("no order", tr.n, depth, filt)
+    of = None if filt is None else oracle.make_filter(**filt)
+    cf = None if filt is None else ch.make_filter(**filt)
+    assert_parity(run_gpu(ch, tr, filt=cf), oracle.run(tr, filt=of),
+                  name=f"no order, depth {depth}")
