@@ -720,20 +720,20 @@ __global__ __launch_bounds__(kBlock) void k_runs_write(
 // window searches of compute records with these wide ones.
 __device__ inline void overlap_gpu(int g, const Runs& R, int64_t* gwin);
 
-// Block 0 also writes the GPU windows.
-__global__ __launch_bounds__(kBlock) void k_comm_records(
-    int G, const uint32_t* korder, const uint32_t* kbeg, const uint32_t* roff,
-    const uint8_t* cdone, const int64_t* start, const int64_t* end, Runs R,
-    int64_t* ovl, int64_t* gwin) {
-  extern __shared__ BSeg s_seg[];   // 2G entries (dynamic LDS)
+// Block 0 (of `blocks`) also writes the GPU windows.
+__device__ inline void comm_records(
+    uint32_t block, uint32_t blocks, BSeg* s_seg, int G,
+    const uint32_t* korder, const uint32_t* kbeg, const uint32_t* roff,
+    const uint8_t* cdone, const int64_t* start, const int64_t* end,
+    const Runs& R, int64_t* ovl, int64_t* gwin) {
   __shared__ uint32_t s_roff[kSegs / 2 + 1];
   for (int i = threadIdx.x; i <= G; i += kBlock) s_roff[i] = roff[i];
   segs_to_lds(s_seg, R.X.seg, 2 * G);
-  if (blockIdx.x == 0)
+  if (block == 0)
     for (int g = threadIdx.x; g < G; g += kBlock) overlap_gpu(g, R, gwin);
   const int64_t total = s_roff[G];
-  for (int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x; v < total;
-       v += (int64_t)gridDim.x * kBlock) {
+  for (int64_t v = (int64_t)block * kBlock + threadIdx.x; v < total;
+       v += (int64_t)blocks * kBlock) {
     if (cdone[v]) continue;        // alone in its run: written with the run
     int lo = 0, hi = G;            // the last g with roff[g] <= v
     while (hi - lo > 1) {
@@ -755,6 +755,15 @@ __global__ __launch_bounds__(kBlock) void k_comm_records(
     }
     ovl[r] = o;
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_comm_records(
+    int G, const uint32_t* korder, const uint32_t* kbeg, const uint32_t* roff,
+    const uint8_t* cdone, const int64_t* start, const int64_t* end, Runs R,
+    int64_t* ovl, int64_t* gwin) {
+  extern __shared__ BSeg s_seg[];   // 2G entries (dynamic LDS)
+  comm_records(blockIdx.x, gridDim.x, s_seg, G, korder, kbeg, roff, cdone,
+               start, end, R, ovl, gwin);
 }
 
 // overlapped time inside each comm run (compute-active time within it) and
@@ -857,18 +866,18 @@ __global__ __launch_bounds__(kBlock) void k_runs_comm_overlap(
 // segment than the tile's first one, or tiles whose window is wider than
 // kRunWin runs, search the bucket index directly.
 constexpr int kRunWin = 256;
+constexpr int64_t kTogether = (int64_t)1 << 20;
 
-__global__ __launch_bounds__(kBlock) void k_overlap_records(
-    int64_t n, int G, const uint32_t* korder, const uint8_t* gpu,
-    const uint8_t* stream, const uint8_t* cls, const int64_t* start,
-    const int64_t* end, Runs R, int64_t* ovl, int64_t* gap,
-    uint32_t* mixed) {
-  extern __shared__ BSeg s_seg[];   // 2G entries (dynamic LDS)
+__device__ inline void overlap_records(
+    uint32_t block, BSeg* s_seg, int64_t n, int G, const uint32_t* korder,
+    const uint8_t* gpu, const uint8_t* stream, const uint8_t* cls,
+    const int64_t* start, const int64_t* end, const Runs& R, int64_t* ovl,
+    int64_t* gap, uint32_t* mixed) {
   __shared__ int64_t s_win[kWavesPerBlock][3][kRunWin];
   segs_to_lds(s_seg, R.X.seg, 2 * G);
   const int lane = lane_id(), wv = (int)(threadIdx.x / kWave);
   const int64_t base =
-      ((int64_t)blockIdx.x * kWavesPerBlock + wv) * (int64_t)kWaveTile;
+      ((int64_t)block * kWavesPerBlock + wv) * (int64_t)kWaveTile;
   if (base >= n) return;
   uint32_t r[kTileIpt], seg[kTileIpt], st[kTileIpt];
   int64_t s[kTileIpt], e[kTileIpt];
@@ -1043,17 +1052,27 @@ __global__ __launch_bounds__(kBlock) void k_overlap_records(
   }
 }
 
+__global__ __launch_bounds__(kBlock) void k_overlap_records(
+    int64_t n, int G, const uint32_t* korder, const uint8_t* gpu,
+    const uint8_t* stream, const uint8_t* cls, const int64_t* start,
+    const int64_t* end, Runs R, int64_t* ovl, int64_t* gap,
+    uint32_t* mixed) {
+  extern __shared__ BSeg s_seg[];   // 2G entries (dynamic LDS)
+  overlap_records(blockIdx.x, s_seg, n, G, korder, gpu, stream, cls, start,
+                  end, R, ovl, gap, mixed);
+}
+
 // Window values of every marker, one per thread (more markers per thread
 // in lockstep measured slower).
 constexpr int kMarkPerThread = 1;
 
-__global__ __launch_bounds__(kBlock) void k_overlap_markers(
+__device__ inline void overlap_markers(
+    uint32_t block, BSeg* s_seg,
     int64_t nm, int G, const uint8_t* mgpu, const int64_t* ms,
-    const int64_t* me, Runs R, int64_t* mwin) {
-  extern __shared__ BSeg s_seg[];   // 2G entries (dynamic LDS)
+    const int64_t* me, const Runs& R, int64_t* mwin) {
   segs_to_lds(s_seg, R.X.seg, 2 * G);
   const int64_t j0 =
-      (int64_t)blockIdx.x * kBlock * kMarkPerThread + threadIdx.x;
+      (int64_t)block * kBlock * kMarkPerThread + threadIdx.x;
   BSeg Pc[kMarkPerThread], Pm[kMarkPerThread];
   uint32_t vg[kMarkPerThread];
   int64_t a[kMarkPerThread], b[kMarkPerThread];
@@ -1078,6 +1097,36 @@ __global__ __launch_bounds__(kBlock) void k_overlap_markers(
     if (j >= nm) continue;
     for (int z = 0; z < 4; ++z) mwin[4 * j + z] = use[q] ? w[q][z] : 0;
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_overlap_markers(
+    int64_t nm, int G, const uint8_t* mgpu, const int64_t* ms,
+    const int64_t* me, Runs R, int64_t* mwin) {
+  extern __shared__ BSeg s_seg[];   // 2G entries (dynamic LDS)
+  overlap_markers(blockIdx.x, s_seg, nm, G, mgpu, ms, me, R, mwin);
+}
+
+// The three query passes in one launch, for traces whose passes each leave
+// most of the chip idle: markers, then communication records, then compute
+// records (nothing passes between them).
+__global__ __launch_bounds__(kBlock) void k_overlap_queries(
+    uint32_t mblocks, uint32_t cblocks, int64_t n, int G,
+    const uint32_t* korder, const uint8_t* gpu, const uint8_t* stream,
+    const uint8_t* cls, const int64_t* start, const int64_t* end, Runs R,
+    int64_t* ovl, int64_t* gap, uint32_t* mixed, const uint32_t* kbeg,
+    const uint32_t* roff, const uint8_t* cdone, int64_t* gwin, int64_t nm,
+    const uint8_t* mgpu, const int64_t* ms, const int64_t* me,
+    int64_t* mwin) {
+  extern __shared__ BSeg s_seg[];   // 2G entries (dynamic LDS)
+  const uint32_t b = blockIdx.x;
+  if (b < mblocks)
+    overlap_markers(b, s_seg, nm, G, mgpu, ms, me, R, mwin);
+  else if (b < mblocks + cblocks)
+    comm_records(b - mblocks, cblocks, s_seg, G, korder, kbeg, roff, cdone,
+                 start, end, R, ovl, gwin);
+  else
+    overlap_records(b - mblocks - cblocks, s_seg, n, G, korder, gpu, stream,
+                    cls, start, end, R, ovl, gap, mixed);
 }
 
 // GPU window: the first run of a (gpu, kind) segment starts at its smallest
@@ -1415,6 +1464,24 @@ extern "C" int chopper_overlap(const chopper_records* rec,
     CHOPPER_HIP(exclusive_scan<int64_t>(L.ovc, L.pov, n,
                                         (const uint32_t*)(L.voff + G),
                                         L.scan_i64, L.tot_i64 + 1, s));
+  }
+  const unsigned mb = nm > 0 ? grid_for(nm, kBlock * kMarkPerThread).x : 0u;
+  const unsigned rb = (unsigned)ceil_div(n, (int64_t)kOvTile);
+  // (2,000 records 23 to 13 us for the three, 245,760 37 to 17; from 2^20
+  // records one launch gains nothing, and at 20M the markers, held to the
+  // records' registers, take 0.09 ms more)
+  const bool together = n > 0 && n < kTogether;
+  if (together)
+    CHOPPER_HIP(launch_shm("ov_queries", k_overlap_queries,
+                           dim3(mb + (unsigned)cg + rb), dim3(kBlock),
+                           segs_bytes, s, (uint32_t)mb, (uint32_t)cg, n, G,
+                           korder, rec->gpu, rec->stream, rec->cls, start_al,
+                           end_al, R, ovl_out, gap_out, L.mixed,
+                           (const uint32_t*)(L.rbeg + 2 * kSegs),
+                           (const uint32_t*)L.roff, (const uint8_t*)L.cdone,
+                           gwin_out, nm, mk ? mk->gpu : nullptr, mstart_al,
+                           mend_al, mwin_out));
+  if (n > 0 && !together) {
     CHOPPER_HIP(launch_shm("ov_records", k_overlap_records,
                        dim3((unsigned)ceil_div(n, (int64_t)kOvTile)),
                        dim3(kBlock), segs_bytes, s, n, G, korder, rec->gpu,
@@ -1427,7 +1494,7 @@ extern "C" int chopper_overlap(const chopper_records* rec,
                            (const uint32_t*)L.roff, (const uint8_t*)L.cdone,
                            start_al, end_al, R, ovl_out, gwin_out));
   }
-  if (nm > 0)
+  if (nm > 0 && !together)
     CHOPPER_HIP(launch_shm("ov_markers", k_overlap_markers,
                            grid_for(nm, kBlock * kMarkPerThread),
                            dim3(kBlock), segs_bytes, s, nm, G, mk->gpu,

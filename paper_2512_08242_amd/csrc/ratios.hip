@@ -34,7 +34,7 @@ static const char* const kKernelNames[] = {
     "agg_exact_keys", "join_resort", "attr_windows", "agg_items",
     "agg_gen_fill", "agg_gen_elect", "agg_gen_count",
     "agg_gen_reduce_records", "agg_gen_count_rows", "agg_gen_reduce_rows",
-    "agg_gen_apply", "agg_stage",
+    "agg_gen_apply", "agg_stage", "ov_queries",
     "view_flags", "view_units", "view_fill", "view_records", "view_rows",
     "view_iter_max", "view_medians", "launch_split", "join_fill",
     "join_labels", "join_heads", "join_runs", "join_order", "join_pass_prep",
