@@ -234,15 +234,15 @@ __global__ __launch_bounds__(kBlock) void k_join_heads(Seq S,
 // consecutive positions, four per lane (more gathers in flight per wave),
 // and writes the head count of its 256 positions (tcnt is per kBlock
 // positions, as k_join_runs reads it).
-__global__ __launch_bounds__(kBlock) void k_join_heads_pass(
-    int64_t m, const uint32_t* qorder, const uint32_t* label,
+__device__ inline void join_heads_pass(
+    uint32_t block, int64_t m, const uint32_t* qorder, const uint32_t* label,
     const uint8_t* kcls, const uint32_t* coff, int C, uint32_t* head,
     uint64_t* key, uint32_t* tcnt) {
   __shared__ uint32_t s_off[256 + 1];
   for (int c = threadIdx.x; c <= C; c += kBlock) s_off[c] = coff[c];
   __syncthreads();
   const int lane = lane_id();
-  const int64_t W = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
+  const int64_t W = (int64_t)block * kWavesPerBlock + threadIdx.x / kWave;
   const int64_t base = W * (kWave * kHeadsIpt);
   if (base >= m) return;                                   // whole wave
   // class of position q: the last c < C with s_off[c] <= q
@@ -317,17 +317,25 @@ __global__ __launch_bounds__(kBlock) void k_join_heads_pass(
   if (lane == 0) tcnt[W] = cnt;
 }
 
+__global__ __launch_bounds__(kBlock) void k_join_heads_pass(
+    int64_t m, const uint32_t* qorder, const uint32_t* label,
+    const uint8_t* kcls, const uint32_t* coff, int C, uint32_t* head,
+    uint64_t* key, uint32_t* tcnt) {
+  join_heads_pass(blockIdx.x, m, qorder, label, kcls, coff, C, head, key,
+                  tcnt);
+}
+
 // run table: start position, (gpu, stream) and label of every run, the run
 // number of a head being the heads before it (prefix tpre of its 256
 // positions + the heads before it among them); excl (optional) gets that
 // count at every position.  Each wave takes 256 consecutive positions, four
 // per lane, as the heads passes do.
-__global__ __launch_bounds__(kBlock) void k_join_runs(
-    int64_t n, const uint32_t* head, const uint32_t* tpre,
-    const uint64_t* key, uint32_t* rstart, uint32_t* rcls, uint32_t* rlab,
-    uint32_t* excl) {
+__device__ inline void join_runs(
+    uint32_t block, int64_t n, const uint32_t* head, const uint32_t* tpre,
+    uint32_t sub, const uint64_t* key, uint32_t* rstart, uint32_t* rcls,
+    uint32_t* rlab, uint32_t* excl) {
   const int lane = lane_id();
-  const int64_t W = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
+  const int64_t W = (int64_t)block * kWavesPerBlock + threadIdx.x / kWave;
   const int64_t base = W * (kWave * kHeadsIpt);
   if (base >= n) return;                                   // whole wave
   const int64_t p0 = base + (int64_t)lane * kHeadsIpt;
@@ -341,7 +349,7 @@ __global__ __launch_bounds__(kBlock) void k_join_runs(
     for (int j = 0; j < kHeadsIpt; ++j) h[j] = p0 + j < n ? head[p0 + j] : 0u;
   }
   const uint32_t c = h[0] + h[1] + h[2] + h[3];
-  uint32_t r = tpre[W] + wave_incl(c, OpAdd(), 0u) - c;
+  uint32_t r = tpre[W] - sub + wave_incl(c, OpAdd(), 0u) - c;
   uint32_t ex[kHeadsIpt];
 #pragma unroll
   for (int j = 0; j < kHeadsIpt; ++j) {
@@ -363,6 +371,13 @@ __global__ __launch_bounds__(kBlock) void k_join_runs(
     for (int j = 0; j < kHeadsIpt; ++j)
       if (p0 + j < n) excl[p0 + j] = ex[j];
   }
+}
+
+__global__ __launch_bounds__(kBlock) void k_join_runs(
+    int64_t n, const uint32_t* head, const uint32_t* tpre,
+    const uint64_t* key, uint32_t* rstart, uint32_t* rcls, uint32_t* rlab,
+    uint32_t* excl) {
+  join_runs(blockIdx.x, n, head, tpre, 0u, key, rstart, rcls, rlab, excl);
 }
 
 // run and ordinal of every record, stored at the record (NONE: no
@@ -390,9 +405,9 @@ __global__ void k_join_rec_pos(int64_t n, const uint32_t* order,
 // label is below that of the previous run (labels decrease).  Otherwise the
 // table is sorted by (gpu, stream, label) and every label has one run.
 // (run tables are short: a fixed grid strides over them)
-__global__ void k_join_order(const uint32_t* nruns, const uint32_t* rcls,
-                             const uint32_t* rlab, uint32_t* status,
-                             uint32_t* flag, uint32_t bit) {
+__device__ inline void join_order(const uint32_t* nruns, const uint32_t* rcls,
+                                  const uint32_t* rlab, uint32_t* status,
+                                  uint32_t* flag, uint32_t bit) {
   const int64_t nr = (int64_t)*nruns;
   bool split = false, dec = false;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nr;
@@ -408,6 +423,12 @@ __global__ void k_join_order(const uint32_t* nruns, const uint32_t* rcls,
   }
 }
 
+__global__ void k_join_order(const uint32_t* nruns, const uint32_t* rcls,
+                             const uint32_t* rlab, uint32_t* status,
+                             uint32_t* flag, uint32_t bit) {
+  join_order(nruns, rcls, rlab, status, flag, bit);
+}
+
 // out[q] = seq[perm[q]]: a sequence reordered by a permutation of its
 // positions
 __global__ void k_join_compose(int64_t n, const uint32_t* seq,
@@ -419,11 +440,11 @@ __global__ void k_join_compose(int64_t n, const uint32_t* seq,
 // pass run of every record run: binary search by (gpu, stream, label); the
 // record run gets the class-order positions [start, next run's start) of
 // that pass run, or an empty range
-__global__ void k_join_match(const uint32_t* nr, const uint32_t* rcls,
-                             const uint32_t* rlab, const uint32_t* nq,
-                             const uint32_t* qcls, const uint32_t* qlab,
-                             const uint32_t* qstart, int64_t m,
-                             uint2* match) {
+__device__ inline void join_match(const uint32_t* nr, const uint32_t* rcls,
+                                  const uint32_t* rlab, const uint32_t* nq,
+                                  const uint32_t* qcls, const uint32_t* qlab,
+                                  const uint32_t* qstart, int64_t m,
+                                  uint2* match) {
   const int64_t n_r = (int64_t)*nr, n_q = (int64_t)*nq;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n_r;
        r += (int64_t)gridDim.x * blockDim.x) {
@@ -442,6 +463,70 @@ __global__ void k_join_match(const uint32_t* nr, const uint32_t* rcls,
                                                 : (uint32_t)m)
                    : make_uint2(0u, 0u);
   }
+}
+
+__global__ void k_join_match(const uint32_t* nr, const uint32_t* rcls,
+                             const uint32_t* rlab, const uint32_t* nq,
+                             const uint32_t* qcls, const uint32_t* qlab,
+                             const uint32_t* qstart, int64_t m,
+                             uint2* match) {
+  join_match(nr, rcls, rlab, nq, qcls, qlab, qstart, m, match);
+}
+
+// All passes at once, pass p in the blocks of blockIdx.y = p.  The head
+// counts of the passes follow each other in one table (pass p's from entry
+// t0 on, `total` entries and a zero), so one scan serves them all; a pass's
+// counts are the differences to its first entry.
+struct JoinPart {
+  int64_t m;
+  const uint32_t* qorder;
+  const uint32_t* label;
+  const uint8_t* kcls;
+  const uint32_t* coff;
+  uint32_t* head;
+  uint64_t* key;
+  uint32_t *qstart, *qcls, *qlab;
+  uint2* match;
+  int64_t t0, t1;           // its entries of the table
+};
+struct JoinParts {
+  JoinPart p[kMaxPasses];
+};
+
+__global__ __launch_bounds__(kBlock) void k_join_heads_all(JoinParts J, int C,
+                                                           int64_t total,
+                                                           uint32_t* tcnt) {
+  const JoinPart& P = J.p[blockIdx.y];
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tcnt[total] = 0;
+  if ((int64_t)blockIdx.x * kWavesPerBlock >= P.t1 - P.t0) return;
+  join_heads_pass(blockIdx.x, P.m, P.qorder, P.label, P.kcls, P.coff, C,
+                  P.head, P.key, tcnt + P.t0);
+}
+
+// (also the number of runs of every pass)
+__global__ __launch_bounds__(kBlock) void k_join_runs_all(JoinParts J,
+                                                          const uint32_t* tpre,
+                                                          uint32_t* nq) {
+  const JoinPart& P = J.p[blockIdx.y];
+  const uint32_t sub = tpre[P.t0];
+  if (blockIdx.x == 0 && threadIdx.x == 0) nq[blockIdx.y] = tpre[P.t1] - sub;
+  if ((int64_t)blockIdx.x * kWavesPerBlock >= P.t1 - P.t0) return;
+  join_runs(blockIdx.x, P.m, P.head, tpre + P.t0, sub, P.key, P.qstart, P.qcls,
+            P.qlab, nullptr);
+}
+
+__global__ void k_join_order_all(JoinParts J, const uint32_t* nq,
+                                 uint32_t* status, uint32_t* flag) {
+  const JoinPart& P = J.p[blockIdx.y];
+  join_order(nq + blockIdx.y, P.qcls, P.qlab, status, flag, 2u << blockIdx.y);
+}
+
+__global__ void k_join_match_all(JoinParts J, const uint32_t* nr,
+                                 const uint32_t* rcls, const uint32_t* rlab,
+                                 const uint32_t* nq) {
+  const JoinPart& P = J.p[blockIdx.y];
+  join_match(nr, rcls, rlab, nq + blockIdx.y, P.qcls, P.qlab, P.qstart, P.m,
+             P.match);
 }
 
 // one pass as the gather sees it
@@ -676,14 +761,18 @@ extern "C" int chopper_join_counters(
   // scratch: record labels, runs and keys, the class map, per-pass
   // temporaries (reused) and what the gather reads of every pass
   const int64_t nmax = n > mmax ? n : mmax;
+  int64_t tmax = 0;                    // head counts of all passes
+  for (int p = 0; p < n_passes; ++p)
+    tmax += ceil_div(passes[p].n, (int64_t)kBlock);
+  if (ceil_div(n, (int64_t)kBlock) > tmax) tmax = ceil_div(n, (int64_t)kBlock);
   struct PassBuf {
     uint2* match;
-    uint32_t *qstart, *qorder, *qcls, *qlab, *coff;
+    uint32_t *qstart, *qorder, *qcls, *qlab, *coff, *head;
     uint64_t* key;
   };
   struct Bufs {
     uint32_t *rlabv, *head, *excl, *rstart, *rcls, *rlab, *tot, *tmp;
-    uint32_t *qhead, *tcnt, *tpre, *rrun, *rord, *perm, *seq2, *scoff, *flag;
+    uint32_t *tcnt, *tpre, *rrun, *rord, *perm, *seq2, *scoff, *flag;
     uint64_t *rkey, *stage;
     uint8_t *pres, *smatched;
     uint16_t* cmap;
@@ -698,13 +787,13 @@ extern "C" int chopper_join_counters(
     B.rlab = sc.take<uint32_t>(n + 1);
     // runs of the records, class count, runs of every pass
     B.tot = sc.take<uint32_t>(2 + kMaxPasses);
-    B.tmp = sc.take<uint32_t>(scan_scratch_elems(nmax));
+    B.tmp = sc.take<uint32_t>(scan_scratch_elems(tmax + 1));
     B.rkey = sc.take<uint64_t>(n);
     B.pres = sc.take<uint8_t>(65536);
     B.cmap = sc.take<uint16_t>(65536);
-    B.qhead = sc.take<uint32_t>(mmax);
-    B.tcnt = sc.take<uint32_t>(ceil_div(nmax, kBlock) + 1);
-    B.tpre = sc.take<uint32_t>(ceil_div(nmax, kBlock) + 1);
+    // (the records' counts, then those of all passes)
+    B.tcnt = sc.take<uint32_t>(tmax + 1);
+    B.tpre = sc.take<uint32_t>(tmax + 1);
     B.rrun = sc.take<uint32_t>(n);
     B.rord = sc.take<uint32_t>(n);
     // re-sort by label of a side whose labels are not one run each
@@ -724,6 +813,7 @@ extern "C" int chopper_join_counters(
       B.pb[p].qlab = sc.take<uint32_t>(m + 1);
       B.pb[p].coff = sc.take<uint32_t>(256 + 1);
       B.pb[p].key = sc.take<uint64_t>(m);
+      B.pb[p].head = sc.take<uint32_t>(m);
     }
   };
   Scratch probe(nullptr);
@@ -803,12 +893,12 @@ extern "C" int chopper_join_counters(
     const dim3 gmw((unsigned)ceil_div((int64_t)gm.x, (int64_t)kWavesPerBlock));
     CHOPPER_HIP(launch("join_heads", k_join_heads_pass, gmw, dim3(kBlock), s,
                        m, (const uint32_t*)Q_.qorder, P.label, P.cls,
-                       (const uint32_t*)Q_.coff, (int)nclass + 1, B.qhead,
+                       (const uint32_t*)Q_.coff, (int)nclass + 1, Q_.head,
                        Q_.key, B.tcnt));
     CHOPPER_HIP(exclusive_scan<uint32_t>(B.tcnt, B.tpre, (int64_t)gm.x,
                                          B.tmp, nq, s));
     CHOPPER_HIP(launch("join_runs", k_join_runs, gmw, dim3(kBlock), s, m,
-                       (const uint32_t*)B.qhead, (const uint32_t*)B.tpre,
+                       (const uint32_t*)Q_.head, (const uint32_t*)B.tpre,
                        (const uint64_t*)Q_.key, Q_.qstart, Q_.qcls, Q_.qlab,
                        (uint32_t*)nullptr));
     if (check)
@@ -839,13 +929,53 @@ extern "C" int chopper_join_counters(
   };
   rc = record_runs(order, true);
   if (rc != CHOPPER_OK) return rc;
-  // every pass: class order, keys and run table
+  // every pass: class order (a stable partition by class: the pass's order is
+  // its time), keys and run table.  All passes in one launch a kernel where
+  // their class tables fit one scan (up to 35 (gpu, stream) pairs with seven
+  // passes): seven times nine launches of a few us each bound small joins
+  // and the scans among them left the chip idle in large ones (seven passes
+  // of 9.83M records 1708 to 1498 us).  Else pass by pass.
+  JoinParts JP;
+  int64_t tcount = 0;
   for (int p = 0; p < n_passes; ++p) {
     const chopper_counter_pass& P = passes[p];
     const PassBuf& Q_ = B.pb[p];
+    const int64_t t = ceil_div(P.n, (int64_t)kBlock);
+    JP.p[p] = JoinPart{P.n, Q_.qorder, P.label, P.cls, Q_.coff, Q_.head,
+                       Q_.key, Q_.qstart, Q_.qcls, Q_.qlab, Q_.match, tcount,
+                       tcount + t};
+    tcount += t;
+  }
+  const bool all = mmax > 0 && (int64_t)(nclass + 1) * n_passes <= 256;
+  const unsigned mb = (unsigned)ceil_div(mmax, (int64_t)kBlock);
+  const dim3 gmw((unsigned)ceil_div((int64_t)mb, (int64_t)kWavesPerBlock),
+                 (unsigned)n_passes);
+  if (all) {
+    ClassLists CL;
+    CL.count = n_passes;
+    for (int p = 0; p < n_passes; ++p) {
+      const chopper_counter_pass& P = passes[p];
+      CL.l[p] = ClassList{KeyRecStream{P.gpu, P.stream, nullptr, B.cmap,
+                                       (int)nclass + 1},
+                          P.n, B.pb[p].qorder, B.pb[p].coff, 0, 0u};
+    }
+    rc = class_partition_lists(CL, SL, s);
+    if (rc != CHOPPER_OK) return rc;
+    CHOPPER_HIP(launch("join_heads", k_join_heads_all, gmw, dim3(kBlock), s,
+                       JP, (int)nclass + 1, tcount, B.tcnt));
+    CHOPPER_HIP(exclusive_scan<uint32_t>(B.tcnt, B.tpre, tcount + 1, B.tmp,
+                                         SL.total, s));
+    CHOPPER_HIP(launch("join_runs", k_join_runs_all, gmw, dim3(kBlock), s, JP,
+                       (const uint32_t*)B.tpre, B.tot + 2));
+    CHOPPER_HIP(launch("join_order", k_join_order_all,
+                       dim3(std::min<unsigned>(mb, 256u), (unsigned)n_passes),
+                       dim3(kBlock), s, JP, (const uint32_t*)(B.tot + 2),
+                       status, B.flag));
+  }
+  for (int p = 0; p < n_passes && !all; ++p) {
+    const chopper_counter_pass& P = passes[p];
+    const PassBuf& Q_ = B.pb[p];
     if (P.n > 0) {
-      // stable partition of the pass by class, in its own order (the
-      // pass's order is its time: the partition needs no time key)
       ClassSortLayout L = SL;
       L.n = P.n;
       L.ntiles = sort_tiles(P.n);
@@ -893,6 +1023,14 @@ extern "C" int chopper_join_counters(
   // needed: seq2 is reused)
   JoinPasses J;
   J.np = n_passes;
+  const bool match_all = all && ((resort >> 1) & 0xFFu) == 0;
+  if (match_all)
+    CHOPPER_HIP(launch("join_match", k_join_match_all,
+                       dim3(std::min<unsigned>(gn.x, 256u),
+                            (unsigned)n_passes),
+                       dim3(kBlock), s, JP, (const uint32_t*)B.tot,
+                       (const uint32_t*)B.rcls, (const uint32_t*)B.rlab,
+                       (const uint32_t*)(B.tot + 2)));
   for (int p = 0; p < n_passes; ++p) {
     const chopper_counter_pass& P = passes[p];
     const PassBuf& Q_ = B.pb[p];
@@ -905,11 +1043,13 @@ extern "C" int chopper_join_counters(
       rc = pass_runs(p, false);
       if (rc != CHOPPER_OK) return rc;
     }
-    CHOPPER_HIP(launch("join_match", k_join_match, gr, dim3(kBlock), s,
-                       (const uint32_t*)B.tot, (const uint32_t*)B.rcls,
-                       (const uint32_t*)B.rlab, (const uint32_t*)(B.tot + 2 + p),
-                       (const uint32_t*)Q_.qcls, (const uint32_t*)Q_.qlab,
-                       (const uint32_t*)Q_.qstart, m, Q_.match));
+    if (!match_all)
+      CHOPPER_HIP(launch("join_match", k_join_match, gr, dim3(kBlock), s,
+                         (const uint32_t*)B.tot, (const uint32_t*)B.rcls,
+                         (const uint32_t*)B.rlab,
+                         (const uint32_t*)(B.tot + 2 + p),
+                         (const uint32_t*)Q_.qcls, (const uint32_t*)Q_.qlab,
+                         (const uint32_t*)Q_.qstart, m, Q_.match));
     PassView& V = J.p[p];
     V.match = Q_.match;
     V.qorder = Q_.qorder;

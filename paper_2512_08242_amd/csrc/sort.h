@@ -344,6 +344,26 @@ int class_sort2(const AccA& a, const AccB& b, const ClassSortLayout& L,
                 uint32_t* outA, uint32_t* coffA, uint32_t* outB,
                 uint32_t* coffB, hipStream_t s, const WaveClasses* wcls);
 
+// Stable partitions by class of several item lists at once (each in its own
+// order): out[n] and coff[C + 1] of every list as class_sort gives them for
+// known_sorted input.  Needs (sum over the lists of classes x tiles) <= 256 x
+// L.ntiles (L sized for the longest list and 256 classes).
+constexpr int kMaxLists = 8;
+struct ClassList {
+  KeyRecStream key;
+  int64_t n;
+  uint32_t* out;
+  uint32_t* coff;
+  int64_t tab;        // filled in: the list's part of the table, and what
+  uint32_t sub;       // the scan counts before it
+};
+struct ClassLists {
+  int count;
+  ClassList l[kMaxLists];
+};
+int class_partition_lists(ClassLists& B, const ClassSortLayout& L,
+                          hipStream_t s);
+
 // Are both permutations of class_sort2, made of input in any order, the
 // stable sorts by (class, time)?  *sorted says; waits for `s`.
 template <typename AccA, typename AccB>

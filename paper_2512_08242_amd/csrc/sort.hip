@@ -119,17 +119,16 @@ __device__ inline void striped_classes(const Acc& acc, int64_t base,
 // With `unsorted`, also a cheap sufficient test of sortedness on the same
 // items, while they are at hand: is the input ordered by (major, time)?
 template <typename Acc>
-__global__ __launch_bounds__(kBlock) void k_class_hist(Acc acc, int64_t n,
-                                                       int64_t ntiles,
-                                                       uint32_t* tilehist,
-                                                       uint32_t* unsorted) {
+__device__ inline void class_hist(const Acc& acc, uint32_t block, int64_t n,
+                                  int64_t ntiles, uint32_t* tilehist,
+                                  uint32_t* unsorted) {
   __shared__ uint32_t h[256];
   h[threadIdx.x] = 0;
   __syncthreads();
   const int nbits = class_bits(acc.nclass());
   const int lane = threadIdx.x & (kWave - 1);
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
+  const int64_t base = (int64_t)block * kSortTile;
   // (counts need no order: eight consecutive items per lane, vector loads)
   uint32_t d[kSortIpt];
   bool v[kSortIpt];
@@ -159,32 +158,42 @@ __global__ __launch_bounds__(kBlock) void k_class_hist(Acc acc, int64_t n,
   }
   __syncthreads();
   if ((int)threadIdx.x < acc.nclass())
-    tilehist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
+    tilehist[(int64_t)threadIdx.x * ntiles + block] = h[threadIdx.x];
+}
+
+template <typename Acc>
+__global__ __launch_bounds__(kBlock) void k_class_hist(Acc acc, int64_t n,
+                                                       int64_t ntiles,
+                                                       uint32_t* tilehist,
+                                                       uint32_t* unsorted) {
+  class_hist(acc, blockIdx.x, n, ntiles, tilehist, unsorted);
 }
 
 // Block 0 also writes the class start offsets: coff[c] = first position of
-// class c (the scanned table's first tile), coff[C] = n.
+// class c (the scanned table's first tile), coff[C] = n.  `sub`: what the
+// scan had counted before this table.
 template <typename Acc, typename Cols>
-__global__ __launch_bounds__(kBlock) void k_class_partition(
-    Acc acc, int64_t n, int64_t ntiles, const uint32_t* tileoff,
-    uint32_t* out, uint32_t* coff, Cols cols) {
-  if (blockIdx.x == 0) {
+__device__ inline void class_partition(
+    const Acc& acc, uint32_t block, int64_t n, int64_t ntiles,
+    const uint32_t* tileoff, uint32_t sub, uint32_t* out, uint32_t* coff,
+    const Cols& cols) {
+  if (block == 0) {
     const int C = acc.nclass();
     for (int c = threadIdx.x; c <= C; c += kBlock)
-      coff[c] = c < C ? tileoff[(int64_t)c * ntiles] : (uint32_t)n;
+      coff[c] = c < C ? tileoff[(int64_t)c * ntiles] - sub : (uint32_t)n;
   }
   __shared__ RankShared sh;
   __shared__ uint32_t s_val[kSortTile];
   __shared__ uint8_t s_dig[kSortTile];
   __shared__ uint32_t s_gbase[256];
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
+  const int64_t base = (int64_t)block * kSortTile;
   uint32_t dig[kSortIpt], rank[kSortIpt];
   bool valid[kSortIpt];
   striped_classes(acc, base, n, s_dig, dig, valid);
   tile_rank(dig, valid, rank, sh, class_bits(acc.nclass()));
   if ((int)threadIdx.x < acc.nclass())
     s_gbase[threadIdx.x] =
-        tileoff[(int64_t)threadIdx.x * ntiles + blockIdx.x];
+        tileoff[(int64_t)threadIdx.x * ntiles + block] - sub;
   for (int j = 0; j < kSortIpt; ++j) {
     if (!valid[j]) continue;
     uint32_t lp = sh.start[dig[j]] + rank[j];
@@ -201,6 +210,31 @@ __global__ __launch_bounds__(kBlock) void k_class_partition(
     out[pos] = s_val[q];
     cols.put(pos, s_val[q], d);
   }
+}
+
+template <typename Acc, typename Cols>
+__global__ __launch_bounds__(kBlock) void k_class_partition(
+    Acc acc, int64_t n, int64_t ntiles, const uint32_t* tileoff,
+    uint32_t* out, uint32_t* coff, Cols cols) {
+  class_partition(acc, blockIdx.x, n, ntiles, tileoff, 0u, out, coff, cols);
+}
+
+// the same for several item lists, one per blockIdx.y
+__global__ __launch_bounds__(kBlock) void k_class_hist_lists(ClassLists B,
+                                                             uint32_t* tilehist) {
+  const ClassList& P = B.l[blockIdx.y];
+  const int64_t T = (P.n + kSortTile - 1) / kSortTile;
+  if ((int64_t)blockIdx.x >= T) return;                    // whole block
+  class_hist(P.key, blockIdx.x, P.n, T, tilehist + P.tab, nullptr);
+}
+
+__global__ __launch_bounds__(kBlock) void k_class_partition_lists(
+    ClassLists B, const uint32_t* tileoff) {
+  const ClassList& P = B.l[blockIdx.y];
+  const int64_t T = (P.n + kSortTile - 1) / kSortTile;
+  if ((int64_t)blockIdx.x >= T) return;                    // whole block
+  class_partition(P.key, blockIdx.x, P.n, T, tileoff + P.tab, P.sub, P.out,
+                  P.coff, NoColumns());
 }
 
 // (stops reading once some wave has found the answer)
@@ -450,6 +484,31 @@ int class_sort(const Acc& acc, const ClassSortLayout& L, uint32_t* out,
                      dim3(kBlock), s, acc, n, (const int64_t*)L.mm, tbits,
                      L.key0, L.val0));
   return radix_sort_pairs(L, tbits + cbits, out, nullptr, s);
+}
+
+int class_partition_lists(ClassLists& B, const ClassSortLayout& L,
+                          hipStream_t s) {
+  int64_t tab = 0, tmax = 0;
+  uint32_t sub = 0;
+  for (int p = 0; p < B.count; ++p) {
+    ClassList& P = B.l[p];
+    const int64_t T = sort_tiles(P.n);
+    P.tab = tab;
+    P.sub = sub;
+    tab += T * P.key.nclass();
+    sub += (uint32_t)P.n;
+    tmax = T > tmax ? T : tmax;
+  }
+  if (tab > 256 * L.ntiles) return CHOPPER_EINVAL;
+  if (tmax == 0) return CHOPPER_OK;
+  const dim3 g((unsigned)tmax, (unsigned)B.count);
+  CHOPPER_HIP(launch("sort_class_hist", k_class_hist_lists, g, dim3(kBlock), s,
+                     B, L.tilehist));
+  CHOPPER_HIP(exclusive_scan<uint32_t>(L.tilehist, L.tileoff, tab, L.scantmp,
+                                       L.total, s));
+  CHOPPER_HIP(launch("sort_class_partition", k_class_partition_lists, g,
+                     dim3(kBlock), s, B, (const uint32_t*)L.tileoff));
+  return CHOPPER_OK;
 }
 
 int radix_sort_pairs(const ClassSortLayout& L, int bits, uint32_t* out,
