@@ -158,6 +158,20 @@ struct Seq {
   }
 };
 
+// bit words of a group of 256 positions of a pass
+constexpr int kGroupWords = 2 * 4;
+
+// class of position q: the last c < C with off[c] <= q
+__device__ inline int class_at(const uint32_t* off, int C, int64_t q) {
+  int lo = 0, hi = C;
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if ((int64_t)off[mid] <= q) lo = mid;
+    else hi = mid;
+  }
+  return lo;
+}
+
 // key of a sequence item: label | class << 32
 __device__ inline uint64_t item_key(const Seq& S, uint32_t i) {
   return (uint64_t)S.lab[i] | (uint64_t)S.cls(i) << 32;
@@ -228,33 +242,26 @@ __global__ __launch_bounds__(kBlock) void k_join_heads(Seq S,
   if (lane == 0) tcnt[W] = cnt;
 }
 
-// The same for a pass in class order: the class of a position comes from
-// the class offsets of the partition (coff[0 .. C]), so only the label and
-// the kernel class are read through the permutation.  Each wave takes 256
-// consecutive positions, four per lane (more gathers in flight per wave),
-// and writes the head count of its 256 positions (tcnt is per kBlock
-// positions, as k_join_runs reads it).
+// The same for a pass in class order: only the label is read through the
+// permutation, and a class starts where the partition's offsets (coff[0 ..
+// C]) say so.  What is left of a position are two bits, is it a head and
+// does it follow a run without belonging to one (position m may): words j
+// and 4 + j of a group of 256 positions (four to a lane) have lane l's bits
+// for position 4 l + j.  (Memory bounds both passes over the entries.  With
+// 64-bit keys and 32-bit heads written here and read by the run table and
+// the gather, seven passes of 9.83M entries took 341 us here and 71 there;
+// now 185 and 30, and the gather reads 5 bytes of an entry besides its
+// values, not 12.)  tcnt: heads of every group.
 __device__ inline void join_heads_pass(
     uint32_t block, int64_t m, const uint32_t* qorder, const uint32_t* label,
-    const uint8_t* kcls, const uint32_t* coff, int C, uint32_t* head,
-    uint64_t* key, uint32_t* tcnt) {
+    const uint32_t* coff, int C, uint64_t* bits, uint32_t* tcnt) {
   __shared__ uint32_t s_off[256 + 1];
   for (int c = threadIdx.x; c <= C; c += kBlock) s_off[c] = coff[c];
   __syncthreads();
   const int lane = lane_id();
   const int64_t W = (int64_t)block * kWavesPerBlock + threadIdx.x / kWave;
   const int64_t base = W * (kWave * kHeadsIpt);
-  if (base >= m) return;                                   // whole wave
-  // class of position q: the last c < C with s_off[c] <= q
-  auto cls_at = [&](int64_t q) {
-    int lo = 0, hi = C;
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if ((int64_t)s_off[mid] <= q) lo = mid;
-      else hi = mid;
-    }
-    return (uint32_t)lo;
-  };
+  if (base > m) return;                                    // whole wave
   const int64_t p0 = base + (int64_t)lane * kHeadsIpt;
   uint32_t e[kHeadsIpt];
   bool ok[kHeadsIpt];
@@ -270,72 +277,115 @@ __device__ inline void join_heads_pass(
       e[j] = ok[j] ? qorder[p0 + j] : 0u;
     }
   }
-  uint64_t k[kHeadsIpt];
-  uint32_t c = ok[0] ? cls_at(p0) : 0u;
+  uint32_t k[kHeadsIpt];
 #pragma unroll
-  for (int j = 0; j < kHeadsIpt; ++j) {
-    if (!ok[j]) {
-      k[j] = 0ull;
-      continue;
-    }
-    while ((int)c + 1 < C && (int64_t)s_off[c + 1] <= p0 + j) ++c;
-    k[j] = (uint64_t)label[e[j]] | (uint64_t)c << 32 |
-           (uint64_t)kcls[e[j]] << 48;
-  }
+  for (int j = 0; j < kHeadsIpt; ++j) k[j] = ok[j] ? label[e[j]] : kNone;
   // the predecessor of the lane's first position: the lane below's last
-  // key; lane 0 reads it
-  uint64_t ka = wave_shr1_any((uint64_t)0, k[kHeadsIpt - 1]);
-  if (lane == 0 && p0 > 0) {
-    const uint32_t ep = qorder[p0 - 1];
-    ka = (uint64_t)label[ep] | (uint64_t)cls_at(p0 - 1) << 32;
-  }
-  const uint64_t kMask = 0x0000FFFFFFFFFFFFull;    // class and label
-  uint32_t h[kHeadsIpt];
+  // label; lane 0 reads it
+  uint32_t ka = wave_shr1_any(kNone, k[kHeadsIpt - 1]);
+  if (lane == 0 && p0 > 0) ka = label[qorder[p0 - 1]];
+  // class starts among the positions
+  int c = class_at(s_off, C, p0);
+  uint64_t h[kHeadsIpt], g[kHeadsIpt];
   uint32_t cnt = 0;
 #pragma unroll
   for (int j = 0; j < kHeadsIpt; ++j) {
-    const uint64_t prev = j == 0 ? ka : k[j - 1];
-    h[j] = (ok[j] && (uint32_t)k[j] != kNone &&
-            (p0 + j == 0 || ((prev ^ k[j]) & kMask) != 0))
-               ? 1u
-               : 0u;
-    cnt += (uint32_t)__popcll(__ballot(h[j] != 0));
+    const uint32_t prev = j == 0 ? ka : k[j - 1];
+    while (c + 1 < C && (int64_t)s_off[c + 1] <= p0 + j) ++c;
+    h[j] = __ballot(k[j] != kNone &&
+                    (prev != k[j] || (int64_t)s_off[c] == p0 + j));
+    g[j] = __ballot(k[j] == kNone && prev != kNone);
+    cnt += (uint32_t)__popcll(h[j]);
   }
-  if (p0 + kHeadsIpt <= m) {
-    *reinterpret_cast<uint4*>(head + p0) = make_uint4(h[0], h[1], h[2], h[3]);
-    ulonglong2* kp = reinterpret_cast<ulonglong2*>(key + p0);
-    kp[0] = make_ulonglong2(k[0], k[1]);
-    kp[1] = make_ulonglong2(k[2], k[3]);
-  } else {
+  uint64_t word = h[0];
 #pragma unroll
-    for (int j = 0; j < kHeadsIpt; ++j)
-      if (ok[j]) {
-        head[p0 + j] = h[j];
-        key[p0 + j] = k[j];
-      }
-  }
+  for (int j = 1; j < kGroupWords; ++j)
+    if (lane == j) word = j < kHeadsIpt ? h[j & 3] : g[j & 3];
+  if (lane < kGroupWords) bits[W * kGroupWords + lane] = word;
   if (lane == 0) tcnt[W] = cnt;
 }
 
 __global__ __launch_bounds__(kBlock) void k_join_heads_pass(
     int64_t m, const uint32_t* qorder, const uint32_t* label,
-    const uint8_t* kcls, const uint32_t* coff, int C, uint32_t* head,
-    uint64_t* key, uint32_t* tcnt) {
-  join_heads_pass(blockIdx.x, m, qorder, label, kcls, coff, C, head, key,
-                  tcnt);
+    const uint32_t* coff, int C, uint64_t* bits, uint32_t* tcnt) {
+  join_heads_pass(blockIdx.x, m, qorder, label, coff, C, bits, tcnt);
+}
+
+// The run table of a pass from the bits: a wave takes kRunGroups groups of
+// 256 positions and passes over those without any.  A run ends at the next
+// one's head or at the first entry after it that has no iteration.
+constexpr int kRunGroups = 4;
+__device__ inline void join_runs_pass(
+    uint32_t block, int64_t m, const uint64_t* bits, const uint32_t* tpre,
+    uint32_t sub, const uint32_t* qorder, const uint32_t* label,
+    const uint32_t* coff, int C, uint32_t* rstart, uint32_t* rend,
+    uint32_t* rcls, uint32_t* rlab) {
+  static_assert(kGroupWords == 2 * kHeadsIpt && kRunGroups * kGroupWords <= kWave,
+                "the words of a wave's groups, one a lane");
+  __shared__ uint32_t s_off[256 + 1];
+  for (int c = threadIdx.x; c <= C; c += kBlock) s_off[c] = coff[c];
+  __syncthreads();
+  const int lane = lane_id();
+  const int64_t groups = m / (kWave * kHeadsIpt) + 1;
+  const int64_t g0 =
+      ((int64_t)block * kWavesPerBlock + threadIdx.x / kWave) * kRunGroups;
+  if (g0 >= groups) return;                                // whole wave
+  const int64_t w = g0 * kGroupWords + lane;
+  const uint64_t word =
+      lane < kRunGroups * kGroupWords && w < groups * kGroupWords ? bits[w]
+                                                                  : 0ull;
+  const uint32_t first =
+      lane < kRunGroups && g0 + lane < groups ? tpre[g0 + lane] : 0u;
+  const uint64_t some = __ballot(word != 0);
+  for (int g = 0; g < kRunGroups; ++g) {
+    if (((some >> (g * kGroupWords)) & ((1u << kGroupWords) - 1)) == 0)
+      continue;
+    uint32_t h[kHeadsIpt], t[kHeadsIpt], cnt = 0;
+#pragma unroll
+    for (int j = 0; j < kHeadsIpt; ++j) {
+      const int src = g * kGroupWords + j;
+      h[j] = (uint32_t)(__shfl((unsigned long long)word, src) >> lane) & 1u;
+      t[j] = (uint32_t)(__shfl((unsigned long long)word, src + kHeadsIpt) >>
+                        lane) & 1u;
+      cnt += h[j];
+    }
+    uint32_t r = __shfl(first, g) - sub + wave_incl(cnt, OpAdd(), 0u) - cnt;
+    const int64_t p0 =
+        (g0 + g) * (kWave * kHeadsIpt) + (int64_t)lane * kHeadsIpt;
+#pragma unroll
+    for (int j = 0; j < kHeadsIpt; ++j) {
+      const int64_t p = p0 + j;
+      if (t[j]) rend[r - 1] = (uint32_t)p;
+      if (h[j]) {
+        if (r > 0 && label[qorder[p - 1]] != kNone) rend[r - 1] = (uint32_t)p;
+        rstart[r] = (uint32_t)p;
+        rcls[r] = (uint32_t)class_at(s_off, C, p);
+        rlab[r] = label[qorder[p]];
+        ++r;
+      }
+    }
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_join_runs_pass(
+    int64_t m, const uint64_t* bits, const uint32_t* tpre,
+    const uint32_t* qorder, const uint32_t* label, const uint32_t* coff, int C,
+    uint32_t* rstart, uint32_t* rend, uint32_t* rcls, uint32_t* rlab) {
+  join_runs_pass(blockIdx.x, m, bits, tpre, 0u, qorder, label, coff, C, rstart,
+                 rend, rcls, rlab);
 }
 
 // run table: start position, (gpu, stream) and label of every run, the run
 // number of a head being the heads before it (prefix tpre of its 256
-// positions + the heads before it among them); excl (optional) gets that
-// count at every position.  Each wave takes 256 consecutive positions, four
+// positions + the heads before it among them); excl gets that count at every
+// position.  Each wave takes 256 consecutive positions, four
 // per lane, as the heads passes do.
-__device__ inline void join_runs(
-    uint32_t block, int64_t n, const uint32_t* head, const uint32_t* tpre,
-    uint32_t sub, const uint64_t* key, uint32_t* rstart, uint32_t* rcls,
-    uint32_t* rlab, uint32_t* excl) {
+__global__ __launch_bounds__(kBlock) void k_join_runs(
+    int64_t n, const uint32_t* head, const uint32_t* tpre,
+    const uint64_t* key, uint32_t* rstart, uint32_t* rcls, uint32_t* rlab,
+    uint32_t* excl) {
   const int lane = lane_id();
-  const int64_t W = (int64_t)block * kWavesPerBlock + threadIdx.x / kWave;
+  const int64_t W = (int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave;
   const int64_t base = W * (kWave * kHeadsIpt);
   if (base >= n) return;                                   // whole wave
   const int64_t p0 = base + (int64_t)lane * kHeadsIpt;
@@ -349,7 +399,7 @@ __device__ inline void join_runs(
     for (int j = 0; j < kHeadsIpt; ++j) h[j] = p0 + j < n ? head[p0 + j] : 0u;
   }
   const uint32_t c = h[0] + h[1] + h[2] + h[3];
-  uint32_t r = tpre[W] - sub + wave_incl(c, OpAdd(), 0u) - c;
+  uint32_t r = tpre[W] + wave_incl(c, OpAdd(), 0u) - c;
   uint32_t ex[kHeadsIpt];
 #pragma unroll
   for (int j = 0; j < kHeadsIpt; ++j) {
@@ -363,7 +413,6 @@ __device__ inline void join_runs(
     }
     r += h[j];
   }
-  if (!excl) return;
   if (full) {
     *reinterpret_cast<uint4*>(excl + p0) = make_uint4(ex[0], ex[1], ex[2], ex[3]);
   } else {
@@ -371,13 +420,6 @@ __device__ inline void join_runs(
     for (int j = 0; j < kHeadsIpt; ++j)
       if (p0 + j < n) excl[p0 + j] = ex[j];
   }
-}
-
-__global__ __launch_bounds__(kBlock) void k_join_runs(
-    int64_t n, const uint32_t* head, const uint32_t* tpre,
-    const uint64_t* key, uint32_t* rstart, uint32_t* rcls, uint32_t* rlab,
-    uint32_t* excl) {
-  join_runs(blockIdx.x, n, head, tpre, 0u, key, rstart, rcls, rlab, excl);
 }
 
 // run and ordinal of every record, stored at the record (NONE: no
@@ -438,12 +480,12 @@ __global__ void k_join_compose(int64_t n, const uint32_t* seq,
 }
 
 // pass run of every record run: binary search by (gpu, stream, label); the
-// record run gets the class-order positions [start, next run's start) of
-// that pass run, or an empty range
+// record run gets the class-order positions [start, end) of that pass run,
+// or an empty range
 __device__ inline void join_match(const uint32_t* nr, const uint32_t* rcls,
                                   const uint32_t* rlab, const uint32_t* nq,
                                   const uint32_t* qcls, const uint32_t* qlab,
-                                  const uint32_t* qstart, int64_t m,
+                                  const uint32_t* qstart, const uint32_t* qend,
                                   uint2* match) {
   const int64_t n_r = (int64_t)*nr, n_q = (int64_t)*nq;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < n_r;
@@ -458,19 +500,16 @@ __device__ inline void join_match(const uint32_t* nr, const uint32_t* rcls,
     }
     const bool hit =
         lo < n_q && ((uint64_t)qcls[lo] << 32 | qlab[lo]) == key;
-    match[r] = hit ? make_uint2(qstart[lo], lo + 1 < n_q
-                                                ? qstart[lo + 1]
-                                                : (uint32_t)m)
-                   : make_uint2(0u, 0u);
+    match[r] = hit ? make_uint2(qstart[lo], qend[lo]) : make_uint2(0u, 0u);
   }
 }
 
 __global__ void k_join_match(const uint32_t* nr, const uint32_t* rcls,
                              const uint32_t* rlab, const uint32_t* nq,
                              const uint32_t* qcls, const uint32_t* qlab,
-                             const uint32_t* qstart, int64_t m,
+                             const uint32_t* qstart, const uint32_t* qend,
                              uint2* match) {
-  join_match(nr, rcls, rlab, nq, qcls, qlab, qstart, m, match);
+  join_match(nr, rcls, rlab, nq, qcls, qlab, qstart, qend, match);
 }
 
 // All passes at once, pass p in the blocks of blockIdx.y = p.  The head
@@ -481,11 +520,9 @@ struct JoinPart {
   int64_t m;
   const uint32_t* qorder;
   const uint32_t* label;
-  const uint8_t* kcls;
   const uint32_t* coff;
-  uint32_t* head;
-  uint64_t* key;
-  uint32_t *qstart, *qcls, *qlab;
+  uint64_t* bits;
+  uint32_t *qstart, *qend, *qcls, *qlab;
   uint2* match;
   int64_t t0, t1;           // its entries of the table
 };
@@ -499,20 +536,20 @@ __global__ __launch_bounds__(kBlock) void k_join_heads_all(JoinParts J, int C,
   const JoinPart& P = J.p[blockIdx.y];
   if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) tcnt[total] = 0;
   if ((int64_t)blockIdx.x * kWavesPerBlock >= P.t1 - P.t0) return;
-  join_heads_pass(blockIdx.x, P.m, P.qorder, P.label, P.kcls, P.coff, C,
-                  P.head, P.key, tcnt + P.t0);
+  join_heads_pass(blockIdx.x, P.m, P.qorder, P.label, P.coff, C, P.bits,
+                  tcnt + P.t0);
 }
 
 // (also the number of runs of every pass)
-__global__ __launch_bounds__(kBlock) void k_join_runs_all(JoinParts J,
+__global__ __launch_bounds__(kBlock) void k_join_runs_all(JoinParts J, int C,
                                                           const uint32_t* tpre,
                                                           uint32_t* nq) {
   const JoinPart& P = J.p[blockIdx.y];
   const uint32_t sub = tpre[P.t0];
   if (blockIdx.x == 0 && threadIdx.x == 0) nq[blockIdx.y] = tpre[P.t1] - sub;
-  if ((int64_t)blockIdx.x * kWavesPerBlock >= P.t1 - P.t0) return;
-  join_runs(blockIdx.x, P.m, P.head, tpre + P.t0, sub, P.key, P.qstart, P.qcls,
-            P.qlab, nullptr);
+  if ((int64_t)blockIdx.x * kWavesPerBlock * kRunGroups >= P.t1 - P.t0) return;
+  join_runs_pass(blockIdx.x, P.m, P.bits, tpre + P.t0, sub, P.qorder, P.label,
+                 P.coff, C, P.qstart, P.qend, P.qcls, P.qlab);
 }
 
 __global__ void k_join_order_all(JoinParts J, const uint32_t* nq,
@@ -525,7 +562,7 @@ __global__ void k_join_match_all(JoinParts J, const uint32_t* nr,
                                  const uint32_t* rcls, const uint32_t* rlab,
                                  const uint32_t* nq) {
   const JoinPart& P = J.p[blockIdx.y];
-  join_match(nr, rcls, rlab, nq + blockIdx.y, P.qcls, P.qlab, P.qstart, P.m,
+  join_match(nr, rcls, rlab, nq + blockIdx.y, P.qcls, P.qlab, P.qstart, P.qend,
              P.match);
 }
 
@@ -534,7 +571,7 @@ struct PassView {
   const uint2* match;       // record run -> class-order positions of its
                             // pass run [x, y) (empty: no such run)
   const uint32_t* qorder;   // class-order position -> entry
-  const uint64_t* qkey;     // class-order position -> entry key
+  const uint8_t* kcls;      // kernel class of an entry
   const uint64_t* values;   // [n_cols][m]
   int64_t m;
   int32_t n_cols;
@@ -547,12 +584,12 @@ struct JoinPasses {
 };
 
 // the entry of every pass for a record of run `run` (kNone: the record has
-// no iteration) at ordinal `ord`, with run key (kc, kl) and kernel class kk:
-// q[p] = entry index, or -1 when none matches.  All entries are found
-// before any value is read, so that the passes' dependent loads overlap.
+// no iteration) at ordinal `ord`, of kernel class kk: q[p] = entry index,
+// or -1 when none matches.  All entries are found before any value is read,
+// so that the passes' dependent loads overlap.
 __device__ inline void join_entries(const JoinPasses& J, uint32_t run,
-                                    uint32_t ord, uint32_t kc, uint32_t kl,
-                                    uint32_t kk, int64_t (&q)[kMaxPasses]) {
+                                    uint32_t ord, uint32_t kk,
+                                    int64_t (&q)[kMaxPasses]) {
 #pragma unroll
   for (int p = 0; p < kMaxPasses; ++p) {
     q[p] = -1;
@@ -560,13 +597,9 @@ __device__ inline void join_entries(const JoinPasses& J, uint32_t run,
     const PassView& P = J.p[p];
     const uint2 qr = P.match[run];
     const int64_t pos = (int64_t)qr.x + ord;
-    // the entry at the ordinal is the record's only if it still has the
-    // run's key (entries without an iteration may follow the run)
     if (pos < (int64_t)qr.y) {
-      const uint64_t k = P.qkey[pos];
-      if ((uint32_t)k == kl && ((uint32_t)(k >> 32) & 0xFFFFu) == kc &&
-          (uint32_t)(k >> 48) == kk)
-        q[p] = P.qorder[pos];
+      const uint32_t e = P.qorder[pos];
+      if ((uint32_t)P.kcls[e] == kk) q[p] = e;
     }
   }
 }
@@ -576,21 +609,18 @@ __device__ inline void join_entries(const JoinPasses& J, uint32_t run,
 // nothing matches); the matched bits are written once
 __global__ __launch_bounds__(kBlock) void k_join_gather(
     int64_t n, const uint32_t* rrun, const uint32_t* rord, const uint8_t* cls,
-    const uint32_t* rcls, const uint32_t* rlab, JoinPasses J,
-    uint64_t* counters, uint8_t* matched, uint32_t* status) {
+    JoinPasses J, uint64_t* counters, uint8_t* matched, uint32_t* status) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   bool miss = false;
   if (r < n) {
     const uint32_t run = rrun[r];
-    uint32_t ord = 0, kc = 0, kl = 0, kk = 0;
+    uint32_t ord = 0, kk = 0;
     if (run != kNone) {
       ord = rord[r];
-      kc = rcls[run];
-      kl = rlab[run];
       kk = cls[r];
     }
     int64_t q[kMaxPasses];
-    join_entries(J, run, ord, kc, kl, kk, q);
+    join_entries(J, run, ord, kk, q);
     uint32_t bits = 0;
 #pragma unroll
     for (int p = 0; p < kMaxPasses; ++p) {
@@ -648,23 +678,21 @@ __global__ void k_join_rec_inv(int64_t n, const uint32_t* seq, uint32_t* pinv) {
 __global__ __launch_bounds__(kBlock) void k_join_gather_sorted(
     int64_t n, const uint32_t* seq, const uint32_t* head, const uint32_t* excl,
     const uint64_t* key, const uint32_t* rstart, const uint8_t* cls,
-    const uint32_t* rcls, const uint32_t* rlab, JoinPasses J, int W,
-    uint64_t* stage, uint8_t* smatched, uint32_t* status) {
+    JoinPasses J, int W, uint64_t* stage, uint8_t* smatched,
+    uint32_t* status) {
   __shared__ uint64_t s_rows[kBlock * 16];
   const int64_t p0 = (int64_t)blockIdx.x * kBlock;
   const int64_t p = p0 + threadIdx.x;
   bool miss = false;
   if (p < n) {
-    uint32_t run = kNone, ord = 0, kc = 0, kl = 0, kk = 0;
+    uint32_t run = kNone, ord = 0, kk = 0;
     if ((uint32_t)key[p] != kNone) {
       run = excl[p] + head[p] - 1;
       ord = (uint32_t)p - rstart[run];
-      kc = rcls[run];
-      kl = rlab[run];
       kk = cls[seq[p]];
     }
     int64_t q[kMaxPasses];
-    join_entries(J, run, ord, kc, kl, kk, q);
+    join_entries(J, run, ord, kk, q);
     uint64_t* row = s_rows + threadIdx.x * W;
     uint32_t bits = 0;
     int k = 0;
@@ -763,12 +791,12 @@ extern "C" int chopper_join_counters(
   const int64_t nmax = n > mmax ? n : mmax;
   int64_t tmax = 0;                    // head counts of all passes
   for (int p = 0; p < n_passes; ++p)
-    tmax += ceil_div(passes[p].n, (int64_t)kBlock);
+    tmax += ceil_div(passes[p].n + 1, (int64_t)kBlock);
   if (ceil_div(n, (int64_t)kBlock) > tmax) tmax = ceil_div(n, (int64_t)kBlock);
   struct PassBuf {
     uint2* match;
-    uint32_t *qstart, *qorder, *qcls, *qlab, *coff, *head;
-    uint64_t* key;
+    uint32_t *qstart, *qend, *qorder, *qcls, *qlab, *coff;
+    uint64_t* bits;
   };
   struct Bufs {
     uint32_t *rlabv, *head, *excl, *rstart, *rcls, *rlab, *tot, *tmp;
@@ -808,12 +836,13 @@ extern "C" int chopper_join_counters(
       const int64_t m = passes[p].n;
       B.pb[p].match = sc.take<uint2>(n + 1);
       B.pb[p].qstart = sc.take<uint32_t>(m + 1);
+      B.pb[p].qend = sc.take<uint32_t>(m + 1);
       B.pb[p].qorder = sc.take<uint32_t>(m);
       B.pb[p].qcls = sc.take<uint32_t>(m + 1);
       B.pb[p].qlab = sc.take<uint32_t>(m + 1);
       B.pb[p].coff = sc.take<uint32_t>(256 + 1);
-      B.pb[p].key = sc.take<uint64_t>(m);
-      B.pb[p].head = sc.take<uint32_t>(m);
+      B.pb[p].bits =
+          sc.take<uint64_t>(ceil_div(m + 1, (int64_t)kBlock) * kGroupWords);
     }
   };
   Scratch probe(nullptr);
@@ -889,18 +918,21 @@ extern "C" int chopper_join_counters(
     const PassBuf& Q_ = B.pb[p];
     const int64_t m = P.n;
     uint32_t* nq = B.tot + 2 + p;
-    const dim3 gm = grid_for(m, kBlock);
+    const dim3 gm = grid_for(m + 1, kBlock);
     const dim3 gmw((unsigned)ceil_div((int64_t)gm.x, (int64_t)kWavesPerBlock));
     CHOPPER_HIP(launch("join_heads", k_join_heads_pass, gmw, dim3(kBlock), s,
-                       m, (const uint32_t*)Q_.qorder, P.label, P.cls,
-                       (const uint32_t*)Q_.coff, (int)nclass + 1, Q_.head,
-                       Q_.key, B.tcnt));
+                       m, (const uint32_t*)Q_.qorder, P.label,
+                       (const uint32_t*)Q_.coff, (int)nclass + 1, Q_.bits,
+                       B.tcnt));
     CHOPPER_HIP(exclusive_scan<uint32_t>(B.tcnt, B.tpre, (int64_t)gm.x,
                                          B.tmp, nq, s));
-    CHOPPER_HIP(launch("join_runs", k_join_runs, gmw, dim3(kBlock), s, m,
-                       (const uint32_t*)Q_.head, (const uint32_t*)B.tpre,
-                       (const uint64_t*)Q_.key, Q_.qstart, Q_.qcls, Q_.qlab,
-                       (uint32_t*)nullptr));
+    CHOPPER_HIP(launch("join_runs", k_join_runs_pass,
+                       dim3((unsigned)ceil_div((int64_t)gmw.x,
+                                               (int64_t)kRunGroups)),
+                       dim3(kBlock), s, m, (const uint64_t*)Q_.bits,
+                       (const uint32_t*)B.tpre, (const uint32_t*)Q_.qorder,
+                       P.label, (const uint32_t*)Q_.coff, (int)nclass + 1,
+                       Q_.qstart, Q_.qend, Q_.qcls, Q_.qlab));
     if (check)
       CHOPPER_HIP(launch("join_order", k_join_order,
                          dim3(std::min<unsigned>(gm.x, 1024u)), dim3(kBlock),
@@ -940,14 +972,14 @@ extern "C" int chopper_join_counters(
   for (int p = 0; p < n_passes; ++p) {
     const chopper_counter_pass& P = passes[p];
     const PassBuf& Q_ = B.pb[p];
-    const int64_t t = ceil_div(P.n, (int64_t)kBlock);
-    JP.p[p] = JoinPart{P.n, Q_.qorder, P.label, P.cls, Q_.coff, Q_.head,
-                       Q_.key, Q_.qstart, Q_.qcls, Q_.qlab, Q_.match, tcount,
-                       tcount + t};
+    const int64_t t = ceil_div(P.n + 1, (int64_t)kBlock);
+    JP.p[p] = JoinPart{P.n, Q_.qorder, P.label, Q_.coff, Q_.bits,
+                       Q_.qstart, Q_.qend, Q_.qcls, Q_.qlab, Q_.match,
+                       tcount, tcount + t};
     tcount += t;
   }
   const bool all = mmax > 0 && (int64_t)(nclass + 1) * n_passes <= 256;
-  const unsigned mb = (unsigned)ceil_div(mmax, (int64_t)kBlock);
+  const unsigned mb = (unsigned)ceil_div(mmax + 1, (int64_t)kBlock);
   const dim3 gmw((unsigned)ceil_div((int64_t)mb, (int64_t)kWavesPerBlock),
                  (unsigned)n_passes);
   if (all) {
@@ -965,7 +997,11 @@ extern "C" int chopper_join_counters(
                        JP, (int)nclass + 1, tcount, B.tcnt));
     CHOPPER_HIP(exclusive_scan<uint32_t>(B.tcnt, B.tpre, tcount + 1, B.tmp,
                                          SL.total, s));
-    CHOPPER_HIP(launch("join_runs", k_join_runs_all, gmw, dim3(kBlock), s, JP,
+    CHOPPER_HIP(launch("join_runs", k_join_runs_all,
+                       dim3((unsigned)ceil_div((int64_t)gmw.x,
+                                               (int64_t)kRunGroups),
+                            (unsigned)n_passes),
+                       dim3(kBlock), s, JP, (int)nclass + 1,
                        (const uint32_t*)B.tpre, B.tot + 2));
     CHOPPER_HIP(launch("join_order", k_join_order_all,
                        dim3(std::min<unsigned>(mb, 256u), (unsigned)n_passes),
@@ -1049,11 +1085,12 @@ extern "C" int chopper_join_counters(
                          (const uint32_t*)B.rlab,
                          (const uint32_t*)(B.tot + 2 + p),
                          (const uint32_t*)Q_.qcls, (const uint32_t*)Q_.qlab,
-                         (const uint32_t*)Q_.qstart, m, Q_.match));
+                         (const uint32_t*)Q_.qstart, (const uint32_t*)Q_.qend,
+                         Q_.match));
     PassView& V = J.p[p];
     V.match = Q_.match;
     V.qorder = Q_.qorder;
-    V.qkey = Q_.key;
+    V.kcls = P.cls;
     V.values = P.values;
     V.m = m;
     V.n_cols = P.n_cols;
@@ -1062,17 +1099,14 @@ extern "C" int chopper_join_counters(
   if (!scattered) {
     CHOPPER_HIP(launch("join_gather", k_join_gather, gn, dim3(kBlock), s, n,
                        (const uint32_t*)B.rrun, (const uint32_t*)B.rord,
-                       rec->cls, (const uint32_t*)B.rcls,
-                       (const uint32_t*)B.rlab, J, counters_out, matched_out,
-                       status));
+                       rec->cls, J, counters_out, matched_out, status));
     return CHOPPER_OK;
   }
   CHOPPER_HIP(launch("join_gather", k_join_gather_sorted, gn, dim3(kBlock), s,
                      n, rseq, (const uint32_t*)B.head,
                      (const uint32_t*)B.excl, (const uint64_t*)B.rkey,
                      (const uint32_t*)B.rstart, rec->cls,
-                     (const uint32_t*)B.rcls, (const uint32_t*)B.rlab, J, W,
-                     B.stage, B.smatched, status));
+                     J, W, B.stage, B.smatched, status));
   StageCols SC;
   SC.W = W;
   {
