@@ -26,21 +26,28 @@ int64_t sort_tiles(int64_t n) { return ceil_div(n, kSortTile); }
 
 // ---------------------------------------------------------------------------
 // In-tile stable ranking of up to 256 digit values.
-// Items are striped: item j of thread t is tile position j * kBlock + t, so
-// tile order is (row j, wave, lane).  Every wave-row counts its digits with
-// `nbits` ballots (lanes with equal digits find each other; the lowest one
-// records the count), one pass turns the counts of the 8 x 4 (row, wave)
-// cells into per-digit exclusive prefixes, and an item's rank is its cell's
-// prefix plus the number of equal lanes below it.
+// Every wave takes kWaveTile consecutive positions of the tile, a row of 64
+// at a time (item j of a lane is tile position tile_pos(j)).  A row counts
+// its digits with `nbits` ballots (lanes with equal digits find each other);
+// an item's rank is the wave's count of its digit so far, kept in LDS, plus
+// the equal lanes below it, and the lowest of them moves the count on: no
+// barrier until the four waves' counts are put in order.  (The partition is
+// bound by what a block keeps in flight; with one count per row and wave,
+// cleared and scanned, 16 KB of LDS a block and four more barriers, the
+// partition of seven passes of 9.83M entries took 182 us, now 130.)
 // On return count[d] = number of valid items with digit d in the tile,
 // start[d] = exclusive prefix of count, rank[j] = stable position of the
 // item among equal digits.
 // ---------------------------------------------------------------------------
 struct RankShared {
-  uint16_t cell[kSortIpt][kWavesPerBlock][256];   // counts, then prefixes
-  uint32_t count[256];
+  uint32_t cell[kWavesPerBlock][256];   // counts, then prefixes over waves
   uint32_t start[256];
 };
+static_assert(kSortIpt == kTileIpt, "a wave's share of a tile");
+
+__device__ inline int tile_pos(int j) {
+  return (int)(threadIdx.x / kWave) * kWaveTile + j * kWave + lane_id();
+}
 
 __device__ inline void tile_rank(const uint32_t (&dig)[kSortIpt],
                                  const bool (&valid)[kSortIpt],
@@ -50,51 +57,44 @@ __device__ inline void tile_rank(const uint32_t (&dig)[kSortIpt],
   const int lane = t & (kWave - 1);
   const int w = t / kWave;
   const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-  {
-    uint4* z = reinterpret_cast<uint4*>(&sh.cell[0][0][0]);
-    constexpr int kZ = (int)(sizeof(sh.cell) / sizeof(uint4));
-    for (int i = t; i < kZ; i += kBlock) z[i] = make_uint4(0u, 0u, 0u, 0u);
-  }
-  __syncthreads();
-  uint32_t rin[kSortIpt];
+  uint32_t* cell = sh.cell[w];
+  reinterpret_cast<uint4*>(cell)[lane] = make_uint4(0u, 0u, 0u, 0u);
+  wave_sync();
 #pragma unroll
   for (int j = 0; j < kSortIpt; ++j) {
     const uint32_t d = dig[j];
     const bool v = valid[j];
     const uint64_t peers = digit_peers(d, v, nbits);
-    rin[j] = __popcll(peers & lt);
-    if (v && rin[j] == 0) sh.cell[j][w][d] = (uint16_t)__popcll(peers);
+    const uint32_t before = (uint32_t)__popcll(peers & lt);
+    const uint32_t base = v ? cell[d] : 0u;
+    rank[j] = base + before;
+    wave_sync();
+    if (v && before == 0) cell[d] = base + (uint32_t)__popcll(peers);
+    wave_sync();
   }
   __syncthreads();
-  {
-    // digit t: exclusive prefix over the cells in tile order
-    uint32_t acc = 0;
+  // digit t: exclusive prefix over the waves
+  uint32_t acc = 0;
 #pragma unroll
-    for (int j = 0; j < kSortIpt; ++j)
-#pragma unroll
-      for (int q = 0; q < kWavesPerBlock; ++q) {
-        const uint32_t c = sh.cell[j][q][t];
-        sh.cell[j][q][t] = (uint16_t)acc;
-        acc += c;
-      }
-    sh.count[t] = acc;
+  for (int q = 0; q < kWavesPerBlock; ++q) {
+    const uint32_t c = sh.cell[q][t];
+    sh.cell[q][t] = acc;
+    acc += c;
   }
+  uint32_t tot;
+  sh.start[t] = block_exclusive(acc, OpAdd(), 0u, &tot);
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kSortIpt; ++j)
-    if (valid[j]) rank[j] = sh.cell[j][w][dig[j]] + rin[j];
-  uint32_t tot;
-  sh.start[t] = block_exclusive(sh.count[t], OpAdd(), 0u, &tot);
-  __syncthreads();
+    if (valid[j]) rank[j] += cell[dig[j]];
 }
 
 // ---------------------------------------------------------------------------
 // Class-partition fast path
 // ---------------------------------------------------------------------------
-// Class ids of the tile in the striped arrangement the ranking needs (item
-// j of thread t at position j * kBlock + t): loaded eight consecutive items
-// per lane and turned around through `s_tmp` (kSortTile bytes; class ids
-// are below 256).
+// Class ids of the tile in the arrangement the ranking needs: loaded eight
+// consecutive items per lane and turned around inside the wave through
+// `s_tmp` (kSortTile bytes; class ids are below 256).
 template <typename Acc>
 __device__ inline void striped_classes(const Acc& acc, int64_t base,
                                        int64_t n, uint8_t* s_tmp,
@@ -103,17 +103,21 @@ __device__ inline void striped_classes(const Acc& acc, int64_t base,
   uint32_t d[kSortIpt];
   bool v[kSortIpt];
   cls_block(acc, base + (int64_t)threadIdx.x * kSortIpt, n, d, v);
+  uint32_t lo = 0, hi = 0;
 #pragma unroll
-  for (int j = 0; j < kSortIpt; ++j)
-    s_tmp[threadIdx.x * kSortIpt + j] = (uint8_t)d[j];
-  __syncthreads();
+  for (int j = 0; j < 4; ++j) {
+    lo |= d[j] << (8 * j);
+    hi |= d[j + 4] << (8 * j);
+  }
+  reinterpret_cast<uint2*>(s_tmp)[threadIdx.x] = make_uint2(lo, hi);
+  wave_sync();
 #pragma unroll
   for (int j = 0; j < kSortIpt; ++j) {
-    const int q = j * kBlock + (int)threadIdx.x;
+    const int q = tile_pos(j);
     valid[j] = base + q < n;
     dig[j] = valid[j] ? (uint32_t)s_tmp[q] : 0u;
   }
-  __syncthreads();
+  wave_sync();
 }
 
 // With `unsorted`, also a cheap sufficient test of sortedness on the same
@@ -184,7 +188,7 @@ __device__ inline void class_partition(
   }
   __shared__ RankShared sh;
   __shared__ uint32_t s_val[kSortTile];
-  __shared__ uint8_t s_dig[kSortTile];
+  __shared__ __attribute__((aligned(8))) uint8_t s_dig[kSortTile];
   __shared__ uint32_t s_gbase[256];
   const int64_t base = (int64_t)block * kSortTile;
   uint32_t dig[kSortIpt], rank[kSortIpt];
@@ -197,7 +201,7 @@ __device__ inline void class_partition(
   for (int j = 0; j < kSortIpt; ++j) {
     if (!valid[j]) continue;
     uint32_t lp = sh.start[dig[j]] + rank[j];
-    s_val[lp] = (uint32_t)(base + (int64_t)j * kBlock + threadIdx.x);
+    s_val[lp] = (uint32_t)(base + tile_pos(j));
     s_dig[lp] = (uint8_t)dig[j];
   }
   __syncthreads();
@@ -324,7 +328,7 @@ __global__ __launch_bounds__(kBlock) void k_digit_scatter(
   uint64_t k[kSortIpt];
   uint32_t v[kSortIpt];
   for (int j = 0; j < kSortIpt; ++j) {
-    int64_t i = base + (int64_t)j * kBlock + threadIdx.x;
+    int64_t i = base + tile_pos(j);
     valid[j] = i < n;
     k[j] = valid[j] ? key_in[i] : 0ull;
     v[j] = valid[j] ? val_in[i] : 0u;
@@ -740,7 +744,7 @@ __global__ __launch_bounds__(kBlock) void k_class_partition2(
   if (!general[blockIdx.x]) return;   // done by the two-class pass
   __shared__ RankShared sh;
   __shared__ uint32_t s_val[kSortTile];
-  __shared__ uint8_t s_dig[kSortTile];
+  __shared__ __attribute__((aligned(8))) uint8_t s_dig[kSortTile];
   __shared__ uint32_t s_gbase[256];
   const int64_t base = (int64_t)blockIdx.x * kSortTile;
   const int64_t tile_n = (n - base) < kSortTile ? (n - base) : kSortTile;
@@ -763,7 +767,7 @@ __global__ __launch_bounds__(kBlock) void k_class_partition2(
     for (int j = 0; j < kSortIpt; ++j) {
       if (!valid[j]) continue;
       const uint32_t lp = sh.start[dig[j]] + rank[j];
-      s_val[lp] = (uint32_t)(base + (int64_t)j * kBlock + threadIdx.x);
+      s_val[lp] = (uint32_t)(base + tile_pos(j));
       s_dig[lp] = (uint8_t)dig[j];
     }
     __syncthreads();
