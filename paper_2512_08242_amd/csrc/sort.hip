@@ -14,6 +14,8 @@
 // gives the rank) and per-wave digit counts in LDS.  Each tile is first
 // reordered in LDS so that the global writes of one digit bucket are
 // contiguous.
+#include <type_traits>
+
 #include "sort.h"
 #include "wave.h"
 
@@ -434,9 +436,16 @@ int class_sort(const Acc& acc, const ClassSortLayout& L, uint32_t* out,
       CHOPPER_HIP(read_back_start(L.flag, sizeof(uint32_t), s, &rb));
     CHOPPER_HIP(exclusive_scan<uint32_t>(L.tilehist, L.tileoff, (int64_t)C * T,
                                          L.scantmp, L.total, s));
-    CHOPPER_HIP(launch("sort_class_partition", k_class_partition<Acc, Cols>,
-                       dim3((unsigned)T), dim3(kBlock), s, acc, n, T,
-                       (const uint32_t*)L.tileoff, out, coff, cols));
+    // The markers' partition may run beside the overlap call on another
+    // stream, whose union runs decide when the step goes on: 12 KB of LDS
+    // that it does not use keep it at five blocks a CU.  (At full occupancy
+    // it takes the union runs' slots: a step of 19.66M records 3193 us
+    // against 3147 with the LDS and 3144 with a ranking that needs it.)
+    constexpr size_t kSpare = std::is_same<Cols, MarkerColumns>::value ? 12288 : 0;
+    CHOPPER_HIP(launch_shm("sort_class_partition",
+                           k_class_partition<Acc, Cols>, dim3((unsigned)T),
+                           dim3(kBlock), kSpare, s, acc, n, T,
+                           (const uint32_t*)L.tileoff, out, coff, cols));
     if (known_sorted < 0) {
       uint32_t unsorted = 1;
       CHOPPER_HIP(read_back_finish(&rb, &unsorted));
