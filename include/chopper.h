@@ -31,7 +31,7 @@
  * owns every buffer.  The library allocates no device memory, frees nothing
  * and keeps no data between calls; all temporary storage comes from the
  * caller's `scratch` (chopper_launch_split_noalloc alone uses a static 6 KiB
- * device table of the library instead).  One exception, on the host: for
+ * device table of the library instead, above 64 GPUs).  One exception, on the host: for
  * its read-backs (below) the library keeps, per device, four 256-byte slots
  * of pinned host memory (hipHostMalloc) with one HIP event each, created on
  * first use and held until the process ends; a read-back finds its value
@@ -44,16 +44,20 @@
  *
  * Streams.  `stream` is a hipStream_t.  Work is enqueued on it.  Some calls
  * read back a few words (counts and flags that size or choose later
- * launches): a one-wave kernel stores them into a pinned slot, and the host
- * waits for an event recorded after it, not for the whole stream, while
+ * launches): the kernel that makes them, or a one-wave kernel after it,
+ * stores them into a pinned slot, and the host waits for an event recorded after it, not for the whole stream, while
  * work that does not depend on them is already queued behind it:
  * chopper_align once (record classes and whether the input is in start
- * order; the markers' clock transform runs meanwhile), chopper_attribute
+ * order; the markers' clock transform runs meanwhile; on input in no start
+ * order it waits once more for a check of the two orders, and once more for
+ * the times' span if they need sorting), chopper_attribute
  * once (whether the markers are in start order; their class partition runs
  * meanwhile), chopper_aggregate once when the records come grouped by GPU
  * in start order (row counts per level, whether groups are runs; the
  * records reduction runs meanwhile and exits on the device if the flags
- * rule it out), twice otherwise and twice more on the general path,
+ * rule it out), once more for records in another order (and, from 2^20 of
+ * them, for a sample of how far korder jumps), once more for groups of
+ * several runs, and twice more on the path for markers that are not nested,
  * chopper_join_counters twice; the sorts wait again when their input is not
  * in time order.  chopper_overlap, the derived metrics, the launch split
  * and the statistics never wait.  So do not capture the waiting calls in a
@@ -438,7 +442,8 @@ int chopper_views(const chopper_records* records, const int64_t* start_al,
  * abutting or overlapping kernels) get 0 and 0.  Outputs in input order.
  * Per-row sums: pass prep_out / call_out to chopper_aggregate as counter
  * columns.  Sets BAD_GPU, and RANGE when |t_l| or |t_l'| >= 2^62.  Scratch
- * protocol as above (n_gpus clock entries).
+ * protocol as above (n_gpus clock entries; used above 64 GPUs, up to which
+ * the clocks travel with the launch).
  */
 int chopper_launch_split(const chopper_records* records,
                          const chopper_clock* clocks,
@@ -452,16 +457,18 @@ int chopper_launch_split(const chopper_records* records,
  * chopper_launch_split_noalloc -- chopper_launch_split for callers that
  * cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): same arguments and results, but
- * no scratch argument.  The clock table that chopper_launch_split keeps in
- * the caller's scratch lives here in a static device array of the library
+ * no scratch argument.  The clocks of up to 64 GPUs travel with the launch;
+ * those of more, which chopper_launch_split keeps in the caller's scratch,
+ * are put here into a static device array of the library
  * (256 entries of 24 bytes, 6 KiB per device, held by every device the
  * library runs on until the process ends).  The call allocates and frees
  * nothing; the device address of the array is looked up once per device, on
  * the first call made on it.  Limits: n_gpus <= 256 (CHOPPER_ESCRATCH
  * otherwise, nothing enqueued); `stream` must belong to the current device
- * (CHOPPER_EHIP otherwise).  The table is rewritten by every call before its
- * kernel reads it, so nothing needs clearing, but calls that overlap on one
- * GPU (different streams, or threads) race on it: serialize them.
+ * (CHOPPER_EHIP otherwise).  The table is rewritten by every call that uses
+ * it before its kernel reads it, so nothing needs clearing, but calls for
+ * more than 64 GPUs that overlap on one GPU (different streams, or threads)
+ * race on it: serialize them.
  */
 int chopper_launch_split_noalloc(const chopper_records* records,
                                  const chopper_clock* clocks,

@@ -6,7 +6,13 @@
 // group of a record is identified by its deepest non-NONE marker among
 // levels 0..l (or its GPU when all are NONE) and its kind; for nested
 // markers that marker determines the whole path.  Rows are numbered in order
-// of each group's first record:
+// of each group's first record.  Where every group is one run of the order,
+// a count of the runs of every wave tile numbers the rows; where groups have
+// several runs, or a filter leaves records out, an election over the pieces
+// of the wave tiles does; both use the same wave-tile reduction (below).
+// Markers that are not nested, whose groups need exact ids, more pieces to
+// add than the overflow list holds, and markers out of range or beyond 2^30
+// take the element-wise path:
 //   1. election: atomicMin of the record position into a per-level owner
 //      table keyed by group (only at positions where the key changes);
 //   2. owners are counted per tile and one exclusive scan over the
