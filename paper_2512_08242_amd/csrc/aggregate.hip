@@ -1737,6 +1737,68 @@ __device__ inline uint32_t gen_heads(const uint32_t (&key)[kAggIpt], int n0,
   return m;
 }
 
+// The kept item before each of a tile's two runs, if there is one.
+template <int MaxD>
+struct GenPrev {
+  uint32_t p[2][MaxD], gk[2];
+  uint32_t slot[2];           // deepest marker of the levels met so far
+  bool kept[2];
+};
+
+template <int MaxD, bool kNat>
+__device__ inline void gen_prev(const FromRecords& src,
+                                const GenTile<MaxD>& X, int D,
+                                GenPrev<MaxD>& Q) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int64_t i = X.prev[k];
+    Q.slot[k] = kNone;
+    Q.kept[k] = i >= 0;
+    const int64_t ii = Q.kept[k] ? i : 0;
+    if constexpr (kNat) {
+      const uint32_t c = src.S.cls[ii];
+      nat_item<MaxD>(src.S, ii, src.S.gpu[ii], D, Q.gk[k], Q.p[k]);
+      if (src.S.f.active)
+        Q.kept[k] = Q.kept[k] && filter_keeps(src.S, Q.gk[k], c, Q.p[k][0]);
+    } else {
+      const uint32_t v = src.S.igk[ii];
+      Q.kept[k] = Q.kept[k] && v != 0xFFFFu;
+      Q.gk[k] = v & 511u;
+#pragma unroll
+      for (int l = 0; l < MaxD; ++l)
+        Q.p[k][l] = l < D ? src.S.ipath[(int64_t)l * src.S.n + ii] : kNone;
+    }
+  }
+}
+
+template <int MaxD>
+__device__ inline void gen_prev_level(GenPrev<MaxD>& Q, int li) {
+#pragma unroll
+  for (int k = 0; k < 2; ++k)
+    Q.slot[k] = Q.p[k][li] != kNone ? Q.p[k][li] : Q.slot[k];
+}
+
+// Bit j: item j of the lane is the first of its run in the tile and belongs
+// to the group of the kept item before the run.
+template <int MaxD, bool kNat>
+__device__ inline uint32_t gen_goes_on(const GenTile<MaxD>& X,
+                                       const GenPrev<MaxD>& Q,
+                                       const uint32_t (&key)[kAggIpt],
+                                       bool marker, int64_t M, int lane) {
+  uint32_t m = 0;
+#pragma unroll
+  for (int j = 0; j < kAggIpt; ++j) {
+    const int v = lane * kAggIpt + j;
+    if (v != 0 && v != X.n0) continue;
+    const int k = kNat && v == X.n0 ? 1 : 0;
+    const uint32_t g = k ? Q.gk[1] : Q.gk[0];
+    const uint32_t qk =
+        marker ? slot_key(k ? Q.slot[1] : Q.slot[0], M, g) : g;
+    if ((k ? Q.kept[1] : Q.kept[0]) && key[j] == qk) m |= 1u << j;
+  }
+  return m;
+}
+
 // kPlain: a piece inside its run of the tile whose marker is numbered above
 // the one before it is new in any trace whose markers are nested and
 // numbered as they open, so it stores its position instead of taking the
@@ -1757,47 +1819,18 @@ __global__ __launch_bounds__(kBlock) void k_gen_elect(
   GenTile<MaxD> X;
   if (!gen_load<MaxD, kNat>(src, N, w, D, lane, X)) return;
   gen_block(X, s_k[wv], lane);
-  // the kept item before each run: a piece that goes on with its group has
-  // nothing to elect (without this every tile would meet at the entries of
-  // the coarse levels: 0.097 instead of 0.034 ms on 2.46M records)
-  uint32_t qp[2][MaxD], qg[2];
-  bool qv[2];
-#pragma unroll
-  for (int k = 0; k < 2; ++k) {
-    const int64_t i = X.prev[k];
-    qv[k] = i >= 0;
-    const int64_t ii = qv[k] ? i : 0;
-    if constexpr (kNat) {
-      const uint32_t c = src.S.cls[ii];
-      nat_item<MaxD>(src.S, ii, src.S.gpu[ii], D, qg[k], qp[k]);
-      if (src.S.f.active)
-        qv[k] = qv[k] && filter_keeps(src.S, qg[k], c, qp[k][0]);
-    } else {
-      const uint32_t v = src.S.igk[ii];
-      qv[k] = qv[k] && v != 0xFFFFu;
-      qg[k] = v & 511u;
-#pragma unroll
-      for (int l = 0; l < MaxD; ++l)
-        qp[k][l] = l < D ? src.S.ipath[(int64_t)l * src.S.n + ii] : kNone;
-    }
-  }
-  uint32_t qs[2] = {kNone, kNone};
+  // a piece that goes on with its group has nothing to elect (without this
+  // every tile would meet at the entries of the coarse levels: 0.097 instead
+  // of 0.034 ms on 2.46M records)
+  GenPrev<MaxD> Q;
+  gen_prev<MaxD, kNat>(src, X, D, Q);
   uint32_t slot[kAggIpt], key[kAggIpt];
 #pragma unroll
   for (int j = 0; j < kAggIpt; ++j) slot[j] = kNone;
   bool unkeyed = false;
   auto elect = [&](uint32_t* own, bool marker) {
     uint32_t m = gen_heads(key, X.n0, X.nv, lane);
-#pragma unroll
-    for (int j = 0; j < kAggIpt; ++j) {
-      const int v = lane * kAggIpt + j;
-      if (v != 0 && v != X.n0) continue;
-      const int k = kNat && v == X.n0 ? 1 : 0;
-      const uint32_t qk = marker ? slot_key(k ? qs[1] : qs[0], M,
-                                            k ? qg[1] : qg[0])
-                                 : (k ? qg[1] : qg[0]);
-      if ((k ? qv[1] : qv[0]) && key[j] == qk) m &= ~(1u << j);
-    }
+    m &= ~gen_goes_on<MaxD, kNat>(X, Q, key, marker, M, lane);
     if (kPlain && marker) {
       uint32_t ps = wave_shr1_u32(0u, slot[kAggIpt - 1]);
 #pragma unroll
@@ -1825,8 +1858,7 @@ __global__ __launch_bounds__(kBlock) void k_gen_elect(
 #pragma unroll
     for (int j = 0; j < kAggIpt; ++j)
       slot[j] = X.p[j][li] != kNone ? X.p[j][li] : slot[j];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) qs[k] = qp[k][li] != kNone ? qp[k][li] : qs[k];
+    gen_prev_level(Q, li);
     if (!((act >> li) & 1u)) continue;
 #pragma unroll
     for (int j = 0; j < kAggIpt; ++j) {
@@ -1846,9 +1878,9 @@ __global__ __launch_bounds__(kBlock) void k_gen_elect(
 
 // Owners of levels [lv0, lv1] per tile: tilecnt[(li - lv0) * stride + entry]
 // and omask[(li - lv0) * mstride + 64 w + lane].  From records also: the
-// kinds present (flags[1]), pieces that neither own their row nor start
-// their run of the tile (interior[li]), and PATH_CONFLICT when two items of
-// a key hold different paths.
+// kinds present (flags[1]), the groups that come back (interior[li]: pieces
+// that do not own their row and are not the rest of a piece of the tile
+// before), and PATH_CONFLICT when two items of a key hold different paths.
 template <int MaxD, typename Src, bool kNat>
 __device__ inline void gen_count(
     const Src& src, const NatGeom& N, uint32_t act, int lv0, int lv1, int D,
@@ -1880,6 +1912,8 @@ __device__ inline void gen_count(
     eq[j] = true;
   }
   bool conflict = false, late = false;
+  GenPrev<MaxD> Q;
+  if constexpr (Src::kRecords) gen_prev<MaxD, kNat>(src, X, D, Q);
   // items of the lane before position n0
   const int b0 = X.n0 - lane * kAggIpt;
   const uint32_t m_run0 = b0 <= 0 ? 0u : (b0 >= kAggIpt ? 0xFFu
@@ -1924,13 +1958,9 @@ __device__ inline void gen_count(
           }
         }
       }
-      uint32_t in = other;
-#pragma unroll
-      for (int j = 0; j < kAggIpt; ++j) {
-        const int v = lane * kAggIpt + j;
-        if (v == 0 || v == X.n0) in &= ~(1u << j);
-      }
-      const uint32_t t = wave_total((uint32_t)__popc(in));
+      const uint32_t back =
+          other & ~gen_goes_on<MaxD, kNat>(X, Q, key, li < D, M, lane);
+      const uint32_t t = wave_total((uint32_t)__popc(back));
       if (lane == 0 && t) atomicAdd(&interior[li], t);
     }
     omask[(int64_t)(li - lv0) * mstride + w * kWave + lane] = (uint8_t)mine;
@@ -1952,6 +1982,7 @@ __device__ inline void gen_count(
         eq[j] = eq[j] && X.p[j][li] == prev;
         prev = X.p[j][li];
       }
+      gen_prev_level(Q, li);
     }
 #pragma unroll
     for (int j = 0; j < kAggIpt; ++j)
@@ -2044,15 +2075,17 @@ struct GenRed {
 __global__ __launch_bounds__(kBlock) void k_gen_apply(
     Overflow ovf, RowsDev R, int nfields, const uint32_t* own,
     const uint32_t* own2) {
-  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   int64_t cnt = (int64_t)*ovf.count;
   if (cnt > ovf.cap) cnt = ovf.cap;
-  if (e >= cnt) return;
-  const uint32_t k = ovf.row[e];
-  const uint32_t row = k >> 31 ? own2[k & 0x7FFFFFFFu] : own[k];
-  if ((int64_t)row >= R.cap) return;
-  for (int f = 0; f < nfields; ++f)
-    atomic_field(R, f, row, ovf.val[(int64_t)f * ovf.cap + e]);
+  const int64_t step = (int64_t)gridDim.x * kBlock;
+  for (int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x; e < cnt;
+       e += step) {
+    const uint32_t k = ovf.row[e];
+    const uint32_t row = k >> 31 ? own2[k & 0x7FFFFFFFu] : own[k];
+    if ((int64_t)row >= R.cap) continue;
+    for (int f = 0; f < nfields; ++f)
+      atomic_field(R, f, row, ovf.val[(int64_t)f * ovf.cap + e]);
+  }
 }
 
 // Piece structure of one level over a wave tile (blocked arrangement: lane
@@ -3523,11 +3556,22 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
   } else {
     ps[np++] = Pass{level == CHOPPER_LEVEL_GPU ? D : level, true, false};
   }
-  // pieces a pass may leave to the overflow list: those inside the tiles
-  // and the first of every run of a tile
+  // Pieces a pass may leave to the overflow list, of either level: the groups
+  // that come back, and the first piece of every run of a tile.  Records: the
+  // tiles the count was made on.  Rows, in order of their groups' first
+  // records: where a group comes back at row b, the row before it belongs to
+  // another group whose first record lies between that group's first record
+  // and b's, so b's first record is in a stretch of the records in which the
+  // group came back too, and in no other such row's stretch: rows come back
+  // at most as often as records, and their own tiles' first pieces are added.
+  // (The stretch may start on a record tile, so the count has to know the
+  // item before it: rows that came back there were once missing.)
   auto left = [&](const Pass& q) {
-    const int64_t tiles = q.records ? (kNat ? 2 : 1) * nwt : Th;
-    return inner[q.li] + tiles + (q.two ? inner[q.li - 1] + tiles : 0);
+    const int64_t runs =
+        q.records ? (kNat ? 2 : 1) * nwt
+                  : ceil_div(lo_h[q.li + 2] - lo_h[q.li + 1],
+                             (int64_t)kWaveTile);
+    return inner[q.li] + runs + (q.two ? inner[q.li - 1] + runs : 0);
   };
   for (int i = 0; i < np; ++i)
     if (left(ps[i]) > ovf.cap) return 1;
