@@ -1799,12 +1799,7 @@ __device__ inline uint32_t gen_goes_on(const GenTile<MaxD>& X,
   return m;
 }
 
-// kPlain: a piece inside its run of the tile whose marker is numbered above
-// the one before it is new in any trace whose markers are nested and
-// numbered as they open, so it stores its position instead of taking the
-// minimum.  A piece for which that was wrong finds a later position than
-// its own in the count pass, and the host elects again with minima only.
-template <int MaxD, bool kNat, bool kPlain>
+template <int MaxD, bool kNat>
 __global__ __launch_bounds__(kBlock) void k_gen_elect(
     FromRecords src, NatGeom N, uint32_t act, int D, int64_t M, int64_t nwt,
     GenTab tab, uint32_t* flags) {
@@ -1831,19 +1826,6 @@ __global__ __launch_bounds__(kBlock) void k_gen_elect(
   auto elect = [&](uint32_t* own, bool marker) {
     uint32_t m = gen_heads(key, X.n0, X.nv, lane);
     m &= ~gen_goes_on<MaxD, kNat>(X, Q, key, marker, M, lane);
-    if (kPlain && marker) {
-      uint32_t ps = wave_shr1_u32(0u, slot[kAggIpt - 1]);
-#pragma unroll
-      for (int j = 0; j < kAggIpt; ++j) {
-        const int v = lane * kAggIpt + j;
-        if ((m >> j) & 1u && v != 0 && v != X.n0 && key[j] != kNone &&
-            slot[j] + 1u > ps + 1u) {
-          own[key[j]] = X.id[j];
-          m &= ~(1u << j);
-        }
-        ps = slot[j];
-      }
-    }
     uint32_t cur[kAggIpt];
 #pragma unroll
     for (int j = 0; j < kAggIpt; ++j)
@@ -1911,7 +1893,7 @@ __device__ inline void gen_count(
     slot[j] = kNone;
     eq[j] = true;
   }
-  bool conflict = false, late = false;
+  bool conflict = false;
   GenPrev<MaxD> Q;
   if constexpr (Src::kRecords) gen_prev<MaxD, kNat>(src, X, D, Q);
   // items of the lane before position n0
@@ -1938,7 +1920,6 @@ __device__ inline void gen_count(
       const bool h = (m >> j) & 1u && key[j] != kNone;
       mine |= h && o[j] == X.id[j] ? 1u << j : 0u;
       other |= h && o[j] != X.id[j] ? 1u << j : 0u;
-      late |= h && o[j] > X.id[j];
     }
     if constexpr (Src::kRecords) {
       if (li < D) {
@@ -2016,8 +1997,6 @@ __device__ inline void gen_count(
       tilecnt[(int64_t)(li - lv0) * stride + X.e1] = 0;
     }
   if constexpr (Src::kRecords) {
-    wave_flag_or(&flags[0], late, 4u);
-    // (a late entry still belongs to the group, so a conflict is one)
     if (__ballot(conflict) != 0 && lane == 0) {
       atomicOr(&flags[0], 2u);
       atomicOr(status, (uint32_t)CHOPPER_ST_PATH_CONFLICT);
@@ -2062,7 +2041,7 @@ __global__ __launch_bounds__(kBlock) void k_gen_count_rows(
 }
 
 // What the reduction needs of this path: the owner masks and tables of the
-// level and the next coarser one, and whether later passes read firstpos.
+// level and the next coarser one.
 struct GenRed {
   const uint8_t* mask = nullptr;
   const uint8_t* mask2 = nullptr;
@@ -3458,8 +3437,6 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
   if (fx > 2048) fx = 2048;
   FromRecords fr{S};
   int64_t st[kStageWords];
-  // (records out of order usually come with markers out of order)
-  bool plain = false;
   bool far = false;            // records in no order: through rows
   if (!kNat) {
     const dim3 gi = grid_for(S.n, kBlock);
@@ -3490,55 +3467,45 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
     fr.S.ipath = L.ipath;
     fr.S.igk = L.igk;
   }
-  for (;;) {
-    CHOPPER_HIP(launch("agg_gen_fill", k_gen_fill, dim3(fx, (unsigned)(D + 1)),
-                       dim3(kBlock), s, tab, act, L.hflags, L.interior,
-                       L.ovf_count));
-    if (plain)
-      CHOPPER_HIP(launch("agg_gen_elect", k_gen_elect<kMD, kNat, kNat>, grid,
-                         dim3(kBlock), s, fr, N, act, D, M, nwt, tab,
-                         L.hflags));
-    else
-      CHOPPER_HIP(launch("agg_gen_elect", k_gen_elect<kMD, kNat, false>, grid,
-                         dim3(kBlock), s, fr, N, act, D, M, nwt, tab,
-                         L.hflags));
-    ReadBack rb;
-    StageOut O;
-    O.L = Lv;
-    O.stride = stride;
-    O.tilecnt = tc;
-    O.tilebase = tb;
-    O.total = L.htotal;
-    O.interior = L.interior;
-    O.nat = kNat;
-    O.workload = want_workload;
-    O.cap = rows->cap;
-    O.level_offset = rows->level_offset;
-    O.stage = L.stage;
-    O.host = read_back_open(sizeof(int64_t) * (size_t)(3 + Lv + 1 + Lv), &rb);
-    O.status = status;
-    O.count = (int64_t)Lv * stride <= kTailScan ? L.interior + kMaxLevels
-                                                : nullptr;
-    CHOPPER_HIP(launch("agg_gen_count", k_gen_count<kMD, kNat>, grid,
-                       dim3(kBlock), s, fr, N, act, 0, Lv - 1, D, M, nwt,
-                       stride, tab, tc, L.omask, L.mstride, L.hflags,
-                       L.interior, status, O));
-    if (!O.count) {
-      CHOPPER_HIP(exclusive_scan<uint32_t>(tc, tb, (int64_t)Lv * stride,
-                                           kNat ? L.nscan : L.hscan,
-                                           L.htotal, s));
-      CHOPPER_HIP(launch("agg_offsets", k_agg_offsets, dim3(1), dim3(64), s,
-                         O, (const uint32_t*)L.hflags));
-    }
-    CHOPPER_HIP(read_back_close(L.stage, s, &rb));
-    if (ready) CHOPPER_HIP(hipStreamWaitEvent(s, ready, 0));
-    CHOPPER_HIP(read_back_finish(&rb, st));
-    if (kNat && st[2] != 0) {
-      *bad_order = true;
-      return 1;
-    }
-    if (!(plain && st[0] == 4)) break;
-    plain = false;
+  CHOPPER_HIP(launch("agg_gen_fill", k_gen_fill, dim3(fx, (unsigned)(D + 1)),
+                     dim3(kBlock), s, tab, act, L.hflags, L.interior,
+                     L.ovf_count));
+  CHOPPER_HIP(launch("agg_gen_elect", k_gen_elect<kMD, kNat>, grid,
+                     dim3(kBlock), s, fr, N, act, D, M, nwt, tab, L.hflags));
+  ReadBack rb;
+  StageOut O;
+  O.L = Lv;
+  O.stride = stride;
+  O.tilecnt = tc;
+  O.tilebase = tb;
+  O.total = L.htotal;
+  O.interior = L.interior;
+  O.nat = kNat;
+  O.workload = want_workload;
+  O.cap = rows->cap;
+  O.level_offset = rows->level_offset;
+  O.stage = L.stage;
+  O.host = read_back_open(sizeof(int64_t) * (size_t)(3 + Lv + 1 + Lv), &rb);
+  O.status = status;
+  O.count = (int64_t)Lv * stride <= kTailScan ? L.interior + kMaxLevels
+                                              : nullptr;
+  CHOPPER_HIP(launch("agg_gen_count", k_gen_count<kMD, kNat>, grid,
+                     dim3(kBlock), s, fr, N, act, 0, Lv - 1, D, M, nwt,
+                     stride, tab, tc, L.omask, L.mstride, L.hflags,
+                     L.interior, status, O));
+  if (!O.count) {
+    CHOPPER_HIP(exclusive_scan<uint32_t>(tc, tb, (int64_t)Lv * stride,
+                                         kNat ? L.nscan : L.hscan,
+                                         L.htotal, s));
+    CHOPPER_HIP(launch("agg_offsets", k_agg_offsets, dim3(1), dim3(64), s,
+                       O, (const uint32_t*)L.hflags));
+  }
+  CHOPPER_HIP(read_back_close(L.stage, s, &rb));
+  if (ready) CHOPPER_HIP(hipStreamWaitEvent(s, ready, 0));
+  CHOPPER_HIP(read_back_finish(&rb, st));
+  if (kNat && st[2] != 0) {
+    *bad_order = true;
+    return 1;
   }
   const int64_t* lo_h = st + 3;
   const int64_t* inner = st + 3 + Lv + 1;
