@@ -15,7 +15,7 @@ TimerHook& timer_hook() {
 static const char* const kKernelNames[] = {
     "align_transform_records", "align_transform_markers", "align_fill",
     "align_dense_classes", "sort_class_hist", "sort_class_partition",
-    "sort_class_verify", "sort_class_offsets", "sort_digit_hist",
+    "sort_class_verify", "sort_digit_hist",
     "sort_digit_scatter", "sort_make_keys", "sort_time_minmax",
     "attr_marker_gather", "attr_marker_links", "attr_records",
     "ov_runs_fixup", "ov_runs_spine", "ov_runs_count", "ov_runs_write",
@@ -26,21 +26,20 @@ static const char* const kKernelNames[] = {
     "agg_zero_rows", "agg_zero", "scan_reduce", "scan_spine", "scan_down",
     "ratios_rows", "ratios_windows", "sort_fill", "sort_init_minmax",
     "sort_class_count", "status_set", "ov_fill",
-    "agg_workload_first", "sort_major_sorted", "agg_heads_records",
+    "agg_workload_first", "agg_heads_records",
     "agg_heads_rows", "agg_fast_reduce_records", "agg_fast_reduce_rows",
-    "agg_workload_from_gpu", "bi_params", "bi_clear", "bi_fill",
-    "bi_fixup", "ov_comm_records", "agg_nat_init", "agg_nat_pre",
+    "bi_params", "bi_clear", "bi_fill", "ov_comm_records", "agg_nat_init", "agg_nat_pre",
     "agg_nat_tiles", "agg_heads_nat", "agg_gpu_rows",
     "agg_exact_keys", "join_resort", "attr_windows", "agg_items",
     "agg_gen_fill", "agg_gen_elect", "agg_gen_count",
     "agg_gen_reduce_records", "agg_gen_count_rows", "agg_gen_reduce_rows",
     "agg_gen_apply", "agg_stage", "ov_queries",
-    "view_flags", "view_units", "view_fill", "view_records", "view_rows",
+    "view_units", "view_fill", "view_records",
     "view_iter_max", "view_medians", "launch_split", "join_fill",
     "join_labels", "join_heads", "join_runs", "join_order", "join_pass_prep",
-    "join_dense", "join_match", "join_gather", "stats_clear", "stats_keys",
+    "join_dense", "join_locality", "join_match", "join_gather", "stats_clear", "stats_keys",
     "stats_offsets", "stats_scatter", "stats_pass", "stats_select",
-    "stats_final"};
+    "stats_final", "stats_cdf", "read_back"};
 
 __global__ __launch_bounds__(kBlock) void k_ratios(
     const int64_t* level_offset, int depth, int64_t cap, const uint64_t* n,
