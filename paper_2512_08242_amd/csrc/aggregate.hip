@@ -74,9 +74,6 @@ struct RecSrc {
   // gpu * 2 + kind (0xFFFF: left out by the filter)
   const uint32_t* ipath;
   const uint16_t* igk;
-  // start, end, gap, ovl and the counters are copies in korder position
-  // order (see k_stage_columns)
-  bool sorted = false;
 };
 
 struct RowsDev {
@@ -186,12 +183,16 @@ __global__ __launch_bounds__(kBlock) void k_agg_items(RecSrc S, uint32_t* ipath,
 // Reading a column through korder fetches a cache line per value where the
 // order jumps (27 ms for the 20 columns of 50M records, and 8 ms for their
 // markers and GPUs).  Such input goes through rows instead: a pass in input
-// order puts up to eight columns of a record side by side in one row of 64
-// bytes (markers, GPU and kind: 32 or 64), and a pass in korder order
-// fetches that row -- one line, not eight -- and writes the columns in korder
-// order, which the reduction then reads as they lie.  Both passes stream but
-// for the row fetch: 50M records STAGEMS.
-constexpr int kRowCols = 8;
+// order puts several columns of a record side by side in one row, and the
+// pass in korder order fetches that row -- one line, not one a column.
+// Markers, GPU and kind (32 or 64 bytes) are written back in korder order,
+// for the passes that read them several times; the fields go four columns at
+// a time (32 bytes) straight into the reduction, one launch a group, so that
+// the scratch is 32 bytes a record in the element-wise path's space.  50M
+// records, depth 6, 16 counters: items 0.5 + 1.5 ms, each of the five groups
+// 0.6 + 2.2 (with eight columns a group written back in korder order for one
+// reduction, 160 bytes a record: 15.0 ms in place of 14.0).
+constexpr int kRowCols = 4;
 constexpr int64_t kStageMin = (int64_t)1 << 20;   // below, columns stay cached
 
 // Do the records lie far from korder?  Positions spread over all of it are
@@ -246,10 +247,9 @@ __global__ __launch_bounds__(kBlock) void k_unstage_items(
   igk[pos] = (uint16_t)v[W - 1];
 }
 
-// kRowCols columns (fewer: the rest of the row is not written or read)
+// kRowCols columns (fewer: the rest of the row is not written)
 struct StageCols {
   const uint64_t* in[kRowCols];
-  uint64_t* out[kRowCols];
 };
 
 __global__ __launch_bounds__(kBlock) void k_stage_columns(StageCols C,
@@ -264,22 +264,6 @@ __global__ __launch_bounds__(kBlock) void k_stage_columns(StageCols C,
   for (int q = 0; q < kRowCols / 2; ++q)
     if (C.in[2 * q])
       rows[i * (kRowCols / 2) + q] = make_ulonglong2(v[2 * q], v[2 * q + 1]);
-}
-
-__global__ __launch_bounds__(kBlock) void k_unstage_columns(
-    StageCols C, const uint32_t* korder, int64_t n, const ulonglong2* rows) {
-  const int64_t pos = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (pos >= n) return;
-  const int64_t r = korder[pos];
-  ulonglong2 v[kRowCols / 2];
-#pragma unroll
-  for (int q = 0; q < kRowCols / 2; ++q)
-    if (C.out[2 * q]) v[q] = rows[r * (kRowCols / 2) + q];
-#pragma unroll
-  for (int q = 0; q < kRowCols / 2; ++q) {
-    if (C.out[2 * q]) C.out[2 * q][pos] = v[q].x;
-    if (C.out[2 * q + 1]) C.out[2 * q + 1][pos] = v[q].y;
-  }
 }
 
 // ------------------------------------------------------------------ election
@@ -2041,12 +2025,19 @@ __global__ __launch_bounds__(kBlock) void k_gen_count_rows(
 }
 
 // What the reduction needs of this path: the owner masks and tables of the
-// level and the next coarser one.
+// level and the next coarser one.  kStaged: the rows of columns
+// [c0, c0 + nc) of start, end, gap, ovl and the counters; the first group's
+// launch has the headers and leaves every tile's first overflow slot of
+// either level in `slots`, so that the others put their pieces' values beside
+// its own.
 struct GenRed {
   const uint8_t* mask = nullptr;
   const uint8_t* mask2 = nullptr;
   uint32_t* own = nullptr;
   uint32_t* own2 = nullptr;
+  const ulonglong2* rows = nullptr;
+  int c0 = 0, nc = 0;
+  uint32_t* slots = nullptr;
 };
 
 // Overflow entries (group keys; top bit: the reduction's second level) to
@@ -2173,10 +2164,12 @@ __device__ inline int64_t piece_row(const LevelTile& T, uint32_t q) {
 // (kSplit; reduce_parts below).
 // kGen: groups of several runs (above): every piece is a head here, the
 // owners' rows are numbered by rank, and a piece's row -- or, top bit set,
-// its overflow slot -- is kept per piece in LDS.
+// its overflow slot -- is kept per piece in LDS.  kStaged: the columns come
+// from rows, four a launch (see k_stage_columns).
 constexpr int kSpecial = 5;
 constexpr int64_t kReduceWaves = 3072;
-template <int MaxD, typename Src, bool kTwo, bool kNat, bool kGen, bool kSplit>
+template <int MaxD, typename Src, bool kTwo, bool kNat, bool kGen, bool kSplit,
+          bool kStaged = false>
 __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
     Src src, NatGeom N, int li, int D, int64_t M, const uint32_t* tilebase,
     const uint32_t* tilebase2, const int64_t* row0, RowsDev R, Overflow ovf,
@@ -2328,6 +2321,8 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
   if (kTwo)
     level_tile(key2, tprev2[0], tprev2[1], n0, tile_n, lane, q0, q1, T2,
                slot2);
+  // the launch, or the part, with the headers
+  const bool first = kSplit ? blockIdx.y == 0 : !kStaged || GR.c0 == 0;
   // (kGen) rows of the pieces: owners by rank, the others an overflow slot
   uint32_t m_own = 0, m_own2 = 0, own_row[kAggIpt], own_row2[kAggIpt];
   auto piece_rows = [&](const LevelTile& T, const uint32_t (&k)[kAggIpt],
@@ -2346,7 +2341,10 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
         (uint32_t)__builtin_amdgcn_readlane((int)(xo + co), kWave - 1);
     uint32_t ob = 0;
     if (no) {                      // uniform
-      if (lane == 0) ob = atomicAdd(ovf.count, no);
+      if (lane == 0) {
+        ob = first ? atomicAdd(ovf.count, no) : GR.slots[2 * w + which];
+        if (kStaged && first) GR.slots[2 * w + which] = ob;
+      }
       ob = (uint32_t)__builtin_amdgcn_readlane((int)ob, 0);
     }
     uint32_t* srow = s_row[wv][which];
@@ -2367,7 +2365,7 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
       } else {
         const uint32_t e = ob + xo + (uint32_t)__popc(other & below);
         if ((int64_t)e < ovf.cap) {
-          ovf.row[e] = k[j] | ((uint32_t)which << 31);
+          if (first) ovf.row[e] = k[j] | ((uint32_t)which << 31);
           v = e | 0x80000000u;
         }
       }
@@ -2420,7 +2418,6 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
       }
     }
   };
-  const bool first = !kSplit || blockIdx.y == 0;  // part with the headers
   if (first) {
     headers(T1, li, own_row, GR.own);
     if (kTwo) headers(T2, li2, own_row2, GR.own2);
@@ -2444,12 +2441,7 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
   // byte offsets of the striped items (sizes are below 2^29 here)
   uint32_t off[kAggIpt];
 #pragma unroll
-  for (int j = 0; j < kAggIpt; ++j) {
-    if constexpr (kGen && !kNat && Src::kRecords)
-      off[j] = (src.S.sorted ? id[j] : rs[j]) << 3;
-    else
-      off[j] = rs[j] << 3;
-  }
+  for (int j = 0; j < kAggIpt; ++j) off[j] = rs[j] << 3;
 
   // piece values at the slots -> rows (and the overflow slots)
   auto store_pieces = [&](const LevelTile& T, int64_t obase, int f,
@@ -2531,6 +2523,42 @@ __global__ __launch_bounds__(kBlock) void k_agg_fast_reduce(
     for (int j = 0; j < kAggIpt; ++j)
       v[j] = *(const uint64_t*)((const char*)col + off[j]);
   };
+
+  if constexpr (kStaged) {
+    uint64_t c[kRowCols][kAggIpt];
+#pragma unroll
+    for (int j = 0; j < kAggIpt; ++j)
+#pragma unroll
+      for (int q = 0; q < kRowCols / 2; ++q) {
+        const ulonglong2 v = GR.rows[(int64_t)rs[j] * (kRowCols / 2) + q];
+        c[2 * q][j] = v.x;
+        c[2 * q + 1][j] = v.y;
+      }
+    if (first) {                   // start, end, gap, ovl
+      uint64_t x[kAggIpt];
+#pragma unroll
+      for (int j = 0; j < kAggIpt; ++j)
+        x[j] = (uint64_t)(lane * kAggIpt + j + 1);
+      put(slot, x);
+      store_pieces(T1, 0, 0, true);
+      if (kTwo) {
+        put(slot2, x);
+        store_pieces(T2, ob2, 0, true);
+      }
+#pragma unroll
+      for (int j = 0; j < kAggIpt; ++j) x[j] = c[1][j] - c[0][j];
+      do_sum(x, 1);
+      do_seg(c[0], 4, CMin());
+      do_seg(c[1], 5, CMax());
+      do_sum(c[2], 2);
+      do_sum(c[3], 3);
+    } else {
+#pragma unroll
+      for (int q = 0; q < kRowCols; ++q)
+        if (q < GR.nc) do_sum(c[q], GR.c0 + q + 2);
+    }
+    return;
+  }
 
   // this part's plain sums: is .. ns - 1 (the special fields, which come to
   // about kSpecial sums, are the first part's)
@@ -2989,10 +3017,9 @@ struct AggLayout {
   ClassSortLayout xsort;
   uint32_t* ipath;        // [D][n] general-path items by korder position
   uint16_t* igk;          // [n]
-  // records in no order: a row per record (in the exact ids' space, which
-  // is then free) and the columns in korder order
-  char* srow;
-  uint64_t* scol;         // [4 + counters][n], null below kStageMin records
+  // records in no order, null below kStageMin of them
+  char* srow;             // a row per record
+  uint32_t* slots;        // [2 * tiles] first overflow slot of either level
   // groups of several runs
   uint8_t* omask;         // [L][mstride] owners of every lane
   int64_t mstride;        // 64 * (natural tiles + G)
@@ -3000,7 +3027,7 @@ struct AggLayout {
 };
 
 static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
-                            int64_t cap, uint32_t act, int G, int nc) {
+                            int64_t cap, uint32_t act, int G) {
   AggLayout L;
   L.L = D + 2;
   L.ntiles = ceil_div(n, kAggTile);
@@ -3010,15 +3037,10 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
     if (li < D && n > ks) ks = n;
     L.ks[li] = ((act >> li) & 1u) ? ks : 1;
     L.own[li] = sc.take<uint32_t>(L.ks[li]);
-    L.rowof[li] = sc.take<uint32_t>(L.ks[li]);
   }
   L.own_tab = sc.take<uint32_t*>(kMaxLevels);
   L.rowof_tab = sc.take<uint32_t*>(kMaxLevels);
   L.ks_dev = sc.take<int64_t>(kMaxLevels);
-  L.tilecnt = sc.take<uint32_t>((int64_t)L.L * L.ntiles);
-  L.tilebase = sc.take<uint32_t>((int64_t)L.L * L.ntiles);
-  L.scantmp = sc.take<uint32_t>(scan_scratch_elems((int64_t)L.L * L.ntiles));
-  L.total = sc.take<uint32_t>(1);
   L.firstpos = sc.take<uint32_t>(cap);
   L.ntiles_h = ceil_div(n, kWaveTile);
   L.nstride = 2 * (L.ntiles_h + G);
@@ -3049,10 +3071,16 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.gs = sc.take<uint32_t>(G);
   L.ge = sc.take<uint32_t>(G);
   L.gtb = sc.take<uint32_t>(G + 1);
-  L.srow = sc.take<char>(0);
-  const size_t row0 = sc.used;
-  L.gk = sc.take<uint32_t>((int64_t)(D > 0 ? D : 1) * n);
   L.xflag = sc.take<uint32_t>(1);
+  // the element-wise path's own, and in the same space what only the tiles
+  // of groups of several runs use
+  Scratch gen = sc;
+  for (int li = 0; li < L.L; ++li) L.rowof[li] = sc.take<uint32_t>(L.ks[li]);
+  L.tilecnt = sc.take<uint32_t>((int64_t)L.L * L.ntiles);
+  L.tilebase = sc.take<uint32_t>((int64_t)L.L * L.ntiles);
+  L.scantmp = sc.take<uint32_t>(scan_scratch_elems((int64_t)L.L * L.ntiles));
+  L.total = sc.take<uint32_t>(1);
+  L.gk = sc.take<uint32_t>((int64_t)(D > 0 ? D : 1) * n);
   L.xskey = sc.take<uint64_t>(n);
   L.xsval = sc.take<uint32_t>(n);
   L.xhead = sc.take<uint32_t>(n);
@@ -3061,18 +3089,20 @@ static AggLayout agg_layout(Scratch& sc, int64_t n, int D, int64_t M,
   L.xtot = sc.take<uint32_t>(1);
   L.xscan = sc.take<uint32_t>(scan_scratch_elems(n));
   L.xsort = class_sort_layout(sc, n, 256);
-  L.scol = nullptr;
+  L.interior = gen.take<uint32_t>(kMaxLevels + 1);
+  L.mstride = (int64_t)kWave * (L.ntiles_h + G);
+  L.omask = gen.take<uint8_t>((int64_t)L.L * L.mstride);
+  L.srow = nullptr;
+  L.slots = nullptr;
   if (n >= kStageMin) {
-    const int64_t have = (int64_t)(sc.used - row0);
-    const int64_t rows = n * (int64_t)(kRowCols * sizeof(uint64_t)) + 512;
-    if (have < rows) (void)sc.take<char>(rows - have);
-    L.scol = sc.take<uint64_t>((4 + nc) * n);
+    // (items, then a group of columns)
+    static_assert(kRowCols * sizeof(uint64_t) <= 32, "rows of 32 bytes");
+    L.srow = gen.take<char>((D < 8 ? 32 : 64) * n);
+    L.slots = gen.take<uint32_t>(2 * L.ntiles_h);
   }
+  if (gen.used > sc.used) sc.used = gen.used;
   L.ipath = sc.take<uint32_t>((int64_t)(D > 0 ? D : 1) * n);
   L.igk = sc.take<uint16_t>(n);
-  L.mstride = (int64_t)kWave * (L.ntiles_h + G);
-  L.omask = sc.take<uint8_t>((int64_t)L.L * L.mstride);
-  L.interior = sc.take<uint32_t>(kMaxLevels + 1);
   return L;
 }
 
@@ -3440,7 +3470,7 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
   bool far = false;            // records in no order: through rows
   if (!kNat) {
     const dim3 gi = grid_for(S.n, kBlock);
-    if (L.scol) {
+    if (L.srow) {
       uint32_t jumps = 0;
       CHOPPER_HIP(launch("agg_stage", k_sample_jumps, dim3(1), dim3(kBlock), s,
                          S.korder, S.n, L.xflag));
@@ -3542,36 +3572,24 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
   };
   for (int i = 0; i < np; ++i)
     if (left(ps[i]) > ovf.cap) return 1;
-  if (far) {
-    // (gap and ovl are complete here: the event above)
-    const int cols = 4 + fr.S.nc;
-    auto in = [&](int c) -> const uint64_t* {
-      return c == 0   ? (const uint64_t*)S.start
-             : c == 1 ? (const uint64_t*)S.end
-             : c == 2 ? (const uint64_t*)S.gap
-             : c == 3 ? (const uint64_t*)S.ovl
-                      : S.ctr + (int64_t)(c - 4) * S.n;
-    };
-    ulonglong2* rows2 = reinterpret_cast<ulonglong2*>(L.srow);
-    for (int c0 = 0; c0 < cols; c0 += kRowCols) {
-      StageCols C;
-      for (int c = 0; c < kRowCols; ++c) {
-        C.in[c] = c0 + c < cols ? in(c0 + c) : nullptr;
-        C.out[c] = c0 + c < cols ? L.scol + (int64_t)(c0 + c) * S.n : nullptr;
-      }
-      CHOPPER_HIP(launch("agg_stage", k_stage_columns, grid_for(S.n, kBlock),
-                         dim3(kBlock), s, C, S.n, rows2));
-      CHOPPER_HIP(launch("agg_stage", k_unstage_columns,
-                         grid_for(S.n, kBlock), dim3(kBlock), s, C, S.korder,
-                         S.n, (const ulonglong2*)rows2));
+  // columns c0 .. c0 + kRowCols - 1 of start, end, gap, ovl and the counters
+  // side by side (gap and ovl are complete here: the event above)
+  const int cols = 4 + S.nc;
+  auto stage = [&](int c0) -> int {
+    StageCols C;
+    for (int i = 0; i < kRowCols; ++i) {
+      const int c = c0 + i;
+      C.in[i] = c == 0    ? (const uint64_t*)S.start
+                : c == 1  ? (const uint64_t*)S.end
+                : c == 2  ? (const uint64_t*)S.gap
+                : c == 3  ? (const uint64_t*)S.ovl
+                : c < cols ? S.ctr + (int64_t)(c - 4) * S.n : nullptr;
     }
-    fr.S.start = (const int64_t*)L.scol;
-    fr.S.end = (const int64_t*)(L.scol + S.n);
-    fr.S.gap = (const int64_t*)(L.scol + 2 * S.n);
-    fr.S.ovl = (const int64_t*)(L.scol + 3 * S.n);
-    fr.S.ctr = L.scol + 4 * S.n;
-    fr.S.sorted = true;
-  }
+    CHOPPER_HIP(launch("agg_stage", k_stage_columns, grid_for(S.n, kBlock),
+                       dim3(kBlock), s, C, S.n,
+                       reinterpret_cast<ulonglong2*>(L.srow)));
+    return CHOPPER_OK;
+  };
   for (int i = 0; i < np; ++i) {
     const Pass& q = ps[i];
     const int li = q.li;
@@ -3582,18 +3600,29 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
       const uint32_t* tbl = tb + (int64_t)li * stride;
       GR.mask = L.omask + (int64_t)li * L.mstride;
       GR.mask2 = q.two ? GR.mask - L.mstride : nullptr;
-      if (q.two)
+      if constexpr (!kNat) {
+        GR.rows = reinterpret_cast<const ulonglong2*>(L.srow);
+        GR.slots = L.slots;
+        for (int c0 = 0; far && c0 < cols; c0 += kRowCols) {
+          const int r = stage(c0);
+          if (r != CHOPPER_OK) return r;
+          GR.c0 = c0;
+          GR.nc = cols - c0 < kRowCols ? cols - c0 : kRowCols;
+          CHOPPER_HIP(launch("agg_gen_reduce_records",
+                             q.two ? k_agg_fast_reduce<kMD, FromRecords, true, false, true, false, true>
+                                   : k_agg_fast_reduce<kMD, FromRecords, false, false, true, false, true>,
+                             grid, dim3(kBlock), s, fr, N, li, D, M, tbl,
+                             tbl - (q.two ? stride : 0),
+                             (const int64_t*)nullptr, R, ovf, nwt, GR));
+        }
+      }
+      if (!far)
         CHOPPER_HIP(launch("agg_gen_reduce_records",
-                           k_agg_fast_reduce<kMD, FromRecords, true, kNat, true, false>,
+                           q.two ? k_agg_fast_reduce<kMD, FromRecords, true, kNat, true, false>
+                                 : k_agg_fast_reduce<kMD, FromRecords, false, kNat, true, false>,
                            grid, dim3(kBlock), s, fr, N, li, D, M, tbl,
-                           tbl - stride, (const int64_t*)nullptr, R, ovf, nwt,
-                           GR));
-      else
-        CHOPPER_HIP(launch("agg_gen_reduce_records",
-                           k_agg_fast_reduce<kMD, FromRecords, false, kNat, true, false>,
-                           grid, dim3(kBlock), s, fr, N, li, D, M, tbl,
-                           (const uint32_t*)nullptr, (const int64_t*)nullptr,
-                           R, ovf, nwt, GR));
+                           tbl - (q.two ? stride : 0),
+                           (const int64_t*)nullptr, R, ovf, nwt, GR));
     } else {
       const int64_t cnt = lo_h[li + 2] - lo_h[li + 1];
       if (cnt == 0) break;
@@ -3698,14 +3727,13 @@ extern "C" int chopper_aggregate(const chopper_records* rec,
   else return CHOPPER_EINVAL;
 
   Scratch probe(nullptr);
-  agg_layout(probe, n, D, M, rows->cap, act, rec->n_gpus, rec->n_counters);
+  agg_layout(probe, n, D, M, rows->cap, act, rec->n_gpus);
   int rc = scratch_check(scratch, scratch_bytes, probe.used);
   if (rc != 0) return rc > 0 ? CHOPPER_OK : rc;
   if (!status) return CHOPPER_EINVAL;
   hipStream_t s = (hipStream_t)stream;
   Scratch sc(scratch);
-  AggLayout L = agg_layout(sc, n, D, M, rows->cap, act, rec->n_gpus,
-                           rec->n_counters);
+  AggLayout L = agg_layout(sc, n, D, M, rows->cap, act, rec->n_gpus);
   const int Lv = L.L;
   const int64_t T = L.ntiles;
   const int nc = rec->n_counters;
