@@ -123,3 +123,22 @@ def test_records_in_no_order(ch, depth, filt):
     cf = None if filt is None else ch.make_filter(**filt)
     assert_parity(run_gpu(ch, tr, filt=cf), oracle.run(tr, filt=of),
                   name=f"no order, depth {depth}")
+
+
+@pytest.mark.parametrize("counters,level", [(0, 255), (1, 255), (3, 1),
+                                            (4, 100), (5, 255), (16, 2)])
+def test_no_order_column_groups(ch, counters, level):
+    """The same pass takes four columns at a time: groups that are whole, that
+    are cut short and that are left out, at all levels and at one."""
+    from test_gpu_periodic_gaps import periodic
+    tr = periodic((1 << 19) + 77, (256, 64, 4), (0,), 3, n_counters=counters,
+                  gpus=2)
+    p = np.random.default_rng(counters).permutation(tr.n)
+    tr = dataclasses.replace(
+        tr, counters=None if tr.counters is None else tr.counters[:, p],
+        **{k: getattr(tr, k)[p] for k in ("gpu", "stream", "start", "end",
+                                          "cls", "op_id")})
+    assert tr.n >= 1 << 20
+    say("no order,", counters, "counters, level", level)
+    assert_parity(run_gpu(ch, tr, level=level), oracle.run(tr, level=level),
+                  name=f"no order, {counters} counters, level {level}")
