@@ -16,7 +16,8 @@
 // selection of six order statistics of the ratio per group, eleven bits and
 // then ten per pass, all groups at once.  The rows of a GPU follow each
 // other, so the instances of a group on one GPU are a stretch of the group's
-// column; one block selects that CDF's order statistics from it.
+// column; one wave, one block or the passes' blocks select that CDF's order
+// statistics from it, by its length.
 #include "common.h"
 #include "sort.h"
 #include "wave.h"
@@ -37,6 +38,7 @@ constexpr int kRowSpan = kRowT * kStatIpt;
 constexpr int kChunk = kStatT * kStatIpt;     // instances per block
 constexpr int kRanks = 6;                     // order statistics per group
 constexpr int kSums = 8;                      // exact moment words per group
+constexpr int kTies = 3;                      // ranks whose times are wanted
 constexpr int kTopBits = 11;                  // digits of a ratio (31 bits)
 constexpr int kLowBits = 10;
 constexpr int kTopBins = 1 << kTopBits;
@@ -178,10 +180,63 @@ struct Cells {
   uint32_t* end;
 };
 
+// A CDF group is selected by one wave, by one block or in parts by many
+// blocks, by the length of its stretch and the instances in it: one wave up
+// to kWaveCell slots, parts of about kPart instances above kLongCell
+// instances (both sides measured: see k_cdf_cells).
+constexpr int kWaveCell = 512;
+constexpr int64_t kLongCell = 32768;
+constexpr int64_t kPart = kChunk;
+constexpr int64_t kPartBlocks = 256;        // for parts, in every pass
+
+// a CDF group in parts
+struct LongCell {
+  uint32_t c;
+  uint32_t part0, parts;      // its parts, numbered over all of these groups
+  unsigned long long ymin;
+};
+
+// the groups in parts (in no order: every group is on its own)
+struct CellLists {
+  unsigned long long* n_long; // number << 32 | their parts
+  LongCell* lng;
+  uint32_t* of_part;          // a part's group in parts
+  uint32_t* ties;             // [3] a part
+};
+
+// ranks 0, (m-1)/4, (m-1)/2, m/2, 3(m-1)/4 and m-1
+__device__ inline int64_t rank_of(int64_t m, int r) {
+  return r == 0 ? 0 : r == 1 ? (m - 1) / 4 : r == 2 ? (m - 1) / 2
+       : r == 3 ? m / 2 : r == 4 ? 3 * (m - 1) / 4 : m - 1;
+}
+
+// rank of tie k: 0, 2 and 3
+__device__ inline int tie_rank(int k) { return k == 0 ? 0 : k + 1; }
+
+// part `q`: its group in parts, GPU, slots [lo, hi), and are they all the
+// group's?
+struct Part {
+  uint32_t i, h;
+  bool all;
+  int64_t lo, hi;
+  __device__ Part(const Cells& C, const CellLists& Q, int NG, uint32_t q) {
+    i = Q.of_part[q];
+    const LongCell L = Q.lng[i];
+    const int64_t beg = C.beg[L.c], len = (int64_t)C.end[L.c] - beg;
+    const int64_t p = q - L.part0;
+    h = L.c % (uint32_t)NG;
+    all = len == (int64_t)C.cnt[L.c];
+    lo = beg + len * p / L.parts;
+    hi = beg + len * (p + 1) / L.parts;
+  }
+};
+
 __global__ void k_stats_clear(int G, uint32_t* hist, int64_t nh,
-                              uint64_t* csum, Cells C, int64_t NGG) {
+                              uint64_t* csum, Cells C, int64_t NGG,
+                              CellLists Q) {
   const int64_t step = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i0 == 0) *Q.n_long = 0;
   for (int64_t i = i0; i < nh; i += step) hist[i] = 0;
   for (int64_t i = i0; i < 3 * (int64_t)G * kCopies; i += step) csum[i] = 0;
   for (int64_t i = i0; i < NGG; i += step) {
@@ -271,14 +326,14 @@ __global__ __launch_bounds__(kRowT) void k_stats_keys(StatArgs A,
 
 // group offsets and counts from the scanned table, chunk offsets and the
 // ranks to select (one block)
-__global__ __launch_bounds__(kStatT) void k_stats_offsets(
+__device__ inline void stats_offsets(
     const uint32_t* tab, int64_t nb, const uint32_t* total, int G,
     uint32_t* cnt, uint32_t* off, uint32_t* coff, uint32_t* spre,
     int64_t* srank) {
-  __shared__ uint32_t s_w[kStatT / kWave];
+  __shared__ uint32_t s_w[kBlock / kWave];
   const int t = threadIdx.x, lane = lane_id(), w = t / kWave;
   uint32_t ccarry = 0;
-  for (int b0 = 0; b0 < G; b0 += kStatT) {
+  for (int b0 = 0; b0 < G; b0 += kBlock) {
     const int g = b0 + t;
     uint32_t v = 0;
     if (g < G) {
@@ -292,20 +347,16 @@ __global__ __launch_bounds__(kStatT) void k_stats_offsets(
     if (lane == kWave - 1) s_w[w] = cincl;
     __syncthreads();
     uint32_t cpre = ccarry, ctot = ccarry;
-    for (int q = 0; q < kStatT / kWave; ++q) {
+    for (int q = 0; q < kBlock / kWave; ++q) {
       if (q < w) cpre += s_w[q];
       ctot += s_w[q];
     }
     if (g < G) {
       coff[g] = cpre + cincl - c;
-      // v[0], v[(m-1)/4], v[(m-1)/2], v[m/2], v[3(m-1)/4], v[m-1]
-      const int64_t m = v;
-      const int64_t want[kRanks] = {0, (m - 1) / 4, (m - 1) / 2, m / 2,
-                                    3 * (m - 1) / 4, m - 1};
 #pragma unroll
       for (int r = 0; r < kRanks; ++r) {
         spre[g * kRanks + r] = 0;
-        srank[g * kRanks + r] = want[r];
+        srank[g * kRanks + r] = rank_of(v, r);
       }
     }
     ccarry = ctot;
@@ -394,20 +445,97 @@ __global__ __launch_bounds__(kRowT) void k_stats_scatter(
     xs[pos] = x > 0x7FFFFFFFull ? 0x7FFFFFFFu : (uint32_t)x;
     ys[pos] = y;
     hs[pos] = (uint8_t)h[k];
-    if (mixed && (int)h[k] < NG) {
-      const int64_t c = (int64_t)g[k] * NG + h[k];
-      atomicAdd(&C.cnt[c], 1u);
+  }
+  // (by one lane for the others of a row and CDF group: instance by instance
+  // a block where one GPU of one group ends took 0.3 ms)
+#pragma unroll 1
+  for (int k = 0; mixed && k < kStatIpt; ++k) {
+    const bool v = g[k] != kNoGroup && (int)h[k] < NG;
+    const uint64_t m = digit_peers(g[k], v, nbits) & digit_peers(h[k], v, 8);
+    if (!v) continue;
+    const int64_t c = (int64_t)g[k] * NG + h[k];
+    const uint32_t pos = s_base[g[k]] + mine[g[k]] + rank[k];
+    if (lanes_below(m) == 0) {
+      atomicAdd(&C.cnt[c], (uint32_t)__popcll(m));
       atomicMin(&C.beg[c], pos);
-      atomicMax(&C.end[c], pos + 1);
     }
+    if (lane == 63 - __clzll((long long)m)) atomicMax(&C.end[c], pos + 1);
   }
   if (__ballot(big) != 0 && lane == 0) atomicOr(status, CHOPPER_ST_RANGE);
 }
 
-// the group and chunk of this block (false past the last chunk)
+// The CDF groups of a (phase, operation) from the blocks of rows on one GPU,
+// in row order (the other blocks have added theirs); those to be selected in
+// parts are listed, and those without instances get their results.  (Before
+// the passes, so that those take the groups in parts along.)  One more block
+// finds the offsets.
+__global__ __launch_bounds__(kBlock) void k_stats_cells(
+    uint32_t* cnt, uint32_t* off, uint32_t* coff, const uint32_t* total,
+    int G, const uint32_t* hist, const uint32_t* tab, int64_t nb,
+    const uint16_t* bgpu, int NG, Cells C, CellLists Q, uint32_t* ghist,
+    uint32_t* spre, int64_t* srank, double* gout, int64_t* gcnt_out) {
+  if (blockIdx.x == 0) {
+    stats_offsets(tab, nb, total, G, cnt, off, coff, spre, srank);
+    return;
+  }
+  __shared__ uint32_t s_n[256], s_b[256], s_e[256];
+  __shared__ uint32_t s_nl, s_long[256];
+  static_assert(kBlock >= 256, "a thread a GPU");
+  const int g = (int)blockIdx.x - 1, t = threadIdx.x;
+  const int64_t c = (int64_t)g * NG + t, NGG = (int64_t)G * NG;
+  const bool any = (g + 1 < G ? tab[(int64_t)(g + 1) * nb] : *total) !=
+                   tab[(int64_t)g * nb];    // (uniform)
+  if (t == 0) s_nl = 0;
+  if (t < NG) {
+    s_n[t] = any ? C.cnt[c] : 0u;
+    s_b[t] = any ? C.beg[c] : 0u;
+    s_e[t] = any ? C.end[c] : 0u;
+  }
+  __syncthreads();
+  for (int64_t b = t; any && b < nb; b += kBlock) {
+    const uint32_t h = bgpu[b], n = hist[(int64_t)g * nb + b];
+    if (n == 0 || h >= (uint32_t)NG) continue;
+    const uint32_t at = tab[(int64_t)g * nb + b];
+    atomicAdd(&s_n[h], n);
+    atomicMin(&s_b[h], at);
+    atomicMax(&s_e[h], at + n);
+  }
+  __syncthreads();
+  if (t < NG && s_n[t] == 0) {
+    for (int k = 0; k < 9; ++k) gout[k * NGG + c] = __builtin_nan("");
+    gcnt_out[c] = 0;
+  } else if (t < NG) {
+    const int64_t m = s_n[t];
+    C.cnt[c] = s_n[t];
+    C.beg[c] = s_b[t];
+    C.end[c] = s_e[t];
+    if (m > kLongCell) {
+      const uint32_t parts = (uint32_t)ceil_div(m, kPart);
+      const unsigned long long q =
+          atomicAdd(Q.n_long, 1ull << 32 | (unsigned long long)parts);
+      const uint32_t i = (uint32_t)(q >> 32);
+      Q.lng[i] = LongCell{(uint32_t)c, (uint32_t)q, parts, ~0ull};
+      for (int r = 0; r < kRanks; ++r) {
+        spre[(int64_t)(G + i) * kRanks + r] = 0;
+        srank[(int64_t)(G + i) * kRanks + r] = rank_of(m, r);
+      }
+      s_long[atomicAdd(&s_nl, 1u)] = i;
+    }
+  }
+  __syncthreads();
+  for (uint32_t k = 0; k < s_nl; ++k) {
+    const uint32_t i = s_long[k];
+    const LongCell L = Q.lng[i];
+    for (uint32_t q = t; q < L.parts; q += kBlock) Q.of_part[L.part0 + q] = i;
+    for (int q = t; q < kHistW; q += kBlock)
+      ghist[(int64_t)(G + i) * kHistW + q] = 0;
+  }
+}
+
+// the group and slots of chunk c (false past the last chunk)
 __device__ inline bool chunk_of(const uint32_t* coff, const uint32_t* off,
-                                int G, int64_t& b, int64_t& e, int& g) {
-  const uint32_t c = blockIdx.x;
+                                int G, uint32_t c, int64_t& b, int64_t& e,
+                                int& g) {
   if (c >= coff[G]) return false;
   int lo = 0, hi = G;        // the last g with coff[g] <= c
   while (hi - lo > 1) {
@@ -448,65 +576,119 @@ __device__ inline void block_sums(uint64_t (&v)[kSums],
 // counter sums come from the grouping pass.  After the eleven bits of the
 // first pass few instances are candidates but for those that share one
 // value (no overlap at all), which one LDS add per wave counts.
-template <bool First>
-__global__ __launch_bounds__(kStatT) void k_stats_pass(
-    const uint32_t* off, const uint32_t* coff, int G, const uint32_t* xs,
-    const uint64_t* ys,
-    const uint32_t* spre, int sh, uint32_t* ghist, uint64_t* part) {
+//
+// The blocks after the groups' do the same for the parts of CDF groups, whose
+// histograms follow the groups'; instead of the sums they keep the smallest y.
+// (Code of their own: the checks a part needs, in the groups' loop, took the
+// pass over 6.1M instances from 23 to 32 us.)
+struct PassShared {
+  uint32_t h[kHistW];
+  uint64_t w[kStatT / kWave][kSums];
+};
+template <bool First, bool Whole>
+__device__ inline void stats_pass(int64_t b, int64_t e, bool all, uint32_t h,
+                                  const uint32_t* xs, const uint64_t* ys,
+                                  const uint8_t* hs, const uint32_t* spre,
+                                  int sh, uint32_t* gh, uint64_t* part,
+                                  unsigned long long* ymin, PassShared& S) {
   constexpr int kBins = First ? kTopBins : kHistW;
-  __shared__ uint32_t s_h[kBins];
-  __shared__ uint64_t s_w[kStatT / kWave][kSums];
-  int64_t b, e;
-  int g;
-  if (!chunk_of(coff, off, G, b, e, g)) return;
   const int t = threadIdx.x;
   uint32_t x[kStatIpt];
   uint64_t y[kStatIpt];
+  bool on[kStatIpt];
+  auto load = [&](int64_t b0) {
 #pragma unroll
-  for (int k = 0; k < kStatIpt; ++k) {
-    const int64_t i = b + (int64_t)k * kStatT + t;
-    x[k] = i < e ? xs[i] : 0u;
-    if (First) y[k] = i < e ? ys[i] : 0ull;
-  }
-  for (int q = t; q < kBins; q += kStatT) s_h[q] = 0;
+    for (int k = 0; k < kStatIpt; ++k) {
+      const int64_t i = b0 + (int64_t)k * kStatT + t;
+      on[k] = i < e;
+      x[k] = i < e ? xs[i] : 0u;
+      if (First) y[k] = i < e ? ys[i] : 0ull;
+    }
+    if (!Whole && !all) {
+#pragma unroll
+      for (int k = 0; k < kStatIpt; ++k)
+        on[k] = on[k] && (uint32_t)hs[b0 + (int64_t)k * kStatT + t] == h;
+    }
+  };
+  load(b);
+  for (int q = t; q < kBins; q += kStatT) S.h[q] = 0;
   uint32_t pre[kRanks];
 #pragma unroll
-  for (int r = 0; r < kRanks; ++r) pre[r] = First ? 0u : spre[g * kRanks + r];
+  for (int r = 0; r < kRanks; ++r) pre[r] = First ? 0u : spre[r];
   const uint32_t own = own_hist(pre);
   __syncthreads();
-  uint64_t acc[kSums];
+  uint64_t acc[kSums], low = ~0ull;
   Ends ends;
 #pragma unroll
   for (int k = 0; k < kSums; ++k) acc[k] = 0;
+  auto count = [&]() {
 #pragma unroll
-  for (int k = 0; k < kStatIpt; ++k) {
-    const bool ok = b + (int64_t)k * kStatT + t < e;
-    if (First) {
-      lds_count(s_h, x[k] >> sh, ends.count(x[k], ok));
-      if (ok) {
-        const uint64_t xx = (uint64_t)x[k] * x[k];
-        const u128 yy = (u128)y[k] * y[k];
-        const uint64_t xy = (uint64_t)x[k] * y[k];
-        acc[0] += x[k];
-        acc[1] += y[k];
-        acc[2] += xx & 0xFFFFFFFFull;
-        acc[3] += xx >> 32;
-        acc[4] += (uint64_t)yy & 0xFFFFFFFFull;
-        acc[5] += (uint64_t)(yy >> 32);
-        acc[6] += xy & 0xFFFFFFFFull;
-        acc[7] += xy >> 32;
+    for (int k = 0; k < kStatIpt; ++k) {
+      if (First) {
+        lds_count(S.h, x[k] >> sh, ends.count(x[k], on[k]));
+        if (Whole && on[k]) {
+          const uint64_t xx = (uint64_t)x[k] * x[k];
+          const u128 yy = (u128)y[k] * y[k];
+          const uint64_t xy = (uint64_t)x[k] * y[k];
+          acc[0] += x[k];
+          acc[1] += y[k];
+          acc[2] += xx & 0xFFFFFFFFull;
+          acc[3] += xx >> 32;
+          acc[4] += (uint64_t)yy & 0xFFFFFFFFull;
+          acc[5] += (uint64_t)(yy >> 32);
+          acc[6] += xy & 0xFFFFFFFFull;
+          acc[7] += xy >> 32;
+        }
+        if (!Whole && on[k]) low = y[k] < low ? y[k] : low;
+      } else {
+        count_digit(S.h, pre, own, x[k], sh, ends.count(x[k], on[k]));
       }
-    } else {
-      count_digit(s_h, pre, own, x[k], sh, ends.count(x[k], ok));
     }
+  };
+  count();
+  // (a part with other GPUs' slots between may be longer than a chunk)
+  for (int64_t b0 = b + kChunk; !Whole && b0 < e; b0 += kChunk) {
+    load(b0);
+    count();
   }
-  if (First) ends.add_top(s_h);
-  else ends.add_low(s_h, pre, own, sh);
-  if (First) block_sums(acc, s_w, part + (int64_t)blockIdx.x * kSums);
+  if (First) ends.add_top(S.h);
+  else ends.add_low(S.h, pre, own, sh);
+  if (First && Whole) block_sums(acc, S.w, part);
+  if (First && !Whole) {
+    low = lane63(wave_incl(low, OpMin(), (uint64_t)~0ull));
+    if (lane_id() == 0) atomicMin(ymin, (unsigned long long)low);
+  }
   __syncthreads();
-  uint32_t* gh = ghist + (int64_t)g * kHistW;
   for (int q = t; q < kBins; q += kStatT)
-    if (s_h[q]) atomicAdd(&gh[q], s_h[q]);
+    if (S.h[q]) atomicAdd(&gh[q], S.h[q]);
+}
+
+template <bool First>
+__global__ __launch_bounds__(kStatT, 8) void k_stats_pass(
+    const uint32_t* off, const uint32_t* coff, int G, const uint32_t* xs,
+    const uint64_t* ys, const uint8_t* hs, int NG, Cells C, CellLists Q,
+    uint32_t nchunk, const uint32_t* spre, int sh, uint32_t* ghist,
+    uint64_t* part) {
+  __shared__ PassShared S;
+  if (blockIdx.x < nchunk) {
+    int64_t b, e;
+    int g;
+    if (!chunk_of(coff, off, G, blockIdx.x, b, e, g)) return;
+    stats_pass<First, true>(b, e, true, 0u, xs, ys, hs,
+                            spre + (int64_t)g * kRanks, sh,
+                            ghist + (int64_t)g * kHistW,
+                            part + (int64_t)blockIdx.x * kSums, nullptr, S);
+    return;
+  }
+  const uint32_t parts = (uint32_t)*Q.n_long;
+  for (uint32_t q = blockIdx.x - nchunk; q < parts; q += gridDim.x - nchunk) {
+    const Part X(C, Q, NG, q);
+    stats_pass<First, false>(X.lo, X.hi, X.all, X.h, xs, ys, hs,
+                             spre + (int64_t)(G + X.i) * kRanks, sh,
+                             ghist + (int64_t)(G + X.i) * kHistW, nullptr,
+                             &Q.lng[X.i].ymin, S);
+    __syncthreads();                        // (S is used again)
+  }
 }
 
 // The bin of a histogram of kPer * 64 counts in which rank `rank` falls and
@@ -540,13 +722,15 @@ __device__ inline void wave_find(const uint32_t* hist, int64_t rank,
 
 // the digit of every rank of a group from its histogram; the prefix and
 // the rank within the remaining candidates move on, and the histograms are
-// cleared for the next pass
+// cleared for the next pass (the blocks after the groups': CDF groups in
+// parts)
 template <bool First>
 __global__ __launch_bounds__(kRanks * kWave) void k_stats_select(
-    const uint32_t* cnt, int sh, uint32_t* ghist, uint32_t* spre,
-    int64_t* srank) {
+    const uint32_t* cnt, int G, const unsigned long long* n_long, int sh,
+    uint32_t* ghist, uint32_t* spre, int64_t* srank) {
   const int g = blockIdx.x, w = threadIdx.x / kWave, lane = lane_id();
-  if (cnt[g] == 0) return;
+  if (g < G ? cnt[g] == 0 : (uint32_t)(g - G) >= (uint32_t)(*n_long >> 32))
+    return;
   uint32_t* gh = ghist + (int64_t)g * kHistW;
   uint32_t bin, pre[kRanks];
   int64_t under;
@@ -575,16 +759,50 @@ struct StatOut {
   double f_gemm[128];
 };
 
+// instances of part X that tie with the ratios of the wanted ranks
+__device__ inline void part_ties(const Part& X, const uint32_t* pre,
+                                 const uint32_t* xs, const uint8_t* hs,
+                                 uint32_t* ties) {
+  __shared__ uint32_t s_n[kTies];
+  if (threadIdx.x < kTies) s_n[threadIdx.x] = 0;
+  __syncthreads();
+  uint32_t tx[kTies], n[kTies] = {0, 0, 0};
+#pragma unroll
+  for (int k = 0; k < kTies; ++k)
+    tx[k] = pre[(int64_t)X.i * kRanks + tie_rank(k)];
+#pragma unroll 8
+  for (int64_t i = X.lo + threadIdx.x; i < X.hi; i += kBlock) {
+    const bool ok = X.all || (uint32_t)hs[i] == X.h;
+    const uint32_t x = xs[i];
+#pragma unroll
+    for (int k = 0; k < kTies; ++k) n[k] += ok && x == tx[k] ? 1u : 0u;
+  }
+#pragma unroll
+  for (int k = 0; k < kTies; ++k) {
+    const uint32_t sum = lane63(wave_incl(n[k], OpAdd(), 0u));
+    if (lane_id() == 0 && sum) atomicAdd(&s_n[k], sum);
+  }
+  __syncthreads();
+  if (threadIdx.x < kTies) ties[threadIdx.x] = s_n[threadIdx.x];
+  __syncthreads();                          // (s_n is used again)
+}
+
 // the exact sums of a group from its chunks and the derived values, in the
-// same IEEE operations as their definition; also the group's CDF groups,
-// from the blocks of the row passes
+// same IEEE operations as their definition; the blocks after them count the
+// wanted ties of the parts of CDF groups
 __global__ __launch_bounds__(kBlock) void k_stats_final(
     const uint32_t* cnt, const uint32_t* coff, int G, int O, int nc,
     const uint64_t* part, const uint64_t* csum, const uint32_t* spre,
-    const uint32_t* hist, const uint32_t* tab, int64_t nb,
-    const uint16_t* bgpu, int NG, Cells C, StatOut S) {
+    int NG, Cells C, CellLists Q, const uint32_t* xs, const uint8_t* hs,
+    StatOut S) {
+  if ((int)blockIdx.x >= G) {
+    const uint32_t parts = (uint32_t)*Q.n_long;
+    for (uint32_t q = blockIdx.x - G; q < parts; q += gridDim.x - G)
+      part_ties(Part(C, Q, NG, q), spre + (int64_t)G * kRanks, xs, hs,
+                Q.ties + (int64_t)q * kTies);
+    return;
+  }
   __shared__ uint64_t s_cs[3];
-  __shared__ uint32_t s_n[256], s_b[256], s_e[256];
   __shared__ uint64_t s_w[kBlock / kWave][kSums];
   __shared__ uint64_t s_tot[kSums];
   const int g = blockIdx.x, t = threadIdx.x;
@@ -612,28 +830,7 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(
     const uint64_t sum = lane63(wave_incl(v, OpAdd(), (uint64_t)0));
     if (lane_id() == 0) s_cs[wv] = sum;
   }
-  // CDF groups: the blocks of rows on one GPU (the others have added theirs
-  // instance by instance), in row order
-  for (int h = t; h < NG; h += kBlock) {
-    s_n[h] = C.cnt[(int64_t)g * NG + h];
-    s_b[h] = C.beg[(int64_t)g * NG + h];
-    s_e[h] = C.end[(int64_t)g * NG + h];
-  }
   __syncthreads();
-  for (int64_t b = t; b < nb; b += kBlock) {
-    const uint32_t h = bgpu[b], n = hist[(int64_t)g * nb + b];
-    if (n == 0 || h >= (uint32_t)NG) continue;
-    const uint32_t at = tab[(int64_t)g * nb + b];
-    atomicAdd(&s_n[h], n);
-    atomicMin(&s_b[h], at);
-    atomicMax(&s_e[h], at + n);
-  }
-  __syncthreads();
-  for (int h = t; h < NG; h += kBlock) {
-    C.cnt[(int64_t)g * NG + h] = s_n[h];
-    C.beg[(int64_t)g * NG + h] = s_b[h];
-    C.end[(int64_t)g * NG + h] = s_e[h];
-  }
   if (t != 0) return;
   for (int k = 0; k < kStats; ++k) o[(int64_t)k * G + g] = nan;
   S.cnt[g] = m;
@@ -690,46 +887,59 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(
 // chopper_aggregate writes them; where they do not, those of the other GPUs
 // are passed over.
 //
-// One block per CDF group: the six order statistics by the radix selection
-// of the pooled ones with its histograms in LDS, then, for the three whose
-// times are wanted, the slot of the tie the rank falls on (each wave counts
-// the ties of its part of the stretch in order).  A stretch is read about
-// six times, from cache: 27,000 instances in 224 groups take 0.098 ms, where a
-// stable radix sort of the 6.1M keys took 0.51; one group of every instance
-// would take about as long as that sort.
-__global__ __launch_bounds__(kStatT) void k_cdf_cells(
-    int NG, int64_t NGG, Cells C, const uint32_t* xs, const uint64_t* ys,
-    const uint8_t* hs, double* gout, int64_t* gcnt_out) {
-  constexpr int kWaves = kStatT / kWave;
-  constexpr int kTies = 3;                  // ranks 0, 2 and 3
-  __shared__ uint32_t s_h[kHistW];
-  __shared__ uint32_t s_pre[kRanks];
-  __shared__ int64_t s_rank[kRanks];
-  __shared__ uint32_t s_tie[kTies][kWaves];
-  __shared__ uint64_t s_min[kWaves];
-  __shared__ double s_y[kTies];
-  const int64_t c = blockIdx.x;
-  const int t = (int)threadIdx.x, lane = lane_id(), w = t / kWave;
-  const int64_t m = C.cnt[c];
-  if (m == 0) {
-    if (t < 9) gout[(int64_t)t * NGG + c] = __builtin_nan("");
-    if (t == 0) gcnt_out[c] = 0;
-    return;
-  }
-  const int64_t b = C.beg[c], e = C.end[c];
-  const uint32_t h = (uint32_t)(c % NG);
-  const bool all = e - b == m;              // no other GPU's slots between
-  // wave w takes the w-th part of the stretch, a lane four slots a round
-  // (aligned down), the next round's requested before this one is looked at
-  constexpr int64_t kRound = 4 * kWave;
-  const int64_t a = b & ~(int64_t)3;
-  const int64_t part = ceil_div(ceil_div(e - a, (int64_t)4), kWaves) * 4;
-  const int64_t w0 = a + w * part;
-  const int64_t w1 = w0 + part < e ? w0 + part : e;
+// The six order statistics come from the radix selection of the pooled ones
+// with its histograms in LDS; then, for the three whose times are wanted, the
+// slot of the tie the rank falls on (each wave counts the ties of its part of
+// the stretch in order).  One block does this for a group, reading the
+// stretch about six times, from cache.  It is bound by its own latency and
+// one CU's reads, so long groups go in parts beside the pooled passes, like a
+// (phase, operation) of their own, and only their ties are found here; short
+// ones, where a block's clears and barriers are most of it, are ranked by one
+// wave against each other.  The whole call, us, with one block for any group,
+// with the ways below, and with a stable radix sort of every instance before
+// either:  6.1M rows in 1 group 8175, 479, 661; in 28 517, 370, 743; in 672
+// 361, 362, 848; in 131,072 8936, 930, 1853; 2.46M rows in 8,192 of 300 919,
+// 493, 676.  Between the block and the parts: 46 groups of 64,000 241 and
+// 203, 224 of 27,000 340 and 366.
+constexpr int kWaves = kStatT / kWave;
+constexpr int kWaveIpt = kWaveCell / kWave;
+static_assert(kWaves * kWaveCell >= kHistW, "LDS for either use");
+
+struct CdfArgs {
+  int NG;
+  int64_t NGG;
+  Cells C;
+  CellLists Q;
+  const uint32_t* xs;
+  const uint64_t* ys;
+  const uint8_t* hs;
+  const uint32_t* lpre;       // ratios and ranks among their ties of the
+  const int64_t* lrank;       // groups in parts
+  double* gout;
+  int64_t* gcnt_out;
+};
+
+// Slots lo .. hi - 1 as a block walks them: wave w takes the w-th part, a
+// lane four slots a round (aligned down), the next round's requested before
+// this one is looked at.
+struct Stretch {
+  const uint32_t* xs;
+  const uint8_t* hs;
+  uint32_t h;
+  bool all;                   // no other GPU's slots between
+  int64_t lo, w0, w1;
   struct Four {
     uint32_t x[4], hw;
   };
-  auto load = [&](int64_t i, Four& F) {
+  __device__ Stretch(const CdfArgs& A, uint32_t c, int64_t l, int64_t hi)
+      : xs(A.xs), hs(A.hs), h(c % (uint32_t)A.NG),
+        all(A.C.end[c] - A.C.beg[c] == A.C.cnt[c]), lo(l) {
+    const int64_t a = lo & ~(int64_t)3;
+    const int64_t part = ceil_div(ceil_div(hi - a, (int64_t)4), kWaves) * 4;
+    w0 = a + (int64_t)(threadIdx.x / kWave) * part;
+    w1 = w0 + part < hi ? w0 + part : hi;
+  }
+  __device__ void load(int64_t i, Four& F) const {
     F.hw = 0;
     if (i + 4 <= w1) {
       const uint4 v = *reinterpret_cast<const uint4*>(xs + i);
@@ -745,123 +955,98 @@ __global__ __launch_bounds__(kStatT) void k_cdf_cells(
         if (!all && i + q < w1) F.hw |= (uint32_t)hs[i + q] << (8 * q);
       }
     }
-  };
+  }
   // f(first slot of the lane, x, mask of the slots that count)
-  auto visit = [&](auto f) {
+  template <typename F>
+  __device__ void visit(F f) const {
     if (w0 >= w1) return;                              // (uniform)
+    const int lane = lane_id();
     Four cur, next;
     load(w0 + 4 * lane, cur);
 #pragma unroll 1
-    for (int64_t c = w0; c < w1; c += kRound) {        // (uniform)
+    for (int64_t c = w0; c < w1; c += 4 * kWave) {     // (uniform)
       const int64_t i = c + 4 * lane;
-      load(i + kRound, next);
+      load(i + 4 * kWave, next);
       uint32_t ok = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-        ok |= i + q >= b && i + q < w1 &&
+        ok |= i + q >= lo && i + q < w1 &&
                       (all || ((cur.hw >> (8 * q)) & 255u) == h)
                   ? 1u << q : 0u;
       f(i, cur.x, ok);
       cur = next;
     }
-  };
-  if (t < kRanks) {
-    const int64_t want[kRanks] = {0, (m - 1) / 4, (m - 1) / 2, m / 2,
-                                  3 * (m - 1) / 4, m - 1};
-    s_pre[t] = 0;
-    s_rank[t] = want[t];
   }
-  uint64_t low = ~0ull;
-  Ends ends;
-  for (int pass = 0; pass < 3; ++pass) {
-    const int sh = pass == 0 ? 2 * kLowBits : pass == 1 ? kLowBits : 0;
-    for (int q = t; q < (pass == 0 ? kTopBins : kHistW); q += kStatT)
-      s_h[q] = 0;
-    __syncthreads();
-    uint32_t pre[kRanks];
+  // the first pass: histogram of the top digit; returns the lane's smallest
+  // time
+  __device__ uint64_t count_top(const uint64_t* ys, uint32_t* hist,
+                                Ends& ends) const {
+    uint64_t low = ~0ull;
+    visit([&](int64_t i, const uint32_t (&v)[4], uint32_t ok) {
+      uint64_t y[4];
+      if (i + 4 <= w1) {
+        const ulonglong2 y0 = *reinterpret_cast<const ulonglong2*>(ys + i);
+        const ulonglong2 y1 = *reinterpret_cast<const ulonglong2*>(ys + i + 2);
+        y[0] = y0.x;
+        y[1] = y0.y;
+        y[2] = y1.x;
+        y[3] = y1.y;
+      } else {
 #pragma unroll
-    for (int r = 0; r < kRanks; ++r) pre[r] = s_pre[r];
-    const uint32_t own = own_hist(pre);
-    if (pass == 0) {
-      // (the smallest time on the way)
-      visit([&](int64_t i, const uint32_t (&v)[4], uint32_t ok) {
-        uint64_t y[4];
-        if (i + 4 <= w1) {
-          const ulonglong2 y0 = *reinterpret_cast<const ulonglong2*>(ys + i);
-          const ulonglong2 y1 =
-              *reinterpret_cast<const ulonglong2*>(ys + i + 2);
-          y[0] = y0.x;
-          y[1] = y0.y;
-          y[2] = y1.x;
-          y[3] = y1.y;
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) y[q] = i + q < w1 ? ys[i + q] : 0ull;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          lds_count(s_h, v[q] >> sh, ends.count(v[q], (ok >> q) & 1u));
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if ((ok >> q) & 1u) low = y[q] < low ? y[q] : low;
-      });
-      ends.add_top(s_h);
-    } else {
-      visit([&](int64_t, const uint32_t (&v)[4], uint32_t ok) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          count_digit(s_h, pre, own, v[q], sh,
-                      (ok >> q) & 1u && v[q] != 0u && v[q] != kFull);
-      });
-      ends.add_low(s_h, pre, own, sh);
-    }
-    __syncthreads();
-    if (w < kRanks) {
-      uint32_t bin;
-      int64_t under;
-      const int64_t rank = s_rank[w];
-      if (pass == 0) wave_find<kTopBins / kWave>(s_h, rank, &bin, &under);
-      else
-        wave_find<kLowBins / kWave>(s_h + hist_of(pre, w) * kLowBins, rank,
-                                    &bin, &under);
-      if (lane == 0) {
-        s_pre[w] |= bin << sh;
-        s_rank[w] = rank - under;
+        for (int q = 0; q < 4; ++q) y[q] = i + q < w1 ? ys[i + q] : 0ull;
       }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        lds_count(hist, v[q] >> (2 * kLowBits),
+                  ends.count(v[q], (ok >> q) & 1u));
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if ((ok >> q) & 1u) low = y[q] < low ? y[q] : low;
+    });
+    ends.add_top(hist);
+    return low;
+  }
+  // a later one, `ends` counted by the first
+  __device__ void count_low(const uint32_t (&pre)[kRanks], int sh,
+                            uint32_t* hist, const Ends& ends) const {
+    const uint32_t own = own_hist(pre);
+    visit([&](int64_t, const uint32_t (&v)[4], uint32_t ok) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        count_digit(hist, pre, own, v[q], sh,
+                    (ok >> q) & 1u && v[q] != 0u && v[q] != kFull);
+    });
+    ends.add_low(hist, pre, own, sh);
+  }
+  __device__ void count_ties(const uint32_t (&tx)[kTies],
+                             uint32_t (&n)[kTies]) const {
+#pragma unroll
+    for (int k = 0; k < kTies; ++k) n[k] = 0;
+    visit([&](int64_t, const uint32_t (&v)[4], uint32_t ok) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int k = 0; k < kTies; ++k)
+          n[k] += (ok >> q) & 1u && v[q] == tx[k] ? 1u : 0u;
+    });
+#pragma unroll
+    for (int k = 0; k < kTies; ++k)
+      n[k] = lane63(wave_incl(n[k], OpAdd(), 0u));
+  }
+  // The times of the ties of rank tr[k] among the block's: s_tie has every
+  // wave's ties.
+  __device__ void find_ties(const uint64_t* ys, const uint32_t (&tx)[kTies],
+                            int64_t (&tr)[kTies],
+                            const uint32_t (*s_tie)[kWaves],
+                            double* s_y) const {
+    const int w = (int)(threadIdx.x / kWave);
+    bool here = false;
+#pragma unroll
+    for (int k = 0; k < kTies; ++k) {
+      for (int q = 0; q < w; ++q) tr[k] -= s_tie[k][q];
+      here = here || (tr[k] >= 0 && tr[k] < (int64_t)s_tie[k][w]);
     }
-    __syncthreads();
-  }
-  // the ties of every wave, then the wanted one of each
-  uint32_t tx[kTies], n[kTies] = {0, 0, 0};
-  int64_t tr[kTies];
-#pragma unroll
-  for (int k = 0; k < kTies; ++k) {
-    const int r = k == 0 ? 0 : k + 1;
-    tx[k] = s_pre[r];
-    tr[k] = s_rank[r];
-  }
-  visit([&](int64_t, const uint32_t (&v)[4], uint32_t ok) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int k = 0; k < kTies; ++k)
-        n[k] += (ok >> q) & 1u && v[q] == tx[k] ? 1u : 0u;
-  });
-#pragma unroll
-  for (int k = 0; k < kTies; ++k) {
-    const uint32_t sum = lane63(wave_incl(n[k], OpAdd(), 0u));
-    if (lane == 0) s_tie[k][w] = sum;
-  }
-  low = lane63(wave_incl(low, OpMin(), (uint64_t)~0ull));
-  if (lane == 0) s_min[w] = low;
-  __syncthreads();
-  bool here = false;
-#pragma unroll
-  for (int k = 0; k < kTies; ++k) {
-    for (int q = 0; q < w; ++q) tr[k] -= s_tie[k][q];
-    here = here || (tr[k] >= 0 && tr[k] < (int64_t)s_tie[k][w]);
-  }
-  if (here) {                               // (uniform)
+    if (!here) return;                                 // (uniform)
     // tr[k]: rank among the ties from here on (negative: passed)
     visit([&](int64_t i, const uint32_t (&v)[4], uint32_t ok) {
 #pragma unroll
@@ -883,24 +1068,264 @@ __global__ __launch_bounds__(kStatT) void k_cdf_cells(
       }
     });
   }
-  __syncthreads();
-  if (t != 0) return;
-  uint64_t ymin = ~0ull;
-  for (int q = 0; q < kWaves; ++q) ymin = s_min[q] < ymin ? s_min[q] : ymin;
-  auto xq = [&](int r) { return (double)s_pre[r]; };
+};
+
+// results of a CDF group from its six ratios, smallest time and the times of
+// ranks 0, 2 and 3, in the same IEEE operations as their definition
+__device__ inline void cdf_out(const CdfArgs& A, int64_t c, const uint32_t* x,
+                               uint64_t ymin, const double* y) {
+  const int64_t NGG = A.NGG;
+  double* gout = A.gout;
+  auto xq = [&](int r) { return (double)x[r]; };
   const double q = 1.0 / 1073741824.0, dy = (double)ymin;
-  gcnt_out[c] = m;
+  A.gcnt_out[c] = A.C.cnt[c];
   gout[0 * NGG + c] = xq(0) * q;
   gout[1 * NGG + c] = xq(1) * q;
   gout[2 * NGG + c] = (xq(2) + xq(3)) / 2.0 * q;
   gout[3 * NGG + c] = xq(4) * q;
   gout[4 * NGG + c] = xq(5) * q;
   gout[5 * NGG + c] = dy;
-  const double c0 = s_y[0] / dy;
-  const double c50 = (s_y[1] / dy + s_y[2] / dy) / 2.0;
+  const double c0 = y[0] / dy;
+  const double c50 = (y[1] / dy + y[2] / dy) / 2.0;
   gout[6 * NGG + c] = c0;
   gout[7 * NGG + c] = c50;
   gout[8 * NGG + c] = c50 / c0;
+}
+
+struct CellShared {
+  uint32_t pre[kRanks];
+  int64_t rank[kRanks];
+  uint32_t tie[kTies][kWaves];
+  uint64_t low[kWaves];
+  double y[kTies];
+  uint32_t part[kTies];
+};
+
+// one block, one CDF group
+__device__ inline void cdf_block(const CdfArgs& A, uint32_t c, uint32_t* s_h,
+                                 CellShared& S) {
+  const int t = (int)threadIdx.x, lane = lane_id(), w = t / kWave;
+  const int64_t m = A.C.cnt[c];
+  const Stretch X(A, c, A.C.beg[c], A.C.end[c]);
+  if (t < kRanks) {
+    S.pre[t] = 0;
+    S.rank[t] = rank_of(m, t);
+  }
+  uint64_t low = ~0ull;
+  Ends ends;
+  for (int pass = 0; pass < 3; ++pass) {
+    const int sh = pass == 0 ? 2 * kLowBits : pass == 1 ? kLowBits : 0;
+    for (int q = t; q < (pass == 0 ? kTopBins : kHistW); q += kStatT)
+      s_h[q] = 0;
+    __syncthreads();
+    uint32_t pre[kRanks];
+#pragma unroll
+    for (int r = 0; r < kRanks; ++r) pre[r] = S.pre[r];
+    // (the smallest time on the way)
+    if (pass == 0) low = X.count_top(A.ys, s_h, ends);
+    else X.count_low(pre, sh, s_h, ends);
+    __syncthreads();
+    if (w < kRanks) {
+      uint32_t bin;
+      int64_t under;
+      const int64_t rank = S.rank[w];
+      if (pass == 0) wave_find<kTopBins / kWave>(s_h, rank, &bin, &under);
+      else
+        wave_find<kLowBins / kWave>(s_h + hist_of(pre, w) * kLowBins, rank,
+                                    &bin, &under);
+      if (lane == 0) {
+        S.pre[w] |= bin << sh;
+        S.rank[w] = rank - under;
+      }
+    }
+    __syncthreads();
+  }
+  // the ties of every wave, then the wanted one of each
+  uint32_t tx[kTies], n[kTies];
+  int64_t tr[kTies];
+#pragma unroll
+  for (int k = 0; k < kTies; ++k) {
+    tx[k] = S.pre[tie_rank(k)];
+    tr[k] = S.rank[tie_rank(k)];
+  }
+  X.count_ties(tx, n);
+  low = lane63(wave_incl(low, OpMin(), (uint64_t)~0ull));
+  if (lane == 0) {
+#pragma unroll
+    for (int k = 0; k < kTies; ++k) S.tie[k][w] = n[k];
+    S.low[w] = low;
+  }
+  __syncthreads();
+  X.find_ties(A.ys, tx, tr, S.tie, S.y);
+  __syncthreads();
+  if (t == 0) {
+    uint64_t ymin = ~0ull;
+    for (int q = 0; q < kWaves; ++q) ymin = S.low[q] < ymin ? S.low[q] : ymin;
+    cdf_out(A, c, S.pre, ymin, S.y);
+  }
+  __syncthreads();                          // (S is used again)
+}
+
+// One wave, one CDF group of at most kWaveCell slots: an instance's place is
+// the number of instances below it, or equal and before it.
+__device__ inline void cdf_wave(const CdfArgs& A, uint32_t c, uint32_t* s_x,
+                                uint32_t* wx, double* wy) {
+  const int lane = lane_id();
+  const int64_t m = A.C.cnt[c], b = A.C.beg[c];
+  const int len = (int)((int64_t)A.C.end[c] - b);
+  const int rows = (len + kWave - 1) / kWave;
+  const uint32_t h = c % (uint32_t)A.NG;
+  const bool all = len == (int)m;
+  uint32_t x[kWaveIpt], place[kWaveIpt];
+  uint64_t low = ~0ull;
+#pragma unroll
+  for (int j = 0; j < kWaveIpt; ++j) {
+    const int i = j * kWave + lane;
+    const bool ok = i < len && (all || (uint32_t)A.hs[b + i] == h);
+    x[j] = ok ? A.xs[b + i] : kNone;        // (above every ratio)
+    if (ok) {
+      const uint64_t y = A.ys[b + i];
+      low = y < low ? y : low;
+    }
+    place[j] = 0;
+    s_x[i] = x[j];
+  }
+  wave_sync();
+  for (int r = 0; r < rows; ++r) {
+    // (the instances of the rows before are placed after their equals here)
+    uint32_t lim[kWaveIpt];
+#pragma unroll
+    for (int j = 0; j < kWaveIpt; ++j)
+      lim[j] = r < j && x[j] != kNone ? x[j] + 1u : x[j];
+    for (int q = 0; q < kWave / 4; ++q) {
+      const uint4 v = reinterpret_cast<const uint4*>(s_x + r * kWave)[q];
+#pragma unroll
+      for (int j = 0; j < kWaveIpt; ++j) {
+        if (j >= rows) continue;
+        place[j] += v.x < lim[j] ? 1u : 0u;
+        place[j] += v.y < lim[j] ? 1u : 0u;
+        place[j] += v.z < lim[j] ? 1u : 0u;
+        place[j] += v.w < lim[j] ? 1u : 0u;
+      }
+    }
+  }
+  // equal ones before it in its own row
+#pragma unroll
+  for (int j = 0; j < kWaveIpt; ++j) {
+    if (j >= rows) continue;
+    for (int q = 0; q < kWave; ++q)
+      place[j] += s_x[j * kWave + q] == x[j] && q < lane ? 1u : 0u;
+  }
+#pragma unroll
+  for (int j = 0; j < kWaveIpt; ++j) {
+    if (x[j] == kNone) continue;
+#pragma unroll
+    for (int r = 0; r < kRanks; ++r)
+      if (place[j] == (uint32_t)rank_of(m, r)) {
+        wx[r] = x[j];
+        if (r == 0 || r == 2 || r == 3)
+          wy[r == 0 ? 0 : r - 1] = (double)A.ys[b + j * kWave + lane];
+      }
+  }
+  low = lane63(wave_incl(low, OpMin(), (uint64_t)~0ull));
+  wave_sync();
+  if (lane == 0) cdf_out(A, c, wx, low, wy);
+  wave_sync();                              // (the LDS is used again)
+}
+
+// one block, one CDF group in parts, whose ties are counted: wave k finds the
+// part with the wanted tie k and its rank there, then the block the tie
+__device__ inline void cdf_long(const CdfArgs& A, uint32_t i, CellShared& S) {
+  const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
+  const LongCell L = A.Q.lng[i];
+  const uint32_t* pre = A.lpre + (int64_t)i * kRanks;
+  if (w < kTies) {
+    const uint32_t* ties = A.Q.ties + (int64_t)L.part0 * kTies + w;
+    int64_t rank = A.lrank[(int64_t)i * kRanks + tie_rank(w)], at = -1;
+    for (int64_t p0 = 0; p0 < L.parts && at < 0; p0 += kWave) {
+      const int64_t p = p0 + lane;
+      const uint32_t v = p < L.parts ? ties[p * kTies] : 0u;
+      const uint32_t incl = wave_incl(v, OpAdd(), 0u);
+      const uint64_t past = __ballot((int64_t)incl > rank);
+      if (past) {
+        const int ln = __ffsll((long long)past) - 1;
+        at = p0 + ln;
+        rank -= readlane64((int64_t)(incl - v), ln);
+      } else {
+        rank -= lane63(incl);
+      }
+    }
+    if (lane == 0) {
+      S.part[w] = (uint32_t)(at < 0 ? 0 : at);
+      S.rank[w] = rank;
+    }
+  }
+  __syncthreads();
+  uint32_t tx[kTies], n[kTies];
+#pragma unroll
+  for (int k = 0; k < kTies; ++k) tx[k] = pre[tie_rank(k)];
+  for (int k = 0; k < kTies; ++k) {
+    const Part P(A.C, A.Q, A.NG, L.part0 + S.part[k]);
+    const Stretch X(A, L.c, P.lo, P.hi);
+    // (the other two are beyond any part)
+    int64_t tr[kTies];
+#pragma unroll
+    for (int j = 0; j < kTies; ++j)
+      tr[j] = j == k ? S.rank[k] : (int64_t)1 << 62;
+    X.count_ties(tx, n);
+    if (lane == 0)
+#pragma unroll
+      for (int j = 0; j < kTies; ++j) S.tie[j][w] = n[j];
+    __syncthreads();
+    X.find_ties(A.ys, tx, tr, S.tie, S.y);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) cdf_out(A, L.c, pre, L.ymin, S.y);
+  __syncthreads();                          // (S is used again)
+}
+
+// The first `long_blocks` blocks take the groups in parts, the next
+// `cell_blocks` those of a block, the others those of a wave.
+__global__ __launch_bounds__(kStatT) void k_cdf_cells(CdfArgs A,
+                                                      uint32_t long_blocks,
+                                                      uint32_t cell_blocks) {
+  __shared__ __attribute__((aligned(16))) uint32_t s_h[kWaves * kWaveCell];
+  __shared__ CellShared S;
+  __shared__ uint32_t s_list[kStatT], s_n;
+  __shared__ uint32_t s_wx[kWaves][kRanks];
+  __shared__ double s_wy[kWaves][kTies];
+  uint32_t b = blockIdx.x;
+  if (b < long_blocks) {
+    const uint32_t n = (uint32_t)(*A.Q.n_long >> 32);
+    for (uint32_t i = b; i < n; i += long_blocks) cdf_long(A, i, S);
+    return;
+  }
+  b -= long_blocks;
+  // a block's groups: every `step`-th, those of its way listed first
+  const bool by_block = b < cell_blocks;
+  uint32_t step = cell_blocks;
+  if (!by_block) {
+    b -= cell_blocks;
+    step = gridDim.x - long_blocks - cell_blocks;
+  }
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  const int64_t c = b + (int64_t)threadIdx.x * step;
+  if (c < A.NGG) {
+    const int64_t m = A.C.cnt[c];
+    const int64_t len = (int64_t)A.C.end[c] - (int64_t)A.C.beg[c];
+    if (m > 0 && m <= kLongCell && (len > kWaveCell) == by_block)
+      s_list[atomicAdd(&s_n, 1u)] = (uint32_t)c;
+  }
+  __syncthreads();
+  const int n = (int)s_n;
+  if (by_block) {
+    for (int i = 0; i < n; ++i) cdf_block(A, s_list[i], s_h, S);
+    return;
+  }
+  const int w = (int)(threadIdx.x / kWave);
+  for (int i = w; i < n; i += kWaves)
+    cdf_wave(A, s_list[i], s_h + w * kWaveCell, s_wx[w], s_wy[w]);
 }
 
 // eq. 9 per (phase, operation), one wave each: the median over its GPUs with
@@ -976,6 +1401,9 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
   const int64_t nh = (int64_t)G * kHistW;
   const int64_t NGG = (int64_t)G * NG;      // CDF groups
   const int64_t nb = ceil_div(cap > 0 ? cap : 1, (int64_t)kRowSpan);
+  // CDF groups in parts, and their parts, at most
+  const int64_t max_long = cap / (kLongCell + 1);
+  const int64_t max_parts = max_long > 0 ? cap / kPart + max_long : 0;
   struct Bufs {
     uint16_t* key;
     uint8_t* hs;
@@ -984,6 +1412,7 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
     uint64_t *ys, *csum, *part;
     int64_t* srank;
     Cells cells;
+    CellLists lists;
     double* gout;
     int64_t* gcnt_out;
   } B;
@@ -998,9 +1427,9 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
     B.ys = sc.take<uint64_t>(cap);
     B.csum = sc.take<uint64_t>(3 * (int64_t)G * kCopies);
     B.part = sc.take<uint64_t>(nchunk * kSums);
-    B.ghist = sc.take<uint32_t>(nh);
-    B.spre = sc.take<uint32_t>((int64_t)G * kRanks);
-    B.srank = sc.take<int64_t>((int64_t)G * kRanks);
+    B.ghist = sc.take<uint32_t>(nh + max_long * kHistW);
+    B.spre = sc.take<uint32_t>((G + max_long) * kRanks);
+    B.srank = sc.take<int64_t>((G + max_long) * kRanks);
     B.hist = sc.take<uint32_t>(G * nb);
     B.tab = sc.take<uint32_t>(G * nb);
     B.scan = sc.take<uint32_t>(scan_scratch_elems(G * nb));
@@ -1008,6 +1437,10 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
     B.cells.cnt = sc.take<uint32_t>(NGG);
     B.cells.beg = sc.take<uint32_t>(NGG);
     B.cells.end = sc.take<uint32_t>(NGG);
+    B.lists.n_long = sc.take<unsigned long long>(1);
+    B.lists.lng = sc.take<LongCell>(max_long);
+    B.lists.of_part = sc.take<uint32_t>(max_parts);
+    B.lists.ties = sc.take<uint32_t>(max_parts * kTies);
     // (per-GPU results in scratch when the caller passes no arrays)
     B.gout = gpu_out ? gpu_out : sc.take<double>(9 * NGG);
     B.gcnt_out = gpu_cnt ? gpu_cnt : sc.take<int64_t>(NGG);
@@ -1029,47 +1462,67 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
   int64_t nclear = nh > NGG ? nh : NGG;
   if (nclear > (int64_t)4096 * kBlock) nclear = (int64_t)4096 * kBlock;
   CHOPPER_HIP(launch("stats_clear", k_stats_clear, grid_for(nclear, kBlock),
-                     dim3(kBlock), s, G, B.ghist, nh, B.csum, B.cells, NGG));
+                     dim3(kBlock), s, G, B.ghist, nh, B.csum, B.cells, NGG,
+                     B.lists));
   const dim3 rb((unsigned)nb);
   CHOPPER_HIP(launch_shm("stats_keys", k_stats_keys, rb, dim3(kRowT),
                          (size_t)G * 28, s, A, B.key, B.hist, B.csum));
   CHOPPER_HIP(exclusive_scan<uint32_t>(B.hist, B.tab, G * nb, B.scan, B.tot,
                                        s));
-  CHOPPER_HIP(launch("stats_offsets", k_stats_offsets, dim3(1), dim3(kStatT),
-                     s, (const uint32_t*)B.tab, nb, (const uint32_t*)B.tot, G,
-                     B.gcnt, B.off, B.coff, B.spre, B.srank));
   const size_t lds = (size_t)G * 4 + (size_t)G * 2 * (kRowT / kWave);
   CHOPPER_HIP(launch_shm("stats_scatter", k_stats_scatter, rb, dim3(kRowT),
                          lds, s, A, rows->gpu, NG, (const uint16_t*)B.key,
                          (const uint32_t*)B.tab, B.xs, B.ys, B.hs, B.bgpu,
                          B.cells, status));
+  CHOPPER_HIP(launch("stats_cells", k_stats_cells, dim3((unsigned)G + 1),
+                     dim3(kBlock), s, B.gcnt, B.off, B.coff,
+                     (const uint32_t*)B.tot, G,
+                     (const uint32_t*)B.hist, (const uint32_t*)B.tab, nb,
+                     (const uint16_t*)B.bgpu, NG, B.cells, B.lists, B.ghist,
+                     B.spre, B.srank, B.gout, B.gcnt_out));
+  auto at_most = [](int64_t n, int64_t most) {
+    return (unsigned)(n < most ? n : most);
+  };
+  // (blocks for parts that there are not cost their launch: 1,100 of them
+  // 5 us a pass)
+  const unsigned parts = at_most(max_parts, kPartBlocks);
   for (int pass = 0; pass < 3; ++pass) {
     const int sh = pass == 0 ? 2 * kLowBits : pass == 1 ? kLowBits : 0;
     CHOPPER_HIP(launch("stats_pass",
                        pass == 0 ? k_stats_pass<true> : k_stats_pass<false>,
-                       dim3((unsigned)nchunk), dim3(kStatT), s,
+                       dim3(parts + (unsigned)nchunk), dim3(kStatT), s,
                        (const uint32_t*)B.off, (const uint32_t*)B.coff, G,
                        (const uint32_t*)B.xs, (const uint64_t*)B.ys,
+                       (const uint8_t*)B.hs, NG, B.cells, B.lists,
+                       (uint32_t)nchunk,
                        (const uint32_t*)B.spre, sh, B.ghist, B.part));
     CHOPPER_HIP(launch("stats_select",
                        pass == 0 ? k_stats_select<true>
                                  : k_stats_select<false>,
-                       dim3((unsigned)G), dim3(kRanks * kWave), s,
-                       (const uint32_t*)B.gcnt, sh, B.ghist, B.spre,
-                       B.srank));
+                       dim3((unsigned)(G + max_long)), dim3(kRanks * kWave),
+                       s, (const uint32_t*)B.gcnt, G,
+                       (const unsigned long long*)B.lists.n_long, sh, B.ghist,
+                       B.spre, B.srank));
   }
-  CHOPPER_HIP(launch("stats_final", k_stats_final, dim3((unsigned)G),
+  CHOPPER_HIP(launch("stats_final", k_stats_final, dim3((unsigned)G + parts),
                      dim3(kBlock), s, (const uint32_t*)B.gcnt,
                      (const uint32_t*)B.coff, G, O, n_counters,
                      (const uint64_t*)B.part, (const uint64_t*)B.csum,
-                     (const uint32_t*)B.spre, (const uint32_t*)B.hist,
-                     (const uint32_t*)B.tab, nb, (const uint16_t*)B.bgpu, NG,
-                     B.cells, S));
+                     (const uint32_t*)B.spre, NG, B.cells, B.lists,
+                     (const uint32_t*)B.xs, (const uint8_t*)B.hs, S));
   // per-GPU overlap CDFs, and eq. 9 / eq. 10 from them
-  CHOPPER_HIP(launch("stats_cdf", k_cdf_cells, dim3((unsigned)NGG),
-                     dim3(kStatT), s, NG, NGG, B.cells,
-                     (const uint32_t*)B.xs, (const uint64_t*)B.ys,
-                     (const uint8_t*)B.hs, B.gout, B.gcnt_out));
+  const CdfArgs K{NG, NGG, B.cells, B.lists, B.xs, B.ys, B.hs,
+                  B.spre + (int64_t)G * kRanks, B.srank + (int64_t)G * kRanks,
+                  B.gout, B.gcnt_out};
+  const unsigned long_blocks = at_most(max_long, 256);
+  // (a thread lists a group: 1,024 blocks of either kind take the largest
+  // call's 2^19)
+  static_assert((int64_t)kMaxGroups * 256 <= 1024 * kStatT, "groups a block");
+  const unsigned cell_blocks = at_most(NGG, 1024);
+  const unsigned wave_blocks = at_most(ceil_div(NGG, (int64_t)kWaves), 1024);
+  CHOPPER_HIP(launch("stats_cdf", k_cdf_cells,
+                     dim3(long_blocks + cell_blocks + wave_blocks),
+                     dim3(kStatT), s, K, long_blocks, cell_blocks));
   CHOPPER_HIP(launch("stats_cdf", k_cdf_pool, dim3((unsigned)G), dim3(kWave),
                      s, G, NG, n_counters, (const int64_t*)B.gcnt_out,
                      (const double*)B.gout, NGG, out));
