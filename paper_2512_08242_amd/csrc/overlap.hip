@@ -1468,9 +1468,11 @@ extern "C" int chopper_overlap(const chopper_records* rec,
   const unsigned mb = nm > 0 ? grid_for(nm, kBlock * kMarkPerThread).x : 0u;
   const unsigned rb = (unsigned)ceil_div(n, (int64_t)kOvTile);
   // (2,000 records 23 to 13 us for the three, 245,760 37 to 17; from 2^20
-  // records one launch gains nothing, and at 20M the markers, held to the
-  // records' registers, take 0.09 ms more)
-  const bool together = n > 0 && n < kTogether;
+  // records one launch gains nothing, nor from 2^20 markers, which are held
+  // to the records' registers and LDS: 960,000 records, the whole call with
+  // one launch and with three, 125 and 125 us with 855,000 markers, 182 and
+  // 161 with 2.64M, 382 and 316 with 7.68M)
+  const bool together = n > 0 && n < kTogether && nm < kTogether;
   if (together)
     CHOPPER_HIP(launch_shm("ov_queries", k_overlap_queries,
                            dim3(mb + (unsigned)cg + rb), dim3(kBlock),
