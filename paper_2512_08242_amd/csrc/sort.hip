@@ -439,8 +439,11 @@ int class_sort(const Acc& acc, const ClassSortLayout& L, uint32_t* out,
     // The markers' partition may run beside the overlap call on another
     // stream, whose union runs decide when the step goes on: 12 KB of LDS
     // that it does not use keep it at five blocks a CU.  (At full occupancy
-    // it takes the union runs' slots: a step of 19.66M records 3193 us
-    // against 3147 with the LDS and 3144 with a ranking that needs it.)
+    // it takes the union runs' slots: a step of 19.66M records 3224 us
+    // against 3196 with the LDS.  Where there is nothing beside it, or fewer
+    // blocks than that, it makes no difference: steps of 2,000, 245,760 and
+    // 2.46M records 220, 299 and 633 us against 219, 299 and 637, 50M
+    // shuffled ones 86.4 ms against 86.5, within what two runs differ.)
     constexpr size_t kSpare = std::is_same<Cols, MarkerColumns>::value ? 12288 : 0;
     CHOPPER_HIP(launch_shm("sort_class_partition",
                            k_class_partition<Acc, Cols>, dim3((unsigned)T),
