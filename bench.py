@@ -31,10 +31,11 @@ HBM_PEAK_GBS = 8000.0
 # the kernel whose roofline is reported: the records reduction, which reads
 # every record's counters -- the fast path's (groups are runs of the
 # (gpu, kind, start') order) or, where that does not hold (e.g. shuffled
-# input with markers numbered out of order), that of groups of several runs
-# or the element-wise one
+# input with markers numbered out of order), that of groups of several runs,
+# the same by groups of four columns (records in no order; the last group's
+# launch of a step is the one timed), or the element-wise one
 ROOF_KERNELS = ("agg_fast_reduce_records", "agg_gen_reduce_records",
-                "agg_reduce_records")
+                "agg_gen_reduce_columns", "agg_reduce_records")
 
 
 def algorithmic_bytes(n, nm, rows, depth, nc, n_rows_finest):
@@ -55,8 +56,14 @@ def roof_kernel_bytes(kernel, n, depth, nc, rows_written, input_order):
     several runs read the gathered path and gpu/kind items, 4 per level + 2
     bytes, in place of gpu, cls and path); per row it produces (the two
     finest levels, the finest one on the element-wise path) its header (path,
-    gpu, kind, first record) and its sums and counters written once."""
-    if kernel == "agg_reduce_records" or (
+    gpu, kind, first record) and its sums and counters written once.  A launch
+    by groups of columns (of start, end, gap, ovl and the counters, four a
+    launch) reads the items, korder and its columns and writes their sums; the
+    last launch, with counters, has no headers."""
+    if kernel == "agg_gen_reduce_columns" and nc:
+        cols = (nc - 1) % 4 + 1
+        return n * (4 + 2 + 4 * depth + 8 * cols) + rows_written * 8 * cols
+    if kernel in ("agg_reduce_records", "agg_gen_reduce_columns") or (
             kernel == "agg_gen_reduce_records" and not input_order):
         per_rec = 4 + 2 + 4 * depth + 8 * 4 + 8 * nc
     else:

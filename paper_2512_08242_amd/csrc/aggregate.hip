@@ -3608,7 +3608,7 @@ static int agg_gen_tiles(const AggLayout& L, RecSrc S, const RowsDev& R,
           if (r != CHOPPER_OK) return r;
           GR.c0 = c0;
           GR.nc = cols - c0 < kRowCols ? cols - c0 : kRowCols;
-          CHOPPER_HIP(launch("agg_gen_reduce_records",
+          CHOPPER_HIP(launch("agg_gen_reduce_columns",
                              q.two ? k_agg_fast_reduce<kMD, FromRecords, true, false, true, false, true>
                                    : k_agg_fast_reduce<kMD, FromRecords, false, false, true, false, true>,
                              grid, dim3(kBlock), s, fr, N, li, D, M, tbl,

@@ -32,7 +32,8 @@ static const char* const kKernelNames[] = {
     "agg_nat_tiles", "agg_heads_nat", "agg_gpu_rows",
     "agg_exact_keys", "join_resort", "attr_windows", "agg_items",
     "agg_gen_fill", "agg_gen_elect", "agg_gen_count",
-    "agg_gen_reduce_records", "agg_gen_count_rows", "agg_gen_reduce_rows",
+    "agg_gen_reduce_records", "agg_gen_reduce_columns", "agg_gen_count_rows",
+    "agg_gen_reduce_rows",
     "agg_gen_apply", "agg_stage", "ov_queries",
     "view_units", "view_fill", "view_records",
     "view_iter_max", "view_medians", "launch_split", "join_fill",

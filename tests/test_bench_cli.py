@@ -43,3 +43,18 @@ def test_roof_kernel_bytes_per_path():
     gen = bench.roof_kernel_bytes("agg_reduce_records", n, depth, nc, rows,
                                   False)
     assert gen == n * (6 + 4 * depth + 32 + 8 * nc) + rows * per_row
+    # records in no order: a launch for every four of the 4 + nc columns, of
+    # which the last is timed; without counters it is the only one
+    for counters, cols in ((16, 4), (7, 3), (1, 1), (4, 4)):
+        last = bench.roof_kernel_bytes("agg_gen_reduce_columns", n, depth,
+                                       counters, rows, False)
+        assert last == n * (6 + 4 * depth + 8 * cols) + rows * 8 * cols
+    assert bench.roof_kernel_bytes(
+        "agg_gen_reduce_columns", n, depth, 0, rows, False) == \
+        bench.roof_kernel_bytes("agg_reduce_records", n, depth, 0, rows, False)
+
+
+def test_roof_kernels_are_launched():
+    import bench
+    import paper_2512_08242_amd as ch
+    assert set(bench.ROOF_KERNELS) <= set(ch.binding.kernel_names())
