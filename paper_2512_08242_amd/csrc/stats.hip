@@ -182,9 +182,14 @@ struct Cells {
 
 // A CDF group is selected by one wave, by one block or in parts by many
 // blocks, by the length of its stretch and the instances in it: one wave up
-// to kWaveCell slots, parts of about kPart instances above kLongCell
-// instances (both sides measured: see k_cdf_cells).
-constexpr int kWaveCell = 512;
+// to kFewCell slots, or up to kWaveCell where there are more than kManyCells
+// groups longer than kFewCell (a wave takes longer than a block, but a CU
+// holds sixteen of them and one block); parts of about kPart instances above
+// kLongCell instances (both sides measured: see k_cdf_cells).
+constexpr int kWaveCell = 1024;
+constexpr int kFewCell = 128;
+constexpr uint32_t kManyCells = 512;
+constexpr int kCountCopies = 16;
 constexpr int64_t kLongCell = 32768;
 constexpr int64_t kPart = kChunk;
 constexpr int64_t kPartBlocks = 256;        // for parts, in every pass
@@ -200,6 +205,7 @@ struct LongCell {
 struct CellLists {
   unsigned long long* n_long; // number << 32 | their parts
   LongCell* lng;
+  uint32_t* n_cells;          // [kCountCopies] longer than kFewCell, by block
   uint32_t* of_part;          // a part's group in parts
   uint32_t* ties;             // [3] a part
 };
@@ -237,6 +243,7 @@ __global__ void k_stats_clear(int G, uint32_t* hist, int64_t nh,
   const int64_t step = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i0 == 0) *Q.n_long = 0;
+  if (i0 < kCountCopies) Q.n_cells[i0] = 0;
   for (int64_t i = i0; i < nh; i += step) hist[i] = 0;
   for (int64_t i = i0; i < 3 * (int64_t)G * kCopies; i += step) csum[i] = 0;
   for (int64_t i = i0; i < NGG; i += step) {
@@ -374,8 +381,8 @@ __device__ inline void stats_offsets(
 // the wave's running counts are in LDS); the block's table entry and the
 // waves before give the slot.  A block whose rows are all on one GPU --
 // every block but the few where one GPU's rows end -- notes the GPU, and the
-// CDF groups get its instances from the table; another block adds them one
-// by one.
+// CDF groups get its instances from the table; another block adds them, one
+// lane for the others of a row and CDF group.
 __global__ __launch_bounds__(kRowT) void k_stats_scatter(
     StatArgs A, const uint8_t* gpu, int NG, const uint16_t* key,
     const uint32_t* tab, uint32_t* xs, uint64_t* ys, uint8_t* hs,
@@ -479,13 +486,13 @@ __global__ __launch_bounds__(kBlock) void k_stats_cells(
     return;
   }
   __shared__ uint32_t s_n[256], s_b[256], s_e[256];
-  __shared__ uint32_t s_nl, s_long[256];
+  __shared__ uint32_t s_nl, s_nc, s_long[256];
   static_assert(kBlock >= 256, "a thread a GPU");
   const int g = (int)blockIdx.x - 1, t = threadIdx.x;
   const int64_t c = (int64_t)g * NG + t, NGG = (int64_t)G * NG;
   const bool any = (g + 1 < G ? tab[(int64_t)(g + 1) * nb] : *total) !=
                    tab[(int64_t)g * nb];    // (uniform)
-  if (t == 0) s_nl = 0;
+  if (t == 0) s_nl = s_nc = 0;
   if (t < NG) {
     s_n[t] = any ? C.cnt[c] : 0u;
     s_b[t] = any ? C.beg[c] : 0u;
@@ -520,9 +527,12 @@ __global__ __launch_bounds__(kBlock) void k_stats_cells(
         srank[(int64_t)(G + i) * kRanks + r] = rank_of(m, r);
       }
       s_long[atomicAdd(&s_nl, 1u)] = i;
+    } else if (s_e[t] - s_b[t] > (uint32_t)kFewCell) {
+      atomicAdd(&s_nc, 1u);
     }
   }
   __syncthreads();
+  if (t == 0 && s_nc) atomicAdd(&Q.n_cells[blockIdx.x % kCountCopies], s_nc);
   for (uint32_t k = 0; k < s_nl; ++k) {
     const uint32_t i = s_long[k];
     const LongCell L = Q.lng[i];
@@ -663,6 +673,8 @@ __device__ inline void stats_pass(int64_t b, int64_t e, bool all, uint32_t h,
     if (S.h[q]) atomicAdd(&gh[q], S.h[q]);
 }
 
+// (eight waves a SIMD, two blocks a CU: the scalar registers of both ways
+// would leave one)
 template <bool First>
 __global__ __launch_bounds__(kStatT, 8) void k_stats_pass(
     const uint32_t* off, const uint32_t* coff, int G, const uint32_t* xs,
@@ -894,16 +906,16 @@ __global__ __launch_bounds__(kBlock) void k_stats_final(
 // stretch about six times, from cache.  It is bound by its own latency and
 // one CU's reads, so long groups go in parts beside the pooled passes, like a
 // (phase, operation) of their own, and only their ties are found here; short
-// ones, where a block's clears and barriers are most of it, are ranked by one
-// wave against each other.  The whole call, us, with one block for any group,
-// with the ways below, and with a stable radix sort of every instance before
-// either:  6.1M rows in 1 group 8175, 479, 661; in 28 517, 370, 743; in 672
-// 361, 362, 848; in 131,072 8936, 930, 1853; 2.46M rows in 8,192 of 300 919,
-// 493, 676.  Between the block and the parts: 46 groups of 64,000 241 and
-// 203, 224 of 27,000 340 and 366.
+// ones, where a block's clears and barriers are most of it, go to a wave.
+// The whole call, us, with one block for any group, with the ways below, and
+// with a stable radix sort of every instance before either:  6.1M rows in 1
+// group 8175, 480, 661; in 28 517, 364, 743; in 672 361, 359, 848; in 16,384
+// 1745, 764, 1290; in 131,072 8936, 1005, 1853; 2.46M rows in 8,192 of 300
+// 919, 460, 676; in 4,096 of 700 675, 483, 716.  Between the block and the
+// parts: 46 groups of 64,000 241 and 203, 224 of 27,000 340 and 366.  Between
+// the wave and the block: 128 groups of 450 109 and 100, 512 124 and 133, 1,024
+// 137 and 183; of 900 134 and 104, 151 and 141, 167 and 193; of 100 84 and 88.
 constexpr int kWaves = kStatT / kWave;
-constexpr int kWaveIpt = kWaveCell / kWave;
-static_assert(kWaves * kWaveCell >= kHistW, "LDS for either use");
 
 struct CdfArgs {
   int NG;
@@ -1166,71 +1178,82 @@ __device__ inline void cdf_block(const CdfArgs& A, uint32_t c, uint32_t* s_h,
   __syncthreads();                          // (S is used again)
 }
 
-// One wave, one CDF group of at most kWaveCell slots: an instance's place is
-// the number of instances below it, or equal and before it.
-__device__ inline void cdf_wave(const CdfArgs& A, uint32_t c, uint32_t* s_x,
-                                uint32_t* wx, double* wy) {
+// One wave, one CDF group of at most R * 64 slots, held in registers.  The
+// least and the largest ratio come from the lanes' own; the others bit by
+// bit, a ratio of rank k being the largest t with at most k instances below
+// it, which ballots count.  (Ranking every instance against every other one
+// took a call on 128 groups of 500 172 us, this 107.)
+template <int R>
+__device__ inline void cdf_wave(const CdfArgs& A, uint32_t c) {
   const int lane = lane_id();
-  const int64_t m = A.C.cnt[c], b = A.C.beg[c];
-  const int len = (int)((int64_t)A.C.end[c] - b);
-  const int rows = (len + kWave - 1) / kWave;
+  auto uni = [](uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)v);
+  };
+  const uint32_t m = uni(A.C.cnt[c]), b = uni(A.C.beg[c]);
+  const uint32_t len = uni(A.C.end[c]) - b;
   const uint32_t h = c % (uint32_t)A.NG;
-  const bool all = len == (int)m;
-  uint32_t x[kWaveIpt], place[kWaveIpt];
+  const bool all = len == m;
+  uint32_t x[R], lo = kNone, hi = 0;
   uint64_t low = ~0ull;
 #pragma unroll
-  for (int j = 0; j < kWaveIpt; ++j) {
-    const int i = j * kWave + lane;
-    const bool ok = i < len && (all || (uint32_t)A.hs[b + i] == h);
-    x[j] = ok ? A.xs[b + i] : kNone;        // (above every ratio)
-    if (ok) {
-      const uint64_t y = A.ys[b + i];
-      low = y < low ? y : low;
-    }
-    place[j] = 0;
-    s_x[i] = x[j];
-  }
-  wave_sync();
-  for (int r = 0; r < rows; ++r) {
-    // (the instances of the rows before are placed after their equals here)
-    uint32_t lim[kWaveIpt];
-#pragma unroll
-    for (int j = 0; j < kWaveIpt; ++j)
-      lim[j] = r < j && x[j] != kNone ? x[j] + 1u : x[j];
-    for (int q = 0; q < kWave / 4; ++q) {
-      const uint4 v = reinterpret_cast<const uint4*>(s_x + r * kWave)[q];
-#pragma unroll
-      for (int j = 0; j < kWaveIpt; ++j) {
-        if (j >= rows) continue;
-        place[j] += v.x < lim[j] ? 1u : 0u;
-        place[j] += v.y < lim[j] ? 1u : 0u;
-        place[j] += v.z < lim[j] ? 1u : 0u;
-        place[j] += v.w < lim[j] ? 1u : 0u;
-      }
-    }
-  }
-  // equal ones before it in its own row
-#pragma unroll
-  for (int j = 0; j < kWaveIpt; ++j) {
-    if (j >= rows) continue;
-    for (int q = 0; q < kWave; ++q)
-      place[j] += s_x[j * kWave + q] == x[j] && q < lane ? 1u : 0u;
-  }
-#pragma unroll
-  for (int j = 0; j < kWaveIpt; ++j) {
-    if (x[j] == kNone) continue;
-#pragma unroll
-    for (int r = 0; r < kRanks; ++r)
-      if (place[j] == (uint32_t)rank_of(m, r)) {
-        wx[r] = x[j];
-        if (r == 0 || r == 2 || r == 3)
-          wy[r == 0 ? 0 : r - 1] = (double)A.ys[b + j * kWave + lane];
-      }
+  for (int j = 0; j < R; ++j) {
+    const uint32_t i = (uint32_t)(j * kWave + lane);
+    const bool ok = i < len && (all || (uint32_t)A.hs[(int64_t)b + i] == h);
+    x[j] = ok ? A.xs[(int64_t)b + i] : kNone;          // (above every ratio)
+    const uint64_t y = ok ? A.ys[(int64_t)b + i] : ~0ull;
+    low = y < low ? y : low;
+    lo = x[j] < lo ? x[j] : lo;
+    hi = ok && x[j] > hi ? x[j] : hi;
   }
   low = lane63(wave_incl(low, OpMin(), (uint64_t)~0ull));
-  wave_sync();
-  if (lane == 0) cdf_out(A, c, wx, low, wy);
-  wave_sync();                              // (the LDS is used again)
+  lo = lane63(wave_incl(lo, OpMin(), kNone));
+  hi = lane63(wave_incl(hi, OpMax(), 0u));
+  auto below = [&](uint32_t v) {
+    uint32_t n = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) n += (uint32_t)__popcll(__ballot(x[j] < v));
+    return n;
+  };
+  uint32_t val[kRanks];
+  const int top = 31 - __clz((int)(lo ^ hi));          // (-1: all the same)
+#pragma unroll
+  for (int r = 0; r < kRanks; ++r)
+    val[r] = top < 0 ? lo : lo & ~(uint32_t)((2ull << top) - 1u);
+  for (int bit = top; bit >= 0; --bit) {
+    uint32_t t = kNone, n = 0;
+#pragma unroll
+    for (int r = 1; r < kRanks - 1; ++r) {
+      // (ranks are ascending: equal ones so far are neighbours)
+      const uint32_t v = val[r] | 1u << bit;
+      if (v != t) n = below(v);
+      t = v;
+      if (n <= (uint32_t)rank_of(m, r)) val[r] = v;
+    }
+  }
+  val[0] = lo;
+  val[kRanks - 1] = hi;
+  double y[kTies];
+#pragma unroll
+  for (int k = 0; k < kTies; ++k) {
+    const uint32_t v = val[tie_rank(k)];
+    uint32_t r = (uint32_t)rank_of(m, tie_rank(k)) - below(v);
+    uint64_t at = 0;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const uint64_t tie = __ballot(x[j] == v);
+      const uint32_t n = (uint32_t)__popcll(tie);
+      const bool here = x[j] == v && lanes_below(tie) == r;
+      const uint64_t one = __ballot(here);
+      if (one) {
+        at = (uint64_t)b + (uint32_t)(j * kWave) + (uint32_t)__ffsll((long long)one) - 1u;
+        r = kNone;                                     // (found)
+      } else if (r != kNone) {
+        r -= n;
+      }
+    }
+    y[k] = (double)A.ys[at];
+  }
+  if (lane == 0) cdf_out(A, c, val, low, y);
 }
 
 // one block, one CDF group in parts, whose ties are counted: wave k finds the
@@ -1289,11 +1312,9 @@ __device__ inline void cdf_long(const CdfArgs& A, uint32_t i, CellShared& S) {
 __global__ __launch_bounds__(kStatT) void k_cdf_cells(CdfArgs A,
                                                       uint32_t long_blocks,
                                                       uint32_t cell_blocks) {
-  __shared__ __attribute__((aligned(16))) uint32_t s_h[kWaves * kWaveCell];
+  __shared__ uint32_t s_h[kHistW];
   __shared__ CellShared S;
   __shared__ uint32_t s_list[kStatT], s_n;
-  __shared__ uint32_t s_wx[kWaves][kRanks];
-  __shared__ double s_wy[kWaves][kTies];
   uint32_t b = blockIdx.x;
   if (b < long_blocks) {
     const uint32_t n = (uint32_t)(*A.Q.n_long >> 32);
@@ -1308,15 +1329,17 @@ __global__ __launch_bounds__(kStatT) void k_cdf_cells(CdfArgs A,
     b -= cell_blocks;
     step = gridDim.x - long_blocks - cell_blocks;
   }
+  const int64_t c = b + (int64_t)threadIdx.x * step;
+  const bool on = c < A.NGG;
+  const int64_t m = on ? A.C.cnt[c] : 0;
+  const int64_t len = on ? (int64_t)A.C.end[c] - (int64_t)A.C.beg[c] : 0;
+  const uint32_t some = lane_id() < kCountCopies ? A.Q.n_cells[lane_id()] : 0u;
+  const int64_t most = lane63(wave_incl(some, OpAdd(), 0u)) > kManyCells
+                           ? kWaveCell : kFewCell;
   if (threadIdx.x == 0) s_n = 0;
   __syncthreads();
-  const int64_t c = b + (int64_t)threadIdx.x * step;
-  if (c < A.NGG) {
-    const int64_t m = A.C.cnt[c];
-    const int64_t len = (int64_t)A.C.end[c] - (int64_t)A.C.beg[c];
-    if (m > 0 && m <= kLongCell && (len > kWaveCell) == by_block)
-      s_list[atomicAdd(&s_n, 1u)] = (uint32_t)c;
-  }
+  if (m > 0 && m <= kLongCell && (len > most) == by_block)
+    s_list[atomicAdd(&s_n, 1u)] = (uint32_t)c;
   __syncthreads();
   const int n = (int)s_n;
   if (by_block) {
@@ -1324,8 +1347,13 @@ __global__ __launch_bounds__(kStatT) void k_cdf_cells(CdfArgs A,
     return;
   }
   const int w = (int)(threadIdx.x / kWave);
-  for (int i = w; i < n; i += kWaves)
-    cdf_wave(A, s_list[i], s_h + w * kWaveCell, s_wx[w], s_wy[w]);
+  for (int i = w; i < n; i += kWaves) {
+    const uint32_t c1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_list[i]);
+    const uint32_t len = A.C.end[c1] - A.C.beg[c1];
+    if (len <= kFewCell) cdf_wave<kFewCell / kWave>(A, c1);
+    else if (len <= 8 * kWave) cdf_wave<8>(A, c1);
+    else cdf_wave<kWaveCell / kWave>(A, c1);
+  }
 }
 
 // eq. 9 per (phase, operation), one wave each: the median over its GPUs with
@@ -1438,6 +1466,7 @@ extern "C" int chopper_op_stats(const chopper_rows* rows, int32_t depth,
     B.cells.beg = sc.take<uint32_t>(NGG);
     B.cells.end = sc.take<uint32_t>(NGG);
     B.lists.n_long = sc.take<unsigned long long>(1);
+    B.lists.n_cells = sc.take<uint32_t>(kCountCopies);
     B.lists.lng = sc.take<LongCell>(max_long);
     B.lists.of_part = sc.take<uint32_t>(max_parts);
     B.lists.ties = sc.take<uint32_t>(max_parts * kTies);

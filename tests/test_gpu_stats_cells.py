@@ -1,8 +1,8 @@
 """Per-GPU overlap CDFs of chopper_op_stats by the length of a CDF group: one
-wave selects it up to 512 slots, one block up to 32,768 instances, parts of
-8,192 above that.  Lengths at the edges of all three, GPUs that follow each
-other and GPUs mixed row by row, ratios with many ties, bit for bit against
-the CPU oracle."""
+wave selects it up to 128 slots (up to 1,024 where more than 512 groups are
+longer), one block up to 32,768 instances, parts of 8,192 above that.  Lengths
+at the edges of all of them, GPUs that follow each other and GPUs mixed row by
+row, ratios with many ties, bit for bit against the CPU oracle."""
 import numpy as np
 import pytest
 
@@ -58,7 +58,8 @@ def stats_of_rows(ch, gpu, phase, op, n_gpus, n_phases, n_ops, seed, ties):
                                 per_gpu=True, **spec)
 
 
-LENGTHS = [1, 2, 3, 63, 64, 65, 511, 512, 513, 540, 1025, 8193]
+LENGTHS = [1, 2, 3, 63, 64, 65, 127, 128, 129, 511, 512, 513, 540, 960, 1023,
+           1024, 1025, 8193]
 
 
 @pytest.mark.parametrize("ties", [False, True])
@@ -106,3 +107,23 @@ def test_gpu_boundary_in_one_block(ch):
     z = np.zeros(len(gpu), np.int64)
     got, ref = stats_of_rows(ch, gpu, z, z, 29, 1, 1, 2, False)
     check(got, ref, "one group, 30 GPUs of which 29 count")
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("groups,length", [(512, 140), (513, 140), (600, 129),
+                                           (600, 513), (640, 1023),
+                                           (640, 1024), (640, 1025)])
+def test_many_middle_groups(ch, groups, length, mixed):
+    """About 512 groups longer than 128, which go to waves above that."""
+    say("op stats:", groups, "CDF groups of", length,
+        "mixed" if mixed else "in turn")
+    # a group a phase, operation and GPU
+    cell = np.repeat(np.arange(groups), length)
+    gpu, rest = cell % 8, cell // 8
+    o = np.random.default_rng(groups + length).permutation(len(cell))
+    if not mixed:
+        o = o[np.argsort(gpu[o], kind="stable")]
+    got, ref = stats_of_rows(ch, gpu[o], rest[o] % 3, rest[o] // 3, 8, 3, 64,
+                             17, length % 2 == 0)
+    check(got, ref, f"{groups} of {length}")
+    assert (got[4] == length).sum() == groups
